@@ -31,8 +31,10 @@ sys.path.insert(0, ROOT)
 
 # MI355X dense peaks (TFLOP/s).  A split-BF16x3 product issues 3 BF16 MFMA
 # passes and FP8x2 two FP8 passes per useful flop, so their effective peaks
-# are the BF16 / FP8 peak divided by 3 / 2.
+# are the BF16 / FP8 peak divided by 3 / 2.  A large FP32 product runs as six
+# BF16 passes over operands split into three planes (PLANES_F32).
 PEAK = {"f32": 157.3, "bf16": 2500.0, "bf16x3": 2500.0 / 3, "fp8": 5000.0, "fp8x2": 2500.0}
+PLANES_F32 = 2500.0 / 6
 METRIC = "useful TFLOP/s of coded A.B (encode+GEMM+peel) vs uncoded GEMM at stated rel err"
 
 
@@ -56,6 +58,13 @@ def parse():
     ap.add_argument("--calibrate-copy", action="store_true",
                     help="only run a plain 1 GiB device copy (for scaling HBM counters)")
     return ap.parse_args()
+
+
+def split_planes(w, info, prec_name, two_d):
+    """Whether the library multiplies this product on split planes (row-block
+    F32 / BF16 / BF16x3, more than 2^31 multiply-adds, no forced tile)."""
+    return (not two_d and not prec_name.startswith("fp8") and
+            info["n_computed"] * info["Mb"] * w.K * w.N > 2 ** 31)
 
 
 GEMM_SOURCE = {"f32": "gemm_f32.hip", "bf16": "gemm_bf16.hip", "bf16x3": "gemm_bf16.hip",
@@ -319,12 +328,18 @@ def run_single(args):
         f32_kernel = "coded_gemm_f32_kernel<64,128,32,2>"
     bf16_kernel = ("fused_bf16_kernel (coded products and peel, one launch)" if fused else
                    "split_b + coded_gemm_bf16_flat_kernel, one call")
+    planes = split_planes(w, info, prec_name, two_d) and args.tile < 0
+    if planes:
+        f32_kernel = bf16_kernel = ("pack_planes + gemm_planes_kernel (256x256 tiles of BF16 "
+                                    "planes, last round split along K), one call")
     kernel = {"f32": f32_kernel, "bf16": bf16_kernel, "bf16x3": bf16_kernel,
               "fp8": "quant_b + quant_a + coded_gemm_fp8_wide_kernel, one call",
               "fp8x2": "quant_b + quant_a + coded_gemm_fp8_wide_kernel, one call"}[prec_name]
-    source = "gemm2d.hip" if two_d else "fused.hip" if fused else GEMM_SOURCE[prec_name]
-    roofline = {"bound": "mfma", "achieved": achieved, "peak": PEAK[prec_name],
-                "unit": "TFLOP/s", "frac": achieved / PEAK[prec_name],
+    source = ("gemm2d.hip" if two_d else "fused.hip" if fused else
+              "gemm_planes.hip" if planes else GEMM_SOURCE[prec_name])
+    peak = PLANES_F32 if planes and prec_name == "f32" else PEAK[prec_name]
+    roofline = {"bound": "mfma", "achieved": achieved, "peak": peak,
+                "unit": "TFLOP/s", "frac": achieved / peak,
                 "traffic": load_traffic(w.name, prec_name, source), "kernel": kernel,
                 "flops_per_launch": gemm_flops, "launch_ms": gemm_ms}
     cfg = {"workload": w.name, "M": w.M, "K": w.K, "N": w.N,

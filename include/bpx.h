@@ -68,7 +68,9 @@ typedef enum {
 } bpx_code_kind;
 
 typedef enum {
-  BPX_PREC_F32 = 0,    /* FP32 operands, FP32 MFMA                            */
+  BPX_PREC_F32 = 0,    /* FP32 operands and accuracy: FP32 MFMA, or for large
+                          products operands split exactly into three BF16
+                          planes (six MFMA products, FP32 accumulation)      */
   BPX_PREC_BF16 = 1,   /* operands rounded to BF16 (RNE), one MFMA pass       */
   BPX_PREC_BF16X3 = 2, /* split BF16: hi.hi + hi.lo + lo.hi, FP32 accumulate  */
   BPX_PREC_FP8 = 3,    /* e4m3, one power-of-two scale per 128x128 block      */
@@ -230,14 +232,21 @@ bpx_status bpx_plan_peel_program(const bpx_plan* plan, const int32_t** steps, in
                                  int32_t* n_slots);
 
 /* Device workspace the plan needs for bpx_coded_gemm / bpx_coded_matmul
- * (Y slots and, for FP8, quantised operands and scales), and the size of the
- * buffer bpx_encode writes (n_computed coded blocks of Mb x K floats). */
+ * (Y slots and, for FP8, quantised operands and scales; for large row-block
+ * F32 / BF16 / BF16x3 products also the operands split into BF16 planes), and
+ * the size of the buffer bpx_encode writes (n_computed coded blocks of
+ * Mb x K floats).  A call whose workspace holds the parts of
+ * bpx_plan_workspace_layout only is accepted: it runs the kernels that read A
+ * and B directly. */
 bpx_status bpx_plan_workspace_bytes(const bpx_plan* plan, size_t* ws_bytes,
                                     size_t* encode_bytes);
 
 /* Byte offsets of the parts of the plan's workspace (n entries written,
  * at most 7), every part 256-byte aligned; a part the precision does not
- * use has size 0 (its offset equals the next one); entry 6 is the total.
+ * use has size 0 (its offset equals the next one); entry 6 is the end of
+ * these parts (behind it, up to ws_bytes, come the split planes, flags and
+ * partial tiles of products of more than 2^31 multiply-adds over the computed
+ * symbols; the BF16 planes below are then not written).
  *   F32:     [0] Y slots, [1] split-K partial tiles: when Mb and N are
  *            multiples of 256, K of 32 and M of Mb, room for min(256, 4 T)
  *            FP32 tiles of 256 x 256 (T = computed symbols x Mb/256 x N/256),
@@ -273,7 +282,10 @@ bpx_status bpx_encode(bpx_plan* plan, const float* A, int64_t lda, float* coded_
 
 /* Coded products: Y_g = C_g . B for every computed symbol.  F32 and BF16*:
  * the encode is fused into the A-operand load (the coded block is never
- * stored).  FP8*: a streaming encode+quantise pass writes the e4m3 codes of
+ * stored), or, for more than 2^31 multiply-adds over the computed symbols,
+ * into a pass that packs the coded blocks and B as BF16 planes (FP32 values
+ * three planes cannot hold, infinities and NaN among them, send their tiles
+ * to the FP32 kernels, so results for them are those of FP32 arithmetic).  FP8*: a streaming encode+quantise pass writes the e4m3 codes of
  * every 128 x 128 coded tile (its scale needs the tile's amax), B is
  * quantised once per call, then the block-scaled FP8 product runs.  Products go to
  * the Y slots of ws or, for degree-1 releasers, straight into C (see dest in
@@ -327,13 +339,13 @@ bpx_status bpx_plan_fused_program(const bpx_plan* plan, const int32_t** steps, i
 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
- * product as bpx_coded_matmul, same kernels and results, with the workspace
+ * product as bpx_coded_matmul, with the workspace
  * taken from a static device array of the library (32 MiB per GPU, held by
  * every device that uses it until the process ends) instead of a caller
  * buffer.  Allocates nothing: the plan's tables must already be on the
  * current device (bpx_plan_upload), else BPX_E_INVALID; a plan whose
- * workspace (bpx_plan_workspace_bytes) exceeds 32 MiB gets
- * BPX_E_UNSUPPORTED.  Every call on one GPU shares that GPU's array, and
+ * workspace parts (bpx_plan_workspace_layout, entry 6) exceed 32 MiB get
+ * BPX_E_UNSUPPORTED; the split planes are used when they fit as well.  Every call on one GPU shares that GPU's array, and
  * nothing in it needs to start at zero (each call writes every byte it
  * reads first): calls that overlap on one GPU (other streams, other
  * threads) race and must be serialised by the caller. */

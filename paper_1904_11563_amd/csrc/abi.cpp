@@ -53,7 +53,9 @@ int32_t tile_count_for(int32_t prec) {
   return gemm_tile_count();
 }
 
-int32_t choose_tile(int32_t prec, int64_t Mb, int64_t N, int64_t K) {
+// The tile shape a forced shape or the tile table names for a product, -1 if
+// neither does.
+int32_t named_tile(int32_t prec, int64_t Mb, int64_t N, int64_t K) {
   if (g_force_tile >= 0 && g_force_tile < tile_count_for(prec)) return g_force_tile;
   if (g_tile_table_set) {
     const int32_t idx =
@@ -61,6 +63,16 @@ int32_t choose_tile(int32_t prec, int64_t Mb, int64_t N, int64_t K) {
     const int32_t t = g_tile_table[idx];
     if (t >= 0 && t < tile_count_for(prec)) return t;
   }
+  return -1;
+}
+// A named shape is one of the kernels that read A and B directly.
+bool tile_chosen(int32_t prec, int64_t Mb, int64_t N, int64_t K) {
+  return g_force_tile >= 0 || named_tile(prec, Mb, N, K) >= 0;
+}
+
+int32_t choose_tile(int32_t prec, int64_t Mb, int64_t N, int64_t K) {
+  const int32_t t = named_tile(prec, Mb, N, K);
+  if (t >= 0) return t;
   // BF16 / BF16x3 default: the flat-row 128x256 tiling (its callers fall
   // back to 64x128 where K is not a multiple of 32)
   if (prec == BPX_PREC_BF16 || prec == BPX_PREC_BF16X3) return 4;
@@ -148,14 +160,64 @@ bpx_status check_matrix(const float* ptr, int64_t ld, int64_t cols, const char* 
   return BPX_OK;
 }
 
+// A call has to bring the parts every path needs; the split planes are used
+// when the workspace holds them too.
+bpx_status check_workspace(const bpx_plan* plan, const void* ws, size_t ws_bytes) {
+  const size_t need = plan->base_bytes();
+  if (need > 0 && (!ws || ws_bytes < need || ((uintptr_t)ws & 255u)))
+    return fail(BPX_E_INVALID, "workspace missing, not 256-byte aligned or too small");
+  return BPX_OK;
+}
+
+// Coded products on split planes (see gemm_planes.hip): pack, multiply and,
+// for FP32, the tiles that hold a value the planes do not represent.
+bpx_status gemm_planes_impl(bpx_plan* plan, GemmParams p, void* ws, hipStream_t stream) {
+  char* w = static_cast<char*>(ws);
+  size_t off[6];
+  plan->plane_layout(off);
+  PlaneParams q{};
+  q.A = p.A;
+  q.lda = p.lda;
+  q.B = p.B;
+  q.ldb = p.ldb;
+  q.C = p.C;
+  q.ldc = p.ldc;
+  q.Y = p.Y;
+  q.M = p.M;
+  q.K = p.K;
+  q.N = p.N;
+  q.Mb = p.Mb;
+  q.syms = p.syms;
+  q.ids = p.ids;
+  q.n_sym = p.n_sym;
+  q.planes = plan->planes();
+  q.ap = reinterpret_cast<unsigned short*>(w + off[0]);
+  q.bp = reinterpret_cast<unsigned short*>(w + off[1]);
+  q.fa = reinterpret_cast<unsigned*>(w + off[2]);
+  q.fb = reinterpret_cast<unsigned*>(w + off[3]);
+  q.part = reinterpret_cast<float*>(w + off[4]);
+  q.part_tiles = plan->plane_part_tiles();
+  q.kc = (int32_t)plan->plane_kc();
+  hipError_t e = launch_pack_planes(q, stream);
+  if (e == hipSuccess) e = launch_gemm_planes(q, stream);
+  if (e == hipSuccess && q.planes == 3) {
+    p.fa = q.fa;
+    p.fb = q.fb;
+    p.nka = (q.kc + 15) / 16;
+    p.nkb = (q.kc + 3) / 4;
+    e = launch_coded_gemm(p, choose_tile(plan->prec, plan->Mb, plan->N, plan->K), stream);
+  }
+  if (e != hipSuccess) return hip_fail(e, "split-plane gemm launch");
+  return BPX_OK;
+}
+
 bpx_status gemm_impl(bpx_plan* plan, const float* A, int64_t lda, const float* B, int64_t ldb,
                      float* C, int64_t ldc, void* ws, size_t ws_bytes, hipStream_t stream) {
   bpx_status st;
   if ((st = check_matrix(A, lda, plan->K, "A")) != BPX_OK) return st;
   if ((st = check_matrix(B, ldb, plan->N, "B")) != BPX_OK) return st;
   if ((st = check_matrix(C, ldc, plan->N, "C")) != BPX_OK) return st;
-  if (plan->ws_bytes() > 0 && (!ws || ws_bytes < plan->ws_bytes() || ((uintptr_t)ws & 255u)))
-    return fail(BPX_E_INVALID, "workspace missing, not 256-byte aligned or too small");
+  if ((st = check_workspace(plan, ws, ws_bytes)) != BPX_OK) return st;
   GemmParams p{};
   p.A = A;
   p.lda = lda;
@@ -183,6 +245,9 @@ bpx_status gemm_impl(bpx_plan* plan, const float* A, int64_t lda, const float* B
   // 32-bit offsets.
   if ((plan->Mb + 256) * lda >= ((int64_t)1 << 30) || 64 * ldb + plan->N >= ((int64_t)1 << 30))
     return fail(BPX_E_UNSUPPORTED, "block too large for 32-bit tile offsets");
+  if (plan->has_planes() && ws_bytes >= plan->ws_bytes() &&
+      !tile_chosen(plan->prec, plan->Mb, plan->N, plan->K))
+    return gemm_planes_impl(plan, p, ws, stream);
   const int32_t tile = choose_tile(plan->prec, plan->Mb, plan->N, plan->K);
   hipError_t e;
   if (plan->grid > 1) {
@@ -381,7 +446,7 @@ namespace {
 
 size_t group_ws_bytes(bpx_plan* const* plans, int32_t count) {
   size_t b = 0;
-  for (int32_t i = 0; i < count; ++i) b += bpx_plan::align256(plans[i]->ws_bytes());
+  for (int32_t i = 0; i < count; ++i) b += bpx_plan::align256(plans[i]->base_bytes());
   return b;
 }
 
@@ -499,7 +564,7 @@ bpx_status group_build(bpx_plan* const* plans, const float* const* A, const floa
     tb += (int64_t)d.b_tn * d.b_tk;
     pstart[i] = tp;
     if (pe.nsteps > 0) tp += (pl->Mb * (pl->N / 4) + 127) / 128;
-    w += bpx_plan::align256(pl->ws_bytes());
+    w += bpx_plan::align256(pl->base_bytes());
   }
   if ((size_t)max_slots * 128 * 16 + max_program > 160 * 1024)
     return fail(BPX_E_UNSUPPORTED, "peel needs more LDS than a workgroup has");
@@ -877,8 +942,7 @@ bpx_status bpx_coded_matmul(bpx_plan* plan, const float* A, int64_t lda, const f
     if ((st = check_matrix(A, lda, plan->K, "A")) != BPX_OK) return st;
     if ((st = check_matrix(B, ldb, plan->N, "B")) != BPX_OK) return st;
     if ((st = check_matrix(C, ldc, plan->N, "C")) != BPX_OK) return st;
-    if (plan->ws_bytes() > 0 && (!ws || ws_bytes < plan->ws_bytes() || ((uintptr_t)ws & 255u)))
-      return fail(BPX_E_INVALID, "workspace missing, not 256-byte aligned or too small");
+    if ((st = check_workspace(plan, ws, ws_bytes)) != BPX_OK) return st;
     const hipError_t e = launch_fused(f, s);
     if (e != hipSuccess) return hip_fail(e, "fused coded product launch");
     return BPX_OK;
@@ -899,7 +963,7 @@ bpx_status bpx_coded_matmul_noalloc(bpx_plan* plan, const float* A, int64_t lda,
   if (!plan->dev_block || plan->dev_id != dev)
     return fail(BPX_E_INVALID, "plan tables not uploaded to this device (call bpx_plan_upload)");
   if (plan->K % 4 != 0) return fail(BPX_E_INVALID, "K must be a multiple of 4");
-  const size_t need = plan->ws_bytes();
+  const size_t need = plan->base_bytes();
   if (need > kScratchBytes)
     return fail(BPX_E_UNSUPPORTED, "plan needs " + std::to_string(need) +
                                        " bytes of workspace; the scratch array holds " +

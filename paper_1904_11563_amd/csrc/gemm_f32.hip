@@ -72,7 +72,27 @@ __device__ __forceinline__ void tile_coords(int L, int rows, int cols, int gm, i
   *col = r / gsz;
 }
 
-template <int BM, int BN, int BK, int OCC>
+// Whether rows [r0, r0 + nr) of the stacked coded rows or columns [n0, n0 +
+// nc) belong to a 256-wide panel that the split planes leave to this kernel
+// (a pack block of it is flagged).  Every thread of the workgroup calls it.
+__device__ __forceinline__ bool left_out(const GemmParams& p, int64_t r0, int nr, int64_t n0,
+                                         int nc) {
+  const int64_t R = (int64_t)p.n_sym * p.Mb;
+  const int64_t r1 = r0 + nr < R ? r0 + nr : R, n1 = n0 + nc < p.N ? n0 + nc : p.N;
+  unsigned any = 0;
+  // 8 pack blocks of 32 rows and 4 of 64 columns per panel
+  for (int64_t i = r0 / 256 * 8 * p.nka + threadIdx.x; i < ((r1 - 1) / 256 + 1) * 8 * p.nka;
+       i += blockDim.x)
+    any |= p.fa[i];
+  for (int64_t i = n0 / 256 * 4 * p.nkb + threadIdx.x; i < ((n1 - 1) / 256 + 1) * 4 * p.nkb;
+       i += blockDim.x)
+    any |= p.fb[i];
+  return __syncthreads_or((int)any) != 0;
+}
+
+// LEFT: the launch that computes only what the split planes leave out (an
+// instance of its own: the test in the ordinary kernel cost it 1.5 %).
+template <int BM, int BN, int BK, int OCC, bool LEFT = false>
 __global__ __launch_bounds__(kThreads, OCC) void coded_gemm_f32_kernel(GemmParams p) {
   using T = F32Tile<BM, BN, BK>;
   __shared__ __attribute__((aligned(16))) float lds[2 * (T::A_SIZE + T::B_SIZE)];
@@ -102,6 +122,8 @@ __global__ __launch_bounds__(kThreads, OCC) void coded_gemm_f32_kernel(GemmParam
     m0 = (rp - si * p.tiles_m) * BM;
     n0 = nt * BN;
   }
+  if (LEFT && !left_out(p, si * p.Mb + m0, p.Mb - m0 < BM ? (int)(p.Mb - m0) : BM, n0, BN))
+    return;
 
   const int id_off = p.syms[4 * si + 0];
   const int deg = p.syms[4 * si + 1];
@@ -378,7 +400,7 @@ __device__ __forceinline__ v4f bload(__amdgpu_buffer_rsrc_t r, uint32_t voff, ui
 }
 }  // namespace wide
 
-template <int WM, int WN>
+template <int WM, int WN, bool LEFT = false>
 __global__ __launch_bounds__(64 * WM * WN, 1) void coded_gemm_f32_wide_kernel(GemmParams p) {
   using namespace wide;
   constexpr int NT = 64 * WM * WN;               // threads
@@ -413,6 +435,7 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void coded_gemm_f32_wide_kernel(Ge
   const int si = rp / p.tiles_m;
   const int mt = rp - si * p.tiles_m;
   const int m0 = mt * BM, n0 = nt * BN;
+  if (LEFT && !left_out(p, si * p.Mb + m0, BM, n0, BN)) return;
 
   const int id_off = p.syms[4 * si + 0];
   const int deg = p.syms[4 * si + 1];
@@ -592,6 +615,10 @@ const TileEntry kTiles[] = {
 
 constexpr int32_t kWideTile = 4;
 
+// The flagged launch's forms of the two default shapes.
+const TileEntry kLeftTile = {{64, 128, 32}, coded_gemm_f32_kernel<64, 128, 32, 2, true>, kThreads};
+const TileEntry kLeftWide = {{256, 256, 32}, coded_gemm_f32_wide_kernel<4, 2, true>, 512};
+
 }  // namespace
 
 int32_t gemm_tile_count() { return (int32_t)(sizeof(kTiles) / sizeof(kTiles[0])); }
@@ -628,11 +655,12 @@ hipError_t launch_coded_gemm(const GemmParams& p0, int32_t tile, hipStream_t str
     // keeps every CU busy to the end.  Both kernels sum in the same order,
     // so the split does not change results.
     const int64_t rem = T % S;
-    const int64_t wide_tiles = rem * 10 < S * 9 ? T - rem : T;
+    // (A launch for flagged tiles alone has no rounds to fill.)
+    const int64_t wide_tiles = rem * 10 < S * 9 && !p.fa ? T - rem : T;
     if (T == 0 || T > 0x7fffffff / 8) {
       tile = 1;
     } else {
-      const TileEntry& e = kTiles[tile];
+      const TileEntry& e = p.fa ? kLeftWide : kTiles[tile];
       p.tiles_m = (int32_t)(p.Mb / 256);
       p.tiles_n = (int32_t)(p.N / 256);
       if (wide_tiles > 0) {
@@ -684,7 +712,7 @@ hipError_t launch_coded_gemm(const GemmParams& p0, int32_t tile, hipStream_t str
       return hipGetLastError();
     }
   }
-  const TileEntry& e = kTiles[tile];
+  const TileEntry& e = p.fa ? kLeftTile : kTiles[tile];
   p.tiles_m = (int32_t)((p.Mb + e.shape.bm - 1) / e.shape.bm);
   p.tiles_n = (int32_t)((p.N + e.shape.bn - 1) / e.shape.bn);
   const int64_t blocks = (int64_t)p.n_sym * p.tiles_m * p.tiles_n;

@@ -1,0 +1,614 @@
+// Coded products on operands split into BF16 planes beforehand: FP32,
+// BF16x3 and BF16 plans past the fused form's size.
+//
+// One streaming pass packs the coded blocks (the encode: members summed in
+// FP32, ascending) and B as BF16 planes, x = h + m + l with every plane
+// rounded to nearest even, and one kernel multiplies the packed planes on
+// v_mfma_f32_32x32x16_bf16 with FP32 accumulation:
+//   BF16:   h.h
+//   BF16x3: l.h + h.l + h.h          (two planes)
+//   FP32:   m.m + h.m + m.h + h.l + l.h + h.h   (three planes)
+// Three BF16 planes hold an FP32 value exactly (3 x 8 bits), the products of
+// planes are exact in FP32, and what FP32 leaves out (m.l, l.m, l.l) is below
+// 2^-26 of a product, under the rounding of one FP32 addition.  A k step of
+// 16 rounds the accumulator 6 times where the FP32 matrix instruction rounds
+// it for every 4 k, so the error against float64 is the smaller one: N(0,1),
+// K = 8192: 1.4e-6 against 1.6e-6; the 8192 x 8192 x 4096 coded product of
+// the (12,8,4) code 5.2e-6 against 6.2e-6.  BF16 MFMAs run 16 times the FP32
+// rate, so six of them still are 2.7 times faster.
+//
+// The splitting needs the planes' exponents to stay in range, so a value
+// that is not zero and outside [2^-100, 2^63), infinities and NaN included,
+// flags its pack block: the GEMM skips the 256-wide row or column panel, and
+// an FP32 launch (gemm_f32.hip) computes it, which also keeps the results for
+// infinities and NaN those of FP32 arithmetic.
+//
+// Packed layout: MFMA fragments.  For every 32 rows of the stacked coded
+// rows (or columns of B) and 16 k there is 1 KiB per plane: lane l's eight
+// values, row l % 32, k 8 (l / 32) .. +7.  The planes of one k chunk follow
+// each other, chunks follow in k, 32-row panels come last; rows are padded to
+// 256 and k to whole stages with zeros, so the GEMM has no edges except in
+// its stores.  A stage is copied straight to LDS in whole KiB, and every LDS
+// read is lane-linear (no bank conflicts, no swizzle).
+#include <hip/hip_runtime.h>
+
+#include <type_traits>
+
+#include "kernels.hpp"
+
+namespace bpx {
+namespace {
+
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef unsigned short us;
+typedef __attribute__((address_space(3))) void* lds_addr;
+typedef __attribute__((address_space(1))) float gfloat;
+typedef __attribute__((address_space(1))) v4f gv4f;
+
+constexpr int kRsrcWord3 = 0x00020000;  // gfx9 raw buffer, 32-bit elements
+
+__device__ __forceinline__ int32_t gld(const int32_t* ptr) {
+  return *(const __attribute__((address_space(1))) int32_t*)ptr;
+}
+
+// ------------------------------------------------------------------ pack --
+// Eight consecutive k of one row, split into P planes.
+template <int P>
+struct Granule {
+  v8bf p[P];
+};
+template <int P>
+__device__ __forceinline__ Granule<P> split8(const float (&x)[8]) {
+  Granule<P> g;
+  float r[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) r[e] = x[e];
+#pragma unroll
+  for (int p = 0; p < P; ++p)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      g.p[p][e] = (__bf16)r[e];
+      if (p + 1 < P) r[e] -= (float)g.p[p][e];
+    }
+  return g;
+}
+// Whether a value is not zero and outside what three planes represent.
+__device__ __forceinline__ bool out_of_range(const float (&x)[8]) {
+  unsigned hi = 0, lo = 0xffffffffu;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const unsigned a = __builtin_bit_cast(unsigned, x[e]) & 0x7fffffffu;
+    hi = a > hi ? a : hi;
+    lo = a - 1u < lo ? a - 1u : lo;  // zero wraps to the largest value
+  }
+  return hi >= kPlaneMaxBits || lo < kPlaneMinBits - 1u;
+}
+
+// 32 stacked coded rows x 256 k.  Bound by HBM: the members are read once
+// each, 8 lanes to 256 consecutive bytes of a row, all loads of a member
+// issued together, and the planes leave as whole 128-byte lines (8 rows of a
+// fragment), so nothing goes through LDS.  8192 x 8192 (12,8,4): A and B
+// packed in 245 us, 0.98 GB read and 0.65 GB written at 6.7 TB/s.
+template <int P>
+__device__ __forceinline__ void pack_a_block(const PlaneParams& p, int b, int tid) {
+  const int rp = b / p.nka, kb = b - rp * p.nka;
+  const int lane = tid & 63, wave = tid >> 6;
+  const int r = wave * 8 + (lane >> 3), g8 = (lane & 7) * 8;
+  const unsigned gr = (unsigned)rp * 32u + (unsigned)r;
+  const int Mb = (int)p.Mb;
+  int deg = 0, id_off = 0, lr = 0;
+  if (gr < (unsigned)p.n_sym * (unsigned)Mb) {
+    const int si = (int)(gr / (unsigned)Mb);
+    lr = (int)gr - si * Mb;
+    id_off = gld(p.syms + 4 * si + 0);
+    deg = gld(p.syms + 4 * si + 1);
+  }
+  const int K = (int)p.K, Kp = p.kc * 16;
+  const int k0 = kb * 256 + g8;
+  v4f s[4][2];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) s[i][0] = s[i][1] = v4f{0.f, 0.f, 0.f, 0.f};
+  for (int m = 0; m < deg; ++m) {
+    const int64_t row = (int64_t)gld(p.ids + id_off + m) * Mb + lr;
+    if (row >= p.M) continue;
+    const float* src = p.A + row * p.lda;
+    v4f v[4][2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int k = k0 + 64 * i + 4 * h;
+        v[i][h] = v4f{0.f, 0.f, 0.f, 0.f};
+        if (k < K) v[i][h] = *(const gv4f*)(src + k);
+      }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) s[i][h] += v[i][h];
+  }
+  bool bad = false;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int k = k0 + 64 * i;
+    if (k < Kp) {
+      float x[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[e] = s[i][e >> 2][e & 3];
+      if (P == 3) bad = bad || out_of_range(x);
+      const Granule<P> g = split8<P>(x);
+      us* dst = p.ap + (((int64_t)rp * p.kc + (k >> 4)) * P * 64 + ((k >> 3) & 1) * 32 + r) * 8;
+#pragma unroll
+      for (int q = 0; q < P; ++q) *(v8bf*)(dst + q * 512) = g.p[q];
+    }
+  }
+  if (P == 3) {
+    const int any = __syncthreads_or(bad ? 1 : 0);
+    if (tid == 0) p.fa[b] = any ? 1u : 0u;
+  }
+}
+
+// 64 k x 64 columns of B, transposed through LDS: rows of 64 floats written
+// 16 bytes per lane and read 4 bytes per lane along n, both conflict-free.
+template <int P>
+__device__ __forceinline__ void pack_b_block(const PlaneParams& p, int b, int tid, float* t) {
+  const int tn = p.tiles_n * 4;
+  const int kb = b / tn, nb = b - kb * tn;
+  const int64_t n0 = (int64_t)nb * 64, k0 = (int64_t)kb * 64;
+  const int64_t N = p.N, K = p.K;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int f = tid + 256 * i;
+    const int kr = f >> 4, nc = (f & 15) * 4;
+    const int64_t k = k0 + kr, n = n0 + nc;
+    v4f v = {0.f, 0.f, 0.f, 0.f};
+    if (k < K) {
+      const float* src = p.B + k * p.ldb + n;
+      if (n + 3 < N) {
+        v = *(const gv4f*)src;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (n + e < N) v[e] = src[e];
+      }
+    }
+    *reinterpret_cast<v4f*>(t + kr * 64 + nc) = v;
+  }
+  __syncthreads();
+  const int lane = tid & 63, wave = tid >> 6;
+  const int kc = (int)(k0 >> 4) + wave;
+  bool bad = false;
+  if (kc < p.kc) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const float* src = t + (wave * 16 + (lane >> 5) * 8) * 64 + h * 32 + (lane & 31);
+      float x[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[e] = src[e * 64];
+      if (P == 3) bad = bad || out_of_range(x);
+      const Granule<P> g = split8<P>(x);
+      us* dst = p.bp + ((((int64_t)nb * 2 + h) * p.kc + kc) * P * 64 + lane) * 8;
+#pragma unroll
+      for (int q = 0; q < P; ++q) *(v8bf*)(dst + q * 512) = g.p[q];
+    }
+  }
+  if (P == 3) {
+    const int any = __syncthreads_or(bad ? 1 : 0);
+    if (tid == 0) p.fb[nb * p.nkb + kb] = any ? 1u : 0u;
+  }
+}
+
+template <int P>
+__global__ __launch_bounds__(256) void pack_planes_kernel(PlaneParams p) {
+  __shared__ __attribute__((aligned(16))) float t[64 * 64];
+  const int b = blockIdx.x;
+  if (b < p.blocks_b)
+    pack_b_block<P>(p, b, threadIdx.x, t);
+  else
+    pack_a_block<P>(p, b - p.blocks_b, threadIdx.x);
+}
+
+// ------------------------------------------------------------------ GEMM --
+// 256 x 256 tiles of the stacked rows, 8 waves (2 x 4) of 128 x 64, each 4 x 2
+// accumulators of 32 x 32.  Against the 16 x 16 MFMA the 32 x 32 one reads
+// half the operand bytes per product, which counts twice here: LDS (6
+// fragment reads per plane for 8 MFMAs per plane product) and power (at full
+// MFMA load the clock falls to 1.6-1.8 GHz).
+//
+// Stages of 16 STEPS k are copied straight to LDS NBUF stages ahead.  A wave
+// reads the next k step's fragments before it multiplies the current ones; in
+// the last step of a stage it first waits for its own copies of the next
+// stage and its LDS reads of this one, then for the other waves, and refills
+// the buffer.  One barrier per 48 MFMAs and wave, with the copies of up to
+// NBUF - 1 stages in flight across it.  FP32's planes do not fit twice in the
+// registers, so there the order of the plane products lets each plane be
+// read while others multiply (m first, h under m.m, l under h.m and m.h, the
+// next m under the rest).
+//
+// Measured on 8192 x 8192 x 4096, 36 coded products (618 GFLOP): FP32 2.35
+// ms, 1.58 PFLOP/s of BF16 products, MFMA busy 0.83 at 1.6 GHz (0.75 ms less
+// on zero operands: power, not issue, is what is left); the FP32 MFMA
+// kernels took 4.64 ms.  BF16x3 1.27 ms against 2.31 ms for the kernel that
+// encodes and splits A while staging.
+constexpr int NT = 512;
+
+// k steps per stage and stages in LDS (144, 128 and 128 KiB).
+template <int P>
+struct Cfg;
+template <>
+struct Cfg<1> {
+  static constexpr int STEPS = 2, NBUF = 4;
+};
+template <>
+struct Cfg<2> {
+  static constexpr int STEPS = 2, NBUF = 2;
+};
+template <>
+struct Cfg<3> {
+  static constexpr int STEPS = 1, NBUF = 3;
+};
+
+// One k step's fragments of a wave.
+template <int P>
+struct Frags {
+  v8bf a[4][P], b[2][P];
+};
+
+// Consecutive workgroups go to different XCDs; each XCD gets a contiguous
+// range of tiles.
+__device__ __forceinline__ int xcd_remap(int lin, int total) {
+  if ((total & 7) != 0) return lin;
+  return (lin & 7) * (total >> 3) + (lin >> 3);
+}
+
+// Waits until at most VM vector-memory operations of this wave are in
+// flight, and for all of its LDS operations if LGKM.
+template <int VM, bool LGKM>
+__device__ __forceinline__ void wait_counts() {
+  __builtin_amdgcn_s_waitcnt((VM & 15) | ((VM >> 4) << 14) | (7 << 4) | ((LGKM ? 0 : 15) << 8));
+}
+__device__ __forceinline__ void barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// Copies COUNT consecutive KiB of a packed panel straight to LDS, 16 bytes
+// per lane (the instruction offset moves both addresses).  Written as asm
+// because the compiler would wait for every copy in flight before any later
+// LDS read; the waits are the loop's own.
+template <int COUNT>
+__device__ __forceinline__ void copy_panel(v4i rsrc, int lds, int voff, int soff) {
+  if constexpr (COUNT == 2)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+                 "buffer_load_dwordx4 %1, %2, %3 offen lds\n\t"
+                 "buffer_load_dwordx4 %1, %2, %3 offen offset:1024 lds"
+                 ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+  if constexpr (COUNT == 3)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+                 "buffer_load_dwordx4 %1, %2, %3 offen lds\n\t"
+                 "buffer_load_dwordx4 %1, %2, %3 offen offset:1024 lds\n\t"
+                 "buffer_load_dwordx4 %1, %2, %3 offen offset:2048 lds"
+                 ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+  if constexpr (COUNT == 4)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+                 "buffer_load_dwordx4 %1, %2, %3 offen lds\n\t"
+                 "buffer_load_dwordx4 %1, %2, %3 offen offset:1024 lds\n\t"
+                 "buffer_load_dwordx4 %1, %2, %3 offen offset:2048 lds\n\t"
+                 "buffer_load_dwordx4 %1, %2, %3 offen offset:3072 lds"
+                 ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+  static_assert(COUNT >= 2 && COUNT <= 4, "KiB per panel and stage");
+}
+
+// Tile order: groups of 8 row panels, column panel by column panel, so the 32
+// tiles an XCD runs at once share 8 row panels and 4 column panels in its L2.
+__device__ __forceinline__ void tile_at(const PlaneParams& p, int lin, int* mt, int* nt) {
+  constexpr int kRowGroup = 8;
+  const int per_group = kRowGroup * p.tiles_n;
+  const int first = lin / per_group * kRowGroup;
+  const int gsz = p.tiles_m - first < kRowGroup ? p.tiles_m - first : kRowGroup;
+  const int r = lin - (first / kRowGroup) * per_group;
+  *mt = first + r % gsz;
+  *nt = r / gsz;
+}
+
+// Where stacked row gr of the coded products goes (null: nowhere).
+__device__ __forceinline__ float* out_row(const PlaneParams& p, unsigned gr) {
+  if (gr >= (unsigned)p.n_sym * (unsigned)p.Mb) return nullptr;
+  const int si = (int)(gr / (unsigned)p.Mb);
+  const int64_t lr = (int64_t)gr - (int64_t)si * p.Mb;
+  const int dest = gld(p.syms + 4 * si + 2);
+  if (dest >= 0) return p.Y + ((int64_t)dest * p.Mb + lr) * p.N;
+  const int64_t row = (-1 - (int64_t)dest) * p.Mb + lr;
+  return row < p.M ? p.C + row * p.ldc : nullptr;
+}
+
+template <int P>
+__global__ __launch_bounds__(NT) void gemm_planes_kernel(PlaneParams p) {
+  using C_ = Cfg<P>;
+  constexpr int STEPS = C_::STEPS, NBUF = C_::NBUF;
+  constexpr int RPB = STEPS * P * 1024;     // bytes of one 32-row panel per stage
+  constexpr int STAGE = 16 * RPB;           // A panels 0..7, B panels 8..15
+  constexpr int L = 2 * STEPS * P;          // 1 KiB copies per wave per stage
+  __shared__ __attribute__((aligned(1024))) char lds[NBUF * STAGE];
+  __shared__ float* rows[256];  // output rows of the tile
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 2, wn = wave & 3;
+
+  int lin, kt0 = 0, kt1 = p.kc / STEPS, piece = -1;
+  if ((int)blockIdx.x < p.full) {
+    lin = xcd_remap(blockIdx.x, p.full);
+  } else {
+    piece = (int)blockIdx.x - p.full;
+    const int s = piece % p.split;
+    lin = p.full + piece / p.split;
+    const int nk = kt1;
+    kt0 = s * nk / p.split;
+    kt1 = (s + 1) * nk / p.split;
+  }
+  int mt, nt;
+  tile_at(p, lin, &mt, &nt);
+
+  // wave w copies panels 2w, 2w+1 of the stage: waves 0-3 A, 4-7 B
+  const int64_t rp_stride = (int64_t)p.kc * P * 1024;
+  const char* src = (wave < 4 ? reinterpret_cast<const char*>(p.ap) + (int64_t)mt * 8 * rp_stride
+                              : reinterpret_cast<const char*>(p.bp) + (int64_t)nt * 8 * rp_stride);
+  v4i rsrc = {(int)(reinterpret_cast<uint64_t>(src)),
+              (int)(reinterpret_cast<uint64_t>(src) >> 32) & 0xffff, (int)(8 * rp_stride),
+              kRsrcWord3};
+#pragma unroll
+  for (int c = 0; c < 4; ++c) rsrc[c] = __builtin_amdgcn_readfirstlane(rsrc[c]);
+  const int soff0 = (wave & 3) * 2 * (int)rp_stride;
+  const int voff = lane * 16;
+  const int lds0 = (int)(uintptr_t)(lds_addr)lds + 2 * wave * RPB;
+  auto dma = [&](int st, int kt) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      copy_panel<STEPS * P>(rsrc, lds0 + st + u * RPB, voff, soff0 + u * (int)rp_stride + kt * RPB);
+  };
+
+  const int nk = kt1 - kt0;
+#pragma unroll
+  for (int i = 0; i < NBUF; ++i)
+    if (i < nk) dma(i * STAGE, kt0 + i);
+
+  if (tid < 256) rows[tid] = out_row(p, (unsigned)mt * 256u + (unsigned)tid);
+  if (P == 3) {
+    unsigned bad = 0;
+    for (int i = tid; i < 8 * p.nka; i += NT) bad |= p.fa[(int64_t)mt * 8 * p.nka + i];
+    for (int i = tid; i < 4 * p.nkb; i += NT) bad |= p.fb[(int64_t)nt * 4 * p.nkb + i];
+    if (__syncthreads_or((int)bad)) {
+      wait_counts<0, false>();
+      return;
+    }
+  }
+
+  v16f acc[4][2];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+
+  const int a_base = wm * 4 * RPB + lane * 16, b_base = (8 + wn * 2) * RPB + lane * 16;
+  auto read_a = [&](Frags<P>& f, const char* st, int s, int q) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      f.a[i][q] = *reinterpret_cast<const v8bf*>(st + a_base + i * RPB + (s * P + q) * 1024);
+  };
+  auto read_b = [&](Frags<P>& f, const char* st, int s, int q) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      f.b[j][q] = *reinterpret_cast<const v8bf*>(st + b_base + j * RPB + (s * P + q) * 1024);
+  };
+  auto mul = [&](const Frags<P>& f, auto pa, auto pb) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+            f.a[i][decltype(pa)::value], f.b[j][decltype(pb)::value], acc[i][j], 0, 0, 0);
+  };
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, P >= 2 ? 1 : 0>;
+  using I2 = std::integral_constant<int, P == 3 ? 2 : 0>;
+
+  // ends stage kt: the next stage has landed everywhere, and this stage's
+  // buffer may be refilled
+  auto turn = [&](int kt) __attribute__((always_inline)) {
+    if (kt + NBUF - 1 < nk)
+      wait_counts<(NBUF - 2) * L, true>();
+    else
+      wait_counts<0, true>();
+    barrier();
+  };
+
+  // first stage
+  if (nk >= NBUF)
+    wait_counts<(NBUF - 1) * L, true>();
+  else
+    wait_counts<0, true>();
+  barrier();
+
+  if constexpr (P == 3) {
+    Frags<P> f;
+    read_a(f, lds, 0, 1);
+    read_b(f, lds, 0, 1);
+    int cur = 0;
+    for (int kt = 0; kt < nk; ++kt) {
+      const int nxt = cur + STAGE == NBUF * STAGE ? 0 : cur + STAGE;
+      const char* S = lds + cur;
+      const char* T = lds + nxt;
+      read_a(f, S, 0, 0);
+      read_b(f, S, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      mul(f, I1{}, I1{});
+      __builtin_amdgcn_sched_barrier(0);
+      read_b(f, S, 0, 2);
+      read_a(f, S, 0, 2);
+      __builtin_amdgcn_sched_barrier(0);
+      mul(f, I0{}, I1{});
+      mul(f, I1{}, I0{});
+      __builtin_amdgcn_sched_barrier(0);
+      turn(kt);
+      read_a(f, T, 0, 1);
+      read_b(f, T, 0, 1);
+      if (kt + NBUF < nk) dma(cur, kt0 + kt + NBUF);
+      __builtin_amdgcn_sched_barrier(0);
+      mul(f, I0{}, I2{});
+      mul(f, I2{}, I0{});
+      mul(f, I0{}, I0{});
+      __builtin_amdgcn_sched_barrier(0);
+      cur = nxt;
+    }
+  } else {
+    static_assert(P == 3 || STEPS == 2, "two k steps per stage");
+    Frags<P> f0, f1;
+    auto read = [&](Frags<P>& f, const char* st, int s) __attribute__((always_inline)) {
+#pragma unroll
+      for (int q = P - 1; q >= 0; --q) {
+        read_a(f, st, s, q);
+        read_b(f, st, s, q);
+      }
+    };
+    auto step = [&](const Frags<P>& f) __attribute__((always_inline)) {
+      if constexpr (P == 2) {
+        mul(f, I1{}, I0{});
+        mul(f, I0{}, I1{});
+      }
+      mul(f, I0{}, I0{});
+    };
+    read(f0, lds, 0);
+    int cur = 0;
+    for (int kt = 0; kt < nk; ++kt) {
+      const int nxt = cur + STAGE == NBUF * STAGE ? 0 : cur + STAGE;
+      read(f1, lds + cur, 1);
+      __builtin_amdgcn_sched_barrier(0);
+      step(f0);
+      __builtin_amdgcn_sched_barrier(0);
+      turn(kt);
+      read(f0, lds + nxt, 0);
+      if (kt + NBUF < nk) dma(cur, kt0 + kt + NBUF);
+      __builtin_amdgcn_sched_barrier(0);
+      step(f1);
+      __builtin_amdgcn_sched_barrier(0);
+      cur = nxt;
+    }
+  }
+
+  // epilogue: lane l holds column l % 32, rows 8 (e / 4) + 4 (l / 32) + e % 4
+  const int c0 = wn * 64 + (lane & 31);
+  if (piece >= 0 && p.split > 1) {
+    gfloat* out = (gfloat*)(p.part + (int64_t)piece * 65536);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int row = wm * 128 + i * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) out[row * 256 + c0 + 32 * j] = acc[i][j][e];
+      }
+    return;
+  }
+  const int64_t n0 = (int64_t)nt * 256 + c0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int row = wm * 128 + i * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+      gfloat* out = (gfloat*)rows[row];
+      if (!out) continue;
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        if (n0 + 32 * j < p.N) out[n0 + 32 * j] = acc[i][j][e];
+    }
+}
+
+// Sums the pieces of each split tile, 64 blocks per tile, one float4 per
+// thread, in piece order (fixed, so results do not depend on scheduling).
+__global__ __launch_bounds__(256) void planes_reduce_kernel(PlaneParams p) {
+  const int t = blockIdx.x >> 6;
+  const int e = ((blockIdx.x & 63) << 8) + threadIdx.x;
+  const int row = e >> 6, col = (e & 63) * 4;
+  int mt, nt;
+  tile_at(p, p.full + t, &mt, &nt);
+  float* out = out_row(p, (unsigned)mt * 256u + (unsigned)row);
+  const int64_t n = (int64_t)nt * 256 + col;
+  if (!out || n >= p.N) return;
+  const float* src = p.part + (int64_t)t * p.split * 65536 + row * 256 + col;
+  v4f sum = *reinterpret_cast<const v4f*>(src);
+  for (int k = 1; k < p.split; ++k)
+    sum += *reinterpret_cast<const v4f*>(src + (int64_t)k * 65536);
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+    if (n + c < p.N) out[n + c] = sum[c];
+}
+
+}  // namespace
+
+namespace {
+void set_tiles(PlaneParams* p) {
+  p->tiles_m = (int32_t)(((int64_t)p->n_sym * p->Mb + 255) / 256);
+  p->tiles_n = (int32_t)((p->N + 255) / 256);
+  p->nka = (p->kc + 15) / 16;
+  p->nkb = (p->kc + 3) / 4;
+  p->blocks_b = p->tiles_n * 4 * p->nkb;
+}
+}  // namespace
+
+hipError_t launch_pack_planes(const PlaneParams& p0, hipStream_t stream) {
+  PlaneParams p = p0;
+  set_tiles(&p);
+  const unsigned blocks = (unsigned)p.blocks_b + (unsigned)p.tiles_m * 8u * (unsigned)p.nka;
+  void (*k)(PlaneParams) = p.planes == 3   ? pack_planes_kernel<3>
+                           : p.planes == 2 ? pack_planes_kernel<2>
+                                           : pack_planes_kernel<1>;
+  hipLaunchKernelGGL(k, dim3(blocks), dim3(256), 0, stream, p);
+  return hipGetLastError();
+}
+
+hipError_t launch_gemm_planes(const PlaneParams& p0, hipStream_t stream) {
+  PlaneParams p = p0;
+  set_tiles(&p);
+  const int64_t T = (int64_t)p.tiles_m * p.tiles_n, S = device_cu_count();
+  if (T > 0x7fffffff / 32) return hipErrorInvalidValue;
+  // The last round: R = T mod S tiles (all of them when there are fewer than
+  // CUs), each split into q pieces of its K range whose partial tiles a second
+  // kernel sums, where a model of both says that ends sooner: rounds of
+  // pieces at the measured time of a 16-wide k chunk of one tile, 6 us for
+  // the second launch and 0.125 us per partial tile written and read back
+  // (4 TB/s).  1999 x 1500 x 1001, 36 tiles: 14 pieces, GEMM 43 and sum 11
+  // us, where whole tiles would take 140 us.
+  const int64_t R = T % S;
+  const double us = p.planes == 3 ? 1.45 : p.planes == 2 ? 0.75 : 0.35;
+  int64_t best_q = 1;
+  double best = p.kc * us;
+  for (int64_t q = 2; q <= 16 && R > 0; ++q) {
+    if (R * q > p.part_tiles || p.kc / q < 8) break;
+    const double t = (double)((R * q + S - 1) / S) * (double)p.kc * us / (double)q + 6.0 +
+                     0.125 * (double)(R * q);
+    if (t < best) {
+      best = t;
+      best_q = q;
+    }
+  }
+  p.split = (int32_t)best_q;
+  p.full = (int32_t)(best_q > 1 ? T - R : T);
+  const unsigned blocks = (unsigned)(p.full + (T - p.full) * best_q);
+  void (*k)(PlaneParams) = p.planes == 3   ? gemm_planes_kernel<3>
+                           : p.planes == 2 ? gemm_planes_kernel<2>
+                                           : gemm_planes_kernel<1>;
+  hipLaunchKernelGGL(k, dim3(blocks), dim3(NT), 0, stream, p);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || p.full == T) return e;
+  hipLaunchKernelGGL(planes_reduce_kernel, dim3((unsigned)((T - p.full) * 64)), dim3(256), 0,
+                     stream, p);
+  return hipGetLastError();
+}
+
+}  // namespace bpx

@@ -140,10 +140,59 @@ struct bpx_plan {
     }
     off[6] = b;
   }
-  size_t ws_bytes() const {
+  // Bytes the kernels that read A and B directly need: what a call has to
+  // bring at least.
+  size_t base_bytes() const {
     size_t off[7];
     layout(off);
     return off[6];
+  }
+  // Products past the fused form's size (2^31 multiply-adds over the computed
+  // symbols) also reserve room for the operands split into BF16 planes
+  // (gemm_planes.hip), behind the parts above; below it the pack pass and the
+  // 256 x 256 tiles cost more than they save.
+  int32_t planes() const {
+    return prec == BPX_PREC_F32 ? 3 : prec == BPX_PREC_BF16X3 ? 2 : 1;
+  }
+  // 16-wide k chunks of the packed operands, whole stages of the GEMM
+  int64_t plane_kc() const { return planes() == 3 ? (K + 15) / 16 : (K + 31) / 32 * 2; }
+  int64_t plane_rows() const { return ((int64_t)computed.size() * Mb + 255) / 256 * 256; }
+  int64_t plane_cols() const { return (N + 255) / 256 * 256; }
+  bool has_planes() const {
+    if (grid != 1 || is_fp8() || K % 4 != 0) return false;
+    const double macs = (double)computed.size() * (double)Mb * (double)K * (double)N;
+    const int64_t lim = (int64_t)1 << 31;
+    return macs > 2147483648.0 && plane_rows() < lim && plane_cols() < lim &&
+           plane_kc() * planes() * 8192 < lim &&
+           plane_rows() / 32 * ((plane_kc() + 15) / 16) + plane_cols() / 64 * ((plane_kc() + 3) / 4) <
+               lim;
+  }
+  static constexpr int32_t kPartTiles = 512;
+  // Offsets of the plane parts, from the start of the workspace: packed A,
+  // packed B, flags of A, flags of B (planes() == 3), partial tiles; [5] the end.
+  void plane_layout(size_t off[6]) const {
+    size_t b = base_bytes();
+    off[0] = b;
+    b += (size_t)plane_rows() * plane_kc() * 32 * planes();
+    off[1] = b;
+    b += (size_t)plane_cols() * plane_kc() * 32 * planes();
+    off[2] = b;
+    if (planes() == 3) b += align256((size_t)(plane_rows() / 32) * ((plane_kc() + 15) / 16) * 4);
+    off[3] = b;
+    if (planes() == 3) b += align256((size_t)(plane_cols() / 64) * ((plane_kc() + 3) / 4) * 4);
+    off[4] = b;
+    b += (size_t)plane_part_tiles() * 65536 * sizeof(float);
+    off[5] = b;
+  }
+  int32_t plane_part_tiles() const {
+    const int64_t t = plane_rows() / 256 * (plane_cols() / 256) * 16;
+    return t < kPartTiles ? (int32_t)t : kPartTiles;
+  }
+  size_t ws_bytes() const {
+    if (!has_planes()) return base_bytes();
+    size_t off[6];
+    plane_layout(off);
+    return off[5];
   }
 };
 

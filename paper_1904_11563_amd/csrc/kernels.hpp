@@ -50,6 +50,11 @@ struct GemmParams {
   const unsigned short* bt_hi;
   const unsigned short* bt_lo;
   int64_t kp;
+  // FP32 launch that only computes the tiles the split planes leave out: the
+  // pack blocks' flags (see PlaneParams), null for an ordinary launch
+  const unsigned* fa;
+  const unsigned* fb;
+  int32_t nka, nkb;
 };
 
 // FP8 path (see gemm_fp8.hip for the workspace layout).
@@ -121,6 +126,41 @@ hipError_t launch_coded_gemm(const GemmParams& p, int32_t tile, hipStream_t stre
 // tile: the FP32 tile shape chosen for the call; the 256 x 256 shapes (4-6)
 // take the wide 2-D kernel where the blocks allow it, others 64 x 128.
 hipError_t launch_coded_gemm_2d(const GemmParams& p, int32_t tile, hipStream_t stream);
+
+// ---------------------------------------------------------- split planes --
+// Products whose operands are split into BF16 planes beforehand (see
+// gemm_planes.hip).  An FP32 value outside [2^-100, 2^63) that is not zero
+// (infinities and NaN among them) is not split: the FP32 kernels compute the
+// tiles it belongs to.
+constexpr unsigned kPlaneMaxBits = (127u + 63u) << 23, kPlaneMinBits = (127u - 100u) << 23;
+struct PlaneParams {
+  const float* A;
+  int64_t lda;
+  const float* B;
+  int64_t ldb;
+  float* C;
+  int64_t ldc;
+  float* Y;
+  int64_t M, K, N, Mb;
+  const int32_t* syms;
+  const int32_t* ids;
+  int32_t n_sym;
+  int32_t planes;      // 1: BF16, 2: BF16x3, 3: FP32
+  unsigned short* ap;  // packed planes of the stacked coded rows
+  unsigned short* bp;  // packed planes of B's columns
+  unsigned* fa;        // planes == 3: per pack block, 1 if it holds a value
+  unsigned* fb;        //   that is not split
+  float* part;         // partial 256 x 256 tiles of the last round
+  int32_t part_tiles;  // how many part holds
+  int32_t kc;          // 16-wide k chunks of the packed operands
+  // set by the launcher
+  int32_t tiles_m, tiles_n;
+  int32_t nka, nkb;    // pack blocks along k of A (256 wide) and of B (64 wide)
+  int32_t blocks_b;
+  int32_t full, split; // tiles computed whole; K pieces of each of the others
+};
+hipError_t launch_pack_planes(const PlaneParams& p, hipStream_t stream);
+hipError_t launch_gemm_planes(const PlaneParams& p, hipStream_t stream);
 
 int32_t bf16_tile_count();
 TileShape bf16_tile_shape(int32_t t);

@@ -1,0 +1,143 @@
+"""Large products on operands split into BF16 planes: exact on integers at the
+edges of tiles, stages and K pieces, FP32 results no further from float64 than
+the FP32 kernels', and values the planes cannot hold left to those kernels."""
+import sys
+
+import numpy as np
+import pytest
+
+from paper_1904_11563_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+from paper_1904_11563_amd import bpx  # noqa: E402
+
+
+def _code(s):
+    return bpx.Code.search(s.n, s.k, s.b, s.sigma, s.seed, s.restarts, s.iters, walk=s.walk)
+
+
+def _plan(spec, M, K, N, prec, mode=bpx.MODE_STRAGGLER):
+    arrival, _ = inputs.shifted_exp_arrival(0, spec.n)
+    plan = bpx.Plan(_code(spec), arrival, 0, mode, M, K, N, prec)
+    # above the size at which the operands are split
+    inf = plan.info()
+    assert inf["n_computed"] * inf["Mb"] * K * N > 2 ** 31
+    assert plan.workspace_bytes()[0] > plan.workspace_layout()[6]
+    return plan
+
+
+def _view(x, pad):
+    """x in a buffer whose rows are `pad` floats (rounded up to 4) longer."""
+    r, c = x.shape
+    t = torch.full((r, -(-(c + pad) // 4) * 4), float("nan"), device="cuda")
+    t[:, :c] = x
+    return t[:, :c]
+
+
+def _run(plan, A, B, tile=-1, pad=0, ws=None):
+    A, B = _view(A, pad), _view(B, pad)
+    C = _view(torch.full((plan.M, plan.N), float("nan"), device="cuda"), pad)
+    if ws is None:
+        ws = torch.full((plan.workspace_bytes()[0],), 0xA5, dtype=torch.uint8, device="cuda")
+    bpx.force_tile(tile)
+    try:
+        bpx.coded_matmul(plan, A, B, C, ws)
+        torch.cuda.synchronize()
+    finally:
+        bpx.force_tile(-1)
+    return C.clone()
+
+
+def _ops(seed, M, K, N, integer):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    if integer:
+        return (torch.randint(-8, 9, (M, K), generator=g, device="cuda").float(),
+                torch.randint(-8, 9, (K, N), generator=g, device="cuda").float())
+    return (torch.randn((M, K), generator=g, device="cuda"),
+            torch.randn((K, N), generator=g, device="cuda"))
+
+
+def _err(X, R):
+    return float(torch.linalg.norm(X.double() - R) / torch.linalg.norm(R))
+
+
+# M, K, N: one k chunk and a granule past a chunk (the shortest loops), K a
+# multiple of neither stage, blocks and columns of one past a tile, a last
+# round split along K (few tiles) and one that is not (short K), odd N
+SHAPES = [(6000, 16, 30000), (6000, 20, 25000), (6000, 44, 9001), (6000, 64, 7000),
+          (2056, 1000, 1025), (999, 4100, 769), (4104, 1048, 2306)]
+PRECS = [bpx.PREC_F32, bpx.PREC_BF16X3, bpx.PREC_BF16]
+
+
+@pytest.mark.parametrize("prec", PRECS)
+@pytest.mark.parametrize("shape", SHAPES)
+def test_split_planes_exact_and_accurate(shape, prec):
+    M, K, N = shape
+    plan = _plan(inputs.CODE_642, M, K, N, prec, bpx.MODE_FULL)
+    A, B = _ops(1, M, K, N, True)
+    print("planes", shape, prec, file=sys.stderr, flush=True)
+    C = _run(plan, A, B, pad=8)
+    # members' sums of at most 4 x 8 and K products of at most 32 x 8 are exact
+    assert torch.equal(C.double(), A.double() @ B.double())
+    A, B = _ops(2, M, K, N, False)
+    R = A.double() @ B.double()
+    new, old = _run(plan, A, B), _run(plan, A, B, tile=1)
+    print("  error", _err(new, R), "direct kernels", _err(old, R), file=sys.stderr, flush=True)
+    # The same splits in BF16*, so the same error up to the order of the sums
+    # (1e-6 at K = 4100); FP32: dropped plane products (2^-26 of a product) and
+    # fewer roundings than the FP32 matrix instruction's K / 4 per output.
+    assert _err(new, R) <= _err(old, R) * (1.0 if K > 256 else 1.1) + 1e-7
+    assert torch.equal(new, _run(plan, A, B))          # deterministic
+    small = torch.empty(plan.workspace_layout()[6], dtype=torch.uint8, device="cuda")
+    if prec == bpx.PREC_F32:   # a workspace without the planes: the direct kernels
+        assert _err(_run(plan, A, B, ws=small), R) <= 1e-5
+
+
+@pytest.mark.parametrize("shape", [(2048, 1024, 2048), (1999, 1500, 1001)])
+def test_split_planes_leave_out_of_range_values_to_fp32(shape):
+    """Infinities, NaN and values outside the planes' range: the same
+    non-finite outputs as the FP32 kernels and, elsewhere, FP32 accuracy."""
+    M, K, N = shape
+    plan = _plan(inputs.CODE_1284, M, K, N, bpx.PREC_F32)
+    for what in ("inf a", "nan b", "tiny a", "huge b", "max"):
+        A, B = _ops(3, M, K, N, False)
+        if what == "inf a":
+            A[M - 1, K - 1] = float("inf")
+        elif what == "nan b":
+            B[0, N - 1] = float("nan")
+        elif what == "tiny a":                # below the smallest normal number
+            A[5, :] *= 1e-39
+        elif what == "huge b":
+            B[:, 7] *= 2.0 ** 100
+        else:                                 # rounds up to infinity in BF16
+            A[3, 4] = torch.finfo(torch.float32).max
+            B[:, 2] = 2.0 ** -10
+        new, old = _run(plan, A, B), _run(plan, A, B, tile=1)
+        fin = torch.isfinite(old)
+        print("planes range", shape, what, int((~fin).sum()), file=sys.stderr, flush=True)
+        assert torch.equal(torch.isnan(new), torch.isnan(old)), what
+        assert torch.equal(torch.isfinite(new), fin), what
+        R = A.double() @ B.double()
+        scale = torch.linalg.norm(torch.where(fin, R, 0.0), dim=0).clamp_min(1e-300)
+        e = lambda X: float((torch.linalg.norm(torch.where(fin, X.double() - R, 0.0), dim=0) /
+                             scale).max())
+        # per column, since a huge column would hide the others; coded sums mix
+        # rows, so a row with a huge element is as far off as the direct kernels'
+        assert e(new) <= max(e(old) * 1.1, 1e-5), what
+
+
+@pytest.mark.parametrize("exps", [(0, 0), (-60, -40), (-70, -68), (30, 30)])
+def test_split_planes_scale_of_operands(exps):
+    """Operands far from 1 (results down to subnormal numbers) are no further
+    from float64 than the FP32 kernels' results plus one subnormal unit."""
+    M, K, N = 2048, 1024, 2048
+    plan = _plan(inputs.CODE_642, M, K, N, bpx.PREC_F32)
+    A, B = _ops(4, M, K, N, False)
+    A, B = A * 2.0 ** exps[0], B * 2.0 ** exps[1]
+    R = A.double() @ B.double()
+    d = lambda X: float(torch.linalg.norm(X.double() - R))
+    new, old = d(_run(plan, A, B)), d(_run(plan, A, B, tile=1))
+    print("planes scale", exps, new, old, file=sys.stderr, flush=True)
+    assert new <= old + 2.0 ** -149 * np.sqrt(M * N)
