@@ -184,7 +184,8 @@ bpx_status bpx_plan_create(const bpx_code* code, const int32_t* arrival, int32_t
  * grid*Nb, K a multiple of 32) run on 256x256 tiles when the FP32 tile
  * shape is one of the 256x256 ones (the default), other shapes and calls on
  * 64x128 tiles; both sum every product in the same order (identical
- * results).  bpx_encode and grouped launches do not take such plans. */
+ * results).  Products of more than 2^31 multiply-adds over all passes run on
+ * split planes (bpx_coded_gemm).  bpx_encode and grouped launches do not take such plans. */
 bpx_status bpx_plan_create2d(const bpx_code* code, const int32_t* arrival, int32_t n_arrival,
                              int32_t n_lost, int32_t mode, int64_t M, int64_t K, int64_t N,
                              int32_t prec, bpx_plan** out);
@@ -232,8 +233,8 @@ bpx_status bpx_plan_peel_program(const bpx_plan* plan, const int32_t** steps, in
                                  int32_t* n_slots);
 
 /* Device workspace the plan needs for bpx_coded_gemm / bpx_coded_matmul
- * (Y slots and, for FP8, quantised operands and scales; for large row-block
- * F32 / BF16 / BF16x3 products also the operands split into BF16 planes), and
+ * (Y slots and, for FP8, quantised operands and scales; for large F32 / BF16 /
+ * BF16x3 products also the operands split into BF16 planes), and
  * the size of the buffer bpx_encode writes (n_computed coded blocks of
  * Mb x K floats).  A call whose workspace holds the parts of
  * bpx_plan_workspace_layout only is accepted: it runs the kernels that read A
@@ -246,7 +247,7 @@ bpx_status bpx_plan_workspace_bytes(const bpx_plan* plan, size_t* ws_bytes,
  * use has size 0 (its offset equals the next one); entry 6 is the end of
  * these parts (behind it, up to ws_bytes, come the split planes, flags and
  * partial tiles of products of more than 2^31 multiply-adds over the computed
- * symbols; the BF16 planes below are then not written).
+ * symbols and their passes; the BF16 planes below are then not written).
  *   F32:     [0] Y slots, [1] split-K partial tiles: when Mb and N are
  *            multiples of 256, K of 32 and M of Mb, room for min(256, 4 T)
  *            FP32 tiles of 256 x 256 (T = computed symbols x Mb/256 x N/256),

@@ -109,7 +109,12 @@ bpx_status upload(bpx_plan* plan) {
   const size_t b4 = bytes_of(plan->fused_steps.size(), sizeof(PeelStep));
   const size_t b5 = bytes_of(plan->fused_subs.size(), 4);
   const size_t b6 = bytes_of(plan->fused_ytile.size(), 4);
-  const size_t total = std::max<size_t>(b0 + b1 + b2 + b3 + b4 + b5 + b6, 256);
+  std::vector<int32_t> ops;
+  for (const std::vector<int32_t>* v : {&plan->ops.a_ops, &plan->ops.b_ops, &plan->ops.ids,
+                                        &plan->ops.sym_passes, &plan->ops.passes})
+    ops.insert(ops.end(), v->begin(), v->end());
+  const size_t b7 = bytes_of(ops.size(), 4);
+  const size_t total = std::max<size_t>(b0 + b1 + b2 + b3 + b4 + b5 + b6 + b7, 256);
   std::string host(total, '\0');
   std::memcpy(&host[0], plan->gemm_syms.data(), plan->gemm_syms.size() * 4);
   std::memcpy(&host[b0], plan->gemm_ids.data(), plan->gemm_ids.size() * 4);
@@ -121,6 +126,8 @@ bpx_status upload(bpx_plan* plan) {
               plan->fused_subs.size() * 4);
   std::memcpy(&host[b0 + b1 + b2 + b3 + b4 + b5], plan->fused_ytile.data(),
               plan->fused_ytile.size() * 4);
+  if (!ops.empty())
+    std::memcpy(&host[b0 + b1 + b2 + b3 + b4 + b5 + b6], ops.data(), ops.size() * 4);
   void* d = nullptr;
   e = hipMalloc(&d, total);
   if (e != hipSuccess) return hip_fail(e, "hipMalloc(plan tables)");
@@ -139,6 +146,7 @@ bpx_status upload(bpx_plan* plan) {
   plan->d_fused_steps = reinterpret_cast<const PeelStep*>(base + b0 + b1 + b2 + b3);
   plan->d_fused_subs = reinterpret_cast<const int32_t*>(base + b0 + b1 + b2 + b3 + b4);
   plan->d_fused_ytile = reinterpret_cast<const int32_t*>(base + b0 + b1 + b2 + b3 + b4 + b5);
+  plan->d_ops = reinterpret_cast<const int32_t*>(base + b0 + b1 + b2 + b3 + b4 + b5 + b6);
   return BPX_OK;
 }
 
@@ -198,6 +206,20 @@ bpx_status gemm_planes_impl(bpx_plan* plan, GemmParams p, void* ws, hipStream_t 
   q.part = reinterpret_cast<float*>(w + off[4]);
   q.part_tiles = plan->plane_part_tiles();
   q.kc = (int32_t)plan->plane_kc();
+  q.rows32 = (int32_t)(plan->plane_rows() / 32);
+  q.cols64 = (int32_t)(plan->plane_cols() / 64);
+  q.grid = plan->grid;
+  q.Nb = plan->Nb;
+  if (plan->grid > 1) {
+    q.a_ops = plan->d_ops;
+    q.b_ops = q.a_ops + plan->ops.a_ops.size();
+    q.op_ids = q.b_ops + plan->ops.b_ops.size();
+    q.sym_passes = q.op_ids + plan->ops.ids.size();
+    q.passes = q.sym_passes + plan->ops.sym_passes.size();
+    q.n_passes = (int32_t)plan->n_products();
+    for (size_t i = 1; i < plan->ops.sym_passes.size(); i += 2)
+      q.n_single += plan->ops.sym_passes[i] == 1;
+  }
   hipError_t e = launch_pack_planes(q, stream);
   if (e == hipSuccess) e = launch_gemm_planes(q, stream);
   if (e == hipSuccess && q.planes == 3) {
@@ -205,7 +227,10 @@ bpx_status gemm_planes_impl(bpx_plan* plan, GemmParams p, void* ws, hipStream_t 
     p.fb = q.fb;
     p.nka = (q.kc + 15) / 16;
     p.nkb = (q.kc + 3) / 4;
-    e = launch_coded_gemm(p, choose_tile(plan->prec, plan->Mb, plan->N, plan->K), stream);
+    p.sym_passes = q.sym_passes;
+    p.passes = q.passes;
+    const int32_t tile = choose_tile(plan->prec, plan->Mb, plan->N, plan->K);
+    e = plan->grid > 1 ? launch_coded_gemm_2d(p, tile, stream) : launch_coded_gemm(p, tile, stream);
   }
   if (e != hipSuccess) return hip_fail(e, "split-plane gemm launch");
   return BPX_OK;
@@ -245,17 +270,19 @@ bpx_status gemm_impl(bpx_plan* plan, const float* A, int64_t lda, const float* B
   // 32-bit offsets.
   if ((plan->Mb + 256) * lda >= ((int64_t)1 << 30) || 64 * ldb + plan->N >= ((int64_t)1 << 30))
     return fail(BPX_E_UNSUPPORTED, "block too large for 32-bit tile offsets");
+  if (plan->grid > 1) {
+    p.grid = plan->grid;
+    p.Nb = plan->Nb;
+    if (!gemm_2d_fits(p))
+      return fail(BPX_E_UNSUPPORTED, "block too large for 32-bit buffer offsets");
+  }
   if (plan->has_planes() && ws_bytes >= plan->ws_bytes() &&
       !tile_chosen(plan->prec, plan->Mb, plan->N, plan->K))
     return gemm_planes_impl(plan, p, ws, stream);
   const int32_t tile = choose_tile(plan->prec, plan->Mb, plan->N, plan->K);
   hipError_t e;
   if (plan->grid > 1) {
-    p.grid = plan->grid;
-    p.Nb = plan->Nb;
     e = launch_coded_gemm_2d(p, tile, stream);
-    if (e == hipErrorInvalidValue)
-      return fail(BPX_E_UNSUPPORTED, "block too large for 32-bit buffer offsets");
   } else if (plan->is_fp8()) {
     size_t off[7];
     plan->layout(off);

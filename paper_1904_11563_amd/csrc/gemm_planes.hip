@@ -23,6 +23,11 @@
 // an FP32 launch (gemm_f32.hip) computes it, which also keeps the results for
 // infinities and NaN those of FP32 arithmetic.
 //
+// The two-dimensional form packs the distinct sums of A row blocks and of B
+// column blocks once each, and a tile runs over all passes of its symbol, the
+// K-concatenated product of a gray symbol being one longer loop: 8192^3,
+// (12,8,2) on the 4 x 4 grid, 37 passes: 22.9 -> 10.8 ms per call.
+//
 // Packed layout: MFMA fragments.  For every 32 rows of the stacked coded
 // rows (or columns of B) and 16 k there is 1 KiB per plane: lane l's eight
 // values, row l % 32, k 8 (l / 32) .. +7.  The planes of one k chunk follow
@@ -32,6 +37,7 @@
 // read is lane-linear (no bank conflicts, no swizzle).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "kernels.hpp"
@@ -92,19 +98,21 @@ __device__ __forceinline__ bool out_of_range(const float (&x)[8]) {
 // issued together, and the planes leave as whole 128-byte lines (8 rows of a
 // fragment), so nothing goes through LDS.  8192 x 8192 (12,8,4): A and B
 // packed in 245 us, 0.98 GB read and 0.65 GB written at 6.7 TB/s.
-template <int P>
+template <int P, bool GRID>
 __device__ __forceinline__ void pack_a_block(const PlaneParams& p, int b, int tid) {
   const int rp = b / p.nka, kb = b - rp * p.nka;
   const int lane = tid & 63, wave = tid >> 6;
   const int r = wave * 8 + (lane >> 3), g8 = (lane & 7) * 8;
   const unsigned gr = (unsigned)rp * 32u + (unsigned)r;
+  // the op (symbol) of the row, and the row of its blocks
   const int Mb = (int)p.Mb;
-  int deg = 0, id_off = 0, lr = 0;
-  if (gr < (unsigned)p.n_sym * (unsigned)Mb) {
-    const int si = (int)(gr / (unsigned)Mb);
-    lr = (int)gr - si * Mb;
-    id_off = gld(p.syms + 4 * si + 0);
-    deg = gld(p.syms + 4 * si + 1);
+  const unsigned per = GRID ? (unsigned)p.tiles_m * 256u : (unsigned)Mb;
+  const int32_t* ids = GRID ? p.op_ids : p.ids;
+  const int op = (int)(gr / per), lr = (int)(gr - (unsigned)op * per);
+  int deg = 0, id_off = 0;
+  if (GRID ? lr < Mb : op < p.n_sym) {
+    id_off = gld(GRID ? p.a_ops + 2 * op : p.syms + 4 * op);
+    deg = gld(GRID ? p.a_ops + 2 * op + 1 : p.syms + 4 * op + 1);
   }
   const int K = (int)p.K, Kp = p.kc * 16;
   const int k0 = kb * 256 + g8;
@@ -112,7 +120,7 @@ __device__ __forceinline__ void pack_a_block(const PlaneParams& p, int b, int ti
 #pragma unroll
   for (int i = 0; i < 4; ++i) s[i][0] = s[i][1] = v4f{0.f, 0.f, 0.f, 0.f};
   for (int m = 0; m < deg; ++m) {
-    const int64_t row = (int64_t)gld(p.ids + id_off + m) * Mb + lr;
+    const int64_t row = (int64_t)gld(ids + id_off + m) * Mb + lr;
     if (row >= p.M) continue;
     const float* src = p.A + row * p.lda;
     v4f v[4][2];
@@ -152,26 +160,29 @@ __device__ __forceinline__ void pack_a_block(const PlaneParams& p, int b, int ti
 
 // 64 k x 64 columns of B, transposed through LDS: rows of 64 floats written
 // 16 bytes per lane and read 4 bytes per lane along n, both conflict-free.
-template <int P>
+template <int P, bool GRID>
 __device__ __forceinline__ void pack_b_block(const PlaneParams& p, int b, int tid, float* t) {
-  const int tn = p.tiles_n * 4;
-  const int kb = b / tn, nb = b - kb * tn;
-  const int64_t n0 = (int64_t)nb * 64, k0 = (int64_t)kb * 64;
-  const int64_t N = p.N, K = p.K;
+  const int kb = b / p.cols64, nb = b - kb * p.cols64;
+  const int64_t k0 = (int64_t)kb * 64, K = p.K, Nb = p.Nb;
+  // the op of the columns (in the row-block form B itself)
+  const int per = p.tiles_n * 4, op = GRID ? nb / per : 0;
+  const int64_t n0 = (int64_t)(nb - op * per) * 64;
+  const int id_off = GRID ? p.b_ops[2 * op] : 0, deg = GRID ? p.b_ops[2 * op + 1] : 1;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int f = tid + 256 * i;
     const int kr = f >> 4, nc = (f & 15) * 4;
     const int64_t k = k0 + kr, n = n0 + nc;
     v4f v = {0.f, 0.f, 0.f, 0.f};
-    if (k < K) {
-      const float* src = p.B + k * p.ldb + n;
-      if (n + 3 < N) {
-        v = *(const gv4f*)src;
+    for (int m = 0; m < deg; ++m) {
+      if (k >= K) break;
+      const float* src = p.B + k * p.ldb + (GRID ? p.op_ids[id_off + m] * Nb : 0) + n;
+      if (n + 3 < Nb) {
+        v += *(const gv4f*)src;
       } else {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          if (n + e < N) v[e] = src[e];
+          if (n + e < Nb) v[e] += src[e];
       }
     }
     *reinterpret_cast<v4f*>(t + kr * 64 + nc) = v;
@@ -200,14 +211,14 @@ __device__ __forceinline__ void pack_b_block(const PlaneParams& p, int b, int ti
   }
 }
 
-template <int P>
+template <int P, bool GRID>
 __global__ __launch_bounds__(256) void pack_planes_kernel(PlaneParams p) {
   __shared__ __attribute__((aligned(16))) float t[64 * 64];
-  const int b = blockIdx.x;
-  if (b < p.blocks_b)
-    pack_b_block<P>(p, b, threadIdx.x, t);
+  const int b = blockIdx.x, blocks_b = p.cols64 * p.nkb;
+  if (b < blocks_b)
+    pack_b_block<P, GRID>(p, b, threadIdx.x, t);
   else
-    pack_a_block<P>(p, b - p.blocks_b, threadIdx.x);
+    pack_a_block<P, GRID>(p, b - blocks_b, threadIdx.x);
 }
 
 // ------------------------------------------------------------------ GEMM --
@@ -304,8 +315,20 @@ __device__ __forceinline__ void copy_panel(v4i rsrc, int lds, int voff, int soff
 
 // Tile order: groups of 8 row panels, column panel by column panel, so the 32
 // tiles an XCD runs at once share 8 row panels and 4 column panels in its L2.
-__device__ __forceinline__ void tile_at(const PlaneParams& p, int lin, int* mt, int* nt) {
-  constexpr int kRowGroup = 8;
+// In the two-dimensional form one symbol comes after the other, and an eighth
+// of each goes to each XCD, in groups of 4 row panels (whole ranges of 32
+// tiles per XCD gave some XCDs more of the long symbols: 12.2 against 10.8 ms
+// for the 8192^3 workload's call).
+template <bool GRID>
+__device__ __forceinline__ void tile_at(const PlaneParams& p, int lin, int* si, int* mt, int* nt) {
+  constexpr int kRowGroup = GRID ? 4 : 8;
+  *si = 0;
+  if (GRID) {
+    const int per_sym = p.tiles_m * p.tiles_n;
+    *si = lin / per_sym;
+    lin -= *si * per_sym;
+    if ((per_sym & 7) == 0) lin = (lin & 7) * (per_sym >> 3) + (lin >> 3);
+  }
   const int per_group = kRowGroup * p.tiles_n;
   const int first = lin / per_group * kRowGroup;
   const int gsz = p.tiles_m - first < kRowGroup ? p.tiles_m - first : kRowGroup;
@@ -314,18 +337,25 @@ __device__ __forceinline__ void tile_at(const PlaneParams& p, int lin, int* mt, 
   *nt = r / gsz;
 }
 
-// Where stacked row gr of the coded products goes (null: nowhere).
-__device__ __forceinline__ float* out_row(const PlaneParams& p, unsigned gr) {
-  if (gr >= (unsigned)p.n_sym * (unsigned)p.Mb) return nullptr;
-  const int si = (int)(gr / (unsigned)p.Mb);
-  const int64_t lr = (int64_t)gr - (int64_t)si * p.Mb;
+// Where row r of the coded products goes (null: nowhere): of the stacked rows
+// of all symbols, or of symbol si's product in the two-dimensional form.
+template <bool GRID>
+__device__ __forceinline__ float* out_row(const PlaneParams& p, int si, unsigned r) {
+  if (!GRID) {
+    if (r >= (unsigned)p.n_sym * (unsigned)p.Mb) return nullptr;
+    si = (int)(r / (unsigned)p.Mb);
+    r -= (unsigned)si * (unsigned)p.Mb;
+  } else if (r >= (unsigned)p.Mb) {
+    return nullptr;
+  }
   const int dest = gld(p.syms + 4 * si + 2);
-  if (dest >= 0) return p.Y + ((int64_t)dest * p.Mb + lr) * p.N;
-  const int64_t row = (-1 - (int64_t)dest) * p.Mb + lr;
-  return row < p.M ? p.C + row * p.ldc : nullptr;
+  if (dest >= 0) return p.Y + ((int64_t)dest * p.Mb + r) * p.Nb;
+  const int s = -1 - dest, br = GRID ? s / p.grid : s;
+  const int64_t row = (int64_t)br * p.Mb + r;
+  return row < p.M ? p.C + row * p.ldc + (int64_t)(s - br * p.grid) * (GRID ? p.Nb : 0) : nullptr;
 }
 
-template <int P>
+template <int P, bool GRID>
 __global__ __launch_bounds__(NT) void gemm_planes_kernel(PlaneParams p) {
   using C_ = Cfg<P>;
   constexpr int STEPS = C_::STEPS, NBUF = C_::NBUF;
@@ -339,48 +369,77 @@ __global__ __launch_bounds__(NT) void gemm_planes_kernel(PlaneParams p) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 2, wn = wave & 3;
 
-  int lin, kt0 = 0, kt1 = p.kc / STEPS, piece = -1;
-  if ((int)blockIdx.x < p.full) {
-    lin = xcd_remap(blockIdx.x, p.full);
-  } else {
-    piece = (int)blockIdx.x - p.full;
-    const int s = piece % p.split;
+  // The tile and its stages: all of its passes over K, or one piece of them.
+  // Row blocks give each XCD one contiguous range of tiles; in the
+  // two-dimensional form, whose symbols come longest first, each XCD takes its
+  // share of every symbol (tile_at).
+  int lin = (int)blockIdx.x, piece = -1;
+  if (lin >= p.full) {
+    piece = lin - p.full;
     lin = p.full + piece / p.split;
-    const int nk = kt1;
-    kt0 = s * nk / p.split;
-    kt1 = (s + 1) * nk / p.split;
+  } else if (!GRID) {
+    lin = xcd_remap(lin, p.full);
   }
-  int mt, nt;
-  tile_at(p, lin, &mt, &nt);
+  int si, mt, nt;
+  tile_at<GRID>(p, lin, &si, &mt, &nt);
+  const int nk1 = p.kc / STEPS;  // stages of one pass
+  const int32_t* passes = GRID ? p.passes + 2 * p.sym_passes[2 * si] : nullptr;
+  const int n_pass = GRID ? p.sym_passes[2 * si + 1] : 1;
+  int kt0 = 0, kt1 = nk1 * n_pass;
+  if (piece >= 0) {
+    const int s = piece % p.split, n = kt1;
+    kt0 = (int)((int64_t)s * n / p.split);
+    kt1 = (int)((int64_t)(s + 1) * n / p.split);
+  }
 
   // wave w copies panels 2w, 2w+1 of the stage: waves 0-3 A, 4-7 B
   const int64_t rp_stride = (int64_t)p.kc * P * 1024;
-  const char* src = (wave < 4 ? reinterpret_cast<const char*>(p.ap) + (int64_t)mt * 8 * rp_stride
-                              : reinterpret_cast<const char*>(p.bp) + (int64_t)nt * 8 * rp_stride);
-  v4i rsrc = {(int)(reinterpret_cast<uint64_t>(src)),
-              (int)(reinterpret_cast<uint64_t>(src) >> 32) & 0xffff, (int)(8 * rp_stride),
-              kRsrcWord3};
+  int pass = 0, kp = kt0;  // the next stage to copy
+  v4i rsrc;
+  auto set_pass = [&]() __attribute__((always_inline)) {
+    int64_t panel = wave < 4 ? mt : nt;
+    if (GRID)
+      panel += wave < 4 ? (int64_t)passes[2 * pass] * p.tiles_m
+                        : (int64_t)passes[2 * pass + 1] * p.tiles_n;
+    const uint64_t src =
+        reinterpret_cast<uint64_t>(wave < 4 ? p.ap : p.bp) + (uint64_t)(panel * 8 * rp_stride);
+    rsrc = v4i{(int)src, (int)(src >> 32) & 0xffff, (int)(8 * rp_stride), kRsrcWord3};
 #pragma unroll
-  for (int c = 0; c < 4; ++c) rsrc[c] = __builtin_amdgcn_readfirstlane(rsrc[c]);
+    for (int c = 0; c < 4; ++c) rsrc[c] = __builtin_amdgcn_readfirstlane(rsrc[c]);
+  };
+  if (GRID) {
+    pass = kt0 / nk1;
+    kp = kt0 - pass * nk1;
+  }
+  set_pass();
   const int soff0 = (wave & 3) * 2 * (int)rp_stride;
   const int voff = lane * 16;
   const int lds0 = (int)(uintptr_t)(lds_addr)lds + 2 * wave * RPB;
-  auto dma = [&](int st, int kt) __attribute__((always_inline)) {
+  auto dma = [&](int st) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < 2; ++u)
-      copy_panel<STEPS * P>(rsrc, lds0 + st + u * RPB, voff, soff0 + u * (int)rp_stride + kt * RPB);
+      copy_panel<STEPS * P>(rsrc, lds0 + st + u * RPB, voff, soff0 + u * (int)rp_stride + kp * RPB);
+    ++kp;
+    if (GRID && kp == nk1) {
+      kp = 0;
+      if (++pass < n_pass) set_pass();
+    }
   };
 
   const int nk = kt1 - kt0;
 #pragma unroll
   for (int i = 0; i < NBUF; ++i)
-    if (i < nk) dma(i * STAGE, kt0 + i);
+    if (i < nk) dma(i * STAGE);
 
-  if (tid < 256) rows[tid] = out_row(p, (unsigned)mt * 256u + (unsigned)tid);
+  if (tid < 256) rows[tid] = out_row<GRID>(p, si, (unsigned)mt * 256u + (unsigned)tid);
   if (P == 3) {
     unsigned bad = 0;
-    for (int i = tid; i < 8 * p.nka; i += NT) bad |= p.fa[(int64_t)mt * 8 * p.nka + i];
-    for (int i = tid; i < 4 * p.nkb; i += NT) bad |= p.fb[(int64_t)nt * 4 * p.nkb + i];
+    for (int i = 0; i < n_pass; ++i) {
+      const int64_t pa = GRID ? (int64_t)passes[2 * i] * p.tiles_m + mt : mt;
+      const int64_t pb = GRID ? (int64_t)passes[2 * i + 1] * p.tiles_n + nt : nt;
+      for (int t = tid; t < 8 * p.nka; t += NT) bad |= p.fa[pa * 8 * p.nka + t];
+      for (int t = tid; t < 4 * p.nkb; t += NT) bad |= p.fb[pb * 4 * p.nkb + t];
+    }
     if (__syncthreads_or((int)bad)) {
       wait_counts<0, false>();
       return;
@@ -458,7 +517,7 @@ __global__ __launch_bounds__(NT) void gemm_planes_kernel(PlaneParams p) {
       turn(kt);
       read_a(f, T, 0, 1);
       read_b(f, T, 0, 1);
-      if (kt + NBUF < nk) dma(cur, kt0 + kt + NBUF);
+      if (kt + NBUF < nk) dma(cur);
       __builtin_amdgcn_sched_barrier(0);
       mul(f, I0{}, I2{});
       mul(f, I2{}, I0{});
@@ -493,7 +552,7 @@ __global__ __launch_bounds__(NT) void gemm_planes_kernel(PlaneParams p) {
       __builtin_amdgcn_sched_barrier(0);
       turn(kt);
       read(f0, lds + nxt, 0);
-      if (kt + NBUF < nk) dma(cur, kt0 + kt + NBUF);
+      if (kt + NBUF < nk) dma(cur);
       __builtin_amdgcn_sched_barrier(0);
       step(f1);
       __builtin_amdgcn_sched_barrier(0);
@@ -525,49 +584,51 @@ __global__ __launch_bounds__(NT) void gemm_planes_kernel(PlaneParams p) {
       if (!out) continue;
 #pragma unroll
       for (int j = 0; j < 2; ++j)
-        if (n0 + 32 * j < p.N) out[n0 + 32 * j] = acc[i][j][e];
+        if (n0 + 32 * j < p.Nb) out[n0 + 32 * j] = acc[i][j][e];
     }
 }
 
 // Sums the pieces of each split tile, 64 blocks per tile, one float4 per
 // thread, in piece order (fixed, so results do not depend on scheduling).
+template <bool GRID>
 __global__ __launch_bounds__(256) void planes_reduce_kernel(PlaneParams p) {
   const int t = blockIdx.x >> 6;
   const int e = ((blockIdx.x & 63) << 8) + threadIdx.x;
   const int row = e >> 6, col = (e & 63) * 4;
-  int mt, nt;
-  tile_at(p, p.full + t, &mt, &nt);
-  float* out = out_row(p, (unsigned)mt * 256u + (unsigned)row);
+  int si, mt, nt;
+  tile_at<GRID>(p, p.full + t, &si, &mt, &nt);
+  float* out = out_row<GRID>(p, si, (unsigned)mt * 256u + (unsigned)row);
   const int64_t n = (int64_t)nt * 256 + col;
-  if (!out || n >= p.N) return;
+  if (!out || n >= p.Nb) return;
   const float* src = p.part + (int64_t)t * p.split * 65536 + row * 256 + col;
   v4f sum = *reinterpret_cast<const v4f*>(src);
   for (int k = 1; k < p.split; ++k)
     sum += *reinterpret_cast<const v4f*>(src + (int64_t)k * 65536);
 #pragma unroll
   for (int c = 0; c < 4; ++c)
-    if (n + c < p.N) out[n + c] = sum[c];
+    if (n + c < p.Nb) out[n + c] = sum[c];
 }
 
 }  // namespace
 
 namespace {
 void set_tiles(PlaneParams* p) {
-  p->tiles_m = (int32_t)(((int64_t)p->n_sym * p->Mb + 255) / 256);
-  p->tiles_n = (int32_t)((p->N + 255) / 256);
+  const int64_t rows = p->grid > 1 ? p->Mb : (int64_t)p->n_sym * p->Mb;
+  p->tiles_m = (int32_t)((rows + 255) / 256);
+  p->tiles_n = (int32_t)((p->Nb + 255) / 256);
   p->nka = (p->kc + 15) / 16;
   p->nkb = (p->kc + 3) / 4;
-  p->blocks_b = p->tiles_n * 4 * p->nkb;
 }
 }  // namespace
 
 hipError_t launch_pack_planes(const PlaneParams& p0, hipStream_t stream) {
   PlaneParams p = p0;
   set_tiles(&p);
-  const unsigned blocks = (unsigned)p.blocks_b + (unsigned)p.tiles_m * 8u * (unsigned)p.nka;
-  void (*k)(PlaneParams) = p.planes == 3   ? pack_planes_kernel<3>
-                           : p.planes == 2 ? pack_planes_kernel<2>
-                                           : pack_planes_kernel<1>;
+  const unsigned blocks = (unsigned)p.cols64 * (unsigned)p.nkb + (unsigned)p.rows32 * (unsigned)p.nka;
+  void (*k)(PlaneParams) = p.grid > 1      ? pack_planes_kernel<3, true>
+                           : p.planes == 3 ? pack_planes_kernel<3, false>
+                           : p.planes == 2 ? pack_planes_kernel<2, false>
+                                           : pack_planes_kernel<1, false>;
   hipLaunchKernelGGL(k, dim3(blocks), dim3(256), 0, stream, p);
   return hipGetLastError();
 }
@@ -575,22 +636,29 @@ hipError_t launch_pack_planes(const PlaneParams& p0, hipStream_t stream) {
 hipError_t launch_gemm_planes(const PlaneParams& p0, hipStream_t stream) {
   PlaneParams p = p0;
   set_tiles(&p);
-  const int64_t T = (int64_t)p.tiles_m * p.tiles_n, S = device_cu_count();
+  const int64_t T = (int64_t)p.tiles_m * p.tiles_n * (p.grid > 1 ? p.n_sym : 1);
+  const int64_t S = device_cu_count();
   if (T > 0x7fffffff / 32) return hipErrorInvalidValue;
-  // The last round: R = T mod S tiles (all of them when there are fewer than
-  // CUs), each split into q pieces of its K range whose partial tiles a second
-  // kernel sums, where a model of both says that ends sooner: rounds of
-  // pieces at the measured time of a 16-wide k chunk of one tile, 6 us for
-  // the second launch and 0.125 us per partial tile written and read back
-  // (4 TB/s).  1999 x 1500 x 1001, 36 tiles: 14 pieces, GEMM 43 and sum 11
-  // us, where whole tiles would take 140 us.
-  const int64_t R = T % S;
+  // The last round: R of the tiles, each split into q pieces of its K range
+  // whose partial tiles a second kernel sums, where a model of both says that
+  // ends sooner: rounds of pieces at the measured time of a 16-wide k chunk of
+  // one tile, 6 us for the second launch and 0.125 us per partial tile written
+  // and read back (4 TB/s).  1999 x 1500 x 1001, 36 tiles: 14 pieces, GEMM 43
+  // and sum 11 us, where whole tiles would take 140 us.  R is what the products
+  // of all tiles leave over after whole rounds (everything if that is less
+  // than one round); in the two-dimensional form only one-pass tiles, which
+  // come last, can fill up a round.
+  const int64_t per = p.grid > 1 ? T / p.n_sym : 1;
+  const int64_t units = p.grid > 1 ? p.n_passes * per : T;
+  const int64_t R = units <= S ? T
+                    : p.grid > 1 ? std::min(units % S, p.n_single * per) : T % S;
+  const int64_t ru = units <= S ? units : R;
   const double us = p.planes == 3 ? 1.45 : p.planes == 2 ? 0.75 : 0.35;
   int64_t best_q = 1;
   double best = p.kc * us;
   for (int64_t q = 2; q <= 16 && R > 0; ++q) {
     if (R * q > p.part_tiles || p.kc / q < 8) break;
-    const double t = (double)((R * q + S - 1) / S) * (double)p.kc * us / (double)q + 6.0 +
+    const double t = (double)((ru * q + S - 1) / S) * (double)p.kc * us / (double)q + 6.0 +
                      0.125 * (double)(R * q);
     if (t < best) {
       best = t;
@@ -600,14 +668,15 @@ hipError_t launch_gemm_planes(const PlaneParams& p0, hipStream_t stream) {
   p.split = (int32_t)best_q;
   p.full = (int32_t)(best_q > 1 ? T - R : T);
   const unsigned blocks = (unsigned)(p.full + (T - p.full) * best_q);
-  void (*k)(PlaneParams) = p.planes == 3   ? gemm_planes_kernel<3>
-                           : p.planes == 2 ? gemm_planes_kernel<2>
-                                           : gemm_planes_kernel<1>;
+  void (*k)(PlaneParams) = p.grid > 1      ? gemm_planes_kernel<3, true>
+                           : p.planes == 3 ? gemm_planes_kernel<3, false>
+                           : p.planes == 2 ? gemm_planes_kernel<2, false>
+                                           : gemm_planes_kernel<1, false>;
   hipLaunchKernelGGL(k, dim3(blocks), dim3(NT), 0, stream, p);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || p.full == T) return e;
-  hipLaunchKernelGGL(planes_reduce_kernel, dim3((unsigned)((T - p.full) * 64)), dim3(256), 0,
-                     stream, p);
+  hipLaunchKernelGGL(p.grid > 1 ? planes_reduce_kernel<true> : planes_reduce_kernel<false>,
+                     dim3((unsigned)((T - p.full) * 64)), dim3(256), 0, stream, p);
   return hipGetLastError();
 }
 

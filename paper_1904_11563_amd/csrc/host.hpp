@@ -34,6 +34,17 @@ struct PeelStep {
   int32_t bcol;     // block column of s (0 for row blocks)
 };
 
+// Operands of a two-dimensional plan's products on split planes: the distinct
+// sums of A row blocks (a_ops) and of B column blocks (b_ops) its symbols
+// need, each {offset, count} into ids (ascending blocks), and per GEMM-table
+// symbol its passes, {A op, B op} each: one pass for a symbol whose members
+// share a block, one per member for any other.
+struct PlaneOps {
+  std::vector<int32_t> a_ops, b_ops, ids;  // {offset, count}
+  std::vector<int32_t> sym_passes;         // {first pass, passes}
+  std::vector<int32_t> passes;             // {A op, B op}
+};
+
 struct bpx_plan {
   // copy of the code (a plan outlives nothing it does not own)
   bpx_code code;
@@ -73,6 +84,8 @@ struct bpx_plan {
   std::vector<int32_t> fused_ytile;
   int32_t n_ytiles = 0;
 
+  PlaneOps ops;  // grid > 1
+
   // device copies
   void* dev_block = nullptr;
   int32_t dev_id = -1;
@@ -83,6 +96,7 @@ struct bpx_plan {
   const PeelStep* d_fused_steps = nullptr;
   const int32_t* d_fused_subs = nullptr;
   const int32_t* d_fused_ytile = nullptr;
+  const int32_t* d_ops = nullptr;  // PlaneOps: a_ops, b_ops, ids, sym_passes, passes
 
   size_t y_bytes() const { return (size_t)n_yslots * (size_t)Mb * (size_t)Nb * sizeof(float); }
   // K rounded up to the BF16 kernels' 32-wide k step
@@ -156,14 +170,29 @@ struct bpx_plan {
   }
   // 16-wide k chunks of the packed operands, whole stages of the GEMM
   int64_t plane_kc() const { return planes() == 3 ? (K + 15) / 16 : (K + 31) / 32 * 2; }
-  int64_t plane_rows() const { return ((int64_t)computed.size() * Mb + 255) / 256 * 256; }
-  int64_t plane_cols() const { return (N + 255) / 256 * 256; }
+  static int64_t r256(int64_t x) { return (x + 255) / 256 * 256; }
+  int64_t plane_rows() const {
+    return grid > 1 ? (int64_t)(ops.a_ops.size() / 2) * r256(Mb)
+                    : r256((int64_t)computed.size() * Mb);
+  }
+  int64_t plane_cols() const {
+    return grid > 1 ? (int64_t)(ops.b_ops.size() / 2) * r256(Nb) : r256(N);
+  }
+  // Products of Mb x K and K x Nb blocks the computed symbols take.
+  int64_t n_products() const {
+    return grid > 1 ? (int64_t)ops.passes.size() / 2 : (int64_t)computed.size();
+  }
+  int64_t plane_tiles() const {
+    return grid > 1 ? (int64_t)computed.size() * (r256(Mb) / 256) * (r256(Nb) / 256)
+                    : plane_rows() / 256 * (plane_cols() / 256);
+  }
   bool has_planes() const {
-    if (grid != 1 || is_fp8() || K % 4 != 0) return false;
-    const double macs = (double)computed.size() * (double)Mb * (double)K * (double)N;
+    if (is_fp8() || K % 4 != 0) return false;
+    const double macs = (double)n_products() * (double)Mb * (double)K * (double)Nb;
     const int64_t lim = (int64_t)1 << 31;
     return macs > 2147483648.0 && plane_rows() < lim && plane_cols() < lim &&
-           plane_kc() * planes() * 8192 < lim &&
+           (double)n_products() * (double)plane_kc() < (double)lim &&
+           plane_kc() * planes() * 8192 < lim && plane_tiles() < lim / 32 &&
            plane_rows() / 32 * ((plane_kc() + 15) / 16) + plane_cols() / 64 * ((plane_kc() + 3) / 4) <
                lim;
   }
@@ -185,7 +214,7 @@ struct bpx_plan {
     off[5] = b;
   }
   int32_t plane_part_tiles() const {
-    const int64_t t = plane_rows() / 256 * (plane_cols() / 256) * 16;
+    const int64_t t = plane_tiles() * 16;
     return t < kPartTiles ? (int32_t)t : kPartTiles;
   }
   size_t ws_bytes() const {

@@ -55,6 +55,9 @@ struct GemmParams {
   const unsigned* fa;
   const unsigned* fb;
   int32_t nka, nkb;
+  // ... of a two-dimensional product (PlaneParams)
+  const int32_t* sym_passes;
+  const int32_t* passes;
 };
 
 // FP8 path (see gemm_fp8.hip for the workspace layout).
@@ -122,6 +125,9 @@ int32_t gemm_tile_count();
 TileShape gemm_tile_shape(int32_t t);
 
 hipError_t launch_coded_gemm(const GemmParams& p, int32_t tile, hipStream_t stream);
+// Whether a product's blocks are small enough for the two-dimensional
+// kernels' 32-bit offsets.
+bool gemm_2d_fits(const GemmParams& p);
 // FP32 coded GEMM of the two-dimensional form (64 x 128 tiles).
 // tile: the FP32 tile shape chosen for the call; the 256 x 256 shapes (4-6)
 // take the wide 2-D kernel where the blocks allow it, others 64 x 128.
@@ -153,10 +159,21 @@ struct PlaneParams {
   float* part;         // partial 256 x 256 tiles of the last round
   int32_t part_tiles;  // how many part holds
   int32_t kc;          // 16-wide k chunks of the packed operands
+  int32_t rows32, cols64;  // 32-row panels of ap, 64-column pack blocks of bp
+  // Two-dimensional form (grid > 1): ap and bp hold the distinct sums of A row
+  // blocks and of B column blocks the symbols need, op by op, every op padded
+  // to 256 rows or columns; see PlaneOps in host.hpp for the tables.
+  int32_t grid;
+  int64_t Nb;
+  const int32_t* a_ops;   // {id offset, degree} per op
+  const int32_t* b_ops;
+  const int32_t* op_ids;
+  const int32_t* sym_passes;  // {first pass, passes} per symbol
+  const int32_t* passes;      // {A op, B op} per pass
+  int32_t n_passes, n_single;  // passes of all symbols; symbols with one
   // set by the launcher
-  int32_t tiles_m, tiles_n;
+  int32_t tiles_m, tiles_n;   // per symbol in the two-dimensional form
   int32_t nka, nkb;    // pack blocks along k of A (256 wide) and of B (64 wide)
-  int32_t blocks_b;
   int32_t full, split; // tiles computed whole; K pieces of each of the others
 };
 hipError_t launch_pack_planes(const PlaneParams& p, hipStream_t stream);

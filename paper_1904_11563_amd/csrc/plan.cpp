@@ -9,6 +9,7 @@
 // the id directly.
 #include <algorithm>
 #include <functional>
+#include <map>
 #include <numeric>
 
 #include "host.hpp"
@@ -233,6 +234,48 @@ int make_plan(const bpx_code& code, const int32_t* arrival, int32_t n_arrival, i
     plan->gemm_syms.push_back(g);
     for (int32_t e = code.sym_ptr[g]; e < code.sym_ptr[g + 1]; ++e)
       plan->gemm_ids.push_back(code.sym_data[e]);
+  }
+
+  plan->ops = PlaneOps();
+  if (plan->grid > 1) {
+    // Operands of the products: sums are shared by every symbol that needs
+    // the same blocks.
+    const int32_t G = plan->grid;
+    PlaneOps& o = plan->ops;
+    std::map<std::vector<int32_t>, int32_t> a_of, b_of;
+    auto op = [&](std::map<std::vector<int32_t>, int32_t>& seen, std::vector<int32_t>& ops,
+                  const std::vector<int32_t>& blocks) {
+      const auto it = seen.emplace(blocks, (int32_t)(ops.size() / 2));
+      if (it.second) {
+        ops.push_back((int32_t)o.ids.size());
+        ops.push_back((int32_t)blocks.size());
+        o.ids.insert(o.ids.end(), blocks.begin(), blocks.end());
+      }
+      return it.first->second;
+    };
+    for (size_t t = 0; t < plan->gemm_syms.size() / 4; ++t) {
+      const int32_t* ids = &plan->gemm_ids[plan->gemm_syms[4 * t]];
+      const int32_t deg = plan->gemm_syms[4 * t + 1];
+      std::vector<int32_t> r(deg), c(deg);
+      for (int32_t m = 0; m < deg; ++m) {
+        r[m] = ids[m] / G;
+        c[m] = ids[m] % G;
+      }
+      const bool same_r = std::count(r.begin(), r.end(), r[0]) == deg;
+      const bool same_c = std::count(c.begin(), c.end(), c[0]) == deg;
+      o.sym_passes.push_back((int32_t)(o.passes.size() / 2));
+      if (same_r || same_c) {
+        o.sym_passes.push_back(1);
+        o.passes.push_back(op(a_of, o.a_ops, same_c ? r : std::vector<int32_t>{r[0]}));
+        o.passes.push_back(op(b_of, o.b_ops, same_c ? std::vector<int32_t>{c[0]} : c));
+      } else {
+        o.sym_passes.push_back(deg);
+        for (int32_t m = 0; m < deg; ++m) {
+          o.passes.push_back(op(a_of, o.a_ops, {r[m]}));
+          o.passes.push_back(op(b_of, o.b_ops, {c[m]}));
+        }
+      }
+    }
   }
 
   // Peel program: recovered ids in (depth, s) order.  Ids used as

@@ -28,6 +28,14 @@ def _plan(spec, M, K, N, prec, mode=bpx.MODE_STRAGGLER):
     return plan
 
 
+def _plan2d(code, M, K, N, mode):
+    n = code.info()["n"]
+    arrival, _ = inputs.shifted_exp_arrival(1, n)
+    plan = bpx.Plan(code, arrival, 0, mode, M, K, N, two_d=True)
+    assert plan.workspace_bytes()[0] > plan.workspace_layout()[6]
+    return plan
+
+
 def _view(x, pad):
     """x in a buffer whose rows are `pad` floats (rounded up to 4) longer."""
     r, c = x.shape
@@ -93,6 +101,38 @@ def test_split_planes_exact_and_accurate(shape, prec):
     small = torch.empty(plan.workspace_layout()[6], dtype=torch.uint8, device="cuda")
     if prec == bpx.PREC_F32:   # a workspace without the planes: the direct kernels
         assert _err(_run(plan, A, B, ws=small), R) <= 1e-5
+
+
+# every pass count and kind of symbol; blocks of whole tiles, blocks ragged in
+# both directions, a K of a few chunks, and fewer tiles than CUs (all split)
+@pytest.mark.parametrize("mode", [bpx.MODE_FULL, bpx.MODE_MIN])
+@pytest.mark.parametrize("code,shape", [("1282", (4096, 512, 4096)), ("1282", (1100, 3004, 1040)),
+                                        ("1282", (5000, 44, 13008)), ("table1", (3001, 1000, 2600)),
+                                        ("table3", (2000, 1200, 1812))])
+def test_split_planes_two_dimensional(code, shape, mode):
+    M, K, N = shape
+    lib = {"1282": lambda: _code(inputs.CODE_1282), "table1": bpx.Code.table1,
+           "table3": bpx.Code.table3}[code]()
+    plan = _plan2d(lib, M, K, N, mode)
+    print("planes 2-D", code, shape, mode, file=sys.stderr, flush=True)
+    A, B = _ops(5, M, K, N, True)
+    assert torch.equal(_run(plan, A, B, pad=4).double(), A.double() @ B.double())
+    A, B = _ops(6, M, K, N, False)
+    R = A.double() @ B.double()
+    new, old = _run(plan, A, B), _run(plan, A, B, tile=1)
+    print("  error", _err(new, R), "direct kernels", _err(old, R), file=sys.stderr, flush=True)
+    assert _err(new, R) <= _err(old, R) * (1.0 if K > 256 else 1.1) + 1e-7
+    assert torch.equal(new, _run(plan, A, B))
+    small = torch.empty(max(plan.workspace_layout()[6], 256), dtype=torch.uint8, device="cuda")
+    assert _err(_run(plan, A, B, ws=small), R) <= 1e-5
+    for t in (A, B):          # one block's panels go to the FP32 kernels
+        t[t.shape[0] - 1, 3] = float("inf")
+        new, old = _run(plan, A, B), _run(plan, A, B, tile=1)
+        fin = torch.isfinite(old)
+        assert torch.equal(torch.isnan(new), torch.isnan(old))
+        assert torch.equal(torch.isfinite(new), fin)
+        d = torch.where(fin, new.double() - R, 0.0)
+        assert float(torch.linalg.norm(d) / torch.linalg.norm(R)) <= 1e-5
 
 
 @pytest.mark.parametrize("shape", [(2048, 1024, 2048), (1999, 1500, 1001)])
