@@ -538,14 +538,21 @@ def run_batch(args):
     comp_flops = 0.0
     split_bytes = peel_rd = peel_wr = 0
     planes = 2 if prec_name == "bf16x3" else 1
+    # on split planes the first phase also packs the coded blocks of A
+    packed = (bpx.group_workspace_bytes(plans) >
+              sum(-(-p.workspace_layout()[6] // 256) * 256 for p in plans)) and args.tile < 0
     for (M, K, N, k), inf, pl in zip(shapes, meta, plans):
         comp_flops += 2.0 * inf["Mb"] * K * N * inf["n_computed"]
         split_bytes += K * N * 4 + N * (-(-K // 32) * 32) * 2 * planes
+        if packed:
+            col_ptr, sym_ptr, _ = codes[k].csr()
+            for g in pl.schedule()["computed"].tolist():
+                split_bytes += inf["Mb"] * K * (4 * int(sym_ptr[g + 1] - sym_ptr[g]) + 2 * planes)
         r, wb = latency.peel_bytes(pl, M, N)
         peel_rd += r
         peel_wr += wb
     hbm = {"peak_GBps": 8000.0}
-    for name, b, t in (("split_b", split_bytes, phase_ms[0]),
+    for name, b, t in (("pack" if packed else "split_b", split_bytes, phase_ms[0]),
                        ("peel", peel_rd + peel_wr, phase_ms[2])):
         hbm[name] = {"bytes": b, "ms": t, "GBps": b / (t * 1e-3) / 1e9,
                      "frac": b / (t * 1e-3) / 1e9 / 8000.0}
@@ -594,12 +601,15 @@ def run_batch(args):
     out = header(args, value, ms, prec_name, cfg)
     out.update({"rel_err": rel_err, "rel_err_sample": "8 rows x all columns of every product",
                 "rel_err_worst": worst,
-                "times_ms": {"split_b": phase_ms[0], "grouped_gemm": phase_ms[1],
+                "times_ms": {"pack" if packed else "split_b": phase_ms[0],
+                             "grouped_gemm": phase_ms[1],
                              "peel": phase_ms[2]},
                 "roofline": {"bound": "mfma", "achieved": achieved, "peak": PEAK[prec_name],
                              "unit": "TFLOP/s", "frac": achieved / PEAK[prec_name],
-                             "traffic": load_traffic("batch", prec_name, "gemm_bf16.hip"),
-                             "kernel": "gemm_bf16_flat_grouped_kernel (GEMM phase)",
+                             "traffic": load_traffic("batch", prec_name, "gemm_planes.hip" if packed
+                                                     else "gemm_bf16.hip"),
+                             "kernel": ("gemm_planes_grouped_kernel" if packed else
+                                        "gemm_bf16_flat_grouped_kernel") + " (GEMM phase)",
                              "flops_per_launch": comp_flops, "launch_ms": phase_ms[1]},
                 "hbm": hbm})
     out.update(refs)

@@ -362,17 +362,22 @@ bpx_status bpx_coded_matmul_noalloc(bpx_plan* plan, const float* A, int64_t lda,
  * (M x N, ldc = N), K and N multiples of 4, 16-byte aligned.  All plans must
  * share one precision, BF16 or BF16x3.
  *
- * bpx_group_workspace_bytes: device workspace for the plans (each plan's
- *   bpx_plan_workspace_bytes rounded up to 256, back to back).
+ * bpx_group_workspace_bytes: device workspace for the plans: each plan's
+ *   parts (bpx_plan_workspace_layout, entry 6) rounded up to 256, back to
+ *   back, and, for groups of enough work, every product's operands split into
+ *   BF16 planes behind them.  A workspace of the parts alone is accepted: the
+ *   group then runs the kernels that read A directly.
  * bpx_group_create: host setup, done once: uploads the plans' tables and one
  *   block of per-product descriptors and a tile list (hipMalloc + one
  *   synchronous copy).  ws (256-byte aligned) and every operand pointer are
  *   baked into the descriptors and must stay valid while the group lives.
  *   Each product gets the GEMM tile shape bpx_set_tile_table selects for
  *   its (Mb, N, K); tiles of one shape form one persistent launch whose
- *   workgroups stride over the tile list, longest K first.
+ *   workgroups stride over the tile list, longest K first.  On split planes
+ *   all products share one persistent launch of 256x256 tiles, dealt to the
+ *   workgroups by their K.
  *   Returns BPX_E_UNDECODABLE if any plan is undecodable (nothing created).
- * bpx_group_launch: enqueue, on stream: one grouped B-split launch, one
+ * bpx_group_launch: enqueue, on stream: one grouped B-split (pack) launch, one
  *   persistent grouped GEMM launch per tile shape present, one grouped peel
  *   launch.  No allocation, copy or synchronisation: graph-capturable.
  *   Calls on one group must not overlap (they share the workspace).
@@ -383,7 +388,7 @@ bpx_status bpx_group_create(bpx_plan* const* plans, const float* const* A, const
                             float* const* C, int32_t count, void* ws, size_t ws_bytes,
                             bpx_group** out);
 bpx_status bpx_group_launch(bpx_group* group, bpx_stream stream);
-/* One phase of bpx_group_launch (0: B split, 1: GEMMs, 2: peel; -1: all),
+/* One phase of bpx_group_launch (0: B split or pack, 1: GEMMs, 2: peel; -1: all),
  * for timing the phases separately; the phases must run in order. */
 bpx_status bpx_group_launch_phase(bpx_group* group, int32_t phase, bpx_stream stream);
 void bpx_group_free(bpx_group* group);

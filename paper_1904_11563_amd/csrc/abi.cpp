@@ -3,9 +3,12 @@
 
 #include <algorithm>
 #include <cstring>
+#include <functional>
 #include <mutex>
 #include <new>
+#include <queue>
 #include <string>
+#include <utility>
 
 #include "host.hpp"
 #include "kernels.hpp"
@@ -177,13 +180,10 @@ bpx_status check_workspace(const bpx_plan* plan, const void* ws, size_t ws_bytes
   return BPX_OK;
 }
 
-// Coded products on split planes (see gemm_planes.hip): pack, multiply and,
-// for FP32, the tiles that hold a value the planes do not represent.
-bpx_status gemm_planes_impl(bpx_plan* plan, GemmParams p, void* ws, hipStream_t stream) {
-  char* w = static_cast<char*>(ws);
-  size_t off[6];
-  plan->plane_layout(off);
-  PlaneParams q{};
+// A plan's products on split planes, without the workspace's parts.
+void plane_params(const bpx_plan* plan, const GemmParams& p, PlaneParams* out) {
+  PlaneParams& q = *out;
+  q = PlaneParams{};
   q.A = p.A;
   q.lda = p.lda;
   q.B = p.B;
@@ -199,12 +199,6 @@ bpx_status gemm_planes_impl(bpx_plan* plan, GemmParams p, void* ws, hipStream_t 
   q.ids = p.ids;
   q.n_sym = p.n_sym;
   q.planes = plan->planes();
-  q.ap = reinterpret_cast<unsigned short*>(w + off[0]);
-  q.bp = reinterpret_cast<unsigned short*>(w + off[1]);
-  q.fa = reinterpret_cast<unsigned*>(w + off[2]);
-  q.fb = reinterpret_cast<unsigned*>(w + off[3]);
-  q.part = reinterpret_cast<float*>(w + off[4]);
-  q.part_tiles = plan->plane_part_tiles();
   q.kc = (int32_t)plan->plane_kc();
   q.rows32 = (int32_t)(plan->plane_rows() / 32);
   q.cols64 = (int32_t)(plan->plane_cols() / 64);
@@ -220,6 +214,22 @@ bpx_status gemm_planes_impl(bpx_plan* plan, GemmParams p, void* ws, hipStream_t 
     for (size_t i = 1; i < plan->ops.sym_passes.size(); i += 2)
       q.n_single += plan->ops.sym_passes[i] == 1;
   }
+}
+
+// Coded products on split planes (see gemm_planes.hip): pack, multiply and,
+// for FP32, the tiles that hold a value the planes do not represent.
+bpx_status gemm_planes_impl(bpx_plan* plan, GemmParams p, void* ws, hipStream_t stream) {
+  char* w = static_cast<char*>(ws);
+  size_t off[6];
+  plan->plane_layout(off);
+  PlaneParams q;
+  plane_params(plan, p, &q);
+  q.ap = reinterpret_cast<unsigned short*>(w + off[0]);
+  q.bp = reinterpret_cast<unsigned short*>(w + off[1]);
+  q.fa = reinterpret_cast<unsigned*>(w + off[2]);
+  q.fb = reinterpret_cast<unsigned*>(w + off[3]);
+  q.part = reinterpret_cast<float*>(w + off[4]);
+  q.part_tiles = plan->plane_part_tiles();
   hipError_t e = launch_pack_planes(q, stream);
   if (e == hipSuccess) e = launch_gemm_planes(q, stream);
   if (e == hipSuccess && q.planes == 3) {
@@ -462,6 +472,9 @@ struct bpx_group {
   const int32_t* d_bmap = nullptr;  // product of each split-B block
   const int32_t* d_pmap = nullptr;  // product of each peel block
   const int64_t* d_wstart = nullptr;  // first peel block of each peel workgroup
+  const int32_t* d_tstart = nullptr;  // planes: first tile of each GEMM workgroup
+  int32_t planes = 0;                 // planes per operand (0: direct kernels)
+  int32_t gemm_grid = 0;
   int64_t total_b = 0, total_p = 0, peel_grid = 0;
   int32_t max_slots = 0;
   size_t max_program = 0;
@@ -471,10 +484,70 @@ struct bpx_group {
 namespace bpx {
 namespace {
 
-size_t group_ws_bytes(bpx_plan* const* plans, int32_t count) {
+// What every grouped launch needs (the plans' own parts, back to back) ...
+size_t group_base_bytes(bpx_plan* const* plans, int32_t count) {
   size_t b = 0;
   for (int32_t i = 0; i < count; ++i) b += bpx_plan::align256(plans[i]->base_bytes());
   return b;
+}
+// ... whether the group runs on split planes: enough 256 x 256 tiles to give
+// every CU one (32 products of 256-1024, 221 tiles, took the same time either
+// way; 272 tiles of 2048 ran 1.2 times as fast), and products large enough
+// that each packed value is multiplied often, in multiply-adds per value
+// (BF16x3: 128-640 with 160 per value lost 3 %, 256-4096 with 650 gained 18 %
+// and with 1180 44 %; BF16, which packs half the bytes, gained 12 % at 160) ...
+bool group_planes(bpx_plan* const* plans, int32_t count) {
+  int64_t tiles = 0;
+  double macs = 0.0, values = 0.0;
+  for (int32_t i = 0; i < count; ++i) {
+    const bpx_plan* p = plans[i];
+    if (!p->planes_fit() || p->grid != 1) return false;
+    tiles += p->plane_tiles();
+    const double rows = (double)p->computed.size() * (double)p->Mb;
+    macs += rows * (double)p->N * (double)p->K;
+    values += (rows + (double)p->N) * (double)p->K;
+  }
+  return tiles >= 256 && tiles < (int64_t)1 << 31 &&
+         macs >= 96.0 * plans[0]->planes() * values;
+}
+// ... and the packed operands behind those parts.
+size_t group_ws_bytes(bpx_plan* const* plans, int32_t count) {
+  size_t b = group_base_bytes(plans, count);
+  if (group_planes(plans, count))
+    for (int32_t i = 0; i < count; ++i) b += bpx_plan::align256(plans[i]->packed_bytes());
+  return b;
+}
+
+// Deals the tiles of a group (sorted longest K first, neighbours sharing
+// panels) to G workgroups: runs of G / 8 tiles go to the XCD with the least
+// work so far, each tile of a run to the least loaded of its workgroups.
+// Workgroup w runs on XCD w % 8.  A tile costs its 32-wide stages plus about 3
+// for its first copies and its stores.
+void deal_tiles(const std::vector<GroupTile>& tiles, const std::vector<int64_t>& stages, int32_t G,
+                std::vector<GroupTile>* dealt, std::vector<int32_t>* start) {
+  const int32_t X = G % 8 == 0 ? 8 : 1, per = G / X;
+  std::vector<std::vector<int32_t>> mine(G);
+  std::vector<int64_t> xload(X, 0);
+  typedef std::pair<int64_t, int32_t> Load;
+  std::vector<std::priority_queue<Load, std::vector<Load>, std::greater<Load>>> wgs(X);
+  for (int32_t w = 0; w < G; ++w) wgs[w % X].push(Load(0, w));
+  for (size_t t = 0; t < tiles.size(); t += per) {
+    const int32_t x =
+        (int32_t)(std::min_element(xload.begin(), xload.end()) - xload.begin());
+    for (size_t u = t; u < std::min(tiles.size(), t + per); ++u) {
+      const Load l = wgs[x].top();
+      wgs[x].pop();
+      mine[l.second].push_back((int32_t)u);
+      const int64_t cost = stages[u] + 3;
+      wgs[x].push(Load(l.first + cost, l.second));
+      xload[x] += cost;
+    }
+  }
+  for (int32_t w = 0; w < G; ++w) {
+    start->push_back((int32_t)dealt->size());
+    for (int32_t u : mine[w]) dealt->push_back(tiles[u]);
+  }
+  start->push_back((int32_t)dealt->size());
 }
 
 bpx_status group_build(bpx_plan* const* plans, const float* const* A, const float* const* B,
@@ -500,14 +573,21 @@ bpx_status group_build(bpx_plan* const* plans, const float* const* A, const floa
     bpx_status st = upload(pl);
     if (st != BPX_OK) return st;
   }
-  if (!ws || ((uintptr_t)ws & 255u) || ws_bytes < group_ws_bytes(plans, count))
+  const size_t base = group_base_bytes(plans, count);
+  if (!ws || ((uintptr_t)ws & 255u) || ws_bytes < base)
     return fail(BPX_E_INVALID, "workspace missing, not 256-byte aligned or too small");
+  // Split planes if the workspace holds them and no product's tile shape is
+  // named by the caller.
+  bool split = group_planes(plans, count) && ws_bytes >= group_ws_bytes(plans, count);
+  for (int32_t i = 0; i < count; ++i)
+    split = split && !tile_chosen(prec, plans[i]->Mb, plans[i]->N, plans[i]->K);
 
   std::vector<GroupDesc> desc(count);
   std::vector<int64_t> bstart(count), pstart(count);
   std::vector<std::vector<GroupTile>> by_tile(bf16_tile_count());
   std::vector<std::vector<int64_t>> key(bf16_tile_count());
   char* w = static_cast<char*>(ws);
+  char* packed = w + base;
   int64_t tb = 0, tp = 0;
   int32_t max_slots = 0;
   size_t max_program = 0;
@@ -539,9 +619,20 @@ bpx_status group_build(bpx_plan* const* plans, const float* const* A, const floa
     p.kp = pl->kp();
     int32_t t = choose_tile(prec, pl->Mb, pl->N, pl->K);
     if (bf16_tile_is_flat(t) && !bf16_flat_ok(p)) t = 1;
+    if (split) t = 0;  // one list
     const TileShape sh = bf16_tile_shape(t);
-    int64_t nt;
-    if (bf16_tile_is_flat(t)) {  // tiles over the stacked rows of all symbols
+    int64_t nt, pack_blocks = 0;
+    if (split) {
+      PlaneParams& q = d.pl;
+      plane_params(pl, p, &q);
+      q.ap = reinterpret_cast<unsigned short*>(packed);
+      q.bp = q.ap + (size_t)pl->plane_rows() * pl->plane_kc() * 16 * q.planes;
+      packed += bpx_plan::align256(pl->packed_bytes());
+      pack_blocks = planes_group_setup(&q);
+      p.tiles_m = q.tiles_m;
+      p.tiles_n = q.tiles_n;
+      nt = (int64_t)p.tiles_m * p.tiles_n;
+    } else if (bf16_tile_is_flat(t)) {  // tiles over the stacked rows of all symbols
       p.tiles_m = (int32_t)(((int64_t)p.n_sym * pl->Mb + sh.bm - 1) / sh.bm);
       p.tiles_n = (int32_t)((pl->N + sh.bn - 1) / sh.bn);
       nt = (int64_t)p.tiles_m * p.tiles_n;
@@ -588,7 +679,7 @@ bpx_status group_build(bpx_plan* const* plans, const float* const* A, const floa
     d.b_tn = (int32_t)((pl->N + 63) / 64);
     d.b_tk = (int32_t)((pl->kp() + 63) / 64);
     bstart[i] = tb;
-    tb += (int64_t)d.b_tn * d.b_tk;
+    tb += split ? pack_blocks : (int64_t)d.b_tn * d.b_tk;
     pstart[i] = tp;
     if (pe.nsteps > 0) tp += (pl->Mb * (pl->N / 4) + 127) / 128;
     w += bpx_plan::align256(pl->base_bytes());
@@ -598,12 +689,24 @@ bpx_status group_build(bpx_plan* const* plans, const float* const* A, const floa
   // tile lists: longest K first (stable), one persistent launch per shape
   std::vector<GroupTile> tiles;
   std::vector<GroupLaunch> launches;
+  std::vector<int32_t> tstart;
   for (int32_t t = 0; t < (int32_t)by_tile.size(); ++t) {
     if (by_tile[t].empty()) continue;
     std::vector<size_t> idx(by_tile[t].size());
     for (size_t j = 0; j < idx.size(); ++j) idx[j] = j;
     std::stable_sort(idx.begin(), idx.end(),
                      [&](size_t a, size_t b) { return key[t][a] > key[t][b]; });
+    if (split) {
+      std::vector<GroupTile> sorted;
+      std::vector<int64_t> stages;
+      for (size_t j : idx) {
+        sorted.push_back(by_tile[t][j]);
+        stages.push_back((key[t][j] + 31) / 32);
+      }
+      g->gemm_grid = (int32_t)std::min<int64_t>((int64_t)sorted.size(), device_cu_count());
+      deal_tiles(sorted, stages, g->gemm_grid, &tiles, &tstart);
+      break;
+    }
     GroupLaunch L{t, (int32_t)tiles.size(), (int32_t)idx.size(), 0};
     for (size_t j : idx) tiles.push_back(by_tile[t][j]);
     const TileShape sh = bf16_tile_shape(t);
@@ -644,7 +747,7 @@ bpx_status group_build(bpx_plan* const* plans, const float* const* A, const floa
       cum += n * c;
     }
   }
-  // one device block: descriptors | bstart | pstart | tiles | bmap | pmap | wstart
+  // one device block: descriptors | bstart | pstart | tiles | bmap | pmap | wstart | tstart
   auto al = [](size_t x) { return (x + 255) / 256 * 256; };
   const size_t s0 = al(desc.size() * sizeof(GroupDesc));
   const size_t s1 = al(bstart.size() * 8);
@@ -653,7 +756,8 @@ bpx_status group_build(bpx_plan* const* plans, const float* const* A, const floa
   const size_t s4 = al(std::max<size_t>(bmap.size(), 1) * 4);
   const size_t s5 = al(std::max<size_t>(pmap.size(), 1) * 4);
   const size_t s6 = al(wstart.size() * 8);
-  std::string host(s0 + s1 + s2 + s3 + s4 + s5 + s6, '\0');
+  const size_t s7 = al(std::max<size_t>(tstart.size(), 1) * 4);
+  std::string host(s0 + s1 + s2 + s3 + s4 + s5 + s6 + s7, '\0');
   std::memcpy(&host[0], desc.data(), desc.size() * sizeof(GroupDesc));
   std::memcpy(&host[s0], bstart.data(), bstart.size() * 8);
   std::memcpy(&host[s0 + s1], pstart.data(), pstart.size() * 8);
@@ -661,6 +765,7 @@ bpx_status group_build(bpx_plan* const* plans, const float* const* A, const floa
   std::memcpy(&host[s0 + s1 + s2 + s3], bmap.data(), bmap.size() * 4);
   std::memcpy(&host[s0 + s1 + s2 + s3 + s4], pmap.data(), pmap.size() * 4);
   std::memcpy(&host[s0 + s1 + s2 + s3 + s4 + s5], wstart.data(), wstart.size() * 8);
+  std::memcpy(&host[s0 + s1 + s2 + s3 + s4 + s5 + s6], tstart.data(), tstart.size() * 4);
   void* dptr = nullptr;
   hipError_t e = hipMalloc(&dptr, host.size());
   if (e != hipSuccess) return hip_fail(e, "hipMalloc(group descriptors)");
@@ -671,18 +776,20 @@ bpx_status group_build(bpx_plan* const* plans, const float* const* A, const floa
   }
   int dev = 0;
   (void)hipGetDevice(&dev);
-  char* base = static_cast<char*>(dptr);
+  char* dblock = static_cast<char*>(dptr);
   g->count = count;
   g->prec = prec;
   g->dev = dptr;
   g->dev_id = dev;
-  g->d_desc = reinterpret_cast<const GroupDesc*>(base);
-  g->d_bstart = reinterpret_cast<const int64_t*>(base + s0);
-  g->d_pstart = reinterpret_cast<const int64_t*>(base + s0 + s1);
-  g->d_tiles = reinterpret_cast<const GroupTile*>(base + s0 + s1 + s2);
-  g->d_bmap = reinterpret_cast<const int32_t*>(base + s0 + s1 + s2 + s3);
-  g->d_pmap = reinterpret_cast<const int32_t*>(base + s0 + s1 + s2 + s3 + s4);
-  g->d_wstart = reinterpret_cast<const int64_t*>(base + s0 + s1 + s2 + s3 + s4 + s5);
+  g->d_desc = reinterpret_cast<const GroupDesc*>(dblock);
+  g->d_bstart = reinterpret_cast<const int64_t*>(dblock + s0);
+  g->d_pstart = reinterpret_cast<const int64_t*>(dblock + s0 + s1);
+  g->d_tiles = reinterpret_cast<const GroupTile*>(dblock + s0 + s1 + s2);
+  g->d_bmap = reinterpret_cast<const int32_t*>(dblock + s0 + s1 + s2 + s3);
+  g->d_pmap = reinterpret_cast<const int32_t*>(dblock + s0 + s1 + s2 + s3 + s4);
+  g->d_wstart = reinterpret_cast<const int64_t*>(dblock + s0 + s1 + s2 + s3 + s4 + s5);
+  g->d_tstart = reinterpret_cast<const int32_t*>(dblock + s0 + s1 + s2 + s3 + s4 + s5 + s6);
+  g->planes = split ? plans[0]->planes() : 0;
   g->peel_grid = pgrid;
   g->total_b = tb;
   g->total_p = tp;
@@ -695,10 +802,16 @@ bpx_status group_build(bpx_plan* const* plans, const float* const* A, const floa
 bpx_status group_launch(bpx_group* g, int32_t phase, hipStream_t stream) {
   hipError_t e;
   if (phase < 0 || phase == 0) {
-    e = launch_split_b_grouped(g->d_desc, g->d_bstart, g->d_bmap, g->total_b, stream);
-    if (e != hipSuccess) return hip_fail(e, "grouped split-B launch");
+    e = g->planes ? launch_pack_planes_grouped(g->d_desc, g->d_bstart, g->d_bmap, g->total_b,
+                                               g->planes, stream)
+                  : launch_split_b_grouped(g->d_desc, g->d_bstart, g->d_bmap, g->total_b, stream);
+    if (e != hipSuccess) return hip_fail(e, "grouped B-split or pack launch");
   }
-  if (phase < 0 || phase == 1) {
+  if (g->planes && (phase < 0 || phase == 1)) {
+    e = launch_gemm_planes_grouped(g->d_desc, g->d_tiles, g->d_tstart, g->planes, g->gemm_grid,
+                                   stream);
+    if (e != hipSuccess) return hip_fail(e, "grouped GEMM launch");
+  } else if (phase < 0 || phase == 1) {
     const int32_t split = g->prec == BPX_PREC_BF16X3 ? 3 : 1;
     for (const GroupLaunch& L : g->launches) {
       e = launch_gemm_bf16_grouped(g->d_desc, g->d_tiles + L.offset, L.n, L.tile, split, L.grid,

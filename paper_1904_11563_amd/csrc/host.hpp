@@ -187,16 +187,24 @@ struct bpx_plan {
                     : plane_rows() / 256 * (plane_cols() / 256);
   }
   bool has_planes() const {
-    if (is_fp8() || K % 4 != 0) return false;
     const double macs = (double)n_products() * (double)Mb * (double)K * (double)Nb;
+    return macs > 2147483648.0 && planes_fit();
+  }
+  // The kernels' 32-bit indices and offsets hold.
+  bool planes_fit() const {
+    if (is_fp8() || K % 4 != 0) return false;
     const int64_t lim = (int64_t)1 << 31;
-    return macs > 2147483648.0 && plane_rows() < lim && plane_cols() < lim &&
+    return plane_rows() < lim && plane_cols() < lim &&
            (double)n_products() * (double)plane_kc() < (double)lim &&
            plane_kc() * planes() * 8192 < lim && plane_tiles() < lim / 32 &&
            plane_rows() / 32 * ((plane_kc() + 15) / 16) + plane_cols() / 64 * ((plane_kc() + 3) / 4) <
                lim;
   }
   static constexpr int32_t kPartTiles = 512;
+  // Packed operands of a grouped product (no flags, no partial tiles).
+  size_t packed_bytes() const {
+    return (size_t)(plane_rows() + plane_cols()) * plane_kc() * 32 * planes();
+  }
   // Offsets of the plane parts, from the start of the workspace: packed A,
   // packed B, flags of A, flags of B (planes() == 3), partial tiles; [5] the end.
   void plane_layout(size_t off[6]) const {

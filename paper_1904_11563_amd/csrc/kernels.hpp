@@ -194,6 +194,7 @@ hipError_t launch_coded_gemm_bf16(const GemmParams& p, int32_t tile, hipStream_t
 // Per-product descriptor of a grouped launch (device memory).
 struct GroupDesc {
   GemmParams g;      // tiles_m / tiles_n set for the product's tile shape
+  PlaneParams pl;    // the product on split planes (planes_group_setup), instead of g
   PeelParams pe;
   int32_t b_tn, b_tk;  // split-B grid of the product (64 x 64 tiles)
   int32_t tile;        // tile shape index
@@ -212,6 +213,17 @@ hipError_t launch_split_b_grouped(const GroupDesc* d, const int64_t* bstart, con
 hipError_t launch_gemm_bf16_grouped(const GroupDesc* d, const GroupTile* tiles, int32_t n_tiles,
                                     int32_t tile, int32_t split, int32_t grid,
                                     hipStream_t stream);
+// Groups on split planes: sets the launch fields of a product and returns its
+// pack blocks; one pack launch over all products' blocks (as split-B's); and
+// one persistent GEMM launch, workgroup w taking tiles[wstart[w]] ..
+// tiles[wstart[w + 1] - 1].
+int64_t planes_group_setup(PlaneParams* p);
+hipError_t launch_pack_planes_grouped(const GroupDesc* d, const int64_t* bstart,
+                                      const int32_t* bmap, int64_t blocks, int32_t planes,
+                                      hipStream_t stream);
+hipError_t launch_gemm_planes_grouped(const GroupDesc* d, const GroupTile* tiles,
+                                      const int32_t* wstart, int32_t planes, int32_t grid,
+                                      hipStream_t stream);
 // Compute units of the current device (cached per device; 256 if unknown).
 int device_cu_count();
 

@@ -181,3 +181,44 @@ def test_split_planes_scale_of_operands(exps):
     new, old = d(_run(plan, A, B)), d(_run(plan, A, B, tile=1))
     print("planes scale", exps, new, old, file=sys.stderr, flush=True)
     assert new <= old + 2.0 ** -149 * np.sqrt(M * N)
+
+
+@pytest.mark.parametrize("prec", [bpx.PREC_BF16X3, bpx.PREC_BF16])
+def test_grouped_split_planes_exact_and_like_direct_kernels(prec):
+    """A group with enough 256 x 256 tiles for every CU (more tiles than CUs,
+    so a workgroup takes several; K of one stage to many, ragged rows, columns
+    and K): exact on integers, and on floats as accurate as the same group on
+    the direct kernels, which a workspace without the planes gets."""
+    specs = {4: _code(inputs.CODE_642), 8: _code(inputs.CODE_1282)}
+    shapes = inputs.batch_shapes(7, 40, lo=256, hi=2048, mult=4)
+    shapes += [(2000, 4, 700, 4), (300, 28, 4, 8), (8, 64, 2050 * 2, 4), (1, 36, 1028, 8)]
+    plans, base = [], 0
+    for i, (M, K, N, k) in enumerate(shapes):
+        n = specs[k].info()["n"]
+        arrival, _ = inputs.erasure_arrival(i, n, n - k)
+        plans.append(bpx.Plan(specs[k], arrival, 0, bpx.MODE_STRAGGLER, M, K, N, prec))
+        base += -(-plans[-1].workspace_layout()[6] // 256) * 256
+    full = bpx.group_workspace_bytes(plans)
+    assert full > base                       # the group runs on split planes
+    for integer in (True, False):
+        ops = [_ops(20 + i, M, K, N, integer) for i, (M, K, N, _) in enumerate(shapes)]
+        As, Bs = [a for a, _ in ops], [b for _, b in ops]
+        outs = []
+        for nbytes in (full, base):
+            Cs = [torch.full((M, N), float("nan"), device="cuda") for M, _, N, _ in shapes]
+            ws = torch.full((nbytes,), 0xA5, dtype=torch.uint8, device="cuda")
+            g = bpx.Group(plans, As, Bs, Cs, ws)
+            print("grouped planes", prec, integer, nbytes, file=sys.stderr, flush=True)
+            for _ in range(2):
+                g.launch()
+            torch.cuda.synchronize()
+            outs.append(Cs)
+            del g
+        for i, (a, b) in enumerate(ops):
+            R = a.double() @ b.double()
+            if integer:
+                assert torch.equal(outs[0][i].double(), R), shapes[i]
+            else:
+                # the same splits, summed in another order
+                new, old = _err(outs[0][i], R), _err(outs[1][i], R)
+                assert new <= old * 1.1 + 1e-6, (shapes[i], new, old)
