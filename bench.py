@@ -60,10 +60,10 @@ def parse():
     return ap.parse_args()
 
 
-def split_planes(gemm_flops, prec_name, tile):
-    """Whether the library multiplies this product on split planes (F32, BF16
-    or BF16x3, more than 2^31 multiply-adds, no forced tile)."""
-    return tile < 0 and not prec_name.startswith("fp8") and gemm_flops > 2 ** 32
+def packed_operands(gemm_flops, tile):
+    """Whether the library multiplies this product on packed operands (more
+    than 2^31 multiply-adds, no forced tile)."""
+    return tile < 0 and gemm_flops > 2 ** 32
 
 
 GEMM_SOURCE = {"f32": "gemm_f32.hip", "bf16": "gemm_bf16.hip", "bf16x3": "gemm_bf16.hip",
@@ -327,14 +327,16 @@ def run_single(args):
         f32_kernel = "coded_gemm_f32_kernel<64,128,32,2>"
     bf16_kernel = ("fused_bf16_kernel (coded products and peel, one launch)" if fused else
                    "split_b + coded_gemm_bf16_flat_kernel, one call")
-    planes = split_planes(gemm_flops, prec_name, args.tile)
+    planes = packed_operands(gemm_flops, args.tile)
+    fp8_kernel = "quant_b + quant_a + coded_gemm_fp8_wide_kernel, one call"
     if planes:
+        fp8_kernel = "pack_fp8 + gemm_fp8_packed_kernel (256x256 tiles), one call"
         f32_kernel = bf16_kernel = ("pack_planes + gemm_planes_kernel (256x256 tiles of BF16 "
                                     "planes, last round split along K), one call")
     kernel = {"f32": f32_kernel, "bf16": bf16_kernel, "bf16x3": bf16_kernel,
-              "fp8": "quant_b + quant_a + coded_gemm_fp8_wide_kernel, one call",
-              "fp8x2": "quant_b + quant_a + coded_gemm_fp8_wide_kernel, one call"}[prec_name]
-    source = ("gemm_planes.hip" if planes else "gemm2d.hip" if two_d else
+              "fp8": fp8_kernel, "fp8x2": fp8_kernel}[prec_name]
+    source = ("gemm_planes.hip" if planes and not prec_name.startswith("fp8") else
+              "gemm2d.hip" if two_d else
               "fused.hip" if fused else GEMM_SOURCE[prec_name])
     peak = PLANES_F32 if planes and prec_name == "f32" else PEAK[prec_name]
     roofline = {"bound": "mfma", "achieved": achieved, "peak": peak,

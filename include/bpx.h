@@ -233,8 +233,9 @@ bpx_status bpx_plan_peel_program(const bpx_plan* plan, const int32_t** steps, in
                                  int32_t* n_slots);
 
 /* Device workspace the plan needs for bpx_coded_gemm / bpx_coded_matmul
- * (Y slots and, for FP8, quantised operands and scales; for large F32 / BF16 /
- * BF16x3 products also the operands split into BF16 planes), and
+ * (Y slots and, for FP8, quantised operands and scales; for large products
+ * also the operands packed for the matrix instructions: BF16 planes or, for
+ * FP8, codes and scales), and
  * the size of the buffer bpx_encode writes (n_computed coded blocks of
  * Mb x K floats).  A call whose workspace holds the parts of
  * bpx_plan_workspace_layout only is accepted: it runs the kernels that read A
@@ -245,9 +246,10 @@ bpx_status bpx_plan_workspace_bytes(const bpx_plan* plan, size_t* ws_bytes,
 /* Byte offsets of the parts of the plan's workspace (n entries written,
  * at most 7), every part 256-byte aligned; a part the precision does not
  * use has size 0 (its offset equals the next one); entry 6 is the end of
- * these parts (behind it, up to ws_bytes, come the split planes, flags and
- * partial tiles of products of more than 2^31 multiply-adds over the computed
- * symbols and their passes; the BF16 planes below are then not written).
+ * these parts (behind it, up to ws_bytes, come the packed operands, flags or
+ * scales and partial tiles of products of more than 2^31 multiply-adds over the
+ * computed symbols and their passes; of the parts below only Y is then
+ * written).
  *   F32:     [0] Y slots, [1] split-K partial tiles: when Mb and N are
  *            multiples of 256, K of 32 and M of Mb, room for min(256, 4 T)
  *            FP32 tiles of 256 x 256 (T = computed symbols x Mb/256 x N/256),
@@ -286,9 +288,11 @@ bpx_status bpx_encode(bpx_plan* plan, const float* A, int64_t lda, float* coded_
  * stored), or, for more than 2^31 multiply-adds over the computed symbols,
  * into a pass that packs the coded blocks and B as BF16 planes (FP32 values
  * three planes cannot hold, infinities and NaN among them, send their tiles
- * to the FP32 kernels, so results for them are those of FP32 arithmetic).  FP8*: a streaming encode+quantise pass writes the e4m3 codes of
- * every 128 x 128 coded tile (its scale needs the tile's amax), B is
- * quantised once per call, then the block-scaled FP8 product runs.  Products go to
+ * to the FP32 kernels, so results for them are those of FP32 arithmetic).
+ * FP8*: a streaming encode+quantise pass writes the e4m3 codes of every 128 x
+ * 128 coded tile (its scale needs the tile's amax), B is quantised once per
+ * call, then the block-scaled FP8 product runs (for more than 2^31
+ * multiply-adds on codes packed for the matrix instruction).  Products go to
  * the Y slots of ws or, for degree-1 releasers, straight into C (see dest in
  * bpx_plan_schedule).  Precision is the plan's.  ws must hold ws_bytes. */
 bpx_status bpx_coded_gemm(bpx_plan* plan, const float* A, int64_t lda, const float* B,

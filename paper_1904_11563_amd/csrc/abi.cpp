@@ -230,6 +230,13 @@ bpx_status gemm_planes_impl(bpx_plan* plan, GemmParams p, void* ws, hipStream_t 
   q.fb = reinterpret_cast<unsigned*>(w + off[3]);
   q.part = reinterpret_cast<float*>(w + off[4]);
   q.part_tiles = plan->plane_part_tiles();
+  if (plan->is_fp8()) {
+    q.ea = reinterpret_cast<unsigned char*>(w + off[2]);
+    q.eb = reinterpret_cast<unsigned*>(w + off[3]);
+    hipError_t e = launch_pack_fp8(q, stream);
+    if (e == hipSuccess) e = launch_gemm_fp8_packed(q, stream);
+    return e == hipSuccess ? BPX_OK : hip_fail(e, "packed FP8 gemm launch");
+  }
   hipError_t e = launch_pack_planes(q, stream);
   if (e == hipSuccess) e = launch_gemm_planes(q, stream);
   if (e == hipSuccess && q.planes == 3) {
@@ -286,6 +293,11 @@ bpx_status gemm_impl(bpx_plan* plan, const float* A, int64_t lda, const float* B
     if (!gemm_2d_fits(p))
       return fail(BPX_E_UNSUPPORTED, "block too large for 32-bit buffer offsets");
   }
+  if (plan->is_fp8()) {
+    const int64_t Mbp = plan->r128(plan->Mb), Kp = plan->r128(plan->K), Np = plan->r128(plan->N);
+    if (Np / 128 > 65535 || Kp / 128 > 65535 || Mbp / 128 > 65535 || p.n_sym > 65535)
+      return fail(BPX_E_UNSUPPORTED, "FP8 grid too large");
+  }
   if (plan->has_planes() && ws_bytes >= plan->ws_bytes() &&
       !tile_chosen(plan->prec, plan->Mb, plan->N, plan->K))
     return gemm_planes_impl(plan, p, ws, stream);
@@ -320,8 +332,6 @@ bpx_status gemm_impl(bpx_plan* plan, const float* A, int64_t lda, const float* B
     f.sa = reinterpret_cast<float*>(w + off[3]);
     f.bq = reinterpret_cast<unsigned char*>(w + off[4]);
     f.sb = reinterpret_cast<float*>(w + off[5]);
-    if (f.Np / 128 > 65535 || f.Kp / 128 > 65535 || f.Mbp / 128 > 65535 || f.n_sym > 65535)
-      return fail(BPX_E_UNSUPPORTED, "FP8 grid too large");
     e = launch_quant_b(f, stream);
     if (e == hipSuccess) e = launch_quant_a(f, stream);
     if (e == hipSuccess) e = launch_coded_gemm_fp8(f, tile, stream);

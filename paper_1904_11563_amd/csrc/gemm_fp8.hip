@@ -1,4 +1,6 @@
 // FP8-e4m3 coded products with one power-of-two scale per 128 x 128 block.
+// Products of more than 2^31 multiply-adds run on packed operands (second half
+// of this file), smaller ones on the kernels right below.
 //
 // quant_a_kernel  - the encode for FP8: per computed symbol g and 128 x 128
 //                   tile of its coded block C_g = sum of its data blocks A_s
@@ -30,12 +32,14 @@
 // up to 128; padding rows/columns are zero codes.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "kernels.hpp"
+#include "planes.hpp"
 
 namespace bpx {
 namespace {
 
-typedef float v4f __attribute__((ext_vector_type(4)));
 typedef int v8i __attribute__((ext_vector_type(8)));
 
 constexpr float kE4M3Max = 448.f;
@@ -52,6 +56,13 @@ __device__ __forceinline__ float pow2_scale(float amax) {
   int e = b - ((bits & 0x7fffffu) <= 0x600000u ? 135 : 134);
   e = e < kMinScaleExp ? kMinScaleExp : e;
   return __uint_as_float((unsigned)(e + 127) << 23);
+}
+// 1 / s, exact: s is a power of two of biased exponent 5 .. 247.  x times it is
+// x / s to the bit (one rounding of the same value); a division costs some ten
+// instructions per element, which bound the quantising passes (the packed one
+// 0.79 -> 0.64 ms on the Mojette workload).
+__device__ __forceinline__ float pow2_inverse(float s) {
+  return __uint_as_float((254u << 23) - __float_as_uint(s));
 }
 // Scales are read through the constant address space (scalar loads).
 typedef __attribute__((address_space(4))) float cfloat;
@@ -130,7 +141,7 @@ __global__ __launch_bounds__(256) void quant_a_kernel(Fp8Params p) {
     amax = fmaxf(amax, fmaxf(fmaxf(fabsf(s[0]), fabsf(s[1])), fmaxf(fabsf(s[2]), fabsf(s[3]))));
   }
   amax = block_amax(amax, red);
-  const float sc = pow2_scale(amax);
+  const float sc = pow2_scale(amax), inv = pow2_inverse(sc);
   const int64_t sym_bytes = p.Mbp * p.Kp;
   unsigned char* q = p.aq + (int64_t)si * sym_bytes;
   unsigned char* q2 = p.aq2 ? p.aq2 + (int64_t)si * sym_bytes : nullptr;
@@ -138,7 +149,7 @@ __global__ __launch_bounds__(256) void quant_a_kernel(Fp8Params p) {
   for (int i = 0; i < 16; ++i) {
     const int f = threadIdx.x + 256 * i;
     const int64_t r = r0 + f / 32, k = k0 + (f % 32) * 4;
-    const v4f v = x[i] / sc;
+    const v4f v = x[i] * inv;
     const int w = pack_e4m3(v);
     *reinterpret_cast<int*>(q + r * p.Kp + k) = w;
     if (q2) *reinterpret_cast<int*>(q2 + r * p.Kp + k) = pack_e4m3((v - unpack_e4m3(w)) * 16.f);
@@ -174,12 +185,12 @@ __global__ __launch_bounds__(256) void quant_b_kernel(Fp8Params p) {
     amax = fmaxf(amax, fmaxf(fmaxf(fabsf(s[0]), fabsf(s[1])), fmaxf(fabsf(s[2]), fabsf(s[3]))));
   }
   amax = block_amax(amax, red);
-  const float sc = pow2_scale(amax);
+  const float sc = pow2_scale(amax), inv = pow2_inverse(sc);
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
     const int f = threadIdx.x + 256 * i;
     const int kl = f / 32, nl = (f % 32) * 4;
-    const int w = pack_e4m3(x[i] / sc);
+    const int w = pack_e4m3(x[i] * inv);
 #pragma unroll
     for (int e = 0; e < 4; ++e) t[nl + e][kl] = (unsigned char)((w >> (8 * e)) & 0xff);
   }
@@ -232,11 +243,6 @@ __device__ __forceinline__ v8i frag(const unsigned char* row, int x0) {
   const v4u hi = *reinterpret_cast<const v4u*>(row + (x0 ^ 16));
   return v8i{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3],
              (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
-}
-
-__device__ __forceinline__ int xcd_remap(int lin, int total) {
-  if ((total & 7) != 0) return lin;
-  return (lin & 7) * (total >> 3) + (lin >> 3);
 }
 
 template <int X2>
@@ -378,14 +384,10 @@ __global__ __launch_bounds__(kThreads, 1) void coded_gemm_fp8_kernel(Fp8Params p
 // per-thread offset).
 namespace wide8 {
 constexpr int BN = 256;
-constexpr int NT = 512;
-constexpr int kRsrcWord3 = 0x00020000;  // gfx9 raw buffer, 32-bit elements
-
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const unsigned char* base) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(base), (short)0, -1,
                                            kRsrcWord3);
 }
-typedef __attribute__((address_space(3))) void* lds_addr;
 __device__ __forceinline__ lds_addr lds_ptr(unsigned char* p) { return (lds_addr)p; }
 }  // namespace wide8
 
@@ -407,7 +409,7 @@ __device__ __forceinline__ void grouped_tile(int L, int rows, int cols, int gm, 
 }
 
 template <int BM, int WM, int WN, int X2>
-__global__ __launch_bounds__(wide8::NT, 1) void coded_gemm_fp8_wide_kernel(Fp8Params p) {
+__global__ __launch_bounds__(NT, 1) void coded_gemm_fp8_wide_kernel(Fp8Params p) {
   using namespace wide8;
   constexpr int TM = BM / WM, TN = BN / WN;   // wave tile
   constexpr int FM = TM / 16, FN = TN / 16;
@@ -575,6 +577,404 @@ __global__ __launch_bounds__(wide8::NT, 1) void coded_gemm_fp8_wide_kernel(Fp8Pa
   }
 }
 
+// ----------------------------------------------------- packed operands --
+// Large products: the same codes and scales, stored in the order of the
+// fragments of v_mfma_scale_f32_32x32x64_f8f6f4 and multiplied on 256 x 256
+// tiles like the BF16 planes (gemm_planes.hip; helpers in planes.hpp).
+//
+// The coded rows are stacked without padding a symbol to 128 rows: that MFMA
+// takes its A scale per lane, lane l that of row l % 32, so rows of different
+// symbols, with different scales, can share a fragment (blocks of 40 rows, M =
+// 5000 on the (24,16,8) Mojette code, otherwise multiply 3.2 times the rows).
+//
+// 16384 x 16384 x 8192, 226 coded products (FP8x2): pack 0.64 ms (3.8 GB, 5.9
+// TB/s), GEMM 5.65 ms, 2.75 PFLOP/s of FP8 products, MFMA busy 0.75 at 1.66
+// GHz; call 6.95 -> 6.2 ms.  5000 x 3000 x 2000 (FP8): GEMM 165 -> 48 us, call
+// 272 -> 128 us.
+//
+// Per 32 rows (columns) and 64 k there are 2 KiB of codes per plane: lane l's
+// 32 codes, row l % 32, k 32 (l / 32) .. +31, as two KiB of 16 bytes per lane.
+// The planes of a k chunk follow each other, chunks follow in k.  Scales: one
+// E8M0 byte per stacked row and 128 k, as one word per lane l % 32 of 128 rows
+// whose byte i is row 32 i + l's (the MFMA selects the byte), and one word of
+// four equal bytes per 128 columns and 128 k.
+
+// One 128 x 128 tile of codes on its way out: through LDS, rows of 33 words
+// (row-consecutive lanes on distinct banks), then 16 bytes per lane, 32 rows
+// to a KiB.
+constexpr int kCodeRow = 33;
+__device__ __forceinline__ void put_codes(const int* t, int rows, unsigned row0, int kb, int kc,
+                                          int planes, int plane, unsigned char* out) {
+  for (int f = threadIdx.x; f < 128 * 8; f += 256) {
+    const int r = f & 127, g = f >> 7;  // granule g: k 16 g .. 16 g + 15 of the tile
+    if (r >= rows) continue;
+    const int* src = t + r * kCodeRow + g * 4;
+    const unsigned gr = row0 + (unsigned)r;
+    unsigned char* dst = out +
+                         (((int64_t)(gr >> 5) * kc + kb * 2 + (g >> 2)) * planes + plane) * 2048 +
+                         (g & 1) * 1024 + (((g >> 1) & 1) * 32 + (gr & 31)) * 16;
+    *reinterpret_cast<v4i*>(dst) = v4i{src[0], src[1], src[2], src[3]};
+  }
+}
+__device__ __forceinline__ int64_t ea_offset(const PlaneParams& p, int kb, unsigned gr) {
+  return ((int64_t)kb * p.tiles_m + (gr >> 8)) * 256 + ((gr >> 7) & 1) * 128 + (gr & 31) * 4 +
+         ((gr >> 5) & 3);
+}
+
+// The encode and quantisation of quant_a_kernel, one symbol's 128 rows x 128 k
+// per workgroup; rows past the block are neither loaded nor stored.  The last
+// symbol's last workgroups also write the rows that pad the stack to 256.
+__device__ __forceinline__ void pack_fp8_a(const PlaneParams& p, int b, int* t, float* red) {
+  const int nkb = p.kc / 2, nrb = (int)((p.Mb + 127) / 128);
+  const int kb = b % nkb, rb = b / nkb % nrb, si = b / nkb / nrb;
+  const int id_off = __builtin_amdgcn_readfirstlane(p.syms[4 * si + 0]);
+  const int deg = __builtin_amdgcn_readfirstlane(p.syms[4 * si + 1]);
+  const int32_t* ids = p.ids + id_off;
+  const int64_t k0 = (int64_t)kb * 128, r0 = (int64_t)rb * 128;
+  const int rows = p.Mb - r0 < 128 ? (int)(p.Mb - r0) : 128;
+  // Chunk i of a thread is 8 i rows below its first; past K it starts past the
+  // range of every buffer.
+  const int64_t lr0 = threadIdx.x / 32, kk = (threadIdx.x % 32) * 4;
+  const uint32_t off0 = k0 + kk < p.K ? (uint32_t)((lr0 * p.lda + kk) * 4) : 0x80000000u;
+  const uint32_t step = (uint32_t)(8 * p.lda * 4);
+  v4f x[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) x[i] = v4f{0.f, 0.f, 0.f, 0.f};
+  for (int m = 0; m < deg; ++m) {
+    const int64_t first = (int64_t)__builtin_amdgcn_readfirstlane(ids[m]) * p.Mb + r0;
+    int64_t have = p.M - first < rows ? p.M - first : rows;
+    if (have < 0) have = 0;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float*>(p.A + first * p.lda + k0), (short)0, (int)(have * p.lda * 4),
+        kRsrcWord3);
+    // eight loads in flight per thread: with sixteen the registers held three
+    // waves per SIMD instead of four
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      if (64 * h >= rows) break;
+      v4f v[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[i] = qload(rs, off0 + (uint32_t)(8 * h + i) * step);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) x[8 * h + i] += v[i];
+    }
+  }
+  float amax = 0.f;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const v4f s = x[i];
+    amax = fmaxf(amax, fmaxf(fmaxf(fabsf(s[0]), fabsf(s[1])), fmaxf(fabsf(s[2]), fabsf(s[3]))));
+  }
+  amax = block_amax(amax, red);
+  const float sc = pow2_scale(amax), inv = pow2_inverse(sc);
+  const unsigned row0 = (unsigned)si * (unsigned)p.Mb + (unsigned)r0;
+#pragma unroll
+  for (int pl = 0; pl < 2; ++pl) {
+    if (pl < p.planes) {
+      if (pl) __syncthreads();
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        if (8 * i >= rows) continue;
+        const int f = threadIdx.x + 256 * i;
+        const v4f v = x[i] * inv;
+        const int w = pack_e4m3(v);
+        t[f / 32 * kCodeRow + f % 32] = pl == 0 ? w : pack_e4m3((v - unpack_e4m3(w)) * 16.f);
+      }
+      __syncthreads();
+      put_codes(t, rows, row0, kb, p.kc, p.planes, pl, reinterpret_cast<unsigned char*>(p.ap));
+    }
+  }
+  for (int r = threadIdx.x; r < rows; r += 256)
+    p.ea[ea_offset(p, kb, row0 + (unsigned)r)] = (unsigned char)e8m0(sc);
+  if (si == p.n_sym - 1 && rb == nrb - 1) {  // pad rows: zero codes
+    const unsigned end = (unsigned)p.tiles_m * 256u, first = row0 + (unsigned)rows;
+    const int pad = (int)(end - first);
+    for (int f = threadIdx.x; f < pad * 8 * p.planes; f += 256) {
+      const unsigned gr = first + (unsigned)(f / (8 * p.planes));
+      const int g = f % 8, pl = f / 8 % p.planes;
+      unsigned char* dst = reinterpret_cast<unsigned char*>(p.ap) +
+                           (((int64_t)(gr >> 5) * p.kc + kb * 2 + (g >> 2)) * p.planes + pl) * 2048 +
+                           (g & 1) * 1024 + (((g >> 1) & 1) * 32 + (gr & 31)) * 16;
+      *reinterpret_cast<v4i*>(dst) = v4i{0, 0, 0, 0};
+    }
+    for (int r = threadIdx.x; r < pad; r += 256)
+      p.ea[ea_offset(p, kb, first + (unsigned)r)] = 127;
+  }
+}
+
+// quant_b_kernel's tile of 128 k x 128 columns.
+__device__ __forceinline__ void pack_fp8_b(const PlaneParams& p, int b, int* t, float* red) {
+  const int tn = p.tiles_n * 2;
+  const int nb = b % tn, kb = b / tn;
+  const int64_t n0 = (int64_t)nb * 128, k0 = (int64_t)kb * 128;
+  v4f x[16];
+  float amax = 0.f;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int f = threadIdx.x + 256 * i;
+    const int64_t k = k0 + f / 32, n = n0 + (f % 32) * 4;
+    v4f s = {0.f, 0.f, 0.f, 0.f};
+    if (k < p.K) {
+      const float* src = p.B + k * p.ldb + n;
+      if (n + 3 < p.N) {
+        s = *reinterpret_cast<const v4f*>(src);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (n + e < p.N) s[e] = src[e];
+      }
+    }
+    x[i] = s;
+    amax = fmaxf(amax, fmaxf(fmaxf(fabsf(s[0]), fabsf(s[1])), fmaxf(fabsf(s[2]), fabsf(s[3]))));
+  }
+  amax = block_amax(amax, red);
+  const float sc = pow2_scale(amax), inv = pow2_inverse(sc);
+  unsigned char* tb = reinterpret_cast<unsigned char*>(t);
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int f = threadIdx.x + 256 * i;
+    const int kl = f / 32, nl = (f % 32) * 4;
+    const int w = pack_e4m3(x[i] * inv);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      tb[(nl + e) * kCodeRow * 4 + kl] = (unsigned char)((w >> (8 * e)) & 0xff);
+  }
+  __syncthreads();
+  put_codes(t, 128, (unsigned)n0, kb, p.kc, 1, 0, reinterpret_cast<unsigned char*>(p.bp));
+  if (threadIdx.x == 0) p.eb[(int64_t)kb * tn + nb] = (unsigned)e8m0(sc) * 0x01010101u;
+}
+
+__global__ __launch_bounds__(256) void pack_fp8_kernel(PlaneParams p) {
+  __shared__ int t[128 * kCodeRow];
+  __shared__ float red[4];
+  const int b = blockIdx.x, blocks_b = p.tiles_n * 2 * (p.kc / 2);
+  if (b < blocks_b)
+    pack_fp8_b(p, b, t, red);
+  else
+    pack_fp8_a(p, b - blocks_b, t, red);
+}
+
+// 64 consecutive words (or one word 64 times) straight to LDS.
+__device__ __forceinline__ void copy_words(v4i rsrc, int lds, int voff, int soff) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+               "buffer_load_dword %1, %2, %3 offen lds"
+               ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+}
+__device__ __forceinline__ v4i uniform_rsrc(const void* base, int64_t bytes) {
+  const uint64_t a = reinterpret_cast<uint64_t>(base);
+  v4i r = {(int)a, (int)(a >> 32) & 0xffff, (int)bytes, kRsrcWord3};
+#pragma unroll
+  for (int c = 0; c < 4; ++c) r[c] = __builtin_amdgcn_readfirstlane(r[c]);
+  return r;
+}
+
+// Stages of 64 k: 8 panels of A, 8 of B, and each wave's own scale words (its
+// 128 rows', its 64 columns').  FP8x2 holds three stages (156 KiB), FP8 four.
+// Wave w copies panel w of A and of B.  As in the FP32 planes' loop a plane is
+// read while the other multiplies: the main codes under the residual products,
+// the next stage's residual codes, columns and scales under the main ones.
+template <int X2>
+struct Fp8Tile {
+  static constexpr int PA = X2 ? 4096 : 2048, PB = 2048;
+  static constexpr int B0 = 8 * PA, S0 = B0 + 8 * PB, STAGE = S0 + 8 * 512;
+  static constexpr int NBUF = X2 ? 3 : 4;
+  static constexpr int L = PA / 1024 + PB / 1024 + 2;  // copies per wave and stage
+};
+
+#define BPX_MX(i, j, a, b, sa, sb)                                                          \
+  acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a[i], b[j], acc[i][j], 0, 0, i, \
+                                                              sa, 0, sb)
+#define BPX_MX_COL(j, a, b, sa, sb)                   \
+  do {                                                \
+    BPX_MX(0, j, a, b, sa, sb);                       \
+    BPX_MX(1, j, a, b, sa, sb);                       \
+    BPX_MX(2, j, a, b, sa, sb);                       \
+    BPX_MX(3, j, a, b, sa, sb);                       \
+  } while (0)
+
+template <int X2>
+__global__ __launch_bounds__(NT) void gemm_fp8_packed_kernel(PlaneParams p) {
+  using T = Fp8Tile<X2>;
+  constexpr int NBUF = T::NBUF, STAGE = T::STAGE, L = T::L;
+  __shared__ __attribute__((aligned(1024))) char lds[NBUF * STAGE];
+  __shared__ float* rows[256];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+  int lin = (int)blockIdx.x, piece = -1;
+  if (lin >= p.full) {
+    piece = lin - p.full;
+    lin = p.full + piece / p.split;
+  } else {
+    lin = xcd_remap(lin, p.full);
+  }
+  int si, mt, nt;
+  tile_at<false>(p, lin, &si, &mt, &nt);
+  int kt0 = 0, kt1 = p.kc;
+  if (piece >= 0) {
+    const int s = piece % p.split;
+    kt0 = (int)((int64_t)s * p.kc / p.split);
+    kt1 = (int)((int64_t)(s + 1) * p.kc / p.split);
+  }
+  const int nk = kt1 - kt0;
+
+  const v4i ra = uniform_rsrc(
+      reinterpret_cast<const char*>(p.ap) + ((int64_t)mt * 8 + wave) * p.kc * T::PA,
+      (int64_t)p.kc * T::PA);
+  const v4i rb = uniform_rsrc(
+      reinterpret_cast<const char*>(p.bp) + ((int64_t)nt * 8 + wave) * p.kc * T::PB,
+      (int64_t)p.kc * T::PB);
+  const v4i rea = uniform_rsrc(p.ea + (int64_t)mt * 256 + (wave >> 2) * 128, -1);
+  const v4i reb = uniform_rsrc(p.eb + nt * 2 + ((wave >> 1) & 1), -1);
+  const int voff = lane * 16, vea = (lane & 31) * 4, vzero = 0;
+  const int base = (int)(uintptr_t)(lds_addr)lds;
+  int kp = kt0;  // next stage to copy
+  auto copy = [&](int st) __attribute__((always_inline)) {
+    copy_panel<T::PA / 1024>(ra, base + st + wave * T::PA, voff, kp * T::PA);
+    copy_panel<T::PB / 1024>(rb, base + st + T::B0 + wave * T::PB, voff, kp * T::PB);
+    copy_words(rea, base + st + T::S0 + wave * 512, vea, (kp >> 1) * p.tiles_m * 256);
+    copy_words(reb, base + st + T::S0 + wave * 512 + 256, vzero, (kp >> 1) * p.tiles_n * 8);
+    ++kp;
+  };
+#pragma unroll
+  for (int i = 0; i < NBUF; ++i)
+    if (i < nk) copy(i * STAGE);
+  if (tid < 256) rows[tid] = out_row<false>(p, 0, (unsigned)mt * 256u + (unsigned)tid);
+
+  Acc acc;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+
+  const int a_base = (wave >> 2) * 4 * T::PA + lane * 16;
+  const int b_base = T::B0 + (wave & 3) * 2 * T::PB + lane * 16;
+  const int s_base = T::S0 + wave * 512 + lane * 4;
+  auto read = [&](const char* at) __attribute__((always_inline)) -> v8i {
+    const v4i lo = *reinterpret_cast<const v4i*>(at);
+    const v4i hi = *reinterpret_cast<const v4i*>(at + 1024);
+    return v8i{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+  };
+  auto read_a = [&](v8i (&a)[4], const char* st, int plane) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a[i] = read(st + a_base + i * T::PA + plane * 2048);
+  };
+  auto read_b = [&](v8i (&b)[2], const char* st, int j) __attribute__((always_inline)) {
+    b[j] = read(st + b_base + j * T::PB);
+  };
+  auto read_s = [&](int& sa, int& sb, const char* st) __attribute__((always_inline)) {
+    sa = *reinterpret_cast<const int*>(st + s_base);
+    sb = *reinterpret_cast<const int*>(st + s_base + 256);
+  };
+  // Ends a stage (see multiply() of the BF16 planes); MORE: a further stage is
+  // copied into its buffer.  The loop body that copies has no branch, so that
+  // nothing is moved from one side of the barrier to the other.
+  using More = std::integral_constant<bool, true>;
+  using Last = std::integral_constant<bool, false>;
+  auto turn = [&](auto more) __attribute__((always_inline)) {
+    wait_counts<decltype(more)::value ? (NBUF - 2) * L : 0, true>();
+    barrier();
+  };
+  if (nk >= NBUF)
+    wait_counts<(NBUF - 1) * L, true>();
+  else
+    wait_counts<0, true>();
+  barrier();
+
+  int cur = 0;
+  v8i a0[4], a1[4], b0[2], b1[2];
+  int sa0, sb0, sa1, sb1;
+  read_a(a0, lds, X2 ? 1 : 0);
+  read_b(b0, lds, 0);
+  read_b(b0, lds, 1);
+  read_s(sa0, sb0, lds);
+  if constexpr (X2) {
+    // a0: residual codes, a1: main codes.  The registers hold one set of
+    // column fragments: each is read again as soon as its products are issued.
+    auto stage = [&](auto more, int sa, int sb, int& san, int& sbn)
+                     __attribute__((always_inline)) {
+      const int nxt = cur + STAGE == NBUF * STAGE ? 0 : cur + STAGE;
+      read_a(a1, lds + cur, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      const int sr = sa - 0x04040404;  // the residual codes carry a factor 16
+      BPX_MX_COL(0, a0, b0, sr, sb);
+      BPX_MX_COL(1, a0, b0, sr, sb);
+      __builtin_amdgcn_sched_barrier(0);
+      turn(more);
+      read_s(san, sbn, lds + nxt);
+      read_a(a0, lds + nxt, 1);
+      if (decltype(more)::value) copy(cur);
+      __builtin_amdgcn_sched_barrier(0);
+      BPX_MX_COL(0, a1, b0, sa, sb);
+      __builtin_amdgcn_sched_barrier(0);
+      read_b(b0, lds + nxt, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      BPX_MX_COL(1, a1, b0, sa, sb);
+      __builtin_amdgcn_sched_barrier(0);
+      read_b(b0, lds + nxt, 1);
+      cur = nxt;
+    };
+    // pairs of stages, so that the scales' registers alternate in place
+    int kt = 0;
+    for (; kt < nk - NBUF - 1; kt += 2) {
+      stage(More{}, sa0, sb0, sa1, sb1);
+      stage(More{}, sa1, sb1, sa0, sb0);
+    }
+    if (kt < nk - NBUF) {
+      stage(More{}, sa0, sb0, sa1, sb1);
+      sa0 = sa1;
+      sb0 = sb1;
+      ++kt;
+    }
+    for (; kt < nk; kt += 2) {
+      stage(Last{}, sa0, sb0, sa1, sb1);
+      if (kt + 1 < nk) stage(Last{}, sa1, sb1, sa0, sb0);
+    }
+  } else {
+    auto stage = [&](auto more, v8i (&a)[4], v8i (&b)[2], int sa, int sb, v8i (&an)[4],
+                     v8i (&bn)[2], int& san, int& sbn) __attribute__((always_inline)) {
+      const int nxt = cur + STAGE == NBUF * STAGE ? 0 : cur + STAGE;
+      turn(more);
+      read_a(an, lds + nxt, 0);
+      read_b(bn, lds + nxt, 0);
+      read_b(bn, lds + nxt, 1);
+      read_s(san, sbn, lds + nxt);
+      if (decltype(more)::value) copy(cur);
+      __builtin_amdgcn_sched_barrier(0);
+      BPX_MX_COL(0, a, b, sa, sb);
+      BPX_MX_COL(1, a, b, sa, sb);
+      __builtin_amdgcn_sched_barrier(0);
+      cur = nxt;
+    };
+    // pairs of stages, so that the two sets of registers alternate in place
+    int kt = 0;
+    for (; kt < nk - NBUF - 1; kt += 2) {
+      stage(More{}, a0, b0, sa0, sb0, a1, b1, sa1, sb1);
+      stage(More{}, a1, b1, sa1, sb1, a0, b0, sa0, sb0);
+    }
+    if (kt < nk - NBUF) {
+      stage(More{}, a0, b0, sa0, sb0, a1, b1, sa1, sb1);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) a0[i] = a1[i];
+      b0[0] = b1[0];
+      b0[1] = b1[1];
+      sa0 = sa1;
+      sb0 = sb1;
+      ++kt;
+    }
+    for (; kt < nk; kt += 2) {
+      stage(Last{}, a0, b0, sa0, sb0, a1, b1, sa1, sb1);
+      if (kt + 1 < nk) stage(Last{}, a1, b1, sa1, sb1, a0, b0, sa0, sb0);
+    }
+  }
+  if (piece >= 0)
+    store_part(acc, p.part + (int64_t)piece * 65536, wave, lane);
+  else
+    store_tile(acc, rows, (int64_t)nt * 256, p.Nb, wave, lane);
+}
+
 }  // namespace
 
 hipError_t launch_quant_a(const Fp8Params& p, hipStream_t stream) {
@@ -590,6 +990,29 @@ hipError_t launch_quant_b(const Fp8Params& p, hipStream_t stream) {
   const dim3 grid((unsigned)(p.Np / 128), (unsigned)(p.Kp / 128));
   hipLaunchKernelGGL(quant_b_kernel, grid, dim3(256), 0, stream, p);
   return hipGetLastError();
+}
+
+hipError_t launch_pack_fp8(const PlaneParams& p0, hipStream_t stream) {
+  PlaneParams p = p0;
+  planes_tiles(&p);
+  if (128 * p.lda * 4 >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
+  const int64_t blocks = (int64_t)p.tiles_n * 2 * (p.kc / 2) +
+                         (int64_t)p.n_sym * ((p.Mb + 127) / 128) * (p.kc / 2);
+  if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(pack_fp8_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, p);
+  return hipGetLastError();
+}
+
+hipError_t launch_gemm_fp8_packed(const PlaneParams& p0, hipStream_t stream) {
+  PlaneParams p = p0;
+  planes_tiles(&p);
+  p.row_group = 2;
+  const int64_t T = (int64_t)p.tiles_m * p.tiles_n;
+  planes_split(&p, T, p.planes == 2 ? 1.3 : 0.7, 4);
+  hipLaunchKernelGGL(p.planes == 2 ? gemm_fp8_packed_kernel<1> : gemm_fp8_packed_kernel<0>,
+                     dim3((unsigned)(p.full + (T - p.full) * p.split)), dim3(NT), 0, stream, p);
+  const hipError_t e = hipGetLastError();
+  return e != hipSuccess ? e : launch_planes_reduce(p, T, stream);
 }
 
 int32_t fp8_tile_count() { return 2; }
@@ -616,10 +1039,10 @@ hipError_t launch_coded_gemm_fp8(const Fp8Params& p0, int32_t tile, hipStream_t 
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;
     if (p.aq2)
       hipLaunchKernelGGL((coded_gemm_fp8_wide_kernel<128, 2, 4, 1>), dim3((unsigned)blocks),
-                         dim3(wide8::NT), 0, stream, p);
+                         dim3(NT), 0, stream, p);
     else
       hipLaunchKernelGGL((coded_gemm_fp8_wide_kernel<128, 2, 4, 0>), dim3((unsigned)blocks),
-                         dim3(wide8::NT), 0, stream, p);
+                         dim3(NT), 0, stream, p);
     return hipGetLastError();
   }
   p.tiles_m = (int32_t)((p.Mb + 127) / 128);

@@ -41,24 +41,13 @@
 #include <type_traits>
 
 #include "kernels.hpp"
+#include "planes.hpp"
 
 namespace bpx {
 namespace {
 
-typedef float v4f __attribute__((ext_vector_type(4)));
-typedef float v16f __attribute__((ext_vector_type(16)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-typedef int v4i __attribute__((ext_vector_type(4)));
 typedef unsigned short us;
-typedef __attribute__((address_space(3))) void* lds_addr;
-typedef __attribute__((address_space(1))) float gfloat;
-typedef __attribute__((address_space(1))) v4f gv4f;
-
-constexpr int kRsrcWord3 = 0x00020000;  // gfx9 raw buffer, 32-bit elements
-
-__device__ __forceinline__ int32_t gld(const int32_t* ptr) {
-  return *(const __attribute__((address_space(1))) int32_t*)ptr;
-}
 
 // ------------------------------------------------------------------ pack --
 // Eight consecutive k of one row, split into P planes.
@@ -243,8 +232,6 @@ __global__ __launch_bounds__(256) void pack_planes_kernel(PlaneParams p) {
 // on zero operands: power, not issue, is what is left); the FP32 MFMA
 // kernels took 4.64 ms.  BF16x3 1.27 ms against 2.31 ms for the kernel that
 // encodes and splits A while staging.
-constexpr int NT = 512;
-
 // k steps per stage and stages in LDS (144, 128 and 128 KiB).
 template <int P>
 struct Cfg;
@@ -267,94 +254,6 @@ struct Frags {
   v8bf a[4][P], b[2][P];
 };
 
-// Consecutive workgroups go to different XCDs; each XCD gets a contiguous
-// range of tiles.
-__device__ __forceinline__ int xcd_remap(int lin, int total) {
-  if ((total & 7) != 0) return lin;
-  return (lin & 7) * (total >> 3) + (lin >> 3);
-}
-
-// Waits until at most VM vector-memory operations of this wave are in
-// flight, and for all of its LDS operations if LGKM.
-template <int VM, bool LGKM>
-__device__ __forceinline__ void wait_counts() {
-  __builtin_amdgcn_s_waitcnt((VM & 15) | ((VM >> 4) << 14) | (7 << 4) | ((LGKM ? 0 : 15) << 8));
-}
-__device__ __forceinline__ void barrier() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
-// Copies COUNT consecutive KiB of a packed panel straight to LDS, 16 bytes
-// per lane (the instruction offset moves both addresses).  Written as asm
-// because the compiler would wait for every copy in flight before any later
-// LDS read; the waits are the loop's own.
-template <int COUNT>
-__device__ __forceinline__ void copy_panel(v4i rsrc, int lds, int voff, int soff) {
-  if constexpr (COUNT == 2)
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
-                 "buffer_load_dwordx4 %1, %2, %3 offen lds\n\t"
-                 "buffer_load_dwordx4 %1, %2, %3 offen offset:1024 lds"
-                 ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
-  if constexpr (COUNT == 3)
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
-                 "buffer_load_dwordx4 %1, %2, %3 offen lds\n\t"
-                 "buffer_load_dwordx4 %1, %2, %3 offen offset:1024 lds\n\t"
-                 "buffer_load_dwordx4 %1, %2, %3 offen offset:2048 lds"
-                 ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
-  if constexpr (COUNT == 4)
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
-                 "buffer_load_dwordx4 %1, %2, %3 offen lds\n\t"
-                 "buffer_load_dwordx4 %1, %2, %3 offen offset:1024 lds\n\t"
-                 "buffer_load_dwordx4 %1, %2, %3 offen offset:2048 lds\n\t"
-                 "buffer_load_dwordx4 %1, %2, %3 offen offset:3072 lds"
-                 ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
-  static_assert(COUNT >= 2 && COUNT <= 4, "KiB per panel and stage");
-}
-
-// Tile order: groups of 8 row panels, column panel by column panel, so the 32
-// tiles an XCD runs at once share 8 row panels and 4 column panels in its L2.
-// In the two-dimensional form one symbol comes after the other, and an eighth
-// of each goes to each XCD, in groups of 4 row panels (whole ranges of 32
-// tiles per XCD gave some XCDs more of the long symbols: 12.2 against 10.8 ms
-// for the 8192^3 workload's call).
-template <bool GRID>
-__device__ __forceinline__ void tile_at(const PlaneParams& p, int lin, int* si, int* mt, int* nt) {
-  constexpr int kRowGroup = GRID ? 4 : 8;
-  *si = 0;
-  if (GRID) {
-    const int per_sym = p.tiles_m * p.tiles_n;
-    *si = lin / per_sym;
-    lin -= *si * per_sym;
-    if ((per_sym & 7) == 0) lin = (lin & 7) * (per_sym >> 3) + (lin >> 3);
-  }
-  const int per_group = kRowGroup * p.tiles_n;
-  const int first = lin / per_group * kRowGroup;
-  const int gsz = p.tiles_m - first < kRowGroup ? p.tiles_m - first : kRowGroup;
-  const int r = lin - (first / kRowGroup) * per_group;
-  *mt = first + r % gsz;
-  *nt = r / gsz;
-}
-
-// Where row r of the coded products goes (null: nowhere): of the stacked rows
-// of all symbols, or of symbol si's product in the two-dimensional form.
-template <bool GRID>
-__device__ __forceinline__ float* out_row(const PlaneParams& p, int si, unsigned r) {
-  if (!GRID) {
-    if (r >= (unsigned)p.n_sym * (unsigned)p.Mb) return nullptr;
-    si = (int)(r / (unsigned)p.Mb);
-    r -= (unsigned)si * (unsigned)p.Mb;
-  } else if (r >= (unsigned)p.Mb) {
-    return nullptr;
-  }
-  const int dest = gld(p.syms + 4 * si + 2);
-  if (dest >= 0) return p.Y + ((int64_t)dest * p.Mb + r) * p.Nb;
-  const int s = -1 - dest, br = GRID ? s / p.grid : s;
-  const int64_t row = (int64_t)br * p.Mb + r;
-  return row < p.M ? p.C + row * p.ldc + (int64_t)(s - br * p.grid) * (GRID ? p.Nb : 0) : nullptr;
-}
-
 template <int P>
 struct Tile {
   static constexpr int STEPS = Cfg<P>::STEPS, NBUF = Cfg<P>::NBUF;
@@ -363,7 +262,6 @@ struct Tile {
   static constexpr int L = 2 * STEPS * P;       // 1 KiB copies per wave per stage
   static constexpr int LDS = NBUF * STAGE;
 };
-typedef v16f Acc[4][2];
 
 // The copies of one tile's stages to LDS, in order: wave w copies panels 2w,
 // 2w + 1 of a stage (waves 0-3 A, 4-7 B).
@@ -467,13 +365,14 @@ __device__ __forceinline__ void multiply(Feed<P, GRID>& feed, int nk, const char
   using I1 = std::integral_constant<int, P >= 2 ? 1 : 0>;
   using I2 = std::integral_constant<int, P == 3 ? 2 : 0>;
 
-  // ends stage kt: the next stage has landed everywhere, and this stage's
-  // buffer may be refilled
-  auto turn = [&](int kt) __attribute__((always_inline)) {
-    if (kt + NBUF - 1 < nk)
-      wait_counts<(NBUF - 2) * L, true>();
-    else
-      wait_counts<0, true>();
+  // Ends a stage: the next stage has landed everywhere, and this stage's
+  // buffer may be refilled.  MORE: a further stage is copied into it; the loop
+  // body that copies has no branch, so that nothing is moved from one side of
+  // the barrier to the other.
+  using More = std::integral_constant<bool, true>;
+  using Last = std::integral_constant<bool, false>;
+  auto turn = [&](auto more) __attribute__((always_inline)) {
+    wait_counts<decltype(more)::value ? (NBUF - 2) * L : 0, true>();
     barrier();
   };
 
@@ -489,7 +388,7 @@ __device__ __forceinline__ void multiply(Feed<P, GRID>& feed, int nk, const char
     Frags<P> f;
     read_a(f, lds, 0, 1);
     read_b(f, lds, 0, 1);
-    for (int kt = 0; kt < nk; ++kt) {
+    auto stage = [&](auto more) __attribute__((always_inline)) {
       const int nxt = cur + STAGE == NBUF * STAGE ? 0 : cur + STAGE;
       const char* S = lds + cur;
       const char* N = lds + nxt;
@@ -504,17 +403,19 @@ __device__ __forceinline__ void multiply(Feed<P, GRID>& feed, int nk, const char
       mul(f, I0{}, I1{});
       mul(f, I1{}, I0{});
       __builtin_amdgcn_sched_barrier(0);
-      turn(kt);
+      turn(more);
       read_a(f, N, 0, 1);  // (past the last stage: read, never used)
       read_b(f, N, 0, 1);
-      if (kt + NBUF < nk) feed.copy(cur);
+      if (decltype(more)::value) feed.copy(cur);
       __builtin_amdgcn_sched_barrier(0);
       mul(f, I0{}, I2{});
       mul(f, I2{}, I0{});
       mul(f, I0{}, I0{});
       __builtin_amdgcn_sched_barrier(0);
       cur = nxt;
-    }
+    };
+    for (int kt = 0; kt < nk - NBUF; ++kt) stage(More{});
+    for (int kt = nk - NBUF < 0 ? 0 : nk - NBUF; kt < nk; ++kt) stage(Last{});
   } else {
     static_assert(P == 3 || T::STEPS == 2, "two k steps per stage");
     Frags<P> f0, f1;
@@ -533,42 +434,22 @@ __device__ __forceinline__ void multiply(Feed<P, GRID>& feed, int nk, const char
       mul(f, I0{}, I0{});
     };
     read(f0, lds, 0);
-    for (int kt = 0; kt < nk; ++kt) {
+    auto stage = [&](auto more) __attribute__((always_inline)) {
       const int nxt = cur + STAGE == NBUF * STAGE ? 0 : cur + STAGE;
       read(f1, lds + cur, 1);
       __builtin_amdgcn_sched_barrier(0);
       step(f0);
       __builtin_amdgcn_sched_barrier(0);
-      turn(kt);
+      turn(more);
       read(f0, lds + nxt, 0);  // (past the last stage: read, never used)
-      if (kt + NBUF < nk) feed.copy(cur);
+      if (decltype(more)::value) feed.copy(cur);
       __builtin_amdgcn_sched_barrier(0);
       step(f1);
       __builtin_amdgcn_sched_barrier(0);
       cur = nxt;
-    }
-  }
-}
-
-// Writes an accumulated tile to its output rows: lane l holds column l % 32,
-// rows 8 (e / 4) + 4 (l / 32) + e % 4 of each 32 x 32.
-__device__ __forceinline__ void store_tile(const Acc& acc, float* const* rows, int64_t n_tile,
-                                           int64_t Nb, int wave, int lane) {
-  const int64_t n0 = n_tile + (wave & 3) * 64 + (lane & 31);
-  const bool in0 = n0 < Nb, in1 = n0 + 32 < Nb;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    float* out[16];  // read together: one LDS latency per 16 rows
-#pragma unroll
-    for (int e = 0; e < 16; ++e)
-      out[e] = rows[(wave >> 2) * 128 + i * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3)];
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      gfloat* o = (gfloat*)out[e] + n0;
-      if (out[e] && in0) o[0] = acc[i][0][e];
-      if (out[e] && in1) o[32] = acc[i][1][e];
-    }
+    };
+    for (int kt = 0; kt < nk - NBUF; ++kt) stage(More{});
+    for (int kt = nk - NBUF < 0 ? 0 : nk - NBUF; kt < nk; ++kt) stage(Last{});
   }
 }
 
@@ -621,15 +502,7 @@ __global__ __launch_bounds__(NT) void gemm_planes_kernel(PlaneParams p) {
   Acc acc;
   multiply<P, GRID>(feed, kt1 - kt0, lds, wave, lane, acc);
   if (piece >= 0) {
-    gfloat* out = (gfloat*)(p.part + (int64_t)piece * 65536) + (wave & 3) * 64 + (lane & 31);
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int row = (wave >> 2) * 128 + i * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
-#pragma unroll
-        for (int j = 0; j < 2; ++j) out[row * 256 + 32 * j] = acc[i][j][e];
-      }
+    store_part(acc, p.part + (int64_t)piece * 65536, wave, lane);
     return;
   }
   store_tile(acc, rows, (int64_t)nt * 256, p.Nb, wave, lane);
@@ -719,18 +592,17 @@ __global__ __launch_bounds__(256) void planes_reduce_kernel(PlaneParams p) {
 
 }  // namespace
 
-namespace {
-void set_tiles(PlaneParams* p) {
+void planes_tiles(PlaneParams* p) {
   const int64_t rows = p->grid > 1 ? p->Mb : (int64_t)p->n_sym * p->Mb;
   p->tiles_m = (int32_t)((rows + 255) / 256);
   p->tiles_n = (int32_t)((p->Nb + 255) / 256);
+  p->row_group = p->grid > 1 ? 4 : 8;
   p->nka = (p->kc + 15) / 16;
   p->nkb = (p->kc + 3) / 4;
 }
-}  // namespace
 
 int64_t planes_group_setup(PlaneParams* p) {
-  set_tiles(p);
+  planes_tiles(p);
   return (int64_t)p->cols64 * p->nkb + (int64_t)p->rows32 * p->nka;
 }
 
@@ -754,7 +626,7 @@ hipError_t launch_gemm_planes_grouped(const GroupDesc* d, const GroupTile* tiles
 
 hipError_t launch_pack_planes(const PlaneParams& p0, hipStream_t stream) {
   PlaneParams p = p0;
-  set_tiles(&p);
+  planes_tiles(&p);
   const unsigned blocks = (unsigned)p.cols64 * (unsigned)p.nkb + (unsigned)p.rows32 * (unsigned)p.nka;
   void (*k)(PlaneParams) = p.grid > 1      ? pack_planes_kernel<3, true>
                            : p.planes == 3 ? pack_planes_kernel<3, false>
@@ -764,51 +636,59 @@ hipError_t launch_pack_planes(const PlaneParams& p0, hipStream_t stream) {
   return hipGetLastError();
 }
 
-hipError_t launch_gemm_planes(const PlaneParams& p0, hipStream_t stream) {
-  PlaneParams p = p0;
-  set_tiles(&p);
-  const int64_t T = (int64_t)p.tiles_m * p.tiles_n * (p.grid > 1 ? p.n_sym : 1);
+// The last round: R of the tiles, each split into q pieces of its K range
+// whose partial tiles a second kernel sums, where a model of both says that
+// ends sooner: rounds of pieces at the measured time of a k chunk of one tile,
+// 6 us for the second launch and 0.125 us per partial tile written and read
+// back (4 TB/s).  1999 x 1500 x 1001, 36 tiles: 14 pieces, GEMM 43 and sum 11
+// us, where whole tiles would take 190 us.  R is what the products of all
+// tiles leave over after whole rounds (everything if that is less than one
+// round); in the two-dimensional form only one-pass tiles, which come last,
+// can fill up a round.
+void planes_split(PlaneParams* p, int64_t T, double us, int min_chunks) {
   const int64_t S = device_cu_count();
-  if (T > 0x7fffffff / 32) return hipErrorInvalidValue;
-  // The last round: R of the tiles, each split into q pieces of its K range
-  // whose partial tiles a second kernel sums, where a model of both says that
-  // ends sooner: rounds of pieces at the measured time of a 16-wide k chunk of
-  // one tile, 6 us for the second launch and 0.125 us per partial tile written
-  // and read back (4 TB/s).  1999 x 1500 x 1001, 36 tiles: 14 pieces, GEMM 43
-  // and sum 11 us, where whole tiles would take 140 us.  R is what the products
-  // of all tiles leave over after whole rounds (everything if that is less
-  // than one round); in the two-dimensional form only one-pass tiles, which
-  // come last, can fill up a round.
-  const int64_t per = p.grid > 1 ? T / p.n_sym : 1;
-  const int64_t units = p.grid > 1 ? p.n_passes * per : T;
-  const int64_t R = units <= S ? T
-                    : p.grid > 1 ? std::min(units % S, p.n_single * per) : T % S;
+  const int64_t per = p->grid > 1 ? T / p->n_sym : 1;
+  const int64_t units = p->grid > 1 ? p->n_passes * per : T;
+  const int64_t R = units <= S      ? T
+                    : p->grid > 1 ? std::min(units % S, p->n_single * per)
+                                  : T % S;
   const int64_t ru = units <= S ? units : R;
-  const double us = p.planes == 3 ? 2.0 : p.planes == 2 ? 1.05 : 0.45;
   int64_t best_q = 1;
-  double best = p.kc * us;
+  double best = p->kc * us;
   for (int64_t q = 2; q <= 16 && R > 0; ++q) {
-    if (R * q > p.part_tiles || p.kc / q < 8) break;
-    const double t = (double)((ru * q + S - 1) / S) * (double)p.kc * us / (double)q + 6.0 +
+    if (R * q > p->part_tiles || p->kc / q < min_chunks) break;
+    const double t = (double)((ru * q + S - 1) / S) * (double)p->kc * us / (double)q + 6.0 +
                      0.125 * (double)(R * q);
     if (t < best) {
       best = t;
       best_q = q;
     }
   }
-  p.split = (int32_t)best_q;
-  p.full = (int32_t)(best_q > 1 ? T - R : T);
-  const unsigned blocks = (unsigned)(p.full + (T - p.full) * best_q);
+  p->split = (int32_t)best_q;
+  p->full = (int32_t)(best_q > 1 ? T - R : T);
+}
+
+hipError_t launch_planes_reduce(const PlaneParams& p, int64_t T, hipStream_t stream) {
+  if (p.full == T) return hipSuccess;
+  hipLaunchKernelGGL(p.grid > 1 ? planes_reduce_kernel<true> : planes_reduce_kernel<false>,
+                     dim3((unsigned)((T - p.full) * 64)), dim3(256), 0, stream, p);
+  return hipGetLastError();
+}
+
+hipError_t launch_gemm_planes(const PlaneParams& p0, hipStream_t stream) {
+  PlaneParams p = p0;
+  planes_tiles(&p);
+  const int64_t T = (int64_t)p.tiles_m * p.tiles_n * (p.grid > 1 ? p.n_sym : 1);
+  if (T > 0x7fffffff / 32) return hipErrorInvalidValue;
+  planes_split(&p, T, p.planes == 3 ? 2.0 : p.planes == 2 ? 1.05 : 0.45, 8);
+  const unsigned blocks = (unsigned)(p.full + (T - p.full) * p.split);
   void (*k)(PlaneParams) = p.grid > 1      ? gemm_planes_kernel<3, true>
                            : p.planes == 3 ? gemm_planes_kernel<3, false>
                            : p.planes == 2 ? gemm_planes_kernel<2, false>
                                            : gemm_planes_kernel<1, false>;
   hipLaunchKernelGGL(k, dim3(blocks), dim3(NT), 0, stream, p);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || p.full == T) return e;
-  hipLaunchKernelGGL(p.grid > 1 ? planes_reduce_kernel<true> : planes_reduce_kernel<false>,
-                     dim3((unsigned)((T - p.full) * 64)), dim3(256), 0, stream, p);
-  return hipGetLastError();
+  const hipError_t e = hipGetLastError();
+  return e != hipSuccess ? e : launch_planes_reduce(p, T, stream);
 }
 
 }  // namespace bpx

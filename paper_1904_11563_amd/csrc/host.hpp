@@ -162,14 +162,23 @@ struct bpx_plan {
     return off[6];
   }
   // Products past the fused form's size (2^31 multiply-adds over the computed
-  // symbols) also reserve room for the operands split into BF16 planes
-  // (gemm_planes.hip), behind the parts above; below it the pack pass and the
-  // 256 x 256 tiles cost more than they save.
+  // symbols) also reserve room for the operands packed in the order of MFMA
+  // fragments (gemm_planes.hip: BF16 planes; gemm_fp8.hip: codes), behind the
+  // parts above; below it the pack pass and the 256 x 256 tiles cost more than
+  // they save.
   int32_t planes() const {
-    return prec == BPX_PREC_F32 ? 3 : prec == BPX_PREC_BF16X3 ? 2 : 1;
+    switch (prec) {
+      case BPX_PREC_F32: return 3;
+      case BPX_PREC_BF16X3: case BPX_PREC_FP8X2: return 2;
+      default: return 1;
+    }
   }
-  // 16-wide k chunks of the packed operands, whole stages of the GEMM
-  int64_t plane_kc() const { return planes() == 3 ? (K + 15) / 16 : (K + 31) / 32 * 2; }
+  // k chunks of the packed operands, whole stages of the GEMM: 16 wide, for
+  // FP8 64 wide (and K padded to 128).
+  int64_t plane_kc() const {
+    if (is_fp8()) return r128(K) / 64;
+    return planes() == 3 ? (K + 15) / 16 : (K + 31) / 32 * 2;
+  }
   static int64_t r256(int64_t x) { return (x + 255) / 256 * 256; }
   int64_t plane_rows() const {
     return grid > 1 ? (int64_t)(ops.a_ops.size() / 2) * r256(Mb)
@@ -190,37 +199,51 @@ struct bpx_plan {
     const double macs = (double)n_products() * (double)Mb * (double)K * (double)Nb;
     return macs > 2147483648.0 && planes_fit();
   }
+  // Bytes of 32 packed rows (columns) and one k chunk, all planes.
+  int64_t a_chunk_bytes() const { return (int64_t)planes() * (is_fp8() ? 2048 : 1024); }
+  int64_t b_chunk_bytes() const { return is_fp8() ? 2048 : a_chunk_bytes(); }
   // The kernels' 32-bit indices and offsets hold.
   bool planes_fit() const {
-    if (is_fp8() || K % 4 != 0) return false;
-    const int64_t lim = (int64_t)1 << 31;
-    return plane_rows() < lim && plane_cols() < lim &&
-           (double)n_products() * (double)plane_kc() < (double)lim &&
-           plane_kc() * planes() * 8192 < lim && plane_tiles() < lim / 32 &&
-           plane_rows() / 32 * ((plane_kc() + 15) / 16) + plane_cols() / 64 * ((plane_kc() + 3) / 4) <
-               lim;
+    if (K % 4 != 0) return false;
+    const int64_t lim = (int64_t)1 << 31, kc = plane_kc();
+    if (plane_rows() >= lim || plane_cols() >= lim || plane_tiles() >= lim / 32 ||
+        (double)n_products() * (double)kc >= (double)lim || kc * a_chunk_bytes() * 8 >= lim)
+      return false;
+    if (is_fp8())
+      return (double)kc * (double)plane_rows() < (double)lim &&
+             (double)kc * (double)plane_cols() < (double)lim &&
+             (double)computed.size() * (double)r128(Mb) / 128 * (double)kc < (double)lim;
+    return plane_rows() / 32 * ((kc + 15) / 16) + plane_cols() / 64 * ((kc + 3) / 4) < lim;
   }
-  static constexpr int32_t kPartTiles = 512;
   // Packed operands of a grouped product (no flags, no partial tiles).
   size_t packed_bytes() const {
-    return (size_t)(plane_rows() + plane_cols()) * plane_kc() * 32 * planes();
+    return (size_t)(plane_rows() + plane_cols()) / 32 * plane_kc() * a_chunk_bytes();
   }
   // Offsets of the plane parts, from the start of the workspace: packed A,
-  // packed B, flags of A, flags of B (planes() == 3), partial tiles; [5] the end.
+  // packed B, flags (FP32) or scales (FP8) of A, of B, partial tiles; [5] the end.
   void plane_layout(size_t off[6]) const {
-    size_t b = base_bytes();
+    const size_t kc = (size_t)plane_kc();
+    size_t b = base_bytes(), sa = 0, sb = 0;
+    if (planes() == 3) {
+      sa = (size_t)(plane_rows() / 32) * ((kc + 15) / 16) * 4;
+      sb = (size_t)(plane_cols() / 64) * ((kc + 3) / 4) * 4;
+    } else if (is_fp8()) {
+      sa = kc / 2 * (size_t)plane_rows();
+      sb = kc / 2 * (size_t)(plane_cols() / 128) * 4;
+    }
     off[0] = b;
-    b += (size_t)plane_rows() * plane_kc() * 32 * planes();
+    b += (size_t)plane_rows() / 32 * kc * a_chunk_bytes();
     off[1] = b;
-    b += (size_t)plane_cols() * plane_kc() * 32 * planes();
+    b += (size_t)plane_cols() / 32 * kc * b_chunk_bytes();
     off[2] = b;
-    if (planes() == 3) b += align256((size_t)(plane_rows() / 32) * ((plane_kc() + 15) / 16) * 4);
+    b += align256(sa);
     off[3] = b;
-    if (planes() == 3) b += align256((size_t)(plane_cols() / 64) * ((plane_kc() + 3) / 4) * 4);
+    b += align256(sb);
     off[4] = b;
     b += (size_t)plane_part_tiles() * 65536 * sizeof(float);
     off[5] = b;
   }
+  static constexpr int32_t kPartTiles = 512;
   int32_t plane_part_tiles() const {
     const int64_t t = plane_tiles() * 16;
     return t < kPartTiles ? (int32_t)t : kPartTiles;

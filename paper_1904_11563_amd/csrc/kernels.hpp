@@ -151,14 +151,14 @@ struct PlaneParams {
   const int32_t* syms;
   const int32_t* ids;
   int32_t n_sym;
-  int32_t planes;      // 1: BF16, 2: BF16x3, 3: FP32
+  int32_t planes;      // 1: BF16, 2: BF16x3, 3: FP32 (FP8: codes of A, 1 or 2)
   unsigned short* ap;  // packed planes of the stacked coded rows
   unsigned short* bp;  // packed planes of B's columns
   unsigned* fa;        // planes == 3: per pack block, 1 if it holds a value
   unsigned* fb;        //   that is not split
   float* part;         // partial 256 x 256 tiles of the last round
   int32_t part_tiles;  // how many part holds
-  int32_t kc;          // 16-wide k chunks of the packed operands
+  int32_t kc;          // 16-wide k chunks of the packed operands (FP8: 64-wide)
   int32_t rows32, cols64;  // 32-row panels of ap, 64-column pack blocks of bp
   // Two-dimensional form (grid > 1): ap and bp hold the distinct sums of A row
   // blocks and of B column blocks the symbols need, op by op, every op padded
@@ -171,13 +171,26 @@ struct PlaneParams {
   const int32_t* sym_passes;  // {first pass, passes} per symbol
   const int32_t* passes;      // {A op, B op} per pass
   int32_t n_passes, n_single;  // passes of all symbols; symbols with one
+  // FP8 (launch_pack_fp8, launch_gemm_fp8_packed): E8M0 scale bytes per 128-wide
+  // k chunk, of every stacked row and of every 128 columns (four equal bytes)
+  unsigned char* ea;
+  unsigned* eb;
   // set by the launcher
   int32_t tiles_m, tiles_n;   // per symbol in the two-dimensional form
+  int32_t row_group;   // row panels per group of the tile order
   int32_t nka, nkb;    // pack blocks along k of A (256 wide) and of B (64 wide)
   int32_t full, split; // tiles computed whole; K pieces of each of the others
 };
 hipError_t launch_pack_planes(const PlaneParams& p, hipStream_t stream);
 hipError_t launch_gemm_planes(const PlaneParams& p, hipStream_t stream);
+hipError_t launch_pack_fp8(const PlaneParams& p, hipStream_t stream);
+hipError_t launch_gemm_fp8_packed(const PlaneParams& p, hipStream_t stream);
+// tiles_m, tiles_n of a row-block product; how many of its T tiles run whole
+// and in how many K pieces the others (full, split), given the time of one
+// k chunk of a tile in us; and the kernel that sums the pieces.
+void planes_tiles(PlaneParams* p);
+void planes_split(PlaneParams* p, int64_t T, double us, int min_chunks);
+hipError_t launch_planes_reduce(const PlaneParams& p, int64_t T, hipStream_t stream);
 
 int32_t bf16_tile_count();
 TileShape bf16_tile_shape(int32_t t);

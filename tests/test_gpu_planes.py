@@ -222,3 +222,54 @@ def test_grouped_split_planes_exact_and_like_direct_kernels(prec):
                 # the same splits, summed in another order
                 new, old = _err(outs[0][i], R), _err(outs[1][i], R)
                 assert new <= old * 1.1 + 1e-6, (shapes[i], new, old)
+
+
+# M, K, N: blocks of 40 and of 300 rows (several symbols in one fragment, a
+# block over three scale blocks), ragged columns and K, the shortest K (two
+# stages) and K of 2, 3 and 5 scale blocks, tiles split along K and not
+@pytest.mark.parametrize("prec", [bpx.PREC_FP8X2, bpx.PREC_FP8])
+@pytest.mark.parametrize("code,shape", [("moj", (5000, 1000, 2001)), ("642", (2400, 500, 3000)),
+                                        ("642", (9000, 100, 8200)), ("642", (9000, 200, 6000)),
+                                        ("642", (2048, 4100, 513)), ("moj", (1500, 640, 2304))])
+def test_packed_fp8_like_direct_kernels(code, shape, prec):
+    """The codes and scales are those of the direct kernels (checked there
+    against the oracle), so the products differ by the MFMA's own summation
+    only: within 1e-4 of them (1.5e-5 measured between that and float64), far
+    below what a wrong row, scale or plane gives."""
+    M, K, N = shape
+    lib = _code(inputs.CODE_642) if code == "642" else bpx.Code.mojette(16, 8, 24, 0)
+    n = lib.info()["n"]
+    arrival, _ = inputs.shifted_exp_arrival(3, n)
+    mode = bpx.MODE_FULL if code == "642" else bpx.MODE_STRAGGLER
+    plan = bpx.Plan(lib, arrival, 0, mode, M, K, N, prec)
+    assert plan.workspace_bytes()[0] > plan.workspace_layout()[6]
+    A, B = _ops(8, M, K, N, False)
+    # rows and columns of very different scale, so that a scale applied to
+    # another row or column shows
+    A = A * torch.logspace(-3, 3, M, device="cuda")[torch.randperm(M, device="cuda")][:, None]
+    B = B * torch.logspace(-3, 3, -(-N // 128), device="cuda").repeat_interleave(128)[:N]
+    print("packed fp8", code, shape, prec, file=sys.stderr, flush=True)
+    ws = torch.full((plan.workspace_bytes()[0],), 0xA5, dtype=torch.uint8, device="cuda")
+    base = torch.empty(plan.workspace_layout()[6], dtype=torch.uint8, device="cuda")
+    Av, Bv = _view(A, 8), _view(B, 8)
+    dest = plan.schedule()["dest"]
+    Mb, ny = plan.info()["Mb"], int((dest >= 0).sum())
+    prods = []
+    for w in (ws, base):
+        C = _view(torch.zeros((M, N), device="cuda"), 8)
+        bpx.coded_gemm(plan, Av, Bv, C, w)
+        torch.cuda.synchronize()
+        Y = w[:ny * Mb * N * 4].view(torch.float32).view(ny, Mb, N)
+        prods.append((Y.clone(), C.clone()))
+    for new, old in zip(prods[0], prods[1]):
+        if new.numel() == 0:
+            continue
+        # per product and column block, the granularity of the scales
+        d = new.double() - old.double()
+        for n0 in range(0, N, 128):
+            num = torch.linalg.norm(d[..., n0:n0 + 128])
+            den = torch.linalg.norm(old[..., n0:n0 + 128].double())
+            assert float(num) <= 1e-4 * float(den), n0
+    again = _view(torch.zeros((M, N), device="cuda"), 8)
+    bpx.coded_gemm(plan, Av, Bv, again, ws)
+    assert torch.equal(again, prods[0][1])
