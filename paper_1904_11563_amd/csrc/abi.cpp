@@ -117,7 +117,10 @@ bpx_status upload(bpx_plan* plan) {
                                         &plan->ops.sym_passes, &plan->ops.passes})
     ops.insert(ops.end(), v->begin(), v->end());
   const size_t b7 = bytes_of(ops.size(), 4);
-  const size_t total = std::max<size_t>(b0 + b1 + b2 + b3 + b4 + b5 + b6 + b7, 256);
+  const size_t b8 = bytes_of(plan->peel_recs.size(), 4);
+  const size_t b9 = bytes_of(plan->peel_more.size(), 4);
+  const size_t o8 = b0 + b1 + b2 + b3 + b4 + b5 + b6 + b7;
+  const size_t total = std::max<size_t>(o8 + b8 + b9, 256);
   std::string host(total, '\0');
   std::memcpy(&host[0], plan->gemm_syms.data(), plan->gemm_syms.size() * 4);
   std::memcpy(&host[b0], plan->gemm_ids.data(), plan->gemm_ids.size() * 4);
@@ -131,6 +134,10 @@ bpx_status upload(bpx_plan* plan) {
               plan->fused_ytile.size() * 4);
   if (!ops.empty())
     std::memcpy(&host[b0 + b1 + b2 + b3 + b4 + b5 + b6], ops.data(), ops.size() * 4);
+  if (!plan->peel_recs.empty())
+    std::memcpy(&host[o8], plan->peel_recs.data(), plan->peel_recs.size() * 4);
+  if (!plan->peel_more.empty())
+    std::memcpy(&host[o8 + b8], plan->peel_more.data(), plan->peel_more.size() * 4);
   void* d = nullptr;
   e = hipMalloc(&d, total);
   if (e != hipSuccess) return hip_fail(e, "hipMalloc(plan tables)");
@@ -149,6 +156,8 @@ bpx_status upload(bpx_plan* plan) {
   plan->d_fused_steps = reinterpret_cast<const PeelStep*>(base + b0 + b1 + b2 + b3);
   plan->d_fused_subs = reinterpret_cast<const int32_t*>(base + b0 + b1 + b2 + b3 + b4);
   plan->d_fused_ytile = reinterpret_cast<const int32_t*>(base + b0 + b1 + b2 + b3 + b4 + b5);
+  plan->d_peel_recs = reinterpret_cast<const int32_t*>(base + o8);
+  plan->d_peel_more = reinterpret_cast<const int32_t*>(base + o8 + b8);
   plan->d_ops = reinterpret_cast<const int32_t*>(base + b0 + b1 + b2 + b3 + b4 + b5 + b6);
   return BPX_OK;
 }
@@ -451,6 +460,9 @@ bpx_status peel_impl(bpx_plan* plan, const void* ws, size_t ws_bytes, float* C, 
   p.nsubs = (int32_t)plan->step_subs.size();
   p.grid = plan->grid;
   p.Nb = plan->Nb;
+  p.recs = plan->peel_recs.empty() ? nullptr : plan->d_peel_recs;
+  p.more = plan->d_peel_more;
+  for (const PeelStep& st : plan->steps) p.nload += st.src < 0;
   hipError_t e = launch_peel(p, stream);
   if (e == hipErrorInvalidConfiguration)
     return fail(BPX_E_UNSUPPORTED, "peel needs more LDS than a workgroup has");

@@ -754,12 +754,6 @@ __global__ __launch_bounds__(256) void pack_fp8_kernel(PlaneParams p) {
     pack_fp8_a(p, b - blocks_b, t, red);
 }
 
-// 64 consecutive words (or one word 64 times) straight to LDS.
-__device__ __forceinline__ void copy_words(v4i rsrc, int lds, int voff, int soff) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
-               "buffer_load_dword %1, %2, %3 offen lds"
-               ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
-}
 __device__ __forceinline__ v4i uniform_rsrc(const void* base, int64_t bytes) {
   const uint64_t a = reinterpret_cast<uint64_t>(base);
   v4i r = {(int)a, (int)(a >> 32) & 0xffff, (int)bytes, kRsrcWord3};

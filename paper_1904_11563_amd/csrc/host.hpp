@@ -73,6 +73,14 @@ struct bpx_plan {
   std::vector<int32_t> step_subs;   // LDS slots of subtrahends
   int32_t n_lds_slots = 0;
 
+  // The same program for the peel whose values all stay in LDS, one record per
+  // step: {src, nsub | f64 << 8 | write << 9, eight subtrahends a byte each (the
+  // steps that recover them), brow | bcol << 16, where in peel_more the other
+  // subtrahends are, 0, 0}.  A record of zeros follows the last.  Empty if the
+  // program has more steps than a byte names.
+  static constexpr int32_t kPeelRec = 8;
+  std::vector<int32_t> peel_recs, peel_more;
+
   // GEMM symbol table: per computed symbol {id_off, deg, dest, 0} + ids
   std::vector<int32_t> gemm_syms;
   std::vector<int32_t> gemm_ids;
@@ -96,6 +104,8 @@ struct bpx_plan {
   const PeelStep* d_fused_steps = nullptr;
   const int32_t* d_fused_subs = nullptr;
   const int32_t* d_fused_ytile = nullptr;
+  const int32_t* d_peel_recs = nullptr;
+  const int32_t* d_peel_more = nullptr;
   const int32_t* d_ops = nullptr;  // PlaneOps: a_ops, b_ops, ids, sym_passes, passes
 
   size_t y_bytes() const { return (size_t)n_yslots * (size_t)Mb * (size_t)Nb * sizeof(float); }

@@ -94,6 +94,10 @@ struct PeelParams {
   int32_t nsteps;
   int32_t nslots;
   int32_t nsubs;  // length of subs
+  // bpx_plan::peel_recs, peel_more; null if the program does not fit
+  const int32_t* recs;
+  const int32_t* more;
+  int32_t nload;  // leading steps that only fetch a block from C
   // Block layout: data block s covers C rows (s / grid) * Mb .., columns
   // (s % grid) * Nb ..; Y slots are Mb x Nb.  grid = 1, Nb = N for row
   // blocks (the vector form assumes that layout).

@@ -4,32 +4,32 @@
 // recovered block is X_s = Y_{g_s} - sum over u in N(g_s)\{s} of X_u.  The
 // schedule is identical for every element of the Mb x N block, so each
 // thread runs the whole program for its own element (row r, column c of
-// every block) with no barriers between release rounds.  Values that later
-// steps subtract are kept in this thread's LDS column, or, for a single
-// product in the vector form whose program needs at most kRegSlots of
-// them, in registers.
+// every block) with no barriers between release rounds.
 //
 // Accumulation: FP32 with Kahan compensation for depth <= 4; FP64 for
 // deeper releases; subtrahends in ascending id order.  Rows past M (padding
 // of the last block) are exactly zero and are neither read nor written.
 //
-// Two forms: a vector form (N and ldc multiples of 4) where a thread owns
-// four adjacent columns and moves 16 bytes per load and store, and a scalar
-// form for ragged N.  Loads of kBatch steps are issued before their
-// arithmetic so that many requests are in flight per thread.  The program
-// (steps and subtrahend slot lists) is the same for every thread, so each
-// workgroup copies it to LDS once, behind its slots; the step loop then
-// reads descriptors from LDS instead of chasing them through global memory.
+// Forms, by where the values that later steps subtract are kept:
+//   LDS form       every step's value in LDS, one wave per workgroup (single
+//                  products; the default)
+//   register slots large blocks with long programs of few live slots (vector
+//                  form, four columns per thread)
+//   LDS slots      the grouped peel, and single products whose program is
+//                  longer than the LDS form's records name (vector form where
+//                  N and ldc are multiples of 4, else scalar).  The program is
+//                  staged in LDS behind the slots, and loads of kBatch steps
+//                  are issued before their arithmetic.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 
 #include "kernels.hpp"
+#include "planes.hpp"
 
 namespace bpx {
 namespace {
 
-typedef float v4f __attribute__((ext_vector_type(4)));
 typedef double v4d __attribute__((ext_vector_type(4)));
 
 constexpr int kBatch = 16;  // steps whose loads are issued together (all of a 16-step program)
@@ -118,7 +118,6 @@ __device__ __forceinline__ void peel_block(const PeelParams& p, int64_t block, f
 // those count on the LDS counter as well, so every wait for an LDS read of
 // the program or a slot would also wait for the HBM loads in flight.  The
 // product buffers are device memory: accessed as global.
-typedef __attribute__((address_space(1))) v4f gv4f;
 __device__ __forceinline__ v4f gload4(const float* ptr) {
   return *(const gv4f*)ptr;
 }
@@ -138,7 +137,6 @@ struct LdsSlots {
 // (so the workgroup's LDS holds only the program, and the chip holds every
 // row of a large block at once instead of in LDS-limited rounds).
 typedef float v32f __attribute__((ext_vector_type(32)));
-typedef float v16f __attribute__((ext_vector_type(16)));
 constexpr int kRegSlots = 12;
 struct RegSlots {
   v32f a = {};
@@ -302,11 +300,6 @@ hipError_t launch_peel_grouped(const GroupDesc* d, const int64_t* pstart, const 
   return hipGetLastError();
 }
 
-// Single products take the vector form (128 threads: 74 us on the
-// 8192 x 4096 FP32 workload, against 87 us for the scalar form with 256
-// threads) when N and ldc are multiples of 4 and the blocks are row blocks;
-// otherwise the scalar form, which also handles the block grid of the
-// two-dimensional form.
 // Single product, row blocks, N and ldc multiples of 4: the vector form.
 template <int THREADS>
 __global__ __launch_bounds__(THREADS) void peel4s_kernel(PeelParams p) {
@@ -333,8 +326,220 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4))) void p
   peel_block4<128, kBatchReg>(p, blockIdx.x, slots, reinterpret_cast<const PeelStep*>(prog_r),
                               prog_r + p.nsteps * (int)(sizeof(PeelStep) / 4));
 }
+// ------------------------------------------------------ LDS form --
+// Single products: one wave per workgroup, V adjacent columns per lane, every
+// step's value in LDS, where its result takes its place.
+//
+// Small blocks are bound by the latency of one thread's program, not by HBM:
+// with a few hundred waves for 1024 SIMDs a step that reads its record, then its
+// subtrahends' slots, then their values costs each latency in turn (0.5 us), and
+// unrolled code costs as much in instruction fetches (a program runs once per
+// wave: 88 steps unrolled with values in registers took 94 us).  So both loops
+// here are a few dozen instructions: the first copies every step's product
+// straight to LDS (all in flight at once, no registers), the second applies the
+// steps, the next value already on its way.
+template <int V>
+struct LdsVec;
+template <>
+struct LdsVec<1> {
+  typedef float T;
+};
+template <>
+struct LdsVec<4> {
+  typedef v4f T;
+};
+typedef __attribute__((address_space(4))) const int32_t cint;
+template <int V>
+__device__ __forceinline__ float elem(const typename LdsVec<V>::T& x, int t) {
+  if constexpr (V == 1)
+    return x;
+  else
+    return x[t];
+}
+template <int V>
+__device__ __forceinline__ void set_elem(typename LdsVec<V>::T& x, int t, float f) {
+  if constexpr (V == 1)
+    x = f;
+  else
+    x[t] = f;
+}
+
+template <int V>
+__global__ __launch_bounds__(64) void peel_lds_kernel(PeelParams p) {
+  typedef typename LdsVec<V>::T T;
+  typedef __attribute__((address_space(1))) T gT;
+  extern __shared__ __attribute__((aligned(1024))) char values[];  // [step][64] of T
+  const int lane = threadIdx.x;
+  const unsigned nv = (unsigned)p.Nb / V, total = (unsigned)p.Mb * nv;
+  const unsigned e0 = blockIdx.x * 64u + (unsigned)lane;
+  const bool active = e0 < total;
+  const unsigned e = active ? e0 : total - 1u;
+  const unsigned r = e / nv, c = (e - r * nv) * V;
+  const unsigned yo = (r * (unsigned)p.Nb + c) * 4u, co = (r * (unsigned)p.ldc + c) * 4u;
+  // One step's words, a step per lane: 64 steps' addresses are computed at once
+  // and a step then costs a few lane reads instead of scalar loads and 64-bit
+  // arithmetic.
+  struct Words {
+    int src, meta, s0, s1, over;
+    unsigned yl, yh, cl, ch;  // where the value comes from, where the block lies in C
+    int rows;                 // rows of the block that exist
+  };
+  auto words_of = [&](int st) __attribute__((always_inline)) {
+    Words w = {};
+    if (st < p.nsteps) {
+      const int32_t* q = p.recs + 8 * st;
+      const int rc = q[4];
+      const int64_t first = (int64_t)(rc & 0xffff) * p.Mb, left = p.M - first;
+      w.src = q[0];
+      w.meta = q[1];
+      w.s0 = q[2];
+      w.s1 = q[3];
+      w.over = q[5];
+      const uint64_t cb = reinterpret_cast<uint64_t>(p.C + first * p.ldc +
+                                                     (int64_t)((unsigned)rc >> 16) * p.Nb);
+      const uint64_t yb =
+          w.src >= 0 ? reinterpret_cast<uint64_t>(p.Y + w.src * (p.Mb * p.Nb)) : cb;
+      w.yl = (unsigned)yb;
+      w.yh = (unsigned)(yb >> 32);
+      w.cl = (unsigned)cb;
+      w.ch = (unsigned)(cb >> 32);
+      w.rows = left < 0 ? 0 : left < p.Mb ? (int)left : (int)p.Mb;
+    }
+    return w;
+  };
+  auto at = [&](unsigned v, int i) __attribute__((always_inline)) {
+    return __builtin_amdgcn_readlane((int)v, i);
+  };
+
+  const int lds0 = (int)(uintptr_t)(lds_addr)values;
+  auto copy = [&](const Words& w, int i, int st, unsigned off) __attribute__((always_inline)) {
+    const v4i rsrc = {at(w.yl, i), at(w.yh, i) & 0xffff, -1, kRsrcWord3};
+    if constexpr (V == 4)
+      copy_panel<1>(rsrc, lds0 + st * 64 * V * 4, (int)off, 0);
+    else
+      copy_words(rsrc, lds0 + st * 64 * V * 4, (int)off, 0);
+  };
+  // The first nload steps only fetch blocks that are in C already (the degree-1
+  // releasers', all of the first round), the others start from a Y slot.
+  for (int c0 = 0; c0 < p.nload; c0 += 64) {
+    const Words w = words_of(c0 + lane);
+    const int n = p.nload - c0 < 64 ? p.nload - c0 : 64;
+#pragma unroll 1
+    for (int i = 0; i < n; ++i) {
+      const int rows = at((unsigned)w.rows, i);  // rows past M: the last row's value, zeroed below
+      const int past = (int)r - (rows - 1);
+      if (rows > 0)
+        copy(w, i, c0 + i, past > 0 ? co - (unsigned)past * (unsigned)p.ldc * 4u : co);
+    }
+  }
+  for (int c0 = p.nload; c0 < p.nsteps; c0 += 64) {
+    const Words w = words_of(c0 + lane);
+    const int n = p.nsteps - c0 < 64 ? p.nsteps - c0 : 64;
+#pragma unroll 1
+    for (int i = 0; i < n; ++i) copy(w, i, c0 + i, yo);  // (a Y slot has all rows)
+  }
+  wait_counts<0, true>();
+  asm volatile("" ::: "memory");
+
+  T* val = reinterpret_cast<T*>(values) + lane;  // this lane's value of step 0
+  for (int c0 = 0; c0 < p.nload; c0 += 64) {
+    const Words w = words_of(c0 + lane);
+    // blocks that end inside or before this block of rows
+    uint64_t ends = __builtin_amdgcn_ballot_w64(c0 + lane < p.nload && w.rows < (int)p.Mb);
+    while (ends) {
+      const int i = __builtin_ctzll(ends);
+      ends &= ends - 1;
+      if ((int)r >= at((unsigned)w.rows, i)) val[64 * (c0 + i)] = T{};
+    }
+  }
+  if (p.nload == p.nsteps) return;
+  T y = val[64 * p.nload];
+  for (int c0 = p.nload; c0 < p.nsteps; c0 += 64) {
+    const Words w = words_of(c0 + lane);
+    const int n = p.nsteps - c0 < 64 ? p.nsteps - c0 : 64;
+#pragma unroll 1
+    for (int i = 0; i < n; ++i) {
+      const int st = c0 + i;
+      const int meta = at((unsigned)w.meta, i), nsub = meta & 255;
+      const unsigned s0 = (unsigned)at((unsigned)w.s0, i);
+      // the first four subtrahends (an absent one reads step 0's place)
+      T sub[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) sub[u] = val[64 * ((s0 >> (8 * u)) & 255)];
+      const T y_n = val[64 * (st + 1 < p.nsteps ? st + 1 : st)];
+      auto more_of = [&](int u) __attribute__((always_inline)) {  // u >= 4
+        if (u >= 8) return (int)((const cint*)p.more)[at((unsigned)w.over, i) + u - 8];
+        return (int)((unsigned)at((unsigned)w.s1, i) >> (8 * (u & 3))) & 255;
+      };
+      T x = y;
+      if (meta & 256) {
+        double acc[V];
+#pragma unroll
+        for (int t = 0; t < V; ++t) acc[t] = (double)elem<V>(y, t);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (u < nsub) {
+#pragma unroll
+            for (int t = 0; t < V; ++t) acc[t] -= (double)elem<V>(sub[u], t);
+          }
+#pragma unroll 1
+        for (int u = 4; u < nsub; ++u) {
+          const T v = val[64 * more_of(u)];
+#pragma unroll
+          for (int t = 0; t < V; ++t) acc[t] -= (double)elem<V>(v, t);
+        }
+#pragma unroll
+        for (int t = 0; t < V; ++t) set_elem<V>(x, t, (float)acc[t]);
+      } else {
+        T comp = {};
+        auto subtract = [&](const T& z) __attribute__((always_inline)) {
+          const T v = -z - comp;
+          const T s = x + v;
+          comp = (s - x) - v;
+          x = s;
+        };
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (u < nsub) subtract(sub[u]);
+#pragma unroll 1
+        for (int u = 4; u < nsub; ++u) subtract(val[64 * more_of(u)]);
+      }
+      const bool ok = (int)r < at((unsigned)w.rows, i);
+      if (!ok) x = T{};
+      val[64 * st] = x;
+      if ((meta & 512) && ok && active) {
+        const uint64_t cb = (unsigned)at(w.cl, i) | (uint64_t)(unsigned)at(w.ch, i) << 32;
+        *(gT*)(cb + co) = x;
+      }
+      y = y_n;
+    }
+  }
+}
+
+template <int V>
+hipError_t launch_peel_lds(const PeelParams& p, hipStream_t stream) {
+  const int64_t total = p.Mb * (p.Nb / V);
+  hipLaunchKernelGGL(peel_lds_kernel<V>, dim3((unsigned)((total + 63) / 64)), dim3(64),
+                     (size_t)p.nsteps * 64 * V * 4, stream, p);
+  return hipGetLastError();
+}
+
 hipError_t launch_peel(const PeelParams& p, hipStream_t stream) {
   if (p.nsteps == 0) return hipSuccess;
+  const bool vec = p.Nb % 4 == 0 && p.ldc % 4 == 0;
+  const int64_t E = p.Mb * p.Nb;
+  // The LDS form, except for large blocks with long programs, whose KiB per step
+  // and wave leaves a CU five waves: there register slots (31 steps, blocks of
+  // 256 x 4096: 45 against 63 us; of 128 x 2048 17 against 26 us; 15 steps of
+  // 512 x 4096 44 against 45 us).  Four columns per lane from 32768 lanes on
+  // (64 x 2048: 8.3 against 9.8 us, one column below).  Offsets inside a block
+  // are 32-bit.
+  const bool regs = vec && p.grid == 1 && p.nslots <= kRegSlots && p.nsteps > 16 && E >= 524288;
+  if (p.recs && !regs && (p.Mb + 1) * std::max(p.Nb, p.ldc) < (int64_t)1 << 29 &&
+      p.M < (int64_t)1 << 31) {
+    if (vec && E >= 4 * 32768 && p.nsteps <= 64) return launch_peel_lds<4>(p, stream);
+    return launch_peel_lds<1>(p, stream);
+  }
   if (p.grid == 1 && (p.N & 3) == 0 && (p.ldc & 3) == 0) {
     const int64_t blocks = (p.Mb * (p.N / 4) + 127) / 128;
     const size_t prog = peel_program_bytes(p.nsteps, p.nsubs);

@@ -380,6 +380,34 @@ int make_plan(const bpx_code& code, const int32_t* arrival, int32_t n_arrival, i
       plan->steps.push_back(st);
     }
   }
+  plan->peel_recs.clear();
+  plan->peel_more.clear();
+  bool fits = plan->steps.size() < 256 && kb < 65536;
+  bool from_y = false;  // blocks fetched from C come first
+  for (const PeelStep& st : plan->steps) {
+    from_y = from_y || st.src >= 0;
+    fits = fits && st.nsub < 256 && (st.src >= 0 || (!from_y && st.nsub == 0 && !st.write));
+  }
+  if (fits && !plan->steps.empty()) {
+    std::vector<int32_t> step_of(kb, -1);
+    for (size_t i = 0; i < plan->steps.size(); ++i) step_of[plan->steps[i].s] = (int32_t)i;
+    for (const PeelStep& st : plan->steps) {
+      uint32_t rec[bpx_plan::kPeelRec] = {};
+      rec[0] = (uint32_t)st.src;
+      rec[1] = (uint32_t)(st.nsub | st.f64 << 8 | st.write << 9);
+      rec[4] = (uint32_t)st.brow | (uint32_t)st.bcol << 16;
+      rec[5] = (uint32_t)plan->peel_more.size();
+      for (int32_t u = 0; u < st.nsub; ++u) {
+        const uint32_t from = (uint32_t)step_of[plan->sub_data[plan->sub_ptr[st.s] + u]];
+        if (u < 8)
+          rec[2 + u / 4] |= from << (8 * (u % 4));
+        else
+          plan->peel_more.push_back((int32_t)from);
+      }
+      plan->peel_recs.insert(plan->peel_recs.end(), rec, rec + bpx_plan::kPeelRec);
+    }
+    plan->peel_recs.insert(plan->peel_recs.end(), bpx_plan::kPeelRec, 0);
+  }
   return ok ? BPX_OK : BPX_E_UNDECODABLE;
 }
 

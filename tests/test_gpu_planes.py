@@ -273,3 +273,69 @@ def test_packed_fp8_like_direct_kernels(code, shape, prec):
     again = _view(torch.zeros((M, N), device="cuda"), 8)
     bpx.coded_gemm(plan, Av, Bv, again, ws)
     assert torch.equal(again, prods[0][1])
+
+
+def _identity_y(plan, X):
+    """Y slots and C as the coded products leave them for blocks X (float64
+    sums rounded to FP32)."""
+    sch, Mb, kb = plan.schedule(), plan.info()["Mb"], X.shape[0]
+    col_ptr, sym_ptr, sym_data = plan.code.csr()
+    ny = int((sch["dest"] >= 0).sum())
+    Y = torch.full((max(ny, 1), Mb, X.shape[2]), float("nan"), device="cuda")
+    C = torch.full((kb * Mb, X.shape[2]), float("nan"), device="cuda")
+    for g, d in zip(sch["computed"].tolist(), sch["dest"].tolist()):
+        s = sum(X[int(u)] for u in sym_data[sym_ptr[g]:sym_ptr[g + 1]])
+        if d >= 0:
+            Y[d] = s
+        else:
+            C[(-1 - d) * Mb:(-d) * Mb] = s
+    return Y, C
+
+
+# programs: one step, chains past depth 4 (FP64), degrees past the four and the
+# eight subtrahends held in a record, 64 and more steps, blocks already in C
+# only; sizes: one element, odd columns, four columns per lane and not, large
+# blocks on both sides of the register form, a ragged last block, an empty one
+@pytest.mark.parametrize("code,M,N", [
+    ("table1", 4, 1), ("table3", 9 * 40 - 3, 333), ("642", 2048, 513), ("1284", 32 * 63 - 17, 1001),
+    ("1284", 32 * 256, 2048), ("1284", 32 * 256 - 5, 1024), ("moj", 5000, 500), ("moj", 128 * 3 - 2, 68),
+    ("wide", 20 * 9, 130), ("wide", 20 * 512, 512)])
+def test_peel_forms_exact(code, M, N):
+    if code == "wide":       # releases by one symbol that covers everything
+        lib = bpx.Code.from_columns(3, 2, 10, [
+            [(i,) for i in range(10)], [(i, i + 1) for i in range(9, 18)] + [tuple(range(20))],
+            [(i,) for i in range(19)]])
+    else:
+        lib = {"table1": bpx.Code.table1, "table3": bpx.Code.table3,
+               "642": lambda: _code(inputs.CODE_642), "1284": lambda: _code(inputs.CODE_1284),
+               "moj": lambda: bpx.Code.mojette(16, 8, 24, 0)}[code]()
+    inf = lib.info()
+    seen = 0
+    for seed in range(3):
+        arrival, _ = inputs.shifted_exp_arrival(seed, inf["n"])
+        lost, mode = 0, bpx.MODE_STRAGGLER
+        if code == "wide":
+            arrival = [0, 1, 2]
+        elif code == "moj":
+            (arrival, lost), mode = inputs.erasure_arrival(seed, inf["n"], inf["n"] // 3), bpx.MODE_ERASURE
+        plan = bpx.Plan(lib, arrival, lost, mode, M, 4, N)
+        if not plan.decodable:
+            continue
+        kb, Mb = inf["k"] * inf["b"], plan.info()["Mb"]
+        g = torch.Generator(device="cuda").manual_seed(seed)
+        # integers: every sum and difference is exact
+        X = torch.randint(-1000, 1001, (kb, Mb, N), generator=g, device="cuda").float()
+        X.view(kb * Mb, N)[M:] = 0
+        Y, C = _identity_y(plan, X)
+        Cv = _view(C[:M], 4)
+        plan.upload()
+        prog = plan.peel_program()
+        print("peel", code, M, N, "steps", len(prog["steps"]), "slots", prog["n_slots"],
+              file=sys.stderr, flush=True)
+        before = Cv._base.clone()
+        bpx.peel_decode(plan, Y.view(torch.uint8).flatten(), Cv)
+        torch.cuda.synchronize()
+        assert torch.equal(Cv, X.view(kb * Mb, N)[:M])
+        assert torch.equal(Cv._base[:, N:].isnan(), before[:, N:].isnan())  # nothing past N
+        seen += 1
+    assert seen
