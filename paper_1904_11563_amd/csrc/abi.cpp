@@ -247,7 +247,10 @@ bpx_status gemm_planes_impl(bpx_plan* plan, GemmParams p, void* ws, hipStream_t 
     return e == hipSuccess ? BPX_OK : hip_fail(e, "packed FP8 gemm launch");
   }
   hipError_t e = launch_pack_planes(q, stream);
-  if (e == hipSuccess) e = launch_gemm_planes(q, stream);
+  std::vector<int32_t> passes;
+  for (size_t i = 1; i < plan->ops.sym_passes.size(); i += 2)
+    passes.push_back(plan->ops.sym_passes[i]);
+  if (e == hipSuccess) e = launch_gemm_planes(q, passes.data(), stream);
   if (e == hipSuccess && q.planes == 3) {
     p.fa = q.fa;
     p.fb = q.fb;

@@ -835,7 +835,7 @@ __global__ __launch_bounds__(NT) void gemm_fp8_packed_kernel(PlaneParams p) {
     if (i < nk) copy(i * STAGE);
   if (tid < 256) rows[tid] = out_row<false>(p, 0, (unsigned)mt * 256u + (unsigned)tid);
 
-  Acc acc;
+  Acc<4> acc;
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -964,9 +964,9 @@ __global__ __launch_bounds__(NT) void gemm_fp8_packed_kernel(PlaneParams p) {
     }
   }
   if (piece >= 0)
-    store_part(acc, p.part + (int64_t)piece * 65536, wave, lane);
+    store_part<4, 4>(acc, p.part + (int64_t)piece * 65536, wave, lane);
   else
-    store_tile(acc, rows, (int64_t)nt * 256, p.Nb, wave, lane);
+    store_tile<4, 4>(acc, rows, (int64_t)nt * 256, p.Nb, wave, lane);
 }
 
 }  // namespace
@@ -1002,7 +1002,7 @@ hipError_t launch_gemm_fp8_packed(const PlaneParams& p0, hipStream_t stream) {
   planes_tiles(&p);
   p.row_group = 2;
   const int64_t T = (int64_t)p.tiles_m * p.tiles_n;
-  planes_split(&p, T, p.planes == 2 ? 1.3 : 0.7, 4);
+  planes_split(&p, nullptr, T, p.planes == 2 ? 1.3 : 0.7, 4);
   hipLaunchKernelGGL(p.planes == 2 ? gemm_fp8_packed_kernel<1> : gemm_fp8_packed_kernel<0>,
                      dim3((unsigned)(p.full + (T - p.full) * p.split)), dim3(NT), 0, stream, p);
   const hipError_t e = hipGetLastError();

@@ -38,6 +38,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <map>
 #include <type_traits>
 
 #include "kernels.hpp"
@@ -212,7 +213,8 @@ __global__ __launch_bounds__(256) void pack_planes_kernel(PlaneParams p) {
 
 // ------------------------------------------------------------------ GEMM --
 // 256 x 256 tiles of the stacked rows, 8 waves (2 x 4) of 128 x 64, each 4 x 2
-// accumulators of 32 x 32.  Against the 16 x 16 MFMA the 32 x 32 one reads
+// accumulators of 32 x 32, or (see launch_gemm_planes) 128 x 128 tiles, 4 waves
+// (2 x 2) of 64 x 64.  Against the 16 x 16 MFMA the 32 x 32 one reads
 // half the operand bytes per product, which counts twice here: LDS (6
 // fragment reads per plane for 8 MFMAs per plane product) and power (at full
 // MFMA load the clock falls to 1.6-1.8 GHz).
@@ -232,6 +234,10 @@ __global__ __launch_bounds__(256) void pack_planes_kernel(PlaneParams p) {
 // on zero operands: power, not issue, is what is left); the FP32 MFMA
 // kernels took 4.64 ms.  BF16x3 1.27 ms against 2.31 ms for the kernel that
 // encodes and splits A while staging.
+// The small tile reads 4/3 of the fragments per product, at two workgroups to
+// a CU: FP32 and BF16x3 stay within 85 % of the MFMA rate, BF16 is bound by LDS
+// (192 of 128 cycles).  1999 x 1500 x 1001: FP32 GEMM and sums 55 -> 42 us;
+// 3000 x 2060 x 1530, all 12 workers' rows: BF16 GEMM 53 -> 35 us.
 // k steps per stage and stages in LDS (144, 128 and 128 KiB).
 template <int P>
 struct Cfg;
@@ -249,42 +255,44 @@ struct Cfg<3> {
 };
 
 // One k step's fragments of a wave.
-template <int P>
+template <int P, int S>
 struct Frags {
-  v8bf a[4][P], b[2][P];
+  v8bf a[S / 64][P], b[2][P];
 };
 
-template <int P>
+template <int P, int S>
 struct Tile {
   static constexpr int STEPS = Cfg<P>::STEPS, NBUF = Cfg<P>::NBUF;
+  static constexpr int MI = S / 64, WN = S / 64;  // 32-row accumulators; waves side by side
+  static constexpr int PANELS = S / 32, THREADS = 128 * WN;
   static constexpr int RPB = STEPS * P * 1024;  // bytes of one 32-row panel per stage
-  static constexpr int STAGE = 16 * RPB;        // A panels 0..7, B panels 8..15
+  static constexpr int STAGE = 2 * PANELS * RPB;  // A's panels, then B's
   static constexpr int L = 2 * STEPS * P;       // 1 KiB copies per wave per stage
   static constexpr int LDS = NBUF * STAGE;
 };
 
 // The copies of one tile's stages to LDS, in order: wave w copies panels 2w,
-// 2w + 1 of a stage (waves 0-3 A, 4-7 B).
-template <int P, bool GRID>
+// 2w + 1 of a stage (the first half of the waves A's, the others B's).
+template <int P, bool GRID, int S>
 struct Feed {
-  using T = Tile<P>;
+  using T = Tile<P, S>;
   const char *ap, *bp;
   const int32_t* passes;
   int64_t rp_stride;
-  int wave, tiles_m, tiles_n, mt, nt;
+  int wave, pad_m, pad_n, mt, nt;
   int soff0, voff, lds0;
   int nk1, n_pass;  // stages of a pass; passes
   int pass, kp;     // the next stage
   v4i rsrc;
 
   __device__ __forceinline__ void set_pass() {
-    int64_t panel = wave < 4 ? mt : nt;
+    int64_t panel = wave < T::WN ? mt : nt;
     if (GRID)
-      panel += wave < 4 ? (int64_t)passes[2 * pass] * tiles_m
-                        : (int64_t)passes[2 * pass + 1] * tiles_n;
+      panel += wave < T::WN ? (int64_t)passes[2 * pass] * pad_m
+                            : (int64_t)passes[2 * pass + 1] * pad_n;
     const uint64_t src =
-        reinterpret_cast<uint64_t>(wave < 4 ? ap : bp) + (uint64_t)(panel * 8 * rp_stride);
-    rsrc = v4i{(int)src, (int)(src >> 32) & 0xffff, (int)(8 * rp_stride), kRsrcWord3};
+        reinterpret_cast<uint64_t>(wave < T::WN ? ap : bp) + (uint64_t)(panel * T::PANELS * rp_stride);
+    rsrc = v4i{(int)src, (int)(src >> 32) & 0xffff, (int)(T::PANELS * rp_stride), kRsrcWord3};
 #pragma unroll
     for (int c = 0; c < 4; ++c) rsrc[c] = __builtin_amdgcn_readfirstlane(rsrc[c]);
   }
@@ -298,11 +306,11 @@ struct Feed {
     rp_stride = (int64_t)p.kc * P * 1024;
     nk1 = p.kc / T::STEPS;
     wave = wave_;
-    tiles_m = p.tiles_m;
-    tiles_n = p.tiles_n;
+    pad_m = p.pad_m;
+    pad_n = p.pad_n;
     mt = mt_;
     nt = nt_;
-    soff0 = (wave & 3) * 2 * (int)rp_stride;
+    soff0 = wave % T::WN * 2 * (int)rp_stride;
     voff = lane * 16;
     lds0 = (int)(uintptr_t)(lds_addr)lds + 2 * wave * T::RPB;
   }
@@ -329,33 +337,34 @@ struct Feed {
 };
 
 // Multiplies the nk stages of a started feed.
-template <int P, bool GRID>
-__device__ __forceinline__ void multiply(Feed<P, GRID>& feed, int nk, const char* lds, int wave,
-                                         int lane, Acc& acc) {
-  using T = Tile<P>;
+template <int P, bool GRID, int S>
+__device__ __forceinline__ void multiply(Feed<P, GRID, S>& feed, int nk, const char* lds, int wave,
+                                         int lane, Acc<S / 64>& acc) {
+  using T = Tile<P, S>;
+  constexpr int MI = T::MI;
   constexpr int NBUF = T::NBUF, STAGE = T::STAGE, RPB = T::RPB, L = T::L;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < MI; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-  const int a_base = (wave >> 2) * 4 * RPB + lane * 16;
-  const int b_base = (8 + (wave & 3) * 2) * RPB + lane * 16;
-  auto read_a = [&](Frags<P>& f, const char* st, int s, int q) __attribute__((always_inline)) {
+  const int a_base = wave / T::WN * MI * RPB + lane * 16;
+  const int b_base = (T::PANELS + wave % T::WN * 2) * RPB + lane * 16;
+  auto read_a = [&](Frags<P, S>& f, const char* st, int s, int q) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < MI; ++i)
       f.a[i][q] = *reinterpret_cast<const v8bf*>(st + a_base + i * RPB + (s * P + q) * 1024);
   };
-  auto read_b = [&](Frags<P>& f, const char* st, int s, int q) __attribute__((always_inline)) {
+  auto read_b = [&](Frags<P, S>& f, const char* st, int s, int q) __attribute__((always_inline)) {
 #pragma unroll
     for (int j = 0; j < 2; ++j)
       f.b[j][q] = *reinterpret_cast<const v8bf*>(st + b_base + j * RPB + (s * P + q) * 1024);
   };
-  auto mul = [&](const Frags<P>& f, auto pa, auto pb) __attribute__((always_inline)) {
+  auto mul = [&](const Frags<P, S>& f, auto pa, auto pb) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < MI; ++i)
 #pragma unroll
       for (int j = 0; j < 2; ++j)
         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
@@ -384,28 +393,78 @@ __device__ __forceinline__ void multiply(Feed<P, GRID>& feed, int nk, const char
   barrier();
 
   int cur = 0;
-  if constexpr (P == 3) {
-    Frags<P> f;
+  if constexpr (P == 3 && S == 128) {
+    // One wave per SIMD or two, 24 MFMAs each: all of the next stage's fragments
+    // are read while this stage's multiply, from a second set of registers.
+    Frags<P, S> f0, f1;
+    auto read = [&](Frags<P, S>& f, const char* st) __attribute__((always_inline)) {
+#pragma unroll
+      for (int q : {1, 0, 2}) {
+        read_a(f, st, 0, q);
+        read_b(f, st, 0, q);
+      }
+    };
+    read(f0, lds);
+    auto stage = [&](auto more, bool refill, const Frags<P, S>& f, Frags<P, S>& g)
+                     __attribute__((always_inline)) {
+      const int nxt = cur + STAGE == NBUF * STAGE ? 0 : cur + STAGE;
+      const char* next = lds + nxt;  // (past the last stage: read, never used)
+      turn(more);
+      mul(f, I1{}, I1{});
+      __builtin_amdgcn_sched_barrier(0);
+      read_a(g, next, 0, 1);
+      read_b(g, next, 0, 1);
+      __builtin_amdgcn_sched_barrier(0);
+      mul(f, I0{}, I1{});
+      __builtin_amdgcn_sched_barrier(0);
+      read_a(g, next, 0, 0);
+      if (refill) feed.copy(cur);
+      __builtin_amdgcn_sched_barrier(0);
+      mul(f, I1{}, I0{});
+      __builtin_amdgcn_sched_barrier(0);
+      read_b(g, next, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      mul(f, I0{}, I2{});
+      __builtin_amdgcn_sched_barrier(0);
+      read_b(g, next, 0, 2);
+      read_a(g, next, 0, 2);
+      __builtin_amdgcn_sched_barrier(0);
+      mul(f, I2{}, I0{});
+      mul(f, I0{}, I0{});
+      __builtin_amdgcn_sched_barrier(0);
+      cur = nxt;
+    };
+    int kt = 0;
+    for (; kt + 2 <= nk - NBUF; kt += 2) {
+      stage(More{}, true, f0, f1);
+      stage(More{}, true, f1, f0);
+    }
+    for (; kt < nk; kt += 2) {
+      stage(Last{}, kt < nk - NBUF, f0, f1);
+      if (kt + 1 < nk) stage(Last{}, false, f1, f0);
+    }
+  } else if constexpr (P == 3) {
+    Frags<P, S> f;
     read_a(f, lds, 0, 1);
     read_b(f, lds, 0, 1);
     auto stage = [&](auto more) __attribute__((always_inline)) {
       const int nxt = cur + STAGE == NBUF * STAGE ? 0 : cur + STAGE;
-      const char* S = lds + cur;
-      const char* N = lds + nxt;
-      read_a(f, S, 0, 0);
-      read_b(f, S, 0, 0);
+      const char* here = lds + cur;
+      const char* next = lds + nxt;
+      read_a(f, here, 0, 0);
+      read_b(f, here, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
       mul(f, I1{}, I1{});
       __builtin_amdgcn_sched_barrier(0);
-      read_b(f, S, 0, 2);
-      read_a(f, S, 0, 2);
+      read_b(f, here, 0, 2);
+      read_a(f, here, 0, 2);
       __builtin_amdgcn_sched_barrier(0);
       mul(f, I0{}, I1{});
       mul(f, I1{}, I0{});
       __builtin_amdgcn_sched_barrier(0);
       turn(more);
-      read_a(f, N, 0, 1);  // (past the last stage: read, never used)
-      read_b(f, N, 0, 1);
+      read_a(f, next, 0, 1);  // (past the last stage: read, never used)
+      read_b(f, next, 0, 1);
       if (decltype(more)::value) feed.copy(cur);
       __builtin_amdgcn_sched_barrier(0);
       mul(f, I0{}, I2{});
@@ -418,15 +477,15 @@ __device__ __forceinline__ void multiply(Feed<P, GRID>& feed, int nk, const char
     for (int kt = nk - NBUF < 0 ? 0 : nk - NBUF; kt < nk; ++kt) stage(Last{});
   } else {
     static_assert(P == 3 || T::STEPS == 2, "two k steps per stage");
-    Frags<P> f0, f1;
-    auto read = [&](Frags<P>& f, const char* st, int s) __attribute__((always_inline)) {
+    Frags<P, S> f0, f1;
+    auto read = [&](Frags<P, S>& f, const char* st, int s) __attribute__((always_inline)) {
 #pragma unroll
       for (int q = P - 1; q >= 0; --q) {
         read_a(f, st, s, q);
         read_b(f, st, s, q);
       }
     };
-    auto step = [&](const Frags<P>& f) __attribute__((always_inline)) {
+    auto step = [&](const Frags<P, S>& f) __attribute__((always_inline)) {
       if constexpr (P == 2) {
         mul(f, I1{}, I0{});
         mul(f, I0{}, I1{});
@@ -453,10 +512,11 @@ __device__ __forceinline__ void multiply(Feed<P, GRID>& feed, int nk, const char
   }
 }
 
-template <int P, bool GRID>
-__global__ __launch_bounds__(NT) void gemm_planes_kernel(PlaneParams p) {
-  __shared__ __attribute__((aligned(1024))) char lds[Tile<P>::LDS];
-  __shared__ float* rows[256];  // output rows of the tile
+template <int P, bool GRID, int S>
+__global__ __launch_bounds__(2 * S, 2) void gemm_planes_kernel(PlaneParams p) {
+  using T = Tile<P, S>;
+  __shared__ __attribute__((aligned(1024))) char lds[T::LDS];
+  __shared__ float* rows[S];  // output rows of the tile
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -474,7 +534,7 @@ __global__ __launch_bounds__(NT) void gemm_planes_kernel(PlaneParams p) {
   }
   int si, mt, nt;
   tile_at<GRID>(p, lin, &si, &mt, &nt);
-  Feed<P, GRID> feed;
+  Feed<P, GRID, S> feed;
   feed.open(p, lds, wave, lane, si, mt, nt);
   int kt0 = 0, kt1 = feed.nk1 * feed.n_pass;
   if (piece >= 0) {
@@ -484,14 +544,15 @@ __global__ __launch_bounds__(NT) void gemm_planes_kernel(PlaneParams p) {
   }
   feed.start(kt0, kt1 - kt0);
 
-  if (tid < 256) rows[tid] = out_row<GRID>(p, si, (unsigned)mt * 256u + (unsigned)tid);
+  if (tid < S) rows[tid] = out_row<GRID>(p, si, (unsigned)(mt * S + tid));
   if (P == 3) {
     unsigned bad = 0;
     for (int i = 0; i < feed.n_pass; ++i) {
-      const int64_t pa = GRID ? (int64_t)feed.passes[2 * i] * p.tiles_m + mt : mt;
-      const int64_t pb = GRID ? (int64_t)feed.passes[2 * i + 1] * p.tiles_n + nt : nt;
-      for (int t = tid; t < 8 * p.nka; t += NT) bad |= p.fa[pa * 8 * p.nka + t];
-      for (int t = tid; t < 4 * p.nkb; t += NT) bad |= p.fb[pb * 4 * p.nkb + t];
+      // (of the 256-wide panels, which the FP32 launch computes whole)
+      const int64_t pa = (GRID ? (int64_t)feed.passes[2 * i] * p.pad_m + mt : mt) / (256 / S);
+      const int64_t pb = (GRID ? (int64_t)feed.passes[2 * i + 1] * p.pad_n + nt : nt) / (256 / S);
+      for (int t = tid; t < 8 * p.nka; t += T::THREADS) bad |= p.fa[pa * 8 * p.nka + t];
+      for (int t = tid; t < 4 * p.nkb; t += T::THREADS) bad |= p.fb[pb * 4 * p.nkb + t];
     }
     if (__syncthreads_or((int)bad)) {
       wait_counts<0, false>();  // no copy may land in LDS that is no longer ours
@@ -499,13 +560,13 @@ __global__ __launch_bounds__(NT) void gemm_planes_kernel(PlaneParams p) {
     }
   }
 
-  Acc acc;
-  multiply<P, GRID>(feed, kt1 - kt0, lds, wave, lane, acc);
+  Acc<T::MI> acc;
+  multiply<P, GRID, S>(feed, kt1 - kt0, lds, wave, lane, acc);
   if (piece >= 0) {
-    store_part(acc, p.part + (int64_t)piece * 65536, wave, lane);
+    store_part<T::MI, T::WN>(acc, p.part + (int64_t)piece * (S * S), wave, lane);
     return;
   }
-  store_tile(acc, rows, (int64_t)nt * 256, p.Nb, wave, lane);
+  store_tile<T::MI, T::WN>(acc, rows, (int64_t)nt * S, p.Nb, wave, lane);
 }
 
 // Grouped form, persistent: workgroup w multiplies tiles tiles[wstart[w]] ..
@@ -519,14 +580,14 @@ template <int P>
 __global__ __launch_bounds__(NT) void gemm_planes_grouped_kernel(
     const GroupDesc* __restrict__ d, const GroupTile* __restrict__ tiles,
     const int32_t* __restrict__ wstart) {
-  __shared__ __attribute__((aligned(1024))) char lds[Tile<P>::LDS];
+  __shared__ __attribute__((aligned(1024))) char lds[Tile<P, 256>::LDS];
   __shared__ float* rows[2][256];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int t = wstart[blockIdx.x];
   const int t1 = wstart[blockIdx.x + 1];
   if (t >= t1) return;
-  Feed<P, false> feed;
+  Feed<P, false, 256> feed;
   int n_tile, Nb;
   auto begin = [&](int i, int buf) __attribute__((always_inline)) {
     const PlaneParams& p = d[__builtin_amdgcn_readfirstlane(tiles[i].prod)].pl;
@@ -543,11 +604,11 @@ __global__ __launch_bounds__(NT) void gemm_planes_grouped_kernel(
   };
   begin(t, 0);
   for (int buf = 0; t < t1; ++t, buf ^= 1) {
-    Acc acc;
-    multiply<P, false>(feed, feed.nk1, lds, wave, lane, acc);
+    Acc<4> acc;
+    multiply<P, false, 256>(feed, feed.nk1, lds, wave, lane, acc);
     const int n0 = n_tile, cols = Nb;
     if (t + 1 < t1) begin(t + 1, buf ^ 1);
-    store_tile(acc, rows[buf], n0, cols, wave, lane);
+    store_tile<4, 4>(acc, rows[buf], n0, cols, wave, lane);
   }
 }
 
@@ -569,22 +630,23 @@ __global__ __launch_bounds__(256) void pack_planes_grouped_kernel(const GroupDes
     pack_a_block<P, false>(p, b - blocks_b, threadIdx.x);
 }
 
-// Sums the pieces of each split tile, 64 blocks per tile, one float4 per
-// thread, in piece order (fixed, so results do not depend on scheduling).
-template <bool GRID>
+// Sums the pieces of each split tile of S x S, one float4 per thread, in
+// piece order (fixed, so results do not depend on scheduling).
+template <bool GRID, int S>
 __global__ __launch_bounds__(256) void planes_reduce_kernel(PlaneParams p) {
-  const int t = blockIdx.x >> 6;
-  const int e = ((blockIdx.x & 63) << 8) + threadIdx.x;
-  const int row = e >> 6, col = (e & 63) * 4;
+  constexpr int BLOCKS = S * S / 1024;
+  const int t = blockIdx.x / BLOCKS;
+  const int e = (blockIdx.x % BLOCKS << 8) + threadIdx.x;
+  const int row = e / (S / 4), col = e % (S / 4) * 4;
   int si, mt, nt;
   tile_at<GRID>(p, p.full + t, &si, &mt, &nt);
-  float* out = out_row<GRID>(p, si, (unsigned)mt * 256u + (unsigned)row);
-  const int64_t n = (int64_t)nt * 256 + col;
+  float* out = out_row<GRID>(p, si, (unsigned)(mt * S + row));
+  const int64_t n = (int64_t)nt * S + col;
   if (!out || n >= p.Nb) return;
-  const float* src = p.part + (int64_t)t * p.split * 65536 + row * 256 + col;
+  const float* src = p.part + (int64_t)t * p.split * (S * S) + row * S + col;
   v4f sum = *reinterpret_cast<const v4f*>(src);
   for (int k = 1; k < p.split; ++k)
-    sum += *reinterpret_cast<const v4f*>(src + (int64_t)k * 65536);
+    sum += *reinterpret_cast<const v4f*>(src + (int64_t)k * (S * S));
 #pragma unroll
   for (int c = 0; c < 4; ++c)
     if (n + c < p.Nb) out[n + c] = sum[c];
@@ -594,11 +656,20 @@ __global__ __launch_bounds__(256) void planes_reduce_kernel(PlaneParams p) {
 
 void planes_tiles(PlaneParams* p) {
   const int64_t rows = p->grid > 1 ? p->Mb : (int64_t)p->n_sym * p->Mb;
-  p->tiles_m = (int32_t)((rows + 255) / 256);
-  p->tiles_n = (int32_t)((p->Nb + 255) / 256);
+  p->tile = 256;
+  p->tiles_m = p->pad_m = (int32_t)((rows + 255) / 256);
+  p->tiles_n = p->pad_n = (int32_t)((p->Nb + 255) / 256);
   p->row_group = p->grid > 1 ? 4 : 8;
   p->nka = (p->kc + 15) / 16;
   p->nkb = (p->kc + 3) / 4;
+}
+static void tiles_of_128(PlaneParams* p) {
+  const int64_t rows = p->grid > 1 ? p->Mb : (int64_t)p->n_sym * p->Mb;
+  p->tile = 128;
+  p->tiles_m = (int32_t)((rows + 127) / 128);
+  p->tiles_n = (int32_t)((p->Nb + 127) / 128);
+  p->pad_m *= 2;
+  p->pad_n *= 2;
 }
 
 int64_t planes_group_setup(PlaneParams* p) {
@@ -636,29 +707,59 @@ hipError_t launch_pack_planes(const PlaneParams& p0, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// Passes the busiest of S CUs runs when every symbol's per tiles, all but the
+// last skip ones, longest symbols first, each go to the CU that is free first.
+static int64_t longest_queue(const int32_t* passes, int64_t n_sym, int64_t per, int64_t skip,
+                             int64_t S) {
+  std::map<int64_t, int64_t> cus = {{0, S}};  // passes dealt -> CUs
+  int64_t left = n_sym * per - skip;
+  for (int64_t i = 0; i < n_sym && left > 0; ++i)
+    for (int64_t n = std::min(per, left); n > 0;) {
+      const auto first = cus.begin();
+      const int64_t m = std::min(n, first->second), to = first->first + passes[i];
+      if (m == first->second)
+        cus.erase(first);
+      else
+        first->second -= m;
+      cus[to] += m;
+      n -= m;
+      left -= m;
+    }
+  return cus.rbegin()->first;
+}
+
 // The last round: R of the tiles, each split into q pieces of its K range
-// whose partial tiles a second kernel sums, where a model of both says that
-// ends sooner: rounds of pieces at the measured time of a k chunk of one tile,
-// 6 us for the second launch and 0.125 us per partial tile written and read
-// back (4 TB/s).  1999 x 1500 x 1001, 36 tiles: 14 pieces, GEMM 43 and sum 11
-// us, where whole tiles would take 190 us.  R is what the products of all
-// tiles leave over after whole rounds (everything if that is less than one
-// round); in the two-dimensional form only one-pass tiles, which come last,
-// can fill up a round.
-void planes_split(PlaneParams* p, int64_t T, double us, int min_chunks) {
+// whose sums a second kernel forms, where a model of both says that ends
+// sooner: rounds of pieces at the measured time of a k chunk of one tile, 6 us
+// for the second launch and 0.125 us per 256 x 256 piece written and read back
+// (4 TB/s).  (Summed by the last of a tile's workgroups instead, over counters,
+// the second launch is saved and 5 to 25 us lost: the pieces are then read at
+// the pace of few CUs.)  R is what the products of all tiles leave over after
+// whole rounds (everything if that is less than one round); in the
+// two-dimensional form only one-pass tiles, which come last, can fill up a
+// round, and the symbols' passes (host memory) give the time of the others:
+// 4096 x 2048 x 4096, 288 large tiles of up to three passes, takes three
+// passes' time on 256 CUs however the last tiles are split.
+double planes_split(PlaneParams* p, const int32_t* passes, int64_t T, double us, int min_chunks) {
   const int64_t S = device_cu_count();
-  const int64_t per = p->grid > 1 ? T / p->n_sym : 1;
-  const int64_t units = p->grid > 1 ? p->n_passes * per : T;
-  const int64_t R = units <= S      ? T
-                    : p->grid > 1 ? std::min(units % S, p->n_single * per)
-                                  : T % S;
+  const bool grid = p->grid > 1;
+  const int64_t per = grid ? T / p->n_sym : 1;
+  const int64_t units = grid ? p->n_passes * per : T;
+  const int64_t rest = units <= S ? units : units % S;  // of the last round
+  const int64_t R = units <= S ? T : grid ? std::min(rest, p->n_single * per) : rest;
   const int64_t ru = units <= S ? units : R;
+  const int64_t pieces = (int64_t)p->part_tiles * (256 / p->tile) * (256 / p->tile);
+  const double piece_us = 0.125 * p->tile * p->tile / 65536.0, tile_us = (double)p->kc * us;
+  const double before = tile_us * (double)(grid ? longest_queue(passes, p->n_sym, per, R, S)
+                                                : (units - rest) / S);
   int64_t best_q = 1;
-  double best = p->kc * us;
+  double best = grid      ? tile_us * (double)longest_queue(passes, p->n_sym, per, 0, S)
+                : rest > 0 ? before + tile_us
+                           : before;
   for (int64_t q = 2; q <= 16 && R > 0; ++q) {
-    if (R * q > p->part_tiles || p->kc / q < min_chunks) break;
-    const double t = (double)((ru * q + S - 1) / S) * (double)p->kc * us / (double)q + 6.0 +
-                     0.125 * (double)(R * q);
+    if (R * q > pieces || p->kc / q < min_chunks) break;
+    const double t = before + (double)((ru * q + S - 1) / S) * tile_us / (double)q + 6.0 +
+                     piece_us * (double)(R * q);
     if (t < best) {
       best = t;
       best_q = q;
@@ -666,29 +767,57 @@ void planes_split(PlaneParams* p, int64_t T, double us, int min_chunks) {
   }
   p->split = (int32_t)best_q;
   p->full = (int32_t)(best_q > 1 ? T - R : T);
+  return best;
 }
 
 hipError_t launch_planes_reduce(const PlaneParams& p, int64_t T, hipStream_t stream) {
   if (p.full == T) return hipSuccess;
-  hipLaunchKernelGGL(p.grid > 1 ? planes_reduce_kernel<true> : planes_reduce_kernel<false>,
-                     dim3((unsigned)((T - p.full) * 64)), dim3(256), 0, stream, p);
+  const bool grid = p.grid > 1, small = p.tile == 128;
+  void (*k)(PlaneParams) = grid    ? small ? planes_reduce_kernel<true, 128> : planes_reduce_kernel<true, 256>
+                           : small ? planes_reduce_kernel<false, 128>
+                                   : planes_reduce_kernel<false, 256>;
+  hipLaunchKernelGGL(k, dim3((unsigned)((T - p.full) * (small ? 16 : 64))), dim3(256), 0, stream, p);
   return hipGetLastError();
 }
 
-hipError_t launch_gemm_planes(const PlaneParams& p0, hipStream_t stream) {
-  PlaneParams p = p0;
-  planes_tiles(&p);
-  const int64_t T = (int64_t)p.tiles_m * p.tiles_n * (p.grid > 1 ? p.n_sym : 1);
-  if (T > 0x7fffffff / 32) return hipErrorInvalidValue;
-  planes_split(&p, T, p.planes == 3 ? 2.0 : p.planes == 2 ? 1.05 : 0.45, 8);
+template <int S>
+static hipError_t launch_gemm_tiles(const PlaneParams& p, int64_t T, hipStream_t stream) {
   const unsigned blocks = (unsigned)(p.full + (T - p.full) * p.split);
-  void (*k)(PlaneParams) = p.grid > 1      ? gemm_planes_kernel<3, true>
-                           : p.planes == 3 ? gemm_planes_kernel<3, false>
-                           : p.planes == 2 ? gemm_planes_kernel<2, false>
-                                           : gemm_planes_kernel<1, false>;
-  hipLaunchKernelGGL(k, dim3(blocks), dim3(NT), 0, stream, p);
+  void (*k)(PlaneParams) = p.grid > 1      ? gemm_planes_kernel<3, true, S>
+                           : p.planes == 3 ? gemm_planes_kernel<3, false, S>
+                           : p.planes == 2 ? gemm_planes_kernel<2, false, S>
+                                           : gemm_planes_kernel<1, false, S>;
+  hipLaunchKernelGGL(k, dim3(blocks), dim3(2 * S), 0, stream, p);
   const hipError_t e = hipGetLastError();
   return e != hipSuccess ? e : launch_planes_reduce(p, T, stream);
+}
+
+// Tiles of 256 x 256 or 128 x 128, whichever the model of planes_split expects
+// to end sooner.  Times of a k chunk on a CU (per tile; two workgroups of the
+// small tile share a CU at the time of two): large ones FP32 2.0, BF16x3 1.05,
+// BF16 0.45 us, small ones 0.53, 0.295 and 0.123 us.  So the large tile is the
+// faster one per product (8192 x 4096 x 4096: FP32 1.15 against 1.22 ms, BF16
+// 284 against 313 us), the small one where large tiles leave CUs idle or have
+// to be split (all of coded_gemm: 2000 x 4000 x 2000, 64 large tiles: BF16 73
+// -> 59, BF16x3 121 -> 113, FP32 187 -> 181 us; 1500^3: 36 -> 26, 52 -> 46, 71
+// -> 67 us).  The large tile keeps what the model puts within 7 %: it draws less
+// power, which the model leaves out (Construction B, 8192 x 8192 x 4096, 3.75
+// rounds of large tiles: FP32 4.52 ms, 4.76 in small ones).
+hipError_t launch_gemm_planes(const PlaneParams& p0, const int32_t* passes, hipStream_t stream) {
+  PlaneParams p = p0;
+  planes_tiles(&p);
+  const int64_t syms = p.grid > 1 ? p.n_sym : 1;
+  const int64_t T = (int64_t)p.tiles_m * p.tiles_n * syms;
+  if (T > 0x7fffffff / 32) return hipErrorInvalidValue;
+  PlaneParams s = p;
+  tiles_of_128(&s);
+  const int64_t T128 = (int64_t)s.tiles_m * s.tiles_n * syms;
+  const double t = planes_split(&p, passes, T, p.planes == 3 ? 2.0 : p.planes == 2 ? 1.05 : 0.45, 8);
+  if (T128 <= 0x7fffffff / 32 &&
+      planes_split(&s, passes, T128, p.planes == 3 ? 0.53 : p.planes == 2 ? 0.295 : 0.123, 8) <
+          0.93 * t)
+    return launch_gemm_tiles<128>(s, T128, stream);
+  return launch_gemm_tiles<256>(p, T, stream);
 }
 
 }  // namespace bpx

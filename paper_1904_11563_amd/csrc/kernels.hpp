@@ -181,19 +181,23 @@ struct PlaneParams {
   unsigned* eb;
   // set by the launcher
   int32_t tiles_m, tiles_n;   // per symbol in the two-dimensional form
+  int32_t tile;        // edge of the GEMM's tiles, 256 or 128
+  int32_t pad_m, pad_n;       // as packed, an op padded to 256 rows and columns
   int32_t row_group;   // row panels per group of the tile order
   int32_t nka, nkb;    // pack blocks along k of A (256 wide) and of B (64 wide)
   int32_t full, split; // tiles computed whole; K pieces of each of the others
 };
 hipError_t launch_pack_planes(const PlaneParams& p, hipStream_t stream);
-hipError_t launch_gemm_planes(const PlaneParams& p, hipStream_t stream);
+// passes: in the two-dimensional form the passes of each symbol (host memory)
+hipError_t launch_gemm_planes(const PlaneParams& p, const int32_t* passes, hipStream_t stream);
 hipError_t launch_pack_fp8(const PlaneParams& p, hipStream_t stream);
 hipError_t launch_gemm_fp8_packed(const PlaneParams& p, hipStream_t stream);
 // tiles_m, tiles_n of a row-block product; how many of its T tiles run whole
 // and in how many K pieces the others (full, split), given the time of one
-// k chunk of a tile in us; and the kernel that sums the pieces.
+// k chunk of a tile in us (returns the time it expects); and the kernel that
+// sums the pieces.
 void planes_tiles(PlaneParams* p);
-void planes_split(PlaneParams* p, int64_t T, double us, int min_chunks);
+double planes_split(PlaneParams* p, const int32_t* passes, int64_t T, double us, int min_chunks);
 hipError_t launch_planes_reduce(const PlaneParams& p, int64_t T, hipStream_t stream);
 
 int32_t bf16_tile_count();

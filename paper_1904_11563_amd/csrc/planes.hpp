@@ -1,5 +1,6 @@
 // Device helpers of the kernels that multiply packed operands on 256 x 256
-// tiles with eight waves (2 x 4) of 128 x 64 (gemm_planes.hip, gemm_fp8.hip).
+// tiles with eight waves (2 x 4) of 128 x 64, or on 128 x 128 tiles with four
+// (2 x 2) of 64 x 64 (gemm_planes.hip, gemm_fp8.hip).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -16,7 +17,7 @@ typedef __attribute__((address_space(3))) void* lds_addr;
 typedef __attribute__((address_space(1))) float gfloat;
 typedef __attribute__((address_space(1))) v4f gv4f;
 
-constexpr int NT = 512;  // threads of a tile's workgroup
+constexpr int NT = 512;  // threads of a 256 x 256 tile's workgroup
 constexpr int kRsrcWord3 = 0x00020000;  // gfx9 raw buffer, 32-bit elements
 
 __device__ __forceinline__ int32_t gld(const int32_t* ptr) {
@@ -123,20 +124,24 @@ __device__ __forceinline__ float* out_row(const PlaneParams& p, int si, unsigned
   return row < p.M ? p.C + row * p.ldc + (int64_t)(s - br * p.grid) * (GRID ? p.Nb : 0) : nullptr;
 }
 
-typedef v16f Acc[4][2];
+// Accumulators of a wave: MI x 2 of 32 x 32.  WN waves side by side and two
+// above each other make a tile of 64 MI rows and 64 WN columns.
+template <int MI>
+using Acc = v16f[MI][2];
 
 // Writes an accumulated tile to its output rows: lane l holds column l % 32,
 // rows 8 (e / 4) + 4 (l / 32) + e % 4 of each 32 x 32.
-__device__ __forceinline__ void store_tile(const Acc& acc, float* const* rows, int64_t n_tile,
+template <int MI, int WN>
+__device__ __forceinline__ void store_tile(const Acc<MI>& acc, float* const* rows, int64_t n_tile,
                                            int64_t Nb, int wave, int lane) {
-  const int64_t n0 = n_tile + (wave & 3) * 64 + (lane & 31);
+  const int64_t n0 = n_tile + wave % WN * 64 + (lane & 31);
   const bool in0 = n0 < Nb, in1 = n0 + 32 < Nb;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < MI; ++i) {
     float* out[16];  // read together: one LDS latency per 16 rows
 #pragma unroll
     for (int e = 0; e < 16; ++e)
-      out[e] = rows[(wave >> 2) * 128 + i * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3)];
+      out[e] = rows[wave / WN * (32 * MI) + i * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3)];
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
@@ -147,16 +152,17 @@ __device__ __forceinline__ void store_tile(const Acc& acc, float* const* rows, i
   }
 }
 
-// Writes an accumulated tile as one piece of a split tile (256 x 256 floats).
-__device__ __forceinline__ void store_part(const Acc& acc, float* part, int wave, int lane) {
-  gfloat* out = (gfloat*)part + (wave & 3) * 64 + (lane & 31);
+// Writes an accumulated tile as one piece of a split tile (row major).
+template <int MI, int WN>
+__device__ __forceinline__ void store_part(const Acc<MI>& acc, float* part, int wave, int lane) {
+  gfloat* out = (gfloat*)part + wave % WN * 64 + (lane & 31);
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < MI; ++i)
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-      const int row = (wave >> 2) * 128 + i * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+      const int row = wave / WN * (32 * MI) + i * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
 #pragma unroll
-      for (int j = 0; j < 2; ++j) out[row * 256 + 32 * j] = acc[i][j][e];
+      for (int j = 0; j < 2; ++j) out[row * (64 * WN) + 32 * j] = acc[i][j][e];
     }
 }
 

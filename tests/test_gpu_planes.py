@@ -339,3 +339,29 @@ def test_peel_forms_exact(code, M, N):
         assert torch.equal(Cv._base[:, N:].isnan(), before[:, N:].isnan())  # nothing past N
         seen += 1
     assert seen
+
+
+# 256-wide and 128-wide tiles: all whole, all in K pieces, a last round in
+# pieces; rows, columns and K that fit neither
+@pytest.mark.parametrize("prec", PRECS)
+@pytest.mark.parametrize("shape", [(4700, 4100, 2560), (4100, 516, 2050), (2600, 2052, 1100),
+                                   (1000, 4100, 777), (3001, 516, 2050)])
+def test_split_planes_tile_sizes(shape, prec):
+    M, K, N = shape
+    plan = _plan(inputs.CODE_642, M, K, N, prec, bpx.MODE_FULL)
+    print("tiles", shape, prec, file=sys.stderr, flush=True)
+    A, B = _ops(7, M, K, N, True)
+    assert torch.equal(_run(plan, A, B, pad=4).double(), A.double() @ B.double())
+    A, B = _ops(8, M, K, N, False)
+    R = A.double() @ B.double()
+    new, old = _run(plan, A, B), _run(plan, A, B, tile=1)
+    assert _err(new, R) <= _err(old, R) + 1e-7      # fewer roundings, as above
+    if prec == bpx.PREC_F32:  # the panels of one element go to the FP32 kernels
+        A[M - 1, 3] = float("inf")
+        B[5, N // 2] = float("nan")
+        new, old = _run(plan, A, B), _run(plan, A, B, tile=1)
+        fin = torch.isfinite(old)
+        assert torch.equal(torch.isnan(new), torch.isnan(old))
+        assert torch.equal(torch.isfinite(new), fin)
+        d = torch.where(fin, new.double() - R, 0.0)
+        assert float(torch.linalg.norm(d) / torch.linalg.norm(R)) <= 1e-5
