@@ -184,8 +184,9 @@ bpx_status bpx_plan_create(const bpx_code* code, const int32_t* arrival, int32_t
  * grid*Nb, K a multiple of 32) run on 256x256 tiles when the FP32 tile
  * shape is one of the 256x256 ones (the default), other shapes and calls on
  * 64x128 tiles; both sum every product in the same order (identical
- * results).  Products of more than 2^31 multiply-adds over all passes run on
- * split planes (bpx_coded_gemm).  bpx_encode and grouped launches do not take such plans. */
+ * results).  Products of more than 2^25 multiply-adds over all passes
+ * and K >= 128, or of more than 2^31, run on split planes (bpx_coded_gemm).
+ * bpx_encode and grouped launches do not take such plans. */
 bpx_status bpx_plan_create2d(const bpx_code* code, const int32_t* arrival, int32_t n_arrival,
                              int32_t n_lost, int32_t mode, int64_t M, int64_t K, int64_t N,
                              int32_t prec, bpx_plan** out);
@@ -247,9 +248,8 @@ bpx_status bpx_plan_workspace_bytes(const bpx_plan* plan, size_t* ws_bytes,
  * at most 7), every part 256-byte aligned; a part the precision does not
  * use has size 0 (its offset equals the next one); entry 6 is the end of
  * these parts (behind it, up to ws_bytes, come the packed operands, flags or
- * scales and partial tiles of products of more than 2^31 multiply-adds over the
- * computed symbols and their passes; of the parts below only Y is then
- * written).
+ * scales and partial tiles of products large enough to run on packed operands;
+ * of the parts below only Y is then written).
  *   F32:     [0] Y slots, [1] split-K partial tiles: when Mb and N are
  *            multiples of 256, K of 32 and M of Mb, room for min(256, 4 T)
  *            FP32 tiles of 256 x 256 (T = computed symbols x Mb/256 x N/256),
@@ -285,8 +285,9 @@ bpx_status bpx_encode(bpx_plan* plan, const float* A, int64_t lda, float* coded_
 
 /* Coded products: Y_g = C_g . B for every computed symbol.  F32 and BF16*:
  * the encode is fused into the A-operand load (the coded block is never
- * stored), or, for more than 2^31 multiply-adds over the computed symbols,
- * into a pass that packs the coded blocks and B as BF16 planes (FP32 values
+ * stored), or, past 2^24 multiply-adds over the computed symbols (FP32: if K >
+ * 192, else 2^31) where the fused form of bpx_coded_matmul is not the faster
+ * one, into a pass that packs the coded blocks and B as BF16 planes (FP32 values
  * three planes cannot hold, infinities and NaN among them, send their tiles
  * to the FP32 kernels, so results for them are those of FP32 arithmetic).
  * FP8*: a streaming encode+quantise pass writes the e4m3 codes of every 128 x
@@ -315,10 +316,10 @@ bpx_status bpx_peel_decode(bpx_plan* plan, const void* ws, size_t ws_bytes, floa
  * products never reach memory and ws is not used).  The fused form runs
  * row-block F32 / BF16 / BF16x3 plans whose workgroup fits in LDS (the
  * whole K extent of a 16..64-column strip of B is staged on chip), by
- * default when the computed symbols hold at most 2^31 multiply-adds
- * (bpx_set_fused_peel).  Both forms compute the same values in the same
- * order of operations within each product: results match the two-launch
- * path. */
+ * default when the computed symbols hold at most 2^31 multiply-adds and it is
+ * expected to be faster than packed operands (bpx_set_fused_peel).  It computes
+ * the same values in the same order of operations within each product as the
+ * two launches on operands read directly: results match those. */
 bpx_status bpx_coded_matmul(bpx_plan* plan, const float* A, int64_t lda, const float* B,
                             int64_t ldb, float* C, int64_t ldc, void* ws, size_t ws_bytes,
                             bpx_stream stream);
@@ -329,8 +330,8 @@ bpx_status bpx_coded_matmul(bpx_plan* plan, const float* A, int64_t lda, const f
 bpx_status bpx_set_fused_peel(int32_t mode);
 
 /* *fused = 1 if bpx_coded_matmul takes the fused form for this plan with
- * dense operands (lda = K, ldb = ldc = N) under the current mode on the
- * current device, else 0. */
+ * dense operands (lda = K, ldb = ldc = N) and a workspace of ws_bytes under the
+ * current mode on the current device, else 0. */
 bpx_status bpx_plan_fused(bpx_plan* plan, int32_t* fused);
 
 /* The fused form's peel program (read-only, owned by the plan): steps in

@@ -17,6 +17,7 @@ namespace bpx {
 
 namespace {
 thread_local std::string g_error;
+constexpr double kFusedMacs = 2147483648.0;  // the fused form's largest products by default
 int32_t g_fused_mode = 1;  // 0 never, 1 small products, 2 whenever it fits
 int32_t g_force_tile = -1;
 int32_t g_group_m = 2;
@@ -225,6 +226,73 @@ void plane_params(const bpx_plan* plan, const GemmParams& p, PlaneParams* out) {
   }
 }
 
+// The fused form's parameters; false where a workgroup does not fit in LDS or
+// the plan has no program for it.
+bool fused_setup(const bpx_plan* plan, const float* A, int64_t lda, const float* B, int64_t ldb,
+                 float* C, int64_t ldc, FusedParams* f) {
+  if (plan->grid != 1 || plan->fused_steps.empty()) return false;
+  *f = FusedParams{};
+  f->A = A;
+  f->lda = lda;
+  f->B = B;
+  f->ldb = ldb;
+  f->C = C;
+  f->ldc = ldc;
+  f->M = plan->M;
+  f->K = plan->K;
+  f->N = plan->N;
+  f->Mb = plan->Mb;
+  f->syms = plan->d_gemm_syms;
+  f->ids = plan->d_gemm_ids;
+  f->ytile = plan->d_fused_ytile;
+  f->n_sym = (int32_t)plan->computed.size();
+  f->n_ytiles = plan->n_ytiles;
+  f->n_ids = (int32_t)plan->gemm_ids.size();
+  f->off_ids = (int32_t)(plan->d_gemm_ids - plan->d_gemm_syms);
+  f->off_steps = (int32_t)(reinterpret_cast<const int32_t*>(plan->d_fused_steps) -
+                           plan->d_gemm_syms);
+  f->off_subs = (int32_t)(plan->d_fused_subs - plan->d_gemm_syms);
+  f->off_ytile = (int32_t)(plan->d_fused_ytile - plan->d_gemm_syms);
+  f->blob_words = f->off_ytile + (int32_t)plan->fused_ytile.size();
+  f->steps = plan->d_fused_steps;
+  f->subs = plan->d_fused_subs;
+  f->nsteps = (int32_t)plan->fused_steps.size();
+  f->nsubs = (int32_t)plan->fused_subs.size();
+  f->nslots = plan->n_lds_slots;
+  f->prec = plan->prec;
+  f->kb = plan->code.kb();
+  f->max_deg = 0;
+  for (size_t i = 0; i < plan->computed.size(); ++i)
+    f->max_deg = std::max(f->max_deg, plan->gemm_syms[4 * i + 1]);
+  return fused_configure(f);
+}
+
+// Whether a call with this much workspace runs its products on packed operands:
+// not where the fused form is expected to be faster (rounds of 16-row tiles
+// whose waves walk all of K: 512^3 FP32 16 us against 28 on packed operands,
+// 768 x 1024 x 768 50 against 36, 913 x 1012 x 1266 75 against 42, BF16 100 x
+// 1800 x 100 31 against 20), nor with that form switched off, so that it and the
+// two launches keep giving the same bits.
+bool on_planes(const bpx_plan* plan, int64_t lda, int64_t ldb, size_t ws_bytes) {
+  if (!plan->has_planes() || ws_bytes < plan->ws_bytes() ||
+      tile_chosen(plan->prec, plan->Mb, plan->N, plan->K))
+    return false;
+  FusedParams f;
+  if (plan->n_macs() > kFusedMacs ||
+      !fused_setup(plan, nullptr, lda, nullptr, ldb, nullptr, plan->N, &f))
+    return true;
+  GemmParams g{};
+  g.M = plan->M;
+  g.K = plan->K;
+  g.N = plan->N;
+  g.Mb = plan->Mb;
+  g.n_sym = f.n_sym;
+  PlaneParams q;
+  plane_params(plan, g, &q);
+  q.part_tiles = plan->plane_part_tiles();
+  return planes_us(q) < fused_us(f);
+}
+
 // Coded products on split planes (see gemm_planes.hip): pack, multiply and,
 // for FP32, the tiles that hold a value the planes do not represent.
 bpx_status gemm_planes_impl(bpx_plan* plan, GemmParams p, void* ws, hipStream_t stream) {
@@ -310,8 +378,7 @@ bpx_status gemm_impl(bpx_plan* plan, const float* A, int64_t lda, const float* B
     if (Np / 128 > 65535 || Kp / 128 > 65535 || Mbp / 128 > 65535 || p.n_sym > 65535)
       return fail(BPX_E_UNSUPPORTED, "FP8 grid too large");
   }
-  if (plan->has_planes() && ws_bytes >= plan->ws_bytes() &&
-      !tile_chosen(plan->prec, plan->Mb, plan->N, plan->K))
+  if (on_planes(plan, lda, ldb, ws_bytes))
     return gemm_planes_impl(plan, p, ws, stream);
   const int32_t tile = choose_tile(plan->prec, plan->Mb, plan->N, plan->K);
   hipError_t e;
@@ -397,50 +464,16 @@ bpx_status scratch_address(void** out) {
 // The fused form (one launch, peel in the GEMM epilogue): row-block plans of
 // F32 / BF16 / BF16x3 whose workgroup LDS fits; in the default mode only
 // products small enough that launches and latency dominate the two-launch
-// path (at most 2^31 multiply-adds over the computed symbols, e.g. 512^3
-// with eight symbols is 2^27).
-bool fused_params(bpx_plan* plan, const float* A, int64_t lda, const float* B, int64_t ldb,
-                  float* C, int64_t ldc, FusedParams* f) {
+// path: at most 2^31 multiply-adds over the computed symbols (512^3 with eight
+// symbols is 2^27), and not on packed operands.
+bool fused_params(const bpx_plan* plan, const float* A, int64_t lda, const float* B, int64_t ldb,
+                  float* C, int64_t ldc, size_t ws_bytes, FusedParams* f) {
   // a forced GEMM tile shape names the two-launch form's tiling
-  if (g_fused_mode == 0 || g_force_tile >= 0 || plan->grid != 1 || plan->fused_steps.empty())
+  if (g_fused_mode == 0 || g_force_tile >= 0) return false;
+  if (g_fused_mode == 1 &&
+      (plan->n_macs() > kFusedMacs || on_planes(plan, lda, ldb, ws_bytes)))
     return false;
-  const double macs = (double)plan->computed.size() * (double)plan->Mb * (double)plan->K *
-                      (double)plan->N;
-  if (g_fused_mode == 1 && macs > 2147483648.0) return false;
-  *f = FusedParams{};
-  f->A = A;
-  f->lda = lda;
-  f->B = B;
-  f->ldb = ldb;
-  f->C = C;
-  f->ldc = ldc;
-  f->M = plan->M;
-  f->K = plan->K;
-  f->N = plan->N;
-  f->Mb = plan->Mb;
-  f->syms = plan->d_gemm_syms;
-  f->ids = plan->d_gemm_ids;
-  f->ytile = plan->d_fused_ytile;
-  f->n_sym = (int32_t)plan->computed.size();
-  f->n_ytiles = plan->n_ytiles;
-  f->n_ids = (int32_t)plan->gemm_ids.size();
-  f->off_ids = (int32_t)(plan->d_gemm_ids - plan->d_gemm_syms);
-  f->off_steps = (int32_t)(reinterpret_cast<const int32_t*>(plan->d_fused_steps) -
-                           plan->d_gemm_syms);
-  f->off_subs = (int32_t)(plan->d_fused_subs - plan->d_gemm_syms);
-  f->off_ytile = (int32_t)(plan->d_fused_ytile - plan->d_gemm_syms);
-  f->blob_words = f->off_ytile + (int32_t)plan->fused_ytile.size();
-  f->steps = plan->d_fused_steps;
-  f->subs = plan->d_fused_subs;
-  f->nsteps = (int32_t)plan->fused_steps.size();
-  f->nsubs = (int32_t)plan->fused_subs.size();
-  f->nslots = plan->n_lds_slots;
-  f->prec = plan->prec;
-  f->kb = plan->code.kb();
-  f->max_deg = 0;
-  for (size_t i = 0; i < plan->computed.size(); ++i)
-    f->max_deg = std::max(f->max_deg, plan->gemm_syms[4 * i + 1]);
-  return fused_configure(f);
+  return fused_setup(plan, A, lda, B, ldb, C, ldc, f);
 }
 
 bpx_status peel_impl(bpx_plan* plan, const void* ws, size_t ws_bytes, float* C, int64_t ldc,
@@ -1101,7 +1134,7 @@ bpx_status bpx_coded_matmul(bpx_plan* plan, const float* A, int64_t lda, const f
   if (st != BPX_OK) return st;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   FusedParams f;
-  if (fused_params(plan, A, lda, B, ldb, C, ldc, &f)) {
+  if (fused_params(plan, A, lda, B, ldb, C, ldc, ws ? ws_bytes : 0, &f)) {
     // same argument contract as the two-launch form (the caller cannot
     // tell which form runs), though the fused launch leaves ws untouched
     if ((st = check_matrix(A, lda, plan->K, "A")) != BPX_OK) return st;
@@ -1136,7 +1169,7 @@ bpx_status bpx_coded_matmul_noalloc(bpx_plan* plan, const float* A, int64_t lda,
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   bpx_status st;
   FusedParams f;
-  if (fused_params(plan, A, lda, B, ldb, C, ldc, &f)) {  // needs no workspace
+  if (fused_params(plan, A, lda, B, ldb, C, ldc, kScratchBytes, &f)) {  // needs no workspace
     if ((st = check_matrix(A, lda, plan->K, "A")) != BPX_OK) return st;
     if ((st = check_matrix(B, ldb, plan->N, "B")) != BPX_OK) return st;
     if ((st = check_matrix(C, ldc, plan->N, "C")) != BPX_OK) return st;
@@ -1238,7 +1271,8 @@ bpx_status bpx_plan_fused(bpx_plan* plan, int32_t* fused) {
   if (!plan || !fused) return fail(BPX_E_INVALID, "null argument");
   FusedParams f;
   *fused = plan->decodable &&
-                   fused_params(plan, nullptr, plan->K, nullptr, plan->N, nullptr, plan->N, &f)
+                   fused_params(plan, nullptr, plan->K, nullptr, plan->N, nullptr, plan->N,
+                                plan->ws_bytes(), &f)
                ? 1
                : 0;
   return BPX_OK;

@@ -673,6 +673,22 @@ bool fused_configure(FusedParams* p) {
   return false;
 }
 
+// Rounds of one workgroup per CU, each 6.5 us and, per k, what a wave's symbols
+// take; wider strips take 1.5 and 2.4 times that.  Measured (us, one round):
+// eight symbols, K = 512 and 1024: FP32 15.7 and 24.7, BF16x3 14.5 and 21.5, BF16
+// 13.3 and 19.7; nine symbols, two to a wave: 22.3 and 37.3, 19.1 and 30.8, 17.1
+// and 26.2.
+double fused_us(const FusedParams& p) {
+  const int64_t cus = device_cu_count();
+  const double rounds = (double)(((int64_t)p.tiles_m * p.tiles_n + cus - 1) / cus);
+  const double s = (double)((p.n_sym + kWaves - 1) / kWaves);
+  const double per_k = p.prec == BPX_PREC_F32      ? 0.006 + 0.0117 * s
+                       : p.prec == BPX_PREC_BF16X3 ? 0.0045 + 0.0092 * s
+                                                   : 0.0072 + 0.0053 * s;
+  const double strip = p.jn == 1 ? 1.0 : p.jn == 2 ? 1.5 : 2.4;
+  return rounds * (6.5 + (double)p.K * per_k * strip);
+}
+
 size_t fused_lds_bytes(const FusedParams& p) { return fused_lds(p).total; }
 
 hipError_t launch_fused(const FusedParams& p, hipStream_t stream) {

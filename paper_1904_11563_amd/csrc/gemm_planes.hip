@@ -803,21 +803,45 @@ static hipError_t launch_gemm_tiles(const PlaneParams& p, int64_t T, hipStream_t
 // -> 67 us).  The large tile keeps what the model puts within 7 %: it draws less
 // power, which the model leaves out (Construction B, 8192 x 8192 x 4096, 3.75
 // rounds of large tiles: FP32 4.52 ms, 4.76 in small ones).
-hipError_t launch_gemm_planes(const PlaneParams& p0, const int32_t* passes, hipStream_t stream) {
-  PlaneParams p = p0;
-  planes_tiles(&p);
-  const int64_t syms = p.grid > 1 ? p.n_sym : 1;
-  const int64_t T = (int64_t)p.tiles_m * p.tiles_n * syms;
-  if (T > 0x7fffffff / 32) return hipErrorInvalidValue;
-  PlaneParams s = p;
+static double choose_tiles(PlaneParams* p, const int32_t* passes, int64_t* tiles) {
+  planes_tiles(p);
+  const int64_t syms = p->grid > 1 ? p->n_sym : 1, lim = 0x7fffffff / 32;
+  const int64_t T = (int64_t)p->tiles_m * p->tiles_n * syms;
+  *tiles = T;
+  if (T > lim) return 0.0;
+  PlaneParams s = *p;
   tiles_of_128(&s);
   const int64_t T128 = (int64_t)s.tiles_m * s.tiles_n * syms;
-  const double t = planes_split(&p, passes, T, p.planes == 3 ? 2.0 : p.planes == 2 ? 1.05 : 0.45, 8);
-  if (T128 <= 0x7fffffff / 32 &&
-      planes_split(&s, passes, T128, p.planes == 3 ? 0.53 : p.planes == 2 ? 0.295 : 0.123, 8) <
-          0.93 * t)
-    return launch_gemm_tiles<128>(s, T128, stream);
-  return launch_gemm_tiles<256>(p, T, stream);
+  const int P = p->planes;
+  const double t = planes_split(p, passes, T, P == 3 ? 2.0 : P == 2 ? 1.05 : 0.45, 8);
+  if (T128 > lim) return t;
+  const double t128 = planes_split(&s, passes, T128, P == 3 ? 0.53 : P == 2 ? 0.295 : 0.123, 8);
+  if (t128 >= 0.93 * t) return t;
+  *p = s;
+  *tiles = T128;
+  return t128;
+}
+
+hipError_t launch_gemm_planes(const PlaneParams& p0, const int32_t* passes, hipStream_t stream) {
+  PlaneParams p = p0;
+  int64_t T;
+  choose_tiles(&p, passes, &T);
+  if (T > 0x7fffffff / 32) return hipErrorInvalidValue;
+  return p.tile == 128 ? launch_gemm_tiles<128>(p, T, stream) : launch_gemm_tiles<256>(p, T, stream);
+}
+
+// 15 us of launches (FP32, with its second product launch, 18), the GEMM's
+// rounds, and the operands, planes and products at 4 TB/s.  512^3 with eight
+// symbols: FP32 29 us expected, 27.7 measured, BF16x3 25 and 23.8, BF16 20 and
+// 17.5; 768 x 1024 x 768: 38 and 36, 32 and 30, 25 and 23.7.
+double planes_us(const PlaneParams& p0) {
+  PlaneParams p = p0;
+  int64_t T;
+  const double gemm = choose_tiles(&p, nullptr, &T);
+  const double K = (double)p.K, N = (double)p.N, rows = (double)p.n_sym * (double)p.Mb;
+  const double bytes = 4.0 * K * ((double)p.M + N) + 4.0 * p.planes * K * (rows + N) +
+                       12.0 * rows * N;
+  return (p.planes == 3 ? 18.0 : 15.0) + gemm + bytes / 4e6;
 }
 
 }  // namespace bpx

@@ -4,6 +4,7 @@
 
 #include "../../include/bpx.h"
 
+#include <algorithm>
 #include <cstddef>
 #include <cstdint>
 #include <string>
@@ -171,11 +172,8 @@ struct bpx_plan {
     layout(off);
     return off[6];
   }
-  // Products past the fused form's size (2^31 multiply-adds over the computed
-  // symbols) also reserve room for the operands packed in the order of MFMA
-  // fragments (gemm_planes.hip: BF16 planes; gemm_fp8.hip: codes), behind the
-  // parts above; below it the pack pass and the 256 x 256 tiles cost more than
-  // they save.
+  // Operands packed in the order of MFMA fragments (gemm_planes.hip: BF16
+  // planes; gemm_fp8.hip: codes), behind the parts above.
   int32_t planes() const {
     switch (prec) {
       case BPX_PREC_F32: return 3;
@@ -201,13 +199,28 @@ struct bpx_plan {
   int64_t n_products() const {
     return grid > 1 ? (int64_t)ops.passes.size() / 2 : (int64_t)computed.size();
   }
+  double n_macs() const { return (double)n_products() * (double)Mb * (double)K * (double)Nb; }
   int64_t plane_tiles() const {
     return grid > 1 ? (int64_t)computed.size() * (r256(Mb) / 256) * (r256(Nb) / 256)
                     : plane_rows() / 256 * (plane_cols() / 256);
   }
+  // Whether the products run on packed operands where the workspace holds them
+  // (small row-block products may still take the fused form).  BF16: from 2^24
+  // multiply-adds, below which nearly all of either way is launches (400 x 64 x
+  // 400 on Construction B, 2^24: 14 and 13 us; 2048 x 300 x 2048 on the (12,8,4)
+  // code: direct 41, packed 34).  FP32 packs six bytes per value, so it takes
+  // longer K to pay: (12,8,4), 1024 x K x 1024: K = 128 direct 28, packed 29 us;
+  // 192 35 and 32; 300 47 and 38; 321 x 3256 x 451 256 and 45; past 2^31 it does
+  // for any K.  Two-dimensional: from 2^25 and K = 128 (Table I's code: 400 x 128 x
+  // 400 17 and 21 us, 1024 x 128 x 1024 45 and 24; K = 32 to 64 within a quarter
+  // of each other).  FP8: past 2^31.
   bool has_planes() const {
-    const double macs = (double)n_products() * (double)Mb * (double)K * (double)Nb;
-    return macs > 2147483648.0 && planes_fit();
+    const double macs = n_macs();
+    const bool enough = is_fp8()    ? false
+                        : is_bf16() ? macs > 16777216.0
+                        : grid > 1  ? macs > 33554432.0 && K >= 128
+                                    : macs > 16777216.0 && K > 192;
+    return (enough || macs > 2147483648.0) && planes_fit();
   }
   // Bytes of 32 packed rows (columns) and one k chunk, all planes.
   int64_t a_chunk_bytes() const { return (int64_t)planes() * (is_fp8() ? 2048 : 1024); }
@@ -253,10 +266,11 @@ struct bpx_plan {
     b += (size_t)plane_part_tiles() * 65536 * sizeof(float);
     off[5] = b;
   }
+  // At most 16 pieces of a tile, of 8 k chunks (FP8: 4) at least.
   static constexpr int32_t kPartTiles = 512;
   int32_t plane_part_tiles() const {
-    const int64_t t = plane_tiles() * 16;
-    return t < kPartTiles ? (int32_t)t : kPartTiles;
+    const int64_t q = std::min<int64_t>(16, plane_kc() / (is_fp8() ? 4 : 8));
+    return q < 2 ? 0 : (int32_t)std::min<int64_t>(plane_tiles() * q, kPartTiles);
   }
   size_t ws_bytes() const {
     if (!has_planes()) return base_bytes();

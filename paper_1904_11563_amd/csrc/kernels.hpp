@@ -190,6 +190,8 @@ struct PlaneParams {
 hipError_t launch_pack_planes(const PlaneParams& p, hipStream_t stream);
 // passes: in the two-dimensional form the passes of each symbol (host memory)
 hipError_t launch_gemm_planes(const PlaneParams& p, const int32_t* passes, hipStream_t stream);
+// Time that pack, product and peel of a row-block product are expected to take, in us.
+double planes_us(const PlaneParams& p);
 hipError_t launch_pack_fp8(const PlaneParams& p, hipStream_t stream);
 hipError_t launch_gemm_fp8_packed(const PlaneParams& p, hipStream_t stream);
 // tiles_m, tiles_n of a row-block product; how many of its T tiles run whole
@@ -301,6 +303,8 @@ struct FusedParams {
 bool fused_configure(FusedParams* p);
 size_t fused_lds_bytes(const FusedParams& p);
 hipError_t launch_fused(const FusedParams& p, hipStream_t stream);
+// Time a configured product is expected to take, in us.
+double fused_us(const FusedParams& p);
 
 hipError_t launch_quant_a(const Fp8Params& p, hipStream_t stream);
 hipError_t launch_quant_b(const Fp8Params& p, hipStream_t stream);

@@ -365,3 +365,34 @@ def test_split_planes_tile_sizes(shape, prec):
         assert torch.equal(torch.isfinite(new), fin)
         d = torch.where(fin, new.double() - R, 0.0)
         assert float(torch.linalg.norm(d) / torch.linalg.norm(R)) <= 1e-5
+
+
+# Small products on packed operands: long K on few tiles (all in pieces), the
+# smallest K and sizes that are packed, and codes the fused form does not run
+@pytest.mark.parametrize("prec", PRECS)
+@pytest.mark.parametrize("code,mode,shape", [
+    ("642", bpx.MODE_FULL, (419, 3428, 373)), ("1284", bpx.MODE_FULL, (330, 196, 301)),
+    ("1284", bpx.MODE_STRAGGLER, (1473, 1000, 1277)), ("moj", bpx.MODE_MIN, (1000, 212, 90)),
+    ("table3", bpx.MODE_FULL, (768, 1024, 769))])
+def test_small_products_on_planes(code, mode, shape, prec):
+    M, K, N = shape
+    lib = {"642": lambda: _code(inputs.CODE_642), "1284": lambda: _code(inputs.CODE_1284),
+           "moj": lambda: bpx.Code.mojette(8, 4, 12, 1), "table3": bpx.Code.table3}[code]()
+    arrival, _ = inputs.shifted_exp_arrival(0, lib.info()["n"])
+    plan = bpx.Plan(lib, arrival, 0, mode, M, K, N, prec)
+    assert plan.workspace_bytes()[0] > plan.workspace_layout()[6] and not plan.fused()
+    print("small planes", code, shape, prec, file=sys.stderr, flush=True)
+    A, B = _ops(9, M, K, N, True)
+    assert torch.equal(_run(plan, A, B, pad=4).double(), A.double() @ B.double())
+    A, B = _ops(10, M, K, N, False)
+    R = A.double() @ B.double()
+    new, old = _run(plan, A, B), _run(plan, A, B, tile=1)
+    print("  error", _err(new, R), "direct kernels", _err(old, R), file=sys.stderr, flush=True)
+    assert _err(new, R) <= _err(old, R) * (1.0 if K > 256 else 1.1) + 1e-7
+    small = torch.empty(max(plan.workspace_layout()[6], 256), dtype=torch.uint8, device="cuda")
+    if prec == bpx.PREC_F32:
+        assert _err(_run(plan, A, B, ws=small), R) <= 1e-5
+        A[3, 5] = float("inf")
+        new, old = _run(plan, A, B), _run(plan, A, B, tile=1)
+        assert torch.equal(torch.isfinite(new), torch.isfinite(old))
+        assert torch.equal(torch.isnan(new), torch.isnan(old))
