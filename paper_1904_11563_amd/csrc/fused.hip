@@ -39,11 +39,11 @@
 #include <type_traits>
 
 #include "kernels.hpp"
+#include "planes.hpp"
 
 namespace bpx {
 namespace {
 
-typedef float v4f __attribute__((ext_vector_type(4)));
 typedef float v2f __attribute__((ext_vector_type(2)));
 typedef double v4d __attribute__((ext_vector_type(4)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
@@ -87,7 +87,11 @@ __host__ __device__ inline FusedLds fused_lds(const FusedParams& p) {
   else
     L.strip = (size_t)BN * (p.kp + 8) * 2 * (p.prec == BPX_PREC_BF16X3 ? 2 : 1);
   L.strip = (L.strip + 15) / 16 * 16;
-  L.astage = 2 * (size_t)p.kb * BM * p.kg * 4;  // two buffers of the k group's A rows
+  // buffers of a k group's A rows (three: no more than there are groups, so that
+  // two workgroups of a short product still fit on a CU)
+  const int64_t groups = p.kp / p.kg;
+  const size_t stages = p.stages == 3 && groups < 3 ? (size_t)groups : (size_t)p.stages;
+  L.astage = stages * (size_t)p.kb * BM * p.kg * 4;
   L.ytiles = (size_t)p.n_ytiles * BM * BN * 4;
   L.slots = (size_t)p.nslots * BM * BN * 4;
   L.prog = ((size_t)p.blob_words * 4 + 15) / 16 * 16;
@@ -107,7 +111,6 @@ struct FusedTables {
 // span starts 256-byte aligned), returns them for store_tables; a second
 // pass covers spans past 16 KiB.
 constexpr int kTabPass = 4;  // int4 per thread per pass
-typedef int v4i __attribute__((ext_vector_type(4)));
 struct TabLoads {
   v4i v[kTabPass];
 };
@@ -155,7 +158,6 @@ __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirs
 // rows past them return zero without a branch; a k past K is sent out of
 // range as well.  The host keeps (Mb + 16) * lda * 4 and K * ldb * 4 below
 // 2^31.
-constexpr int kRsrcWord3 = 0x00020000;  // gfx9 raw buffer, 32-bit elements
 constexpr uint32_t kOut = 0x80000000u;  // beyond any resource's range
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t block_rsrc(const FusedParams& p, int64_t s) {
   const int64_t rows = p.M - s * p.Mb < p.Mb ? p.M - s * p.Mb : p.Mb;
@@ -174,37 +176,75 @@ __device__ __forceinline__ v4f bload(__amdgpu_buffer_rsrc_t r, uint32_t voff) {
 
 // Peel phase: every thread runs the whole program for its own elements.
 // Steps carry src = the releaser's Y tile, and every recovered block is
-// written to C (nothing reached C earlier).
-__device__ __forceinline__ bool row_ok(const FusedParams& p, int64_t s, int64_t r) {
-  return r < p.Mb && s * p.Mb + r < p.M;
-}
-__device__ __forceinline__ void fused_peel(const FusedParams& p, const float* yt, float* xs,
+// written to C (nothing reached C earlier).  Bound by one wave's instructions
+// per step (256 elements, a wave to a SIMD), so lane l works out step l's
+// addresses (at most one step per data block, and one subtrahend less than a
+// symbol's members), a step reads them across lanes, and what it does not use
+// it reads and writes at its own product's place instead of branching.  512^3,
+// eight steps: 5500 -> 5000 cycles, and fewer registers (below 128 two
+// workgroups share a CU where LDS allows: (6,4,2) 768 x 64 x 768, 288 tiles, FP32
+// 14.0 -> 10.3 us).
+constexpr int kMaxDeg = 4;  // members per symbol at most
+__device__ __forceinline__ void fused_peel(const FusedParams& p, float* yt, const float* xs,
                                            const FusedTables& t, int r0, int n0, int BN) {
-  const int tile = BM * BN;
+  const int tile = BM * BN, lane = (int)threadIdx.x & 63;
+  // byte offsets from yt
+  const int x0 = (int)((const char*)xs - (const char*)yt);
+  PeelStep mine = {};
+  int sub[kMaxDeg - 1] = {}, rows = 0;
+  uint64_t block = 0;
+  if (lane < p.nsteps) {
+    mine = t.steps[lane];
+    const int64_t first = (int64_t)mine.s * p.Mb;
+    rows = (int)max((int64_t)0, min(p.M - first, p.Mb));
+    block = reinterpret_cast<uint64_t>(p.C + first * p.ldc);
+#pragma unroll
+    for (int u = 0; u < kMaxDeg - 1; ++u)
+      sub[u] = u < mine.nsub ? x0 + t.subs[mine.sub_off + u] * tile * 4 : mine.src * tile * 4;
+  }
+  const int src = mine.src * tile * 4, kind = mine.nsub + (mine.f64 ? 8 : 0);
+  const int slot = mine.slot >= 0 ? x0 + mine.slot * tile * 4 : src;
+  const int lo = (int)block, hi = (int)(block >> 32);
+  auto of = [](int v, int st) __attribute__((always_inline)) {
+    return __builtin_amdgcn_readlane(v, st);
+  };
   for (int e = threadIdx.x; e < tile; e += kThreads) {
-    const int row = e / BN, col = e - row * BN;
-    const int64_t r = r0 + row, n = n0 + col;
+    const int row = e / BN, r = r0 + row, n = n0 + e - row * BN;
+    const int last = n < p.N ? r : 0x7fffffff;  // (no row of a column past N)
+    const int64_t at = (int64_t)r * p.ldc + n;
+    char* mem = reinterpret_cast<char*>(yt + e);
+    auto word = [&](int off) __attribute__((always_inline)) -> float& {
+      return *reinterpret_cast<float*>(mem + off);
+    };
+    float y = word(of(src, 0));
     for (int st = 0; st < p.nsteps; ++st) {
-      const PeelStep S = t.steps[st];
-      const float y = yt[S.src * tile + e];
-      const int32_t* sub = t.subs + S.sub_off;
+      const float cur = y;
+      const float v0 = word(of(sub[0], st)), v1 = word(of(sub[1], st)), v2 = word(of(sub[2], st));
+      y = word(of(src, st + 1));  // (past the last step: lane's zeros, never used)
+      const int k = of(kind, st);
       float x;
-      if (S.f64) {
-        double acc = (double)y;
-        for (int u = 0; u < S.nsub; ++u) acc -= (double)xs[sub[u] * tile + e];
-        x = (float)acc;
-      } else {
-        float sum = y, comp = 0.f;
-        for (int u = 0; u < S.nsub; ++u) {
-          const float v = -xs[sub[u] * tile + e] - comp;
-          const float tt = sum + v;
-          comp = (tt - sum) - v;
-          sum = tt;
-        }
+      if (k < 8) {
+        float sum = cur, comp = 0.f;
+        auto take = [&](float v, bool on) __attribute__((always_inline)) {
+          const float w = -v - comp, tt = sum + w, c = (tt - sum) - w;
+          comp = on ? c : comp;
+          sum = on ? tt : sum;
+        };
+        take(v0, k > 0);
+        take(v1, k > 1);
+        take(v2, k > 2);
         x = sum;
+      } else {
+        double acc = (double)cur;
+        if (k > 8) acc -= (double)v0;
+        if (k > 9) acc -= (double)v1;
+        if (k > 10) acc -= (double)v2;
+        x = (float)acc;
       }
-      if (S.slot >= 0) xs[S.slot * tile + e] = x;
-      if (n < p.N && row_ok(p, S.s, r)) p.C[((int64_t)S.s * p.Mb + r) * p.ldc + n] = x;
+      word(of(slot, st)) = x;
+      float* out = reinterpret_cast<float*>((uint64_t)(uint32_t)of(lo, st) |
+                                            (uint64_t)(uint32_t)of(hi, st) << 32);
+      if (last < of(rows, st)) out[at] = x;
     }
   }
 }
@@ -263,6 +303,60 @@ struct AStage {
       if (ok[u]) *reinterpret_cast<v4f*>(As + soff[u]) = v[u];
   }
 };
+// The same stage copied straight to LDS, 1 KiB (eight rows of a k half of one
+// block) per instruction, item i = u kWaves + wave.  The swizzle is on the
+// global side: lane l brings the granule that belongs at its 16 bytes; rows and
+// k past the matrix arrive as zeros.
+constexpr int kDmaPer = kAPer;
+template <int KG>
+struct ADma {
+  static constexpr int kItems = KG / 16;  // per block
+  v4i rs[kDmaPer];
+  uint32_t goff[kDmaPer];
+  int kof[kDmaPer];
+  int lds[kDmaPer];
+  int n;  // this wave's items
+  __device__ void init(const FusedParams& p, int r0, const float* As0) {
+    const int wave = uniform((int)threadIdx.x >> 6), lane = (int)threadIdx.x & 63;
+    const int items = p.kb * kItems;
+    n = wave < items ? (items - wave + kWaves - 1) / kWaves : 0;
+#pragma unroll
+    for (int u = 0; u < kDmaPer; ++u) {
+      const int i = min(u * kWaves + wave, items - 1);
+      const int blk = i / kItems, h = i % kItems / 2, row = (i & 1) * 8 + (lane >> 3);
+      const int64_t rows = p.M - blk * p.Mb < p.Mb ? p.M - blk * p.Mb : p.Mb;
+      const uint64_t src = reinterpret_cast<uint64_t>(p.A + blk * p.Mb * p.lda);
+      rs[u] = v4i{(int)src, (int)(src >> 32) & 0xffff, rows > 0 ? (int)(rows * p.lda * 4) : 0,
+                  kRsrcWord3};
+#pragma unroll
+      for (int c = 0; c < 4; ++c) rs[u][c] = uniform(rs[u][c]);
+      kof[u] = 32 * h + 4 * a_slot(row, lane & 7);
+      goff[u] = 4u * (uint32_t)((r0 + row) * (int)p.lda);
+      lds[u] = uniform((int)(uintptr_t)(lds_addr)As0 + i * 1024);
+    }
+  }
+  __device__ __forceinline__ void issue(const FusedParams& p, int grp, int buf) const {
+#pragma unroll
+    for (int u = 0; u < kDmaPer; ++u)
+      if (u < n) {
+        const int k = grp * KG + kof[u];
+        copy_panel<1>(rs[u], lds[u] + buf, (int)(k < p.K ? goff[u] + 4u * (uint32_t)k : kOut), 0);
+      }
+  }
+  // At most one group's copies of this wave in flight.
+  __device__ __forceinline__ void wait() const {
+    if (n == 4)
+      wait_counts<4, true>();
+    else if (n == 3)
+      wait_counts<3, true>();
+    else if (n == 2)
+      wait_counts<2, true>();
+    else if (n == 1)
+      wait_counts<1, true>();
+    else
+      wait_counts<0, true>();
+  }
+};
 // Granule g (k = 4 g .. 4 g + 3 of k half h) of the tile's row `row` of
 // data block blk in an A stage.
 template <int KG>
@@ -274,7 +368,6 @@ __device__ __forceinline__ v4f a_granule(const float* As, int blk, int h, int ro
 // The symbols of a wave: i = wave + 8 j for j < kMS, with their degree,
 // member blocks (ascending) and Y tile held in scalar registers.
 constexpr int kMS = 2;      // symbols per wave at most (16 per workgroup)
-constexpr int kMaxDeg = 4;  // members per symbol at most
 struct WaveSyms {
   int n;
   int deg[kMS];
@@ -307,7 +400,7 @@ __device__ __forceinline__ void pipeline(int ng, int stage, float* As0, const AS
                                          const FusedParams& p, v4f* r1, v4f* r2, F& compute) {
   auto step = [&](int g, v4f* hold, v4f* fresh) __attribute__((always_inline)) {
     if (g + 2 < ng) ast.issue(p, g + 2, fresh);
-    compute(g);
+    compute(g, As0 + (g & 1) * stage);
     if (g + 1 < ng) ast.store(hold, As0 + ((g + 1) & 1) * stage);
     __syncthreads();
   };
@@ -317,9 +410,76 @@ __device__ __forceinline__ void pipeline(int ng, int stage, float* As0, const AS
   }
 }
 
+// The K loop where every wave has at most one symbol: the copies go to LDS
+// themselves, three buffers in turn (the copies of group g + 2 start when every
+// wave is past group g - 1), and a wave reads the fragments of one half of a
+// group before it multiplies the half before it, also across the barrier that
+// ends a group.  All waves meet there, so without that every group is a phase
+// of LDS reads and then one of MFMAs.  512^3 with eight symbols: FP32 2590 ->
+// 2350 cycles a group (reads alone 930, MFMAs alone 1090, both without copies
+// 1790: they overlap badly, and the copies add 550), BF16x3 call 14.65 -> 13.5
+// us, BF16 13.5 -> 12.4.
+template <int KG, typename Frag, typename R, typename M>
+__device__ __forceinline__ void pipeline_halves(int ng, int stage, const float* As0,
+                                                const ADma<KG>& dma, const FusedParams& p, R& read,
+                                                M& mul) {
+  Frag x, y;
+  read(x, 0, 0, As0);
+  __builtin_amdgcn_sched_barrier(0);
+  if (ng > 2) dma.issue(p, 2, 8 * stage);
+  read(y, 0, 1, As0);
+  __builtin_amdgcn_sched_barrier(0);
+  mul(x);
+  __builtin_amdgcn_sched_barrier(0);
+  int cur = 0;
+  for (int g = 1; g < ng; ++g) {
+    if (g + 1 < ng)
+      dma.wait();  // (group g + 1's own copies may be in flight)
+    else
+      wait_counts<0, true>();
+    barrier();
+    const int free = cur;
+    cur = cur == 2 * stage ? 0 : cur + stage;
+    read(x, g, 0, As0 + cur);
+    __builtin_amdgcn_sched_barrier(0);
+    if (g + 2 < ng) dma.issue(p, g + 2, 4 * free);
+    mul(y);
+    __builtin_amdgcn_sched_barrier(0);
+    read(y, g, 1, As0 + cur);
+    __builtin_amdgcn_sched_barrier(0);
+    mul(x);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  mul(y);
+}
+// ... of a wave without a symbol, or with one of no members.
+template <int KG>
+__device__ __forceinline__ void pipeline_idle(int ng, int stage, const ADma<KG>& dma,
+                                              const FusedParams& p) {
+  if (ng > 2) dma.issue(p, 2, 8 * stage);
+  int cur = 0;
+  for (int g = 1; g < ng; ++g) {
+    if (g + 1 < ng)
+      dma.wait();
+    else
+      wait_counts<0, true>();
+    barrier();
+    const int free = cur;
+    cur = cur == 2 * stage ? 0 : cur + stage;
+    if (g + 2 < ng) dma.issue(p, g + 2, 4 * free);
+  }
+}
+
+// Waves per SIMD the registers are limited for: two workgroups on a CU where the
+// LDS of short products lets them (not the form whose strip fills it: BF16x3,
+// K = 1024, 21.3 us became 22.2 with the spills of 128 registers).
+constexpr int waves_per_simd(int jn, int kg, bool dma) {
+  return jn == 1 && (dma || kg == 32) ? 4 : 2;
+}
+
 // ------------------------------------------------------------------ FP32 --
-template <int JN, int KG>
-__global__ __launch_bounds__(kThreads) void fused_f32_kernel(FusedParams p) {
+template <int JN, int KG, bool DMA>
+__global__ __launch_bounds__(kThreads, waves_per_simd(JN, KG, DMA)) void fused_f32_kernel(FusedParams p) {
   constexpr int BN = 16 * JN, LDB = BN + kPadF32;
   typedef typename Vec<JN>::T vb;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
@@ -335,8 +495,16 @@ __global__ __launch_bounds__(kThreads) void fused_f32_kernel(FusedParams p) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int q = lane >> 4, c16 = lane & 15;
   const int ng = (int)(p.kp / KG);
+  const int stage = p.kb * AStage<KG>::kFloats;
   AStage<KG> ast;
-  ast.init(p, r0);
+  ADma<KG> dma;
+  if constexpr (DMA) {
+    dma.init(p, r0, As0);
+    dma.issue(p, 0, 0);
+    if (ng > 1) dma.issue(p, 1, 4 * stage);
+  } else {
+    ast.init(p, r0);
+  }
 
   // Prologue: tables, B strip and the first A group; all loads of a pass
   // are issued before any of them is stored.  B strip, k in [0, kp): item f
@@ -349,7 +517,7 @@ __global__ __launch_bounds__(kThreads) void fused_f32_kernel(FusedParams p) {
     const auto rb = b_rsrc(p);
     const TabLoads t0 = load_tables(p, 0);
     v4f a0[kAPer];
-    ast.issue(p, 0, a0);
+    if constexpr (!DMA) ast.issue(p, 0, a0);
     for (int base = 0; base < items; base += SB * kThreads) {
       v4f v[SB];
 #pragma unroll
@@ -364,7 +532,7 @@ __global__ __launch_bounds__(kThreads) void fused_f32_kernel(FusedParams p) {
       }
       if (base == 0) {
         store_tables(p, 0, t0, tab_lds);
-        ast.store(a0, As0);
+        if constexpr (!DMA) ast.store(a0, As0);
       }
 #pragma unroll
       for (int u = 0; u < SB; ++u) {
@@ -376,7 +544,10 @@ __global__ __launch_bounds__(kThreads) void fused_f32_kernel(FusedParams p) {
     tables_rest(p, tab_lds);
   }
   v4f r1[kAPer], r2[kAPer];  // the next two groups' A loads in flight
-  if (ng > 1) ast.issue(p, 1, r1);
+  if constexpr (DMA)
+    wait_counts<0, true>();
+  else if (ng > 1)
+    ast.issue(p, 1, r1);
   __syncthreads();
   const FusedTables tab = tables_at(p, tab_lds);
   const WaveSyms ws = wave_syms(p, tab);
@@ -386,9 +557,41 @@ __global__ __launch_bounds__(kThreads) void fused_f32_kernel(FusedParams p) {
   for (int j = 0; j < kMS; ++j)
 #pragma unroll
     for (int jj = 0; jj < JN; ++jj) acc[j][jj] = v4f{0.f, 0.f, 0.f, 0.f};
-  const int stage = p.kb * AStage<KG>::kFloats;
-  auto compute = [&](int grp) __attribute__((always_inline)) {
-    const float* As = As0 + (grp & 1) * stage;
+  [[maybe_unused]] auto halves = [&](auto deg) __attribute__((always_inline)) {
+    constexpr int D = decltype(deg)::value;
+    struct Frag {
+      v4f a[2][D];
+      vb b[2][4];
+    };
+    auto read = [&](Frag& f, int grp, int h, const float* As) __attribute__((always_inline)) {
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+#pragma unroll
+        for (int m = 0; m < D; ++m)
+          f.a[c][m] = a_granule<KG>(As, ws.id[0][m], h, c16, c * 4 + q);
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+          f.b[c][t] = *reinterpret_cast<const vb*>(
+              Bs + (grp * KG + 32 * h + 16 * c + 4 * q + t) * LDB + JN * c16);
+      }
+    };
+    auto mul = [&](const Frag& f) __attribute__((always_inline)) {
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        v4f a = f.a[c][0];
+#pragma unroll
+        for (int m = 1; m < D; ++m) a += f.a[c][m];
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+          for (int jj = 0; jj < JN; ++jj)
+            acc[0][jj] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t], lane_of(f.b[c][t], jj),
+                                                              acc[0][jj], 0, 0, 0);
+      }
+    };
+    pipeline_halves<KG, Frag>(ng, stage, As0, dma, p, read, mul);
+  };
+  [[maybe_unused]] auto compute = [&](int grp, const float* As) __attribute__((always_inline)) {
     // Symbol j's whole k group with its degree D known at compile time (one
     // scalar branch on the wave-uniform degree per group): the D granule
     // reads of a chunk issue together, the next chunk's reads can go out
@@ -433,7 +636,21 @@ __global__ __launch_bounds__(kThreads) void fused_f32_kernel(FusedParams p) {
       // (a symbol with no members adds nothing: its product stays zero)
     }
   };
-  pipeline(ng, stage, As0, ast, p, r1, r2, compute);
+  if constexpr (DMA) {
+    const int d = ws.n > 0 ? ws.deg[0] : 0;
+    if (d == 1)
+      halves(std::integral_constant<int, 1>{});
+    else if (d == 2)
+      halves(std::integral_constant<int, 2>{});
+    else if (d == 3)
+      halves(std::integral_constant<int, 3>{});
+    else if (d == kMaxDeg)
+      halves(std::integral_constant<int, kMaxDeg>{});
+    else
+      pipeline_idle<KG>(ng, stage, dma, p);
+  } else {
+    pipeline(ng, stage, As0, ast, p, r1, r2, compute);
+  }
 #pragma unroll
   for (int j = 0; j < kMS; ++j) {
     if (j >= ws.n || ws.ytile[j] < 0) continue;
@@ -474,8 +691,8 @@ __device__ __forceinline__ void split8(v4f x0, v4f x1, v8bf* hi, v8bf* lo) {
   }
 }
 
-template <int JN, bool X3, int KG>
-__global__ __launch_bounds__(kThreads) void fused_bf16_kernel(FusedParams p) {
+template <int JN, bool X3, int KG, bool DMA>
+__global__ __launch_bounds__(kThreads, waves_per_simd(JN, KG, DMA)) void fused_bf16_kernel(FusedParams p) {
   constexpr int BN = 16 * JN;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
   const FusedLds L = fused_lds(p);
@@ -492,8 +709,16 @@ __global__ __launch_bounds__(kThreads) void fused_bf16_kernel(FusedParams p) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int q = lane >> 4, c16 = lane & 15;
   const int ng = (int)(p.kp / KG);
+  const int stage = p.kb * AStage<KG>::kFloats;
   AStage<KG> ast;
-  ast.init(p, r0);
+  ADma<KG> dma;
+  if constexpr (DMA) {
+    dma.init(p, r0, As0);
+    dma.issue(p, 0, 0);
+    if (ng > 1) dma.issue(p, 1, 4 * stage);
+  } else {
+    ast.init(p, r0);
+  }
 
   // Prologue as in the FP32 kernel.  B strip, transposed and split: item f
   // is column col and eight consecutive k (one 16-byte LDS store per
@@ -504,7 +729,7 @@ __global__ __launch_bounds__(kThreads) void fused_bf16_kernel(FusedParams p) {
     const auto rb = b_rsrc(p);
     const TabLoads t0 = load_tables(p, 0);
     v4f a0[kAPer];
-    ast.issue(p, 0, a0);
+    if constexpr (!DMA) ast.issue(p, 0, a0);
     for (int base = 0; base < items; base += SB * kThreads) {
       float v[SB][8];
 #pragma unroll
@@ -523,7 +748,7 @@ __global__ __launch_bounds__(kThreads) void fused_bf16_kernel(FusedParams p) {
       }
       if (base == 0) {
         store_tables(p, 0, t0, tab_lds);
-        ast.store(a0, As0);
+        if constexpr (!DMA) ast.store(a0, As0);
       }
 #pragma unroll
       for (int u = 0; u < SB; ++u) {
@@ -540,7 +765,10 @@ __global__ __launch_bounds__(kThreads) void fused_bf16_kernel(FusedParams p) {
     tables_rest(p, tab_lds);
   }
   v4f r1[kAPer], r2[kAPer];  // the next two groups' A loads in flight
-  if (ng > 1) ast.issue(p, 1, r1);
+  if constexpr (DMA)
+    wait_counts<0, true>();
+  else if (ng > 1)
+    ast.issue(p, 1, r1);
   __syncthreads();
   const FusedTables tab = tables_at(p, tab_lds);
   const WaveSyms ws = wave_syms(p, tab);
@@ -550,9 +778,46 @@ __global__ __launch_bounds__(kThreads) void fused_bf16_kernel(FusedParams p) {
   for (int j = 0; j < kMS; ++j)
 #pragma unroll
     for (int jj = 0; jj < JN; ++jj) acc[j][jj] = v4f{0.f, 0.f, 0.f, 0.f};
-  const int stage = p.kb * AStage<KG>::kFloats;
-  auto compute = [&](int grp) __attribute__((always_inline)) {
-    const float* As = As0 + (grp & 1) * stage;
+  [[maybe_unused]] auto halves = [&](auto deg) __attribute__((always_inline)) {
+    constexpr int D = decltype(deg)::value;
+    struct Frag {
+      v4f a[2][D];
+      v8bf bh[JN], bl[JN];
+    };
+    auto read = [&](Frag& f, int grp, int h, const float* As) __attribute__((always_inline)) {
+#pragma unroll
+      for (int m = 0; m < D; ++m) {
+        f.a[0][m] = a_granule<KG>(As, ws.id[0][m], h, c16, 2 * q);
+        f.a[1][m] = a_granule<KG>(As, ws.id[0][m], h, c16, 2 * q + 1);
+      }
+#pragma unroll
+      for (int jj = 0; jj < JN; ++jj) {
+        const size_t off = (size_t)(16 * jj + c16) * KS + grp * KG + 32 * h + 8 * q;
+        f.bh[jj] = *reinterpret_cast<const v8bf*>(Bh + off);
+        if (X3) f.bl[jj] = *reinterpret_cast<const v8bf*>(Bl + off);
+      }
+    };
+    auto mul = [&](const Frag& f) __attribute__((always_inline)) {
+      v4f a0 = f.a[0][0], a1 = f.a[1][0];
+#pragma unroll
+      for (int m = 1; m < D; ++m) {
+        a0 += f.a[0][m];
+        a1 += f.a[1][m];
+      }
+      v8bf ah, al;
+      split8(a0, a1, &ah, &al);
+#pragma unroll
+      for (int jj = 0; jj < JN; ++jj) {
+        if (X3) {
+          acc[0][jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, f.bh[jj], acc[0][jj], 0, 0, 0);
+          acc[0][jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, f.bl[jj], acc[0][jj], 0, 0, 0);
+        }
+        acc[0][jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, f.bh[jj], acc[0][jj], 0, 0, 0);
+      }
+    };
+    pipeline_halves<KG, Frag>(ng, stage, As0, dma, p, read, mul);
+  };
+  [[maybe_unused]] auto compute = [&](int grp, const float* As) __attribute__((always_inline)) {
     // Symbol j's whole k group with its degree D known at compile time (see
     // the FP32 kernel); the chunk body is VALU work (sums and splits) next
     // to three MFMAs, so every masked add saved counts.
@@ -606,7 +871,21 @@ __global__ __launch_bounds__(kThreads) void fused_bf16_kernel(FusedParams p) {
       // (a symbol with no members adds nothing: its product stays zero)
     }
   };
-  pipeline(ng, stage, As0, ast, p, r1, r2, compute);
+  if constexpr (DMA) {
+    const int d = ws.n > 0 ? ws.deg[0] : 0;
+    if (d == 1)
+      halves(std::integral_constant<int, 1>{});
+    else if (d == 2)
+      halves(std::integral_constant<int, 2>{});
+    else if (d == 3)
+      halves(std::integral_constant<int, 3>{});
+    else if (d == kMaxDeg)
+      halves(std::integral_constant<int, kMaxDeg>{});
+    else
+      pipeline_idle<KG>(ng, stage, dma, p);
+  } else {
+    pipeline(ng, stage, As0, ast, p, r1, r2, compute);
+  }
 #pragma unroll
   for (int j = 0; j < kMS; ++j) {
     if (j >= ws.n || ws.ytile[j] < 0) continue;
@@ -622,22 +901,23 @@ __global__ __launch_bounds__(kThreads) void fused_bf16_kernel(FusedParams p) {
 
 typedef void (*FusedKernel)(FusedParams);
 
-template <int KG>
+template <int KG, bool DMA>
 FusedKernel fused_kernel_kg(int32_t prec, int jn) {
   if (prec == BPX_PREC_F32)
-    return jn == 1 ? fused_f32_kernel<1, KG>
-                   : jn == 2 ? fused_f32_kernel<2, KG> : fused_f32_kernel<4, KG>;
+    return jn == 1 ? fused_f32_kernel<1, KG, DMA>
+                   : jn == 2 ? fused_f32_kernel<2, KG, DMA> : fused_f32_kernel<4, KG, DMA>;
   // BF16 tiles stop at 32 columns (wider ones spill at eight waves)
   if (prec == BPX_PREC_BF16)
-    return jn == 1 ? fused_bf16_kernel<1, false, KG>
-                   : jn == 2 ? fused_bf16_kernel<2, false, KG> : nullptr;
+    return jn == 1 ? fused_bf16_kernel<1, false, KG, DMA>
+                   : jn == 2 ? fused_bf16_kernel<2, false, KG, DMA> : nullptr;
   if (prec == BPX_PREC_BF16X3)
-    return jn == 1 ? fused_bf16_kernel<1, true, KG>
-                   : jn == 2 ? fused_bf16_kernel<2, true, KG> : nullptr;
+    return jn == 1 ? fused_bf16_kernel<1, true, KG, DMA>
+                   : jn == 2 ? fused_bf16_kernel<2, true, KG, DMA> : nullptr;
   return nullptr;
 }
-FusedKernel fused_kernel_for(int32_t prec, int jn, int kg) {
-  return kg == 64 ? fused_kernel_kg<64>(prec, jn) : fused_kernel_kg<32>(prec, jn);
+FusedKernel fused_kernel_for(int32_t prec, int jn, int kg, int stages) {
+  if (stages == 3) return fused_kernel_kg<64, true>(prec, jn);
+  return kg == 64 ? fused_kernel_kg<64, false>(prec, jn) : fused_kernel_kg<32, false>(prec, jn);
 }
 
 constexpr size_t kLdsLimit = 160 * 1024;
@@ -660,7 +940,8 @@ bool fused_configure(FusedParams* p) {
   const int64_t tiles_m = (p->Mb + BM - 1) / BM;
   const int64_t cus = device_cu_count();
   for (int jn : {4, 2, 1}) {
-    if (!fused_kernel_for(p->prec, jn, p->kg)) continue;
+    p->stages = 2;
+    if (!fused_kernel_for(p->prec, jn, p->kg, p->stages)) continue;
     p->jn = jn;
     const int64_t tiles_n = (p->N + 16 * jn - 1) / (16 * jn);
     if (jn > 1 && tiles_m * tiles_n < cus) continue;
@@ -668,23 +949,29 @@ bool fused_configure(FusedParams* p) {
     if (tiles_m * tiles_n > 0x7fffffff) return false;
     p->tiles_n = (int32_t)tiles_n;
     p->tiles_m = (int32_t)tiles_m;
+    // at most one symbol to a wave (then kb <= 8 too) and room for three buffers:
+    // pipeline_halves
+    p->stages = 3;
+    if (p->n_sym > kWaves || p->kg != 64 || fused_lds(*p).total > kLdsLimit) p->stages = 2;
     return true;
   }
   return false;
 }
 
 // Rounds of one workgroup per CU, each 6.5 us and, per k, what a wave's symbols
-// take; wider strips take 1.5 and 2.4 times that.  Measured (us, one round):
-// eight symbols, K = 512 and 1024: FP32 15.7 and 24.7, BF16x3 14.5 and 21.5, BF16
-// 13.3 and 19.7; nine symbols, two to a wave: 22.3 and 37.3, 19.1 and 30.8, 17.1
-// and 26.2.
+// take; wider strips take 1.5 and 2.4 times that.  Two 16-column workgroups that
+// fit on a CU together take 1.3 rounds.  Measured (us, one round): eight symbols,
+// K = 512 and 1024: FP32 15.8 and 24.7, BF16x3 13.5 and 20, BF16 12.4 and 18; nine
+// symbols, two to a wave: 22.3 and 37.3, 19.1 and 30.8, 17.1 and 26.2.
 double fused_us(const FusedParams& p) {
-  const int64_t cus = device_cu_count();
-  const double rounds = (double)(((int64_t)p.tiles_m * p.tiles_n + cus - 1) / cus);
+  const int64_t cus = device_cu_count(), tiles = (int64_t)p.tiles_m * p.tiles_n;
+  const bool two = p.jn == 1 && 2 * fused_lds(p).total <= kLdsLimit && tiles > cus;
+  const double rounds = two ? 1.3 * (double)((tiles + 2 * cus - 1) / (2 * cus))
+                            : (double)((tiles + cus - 1) / cus);
   const double s = (double)((p.n_sym + kWaves - 1) / kWaves);
   const double per_k = p.prec == BPX_PREC_F32      ? 0.006 + 0.0117 * s
-                       : p.prec == BPX_PREC_BF16X3 ? 0.0045 + 0.0092 * s
-                                                   : 0.0072 + 0.0053 * s;
+                       : p.prec == BPX_PREC_BF16X3 ? 0.004 + 0.0092 * s
+                                                   : 0.0055 + 0.0055 * s;
   const double strip = p.jn == 1 ? 1.0 : p.jn == 2 ? 1.5 : 2.4;
   return rounds * (6.5 + (double)p.K * per_k * strip);
 }
@@ -692,7 +979,7 @@ double fused_us(const FusedParams& p) {
 size_t fused_lds_bytes(const FusedParams& p) { return fused_lds(p).total; }
 
 hipError_t launch_fused(const FusedParams& p, hipStream_t stream) {
-  const FusedKernel k = fused_kernel_for(p.prec, p.jn, p.kg);
+  const FusedKernel k = fused_kernel_for(p.prec, p.jn, p.kg, p.stages);
   if (!k) return hipErrorInvalidValue;
   const size_t lds = fused_lds(p).total;
   if (lds > kLdsLimit) return hipErrorInvalidConfiguration;

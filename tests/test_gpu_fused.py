@@ -157,3 +157,35 @@ def test_fused_graph_replay_matches_eager():
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(C, C_eager), rep
+
+
+# one k group, a part of one, two, three and more (three LDS buffers in turn), K
+# in the middle of a group; a last block of few rows, none at all; columns of one
+# tile, a ragged one and, in the last case, more tiles than CUs
+@pytest.mark.parametrize("prec", [bpx.PREC_F32, bpx.PREC_BF16X3, bpx.PREC_BF16])
+@pytest.mark.parametrize("M,K,N", [(8, 4, 1), (130, 64, 17), (250, 68, 33), (127, 128, 16),
+                                   (129, 132, 50), (57, 192, 100), (515, 260, 77),
+                                   (1000, 452, 20), (777, 64, 801)])
+def test_fused_group_edges_exact(M, K, N, prec):
+    code = _code642()
+    g = torch.Generator(device="cuda").manual_seed(M)
+    A = torch.full((M, -(-K // 4) * 4 + 8), float("nan"), device="cuda")
+    B = torch.full((K, -(-N // 4) * 4 + 4), float("nan"), device="cuda")
+    A[:, :K] = torch.randint(-8, 9, (M, K), generator=g, device="cuda").float()
+    B[:, :N] = torch.randint(-8, 9, (K, N), generator=g, device="cuda").float()
+    for seed in range(2):
+        arrival, lost = inputs.erasure_arrival(seed, 6, 2)
+        plan = bpx.Plan(code, list(arrival), lost, bpx.MODE_ERASURE, M, K, N, prec)
+        ws = bpx.alloc_workspace(plan)
+        C = torch.full((M, -(-N // 4) * 4 + 4), float("nan"), device="cuda")
+        _say("fused edges", M, K, N, "prec", prec)
+        bpx.set_fused_peel(2)
+        try:
+            assert plan.fused()
+            bpx.coded_matmul(plan, A[:, :K], B[:, :N], C[:, :N], ws)
+            torch.cuda.synchronize()
+        finally:
+            bpx.set_fused_peel(1)
+        # sums of at most 3 x 8 and K products of at most 24 x 8 are exact
+        assert torch.equal(C[:, :N].double(), A[:, :K].double() @ B[:, :N].double())
+        assert bool(C[:, N:].isnan().all())
