@@ -61,8 +61,9 @@ def parse():
 
 
 def packed_operands(gemm_flops, tile):
-    """Whether the library multiplies this product on packed operands (more
-    than 2^31 multiply-adds, no forced tile)."""
+    """Whether the library multiplies this workload's product on packed operands:
+    those of more than 2^31 multiply-adds, no tile forced (the 512^3 ones take
+    the fused form)."""
     return tile < 0 and gemm_flops > 2 ** 32
 
 

@@ -20,8 +20,8 @@
 // Layout of a workgroup (8 waves): the B column strip B[0:K, n0:n0+BN] is
 // staged in LDS once (FP32: row-major k x BN; BF16: transposed per column,
 // k contiguous, split into hi / lo planes); the tile's 16 rows of every
-// data block pass through LDS one k group at a time (double-buffered, the
-// next groups' loads in flight), and wave w computes the computed symbols
+// data block pass through LDS one k group at a time (double- or triple-buffered,
+// the next groups' loads in flight), and wave w computes the computed symbols
 // w, w+8, ... from them, summing each symbol's members in FP32 registers
 // (BF16: then splitting the sum into hi / lo); releasers' tiles are stored
 // to LDS; after one barrier every thread peels its own elements.

@@ -1,5 +1,6 @@
-// Coded products on operands split into BF16 planes beforehand: FP32,
-// BF16x3 and BF16 plans past the fused form's size.
+// Coded products on operands split into BF16 planes beforehand: FP32, BF16x3
+// and BF16 products that are large enough (bpx_plan::has_planes) and not faster in
+// the fused form.
 //
 // One streaming pass packs the coded blocks (the encode: members summed in
 // FP32, ascending) and B as BF16 planes, x = h + m + l with every plane
