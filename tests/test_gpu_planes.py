@@ -396,3 +396,41 @@ def test_small_products_on_planes(code, mode, shape, prec):
         new, old = _run(plan, A, B), _run(plan, A, B, tile=1)
         assert torch.equal(torch.isfinite(new), torch.isfinite(old))
         assert torch.equal(torch.isnan(new), torch.isnan(old))
+
+
+# The library's own scratch (which holds the first plan's packed operands, not
+# the second's: that one reads A and B directly) and a captured graph, replayed
+# with other work in between; the last one sends a panel to the FP32 kernels
+@pytest.mark.parametrize("prec", PRECS)
+@pytest.mark.parametrize("M,K,N,fits", [(419, 1028, 373, True), (2100, 2052, 1100, False)])
+def test_planes_in_scratch_and_in_a_graph(M, K, N, fits, prec):
+    arrival, _ = inputs.shifted_exp_arrival(0, inputs.CODE_1284.n)
+    plan = bpx.Plan(_code(inputs.CODE_1284), arrival, 0, bpx.MODE_STRAGGLER, M, K, N, prec)
+    print("scratch and graph", M, K, N, prec, file=sys.stderr, flush=True)
+    assert (plan.workspace_bytes()[0] <= 32 << 20) == fits
+    plan.upload()
+    A, B = _ops(11, M, K, N, False)
+    A, B = _view(A, 0), _view(B, 0)
+    want = _run(plan, A, B)
+    C = _view(torch.full((M, N), float("nan"), device="cuda"), 0)
+    bpx.coded_matmul_noalloc(plan, A, B, C)
+    torch.cuda.synchronize()
+    R = A.double() @ B.double()
+    assert torch.equal(C, want) if fits else _err(C, R) <= _err(want, R) * 4 + 1e-6
+    ws = bpx.alloc_workspace(plan)
+    g, s = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        with torch.cuda.graph(g, stream=s):
+            bpx.coded_matmul(plan, A, B, C, ws)
+    torch.cuda.current_stream().wait_stream(s)
+    for rep in range(4):
+        if rep == 3:
+            A[M - 1, 1] = float("inf")
+            want = _run(plan, A, B)
+        C.fill_(float("nan"))
+        ws.fill_(0xA5)
+        torch.matmul(A, B)
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(torch.nan_to_num(C), torch.nan_to_num(want)), rep
