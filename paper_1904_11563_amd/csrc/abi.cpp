@@ -189,6 +189,12 @@ bpx_status check_workspace(const bpx_plan* plan, const void* ws, size_t ws_bytes
     return fail(BPX_E_INVALID, "workspace missing, not 256-byte aligned or too small");
   return BPX_OK;
 }
+// What of a caller's workspace the packed operands may use.  A plan without Y
+// slots and partial tiles needs no workspace, so that a call with none, or with
+// one that is not aligned, is accepted and reads A and B directly.
+size_t usable_workspace(const void* ws, size_t ws_bytes) {
+  return ws && ((uintptr_t)ws & 255u) == 0 ? ws_bytes : 0;
+}
 
 // A plan's products on split planes, without the workspace's parts.
 void plane_params(const bpx_plan* plan, const GemmParams& p, PlaneParams* out) {
@@ -378,7 +384,7 @@ bpx_status gemm_impl(bpx_plan* plan, const float* A, int64_t lda, const float* B
     if (Np / 128 > 65535 || Kp / 128 > 65535 || Mbp / 128 > 65535 || p.n_sym > 65535)
       return fail(BPX_E_UNSUPPORTED, "FP8 grid too large");
   }
-  if (on_planes(plan, lda, ldb, ws_bytes))
+  if (on_planes(plan, lda, ldb, usable_workspace(ws, ws_bytes)))
     return gemm_planes_impl(plan, p, ws, stream);
   const int32_t tile = choose_tile(plan->prec, plan->Mb, plan->N, plan->K);
   hipError_t e;
@@ -1134,7 +1140,7 @@ bpx_status bpx_coded_matmul(bpx_plan* plan, const float* A, int64_t lda, const f
   if (st != BPX_OK) return st;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   FusedParams f;
-  if (fused_params(plan, A, lda, B, ldb, C, ldc, ws ? ws_bytes : 0, &f)) {
+  if (fused_params(plan, A, lda, B, ldb, C, ldc, usable_workspace(ws, ws_bytes), &f)) {
     // same argument contract as the two-launch form (the caller cannot
     // tell which form runs), though the fused launch leaves ws untouched
     if ((st = check_matrix(A, lda, plan->K, "A")) != BPX_OK) return st;
