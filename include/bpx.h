@@ -68,9 +68,15 @@ typedef enum {
 } bpx_code_kind;
 
 typedef enum {
-  BPX_PREC_F32 = 0,    /* FP32 operands and accuracy: FP32 MFMA, or for large
-                          products operands split exactly into three BF16
-                          planes (six MFMA products, FP32 accumulation)      */
+  BPX_PREC_F32 = 0,    /* FP32 operands: FP32 MFMA, or for large products
+                          operands split exactly into three BF16 planes, six
+                          MFMA products, FP32 accumulation.  Sums of many
+                          products of like size are then nearer to the exact
+                          ones than FP32 MFMA's (fewer roundings); an output of
+                          a single product is within 3.05 2^-24 of it, one and
+                          a half units in the last place, where FP32 MFMA is
+                          within half a unit (bpx_force_tile names FP32 MFMA
+                          kernels)                                           */
   BPX_PREC_BF16 = 1,   /* operands rounded to BF16 (RNE), one MFMA pass       */
   BPX_PREC_BF16X3 = 2, /* split BF16: hi.hi + hi.lo + lo.hi, FP32 accumulate  */
   BPX_PREC_FP8 = 3,    /* e4m3, one power-of-two scale per 128x128 block      */

@@ -9,14 +9,20 @@
 //   BF16:   h.h
 //   BF16x3: l.h + h.l + h.h          (two planes)
 //   FP32:   m.m + h.m + m.h + h.l + l.h + h.h   (three planes)
-// Three BF16 planes hold an FP32 value exactly (3 x 8 bits), the products of
-// planes are exact in FP32, and what FP32 leaves out (m.l, l.m, l.l) is below
-// 2^-26 of a product, under the rounding of one FP32 addition.  A k step of
-// 16 rounds the accumulator 6 times where the FP32 matrix instruction rounds
-// it for every 4 k, so the error against float64 is the smaller one: N(0,1),
-// K = 8192: 1.4e-6 against 1.6e-6; the 8192 x 8192 x 4096 coded product of
-// the (12,8,4) code 5.2e-6 against 6.2e-6.  BF16 MFMAs run 16 times the FP32
-// rate, so six of them still are 2.7 times faster.
+// Three BF16 planes hold an FP32 value exactly (3 x 8 bits) and the products of
+// planes are exact in FP32.  Left out are m.l, l.m and l.l: |m| <= 2^-8 and |l|
+// <= 2^-17 of a value's power of two, so up to 2^-24 of a product, and the MFMA
+// cuts its accumulator at the last place of a larger product before it adds the
+// two.  A product on its own (one nonzero per row of A) so comes out within 3.0
+// times 2^-24 of it, one and a half units in the last place, where the FP32
+// matrix instruction is within half a unit, 1.0 times 2^-24 (in the Frobenius
+// norm 3.1e-8 against 2.5e-8, 4.0e-8 for the mantissas that lose most).  In sums
+// of many products the roundings of the accumulator count for more: a k step of
+// 16 rounds it 6 times where the FP32 instruction rounds it for every 4 k,
+// so the error against float64 is the smaller one: N(0,1), K = 8192: 1.4e-6
+// against 1.6e-6; the 8192 x 8192 x 4096 coded product of the (12,8,4) code
+// 5.2e-6 against 6.2e-6.  BF16 MFMAs run 16 times the FP32 rate, so six of them
+// still are 2.7 times faster.
 //
 // The splitting needs the planes' exponents to stay in range, so a value
 // that is not zero and outside [2^-100, 2^63), infinities and NaN included,
