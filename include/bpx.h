@@ -293,9 +293,11 @@ bpx_status bpx_encode(bpx_plan* plan, const float* A, int64_t lda, float* coded_
  * the encode is fused into the A-operand load (the coded block is never
  * stored), or, past 2^24 multiply-adds over the computed symbols (FP32: if K >
  * 192, else 2^31) where the fused form of bpx_coded_matmul is not the faster
- * one, into a pass that packs the coded blocks and B as BF16 planes (FP32 values
- * three planes cannot hold, infinities and NaN among them, send their tiles
- * to the FP32 kernels, so results for them are those of FP32 arithmetic).
+ * one, into a pass that packs the coded blocks and B as BF16 planes.  Three planes hold
+ * every FP32 magnitude from the smallest subnormal number up to 2^40 at K = 8192
+ * (a factor of 2 less per factor of 4 in K); larger ones, infinities and NaN send
+ * the 256 coded rows or columns of B around them to the FP32 kernels, so results
+ * for them are those of FP32 arithmetic, and such a call is slower.
  * FP8*: a streaming encode+quantise pass writes the e4m3 codes of every 128 x
  * 128 coded tile (its scale needs the tile's amax), B is quantised once per
  * call, then the block-scaled FP8 product runs (for more than 2^31

@@ -220,6 +220,7 @@ void plane_params(const bpx_plan* plan, const GemmParams& p, PlaneParams* out) {
   q.cols64 = (int32_t)(plan->plane_cols() / 64);
   q.grid = plan->grid;
   q.Nb = plan->Nb;
+  q.max_bits = plane_max_bits((double)plan->K * (double)plan->max_passes());
   if (plan->grid > 1) {
     q.a_ops = plan->d_ops;
     q.b_ops = q.a_ops + plan->ops.a_ops.size();

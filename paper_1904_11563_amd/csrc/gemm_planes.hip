@@ -24,11 +24,15 @@
 // 5.2e-6 against 6.2e-6.  BF16 MFMAs run 16 times the FP32 rate, so six of them
 // still are 2.7 times faster.
 //
-// The splitting needs the planes' exponents to stay in range, so a value
-// that is not zero and outside [2^-100, 2^63), infinities and NaN included,
-// flags its pack block: the GEMM skips the 256-wide row or column panel, and
-// an FP32 launch (gemm_f32.hip) computes it, which also keeps the results for
-// infinities and NaN those of FP32 arithmetic.
+// Range: BF16 has FP32's exponents, and the conversions and MFMAs keep subnormal
+// values (checked lane by lane against float64), but l's last bit lies 23 bits
+// below x's first.  Packed times 2^16 even the last bit of a subnormal x, 2^-149,
+// is a BF16 value, so no value is too small; sums are stored times 2^-32, exact
+// down to subnormal results.  Upwards the scale costs range: a value whose scaled
+// products could overflow a sum over K (PlaneParams::max_bits: 2^40 at K = 8192),
+// infinities and NaN included, flags its pack block: the GEMM skips the 256-wide
+// row or column panel, and an FP32 launch (gemm_f32.hip) computes it, which also
+// keeps the results for infinities and NaN those of FP32 arithmetic.
 //
 // The two-dimensional form packs the distinct sums of A row blocks and of B
 // column blocks once each, and a tile runs over all passes of its symbol, the
@@ -78,16 +82,16 @@ __device__ __forceinline__ Granule<P> split8(const float (&x)[8]) {
     }
   return g;
 }
-// Whether a value is not zero and outside what three planes represent.
-__device__ __forceinline__ bool out_of_range(const float (&x)[8]) {
-  unsigned hi = 0, lo = 0xffffffffu;
+// FP32: scales the values and returns whether one is too large to be split.
+__device__ __forceinline__ bool scale_up(float (&x)[8], unsigned max_bits) {
+  unsigned hi = 0;
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     const unsigned a = __builtin_bit_cast(unsigned, x[e]) & 0x7fffffffu;
     hi = a > hi ? a : hi;
-    lo = a - 1u < lo ? a - 1u : lo;  // zero wraps to the largest value
+    x[e] *= kPlaneUp;
   }
-  return hi >= kPlaneMaxBits || lo < kPlaneMinBits - 1u;
+  return hi >= max_bits;
 }
 
 // 32 stacked coded rows x 256 k.  Bound by HBM: the members are read once
@@ -142,7 +146,7 @@ __device__ __forceinline__ void pack_a_block(const PlaneParams& p, int b, int ti
       float x[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) x[e] = s[i][e >> 2][e & 3];
-      if (P == 3) bad = bad || out_of_range(x);
+      if (P == 3) bad |= scale_up(x, p.max_bits);
       const Granule<P> g = split8<P>(x);
       us* dst = p.ap + (((int64_t)rp * p.kc + (k >> 4)) * P * 64 + ((k >> 3) & 1) * 32 + r) * 8;
 #pragma unroll
@@ -195,7 +199,7 @@ __device__ __forceinline__ void pack_b_block(const PlaneParams& p, int b, int ti
       float x[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) x[e] = src[e * 64];
-      if (P == 3) bad = bad || out_of_range(x);
+      if (P == 3) bad |= scale_up(x, p.max_bits);
       const Granule<P> g = split8<P>(x);
       us* dst = p.bp + ((((int64_t)nb * 2 + h) * p.kc + kc) * P * 64 + lane) * 8;
 #pragma unroll
@@ -573,7 +577,7 @@ __global__ __launch_bounds__(2 * S, 2) void gemm_planes_kernel(PlaneParams p) {
     store_part<T::MI, T::WN>(acc, p.part + (int64_t)piece * (S * S), wave, lane);
     return;
   }
-  store_tile<T::MI, T::WN>(acc, rows, (int64_t)nt * S, p.Nb, wave, lane);
+  store_tile<T::MI, T::WN, P == 3>(acc, rows, (int64_t)nt * S, p.Nb, wave, lane);
 }
 
 // Grouped form, persistent: workgroup w multiplies tiles tiles[wstart[w]] ..
@@ -654,6 +658,7 @@ __global__ __launch_bounds__(256) void planes_reduce_kernel(PlaneParams p) {
   v4f sum = *reinterpret_cast<const v4f*>(src);
   for (int k = 1; k < p.split; ++k)
     sum += *reinterpret_cast<const v4f*>(src + (int64_t)k * (S * S));
+  sum *= p.planes == 3 ? kPlaneDown : 1.f;
 #pragma unroll
   for (int c = 0; c < 4; ++c)
     if (n + c < p.Nb) out[n + c] = sum[c];

@@ -199,6 +199,12 @@ struct bpx_plan {
   int64_t n_products() const {
     return grid > 1 ? (int64_t)ops.passes.size() / 2 : (int64_t)computed.size();
   }
+  // ... and at most one symbol (summed without rounding to FP32 in between).
+  int32_t max_passes() const {
+    int32_t n = 1;
+    for (size_t i = 1; i < ops.sym_passes.size(); i += 2) n = std::max(n, ops.sym_passes[i]);
+    return n;
+  }
   double n_macs() const { return (double)n_products() * (double)Mb * (double)K * (double)Nb; }
   int64_t plane_tiles() const {
     return grid > 1 ? (int64_t)computed.size() * (r256(Mb) / 256) * (r256(Nb) / 256)

@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 
 #include "host.hpp"
@@ -139,10 +140,20 @@ hipError_t launch_coded_gemm_2d(const GemmParams& p, int32_t tile, hipStream_t s
 
 // ---------------------------------------------------------- split planes --
 // Products whose operands are split into BF16 planes beforehand (see
-// gemm_planes.hip).  An FP32 value outside [2^-100, 2^63) that is not zero
-// (infinities and NaN among them) is not split: the FP32 kernels compute the
-// tiles it belongs to.
-constexpr unsigned kPlaneMaxBits = (127u + 63u) << 23, kPlaneMinBits = (127u - 100u) << 23;
+// gemm_planes.hip).  FP32 operands are packed times 2^kPlaneScale, which the
+// stores take back: the last bit of any FP32 value, 2^-149, is then the smallest
+// BF16 value, so three planes hold everything down to zero.  A magnitude from
+// PlaneParams::max_bits up (infinities and NaN among them) is not split: the
+// FP32 kernels compute the tiles it belongs to.
+constexpr int kPlaneScale = 16;
+constexpr float kPlaneUp = 1 << kPlaneScale, kPlaneDown = 1.f / (kPlaneUp * kPlaneUp);
+// The bits of the largest power of two whose scaled products cannot overflow a
+// sum of n of them: 2^40 for n = 8192, 2^47 for one.
+inline unsigned plane_max_bits(double n) {
+  int lg = 0;
+  while (lg < 100 && (double)(1ull << std::min(lg, 62)) < n) ++lg;
+  return (unsigned)(127 + (126 - lg) / 2 - kPlaneScale) << 23;
+}
 struct PlaneParams {
   const float* A;
   int64_t lda;
@@ -160,6 +171,7 @@ struct PlaneParams {
   unsigned short* bp;  // packed planes of B's columns
   unsigned* fa;        // planes == 3: per pack block, 1 if it holds a value
   unsigned* fb;        //   that is not split
+  unsigned max_bits;   // planes == 3: bits of the smallest magnitude not split
   float* part;         // partial 256 x 256 tiles of the last round
   int32_t part_tiles;  // how many part holds
   int32_t kc;          // 16-wide k chunks of the packed operands (FP8: 64-wide)

@@ -130,10 +130,12 @@ template <int MI>
 using Acc = v16f[MI][2];
 
 // Writes an accumulated tile to its output rows: lane l holds column l % 32,
-// rows 8 (e / 4) + 4 (l / 32) + e % 4 of each 32 x 32.
-template <int MI, int WN>
+// rows 8 (e / 4) + 4 (l / 32) + e % 4 of each 32 x 32.  SCALED: the sums of
+// operands packed times kPlaneUp.
+template <int MI, int WN, bool SCALED = false>
 __device__ __forceinline__ void store_tile(const Acc<MI>& acc, float* const* rows, int64_t n_tile,
                                            int64_t Nb, int wave, int lane) {
+  constexpr float f = SCALED ? kPlaneDown : 1.f;
   const int64_t n0 = n_tile + wave % WN * 64 + (lane & 31);
   const bool in0 = n0 < Nb, in1 = n0 + 32 < Nb;
 #pragma unroll
@@ -146,8 +148,8 @@ __device__ __forceinline__ void store_tile(const Acc<MI>& acc, float* const* row
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
       gfloat* o = (gfloat*)out[e] + n0;
-      if (out[e] && in0) o[0] = acc[i][0][e];
-      if (out[e] && in1) o[32] = acc[i][1][e];
+      if (out[e] && in0) o[0] = acc[i][0][e] * f;
+      if (out[e] && in1) o[32] = acc[i][1][e] * f;
     }
   }
 }
