@@ -312,6 +312,7 @@ bpx_status gemm_planes_impl(bpx_plan* plan, GemmParams p, void* ws, hipStream_t 
   q.bp = reinterpret_cast<unsigned short*>(w + off[1]);
   q.fa = reinterpret_cast<unsigned*>(w + off[2]);
   q.fb = reinterpret_cast<unsigned*>(w + off[3]);
+  q.ft = q.fb + (size_t)q.cols64 * ((q.kc + 3) / 4);
   q.part = reinterpret_cast<float*>(w + off[4]);
   q.part_tiles = plan->plane_part_tiles();
   if (plan->is_fp8()) {
@@ -325,14 +326,12 @@ bpx_status gemm_planes_impl(bpx_plan* plan, GemmParams p, void* ws, hipStream_t 
   std::vector<int32_t> passes;
   for (size_t i = 1; i < plan->ops.sym_passes.size(); i += 2)
     passes.push_back(plan->ops.sym_passes[i]);
-  if (e == hipSuccess) e = launch_gemm_planes(q, passes.data(), stream);
+  if (e == hipSuccess) e = launch_gemm_planes(&q, passes.data(), stream);
   if (e == hipSuccess && q.planes == 3) {
-    p.fa = q.fa;
-    p.fb = q.fb;
-    p.nka = (q.kc + 15) / 16;
-    p.nkb = (q.kc + 3) / 4;
-    p.sym_passes = q.sym_passes;
-    p.passes = q.passes;
+    p.left = q.ft;
+    p.left_edge = q.tile;
+    p.left_m = q.tiles_m;
+    p.left_n = q.tiles_n;
     const int32_t tile = choose_tile(plan->prec, plan->Mb, plan->N, plan->K);
     e = plan->grid > 1 ? launch_coded_gemm_2d(p, tile, stream) : launch_coded_gemm(p, tile, stream);
   }

@@ -51,21 +51,10 @@ __device__ __forceinline__ v4f bload(__amdgpu_buffer_rsrc_t r, uint32_t voff) {
   return __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, 0, 0));
 }
 
-// Whether the tile at (m0, n0) of symbol si belongs to a 256 x 256 tile that
-// the split planes leave to this kernel: a pack block of an operand panel of
-// one of its passes is flagged.  Every thread of the workgroup calls it.
+// Whether the tile at (m0, n0) of symbol si belongs to a tile that the split
+// planes leave to this kernel.
 __device__ __forceinline__ bool left_out(const GemmParams& p, int si, int64_t m0, int64_t n0) {
-  const int64_t pa = (p.Mb + 255) / 256, pb = (p.Nb + 255) / 256;  // panels per op
-  const int np = p.sym_passes[2 * si + 1];
-  const int32_t* ps = p.passes + 2 * p.sym_passes[2 * si];
-  unsigned any = 0;
-  for (int i = 0; i < np; ++i) {
-    const unsigned* fa = p.fa + (ps[2 * i] * pa + m0 / 256) * 8 * p.nka;
-    const unsigned* fb = p.fb + (ps[2 * i + 1] * pb + n0 / 256) * 4 * p.nkb;
-    for (int t = threadIdx.x; t < 8 * p.nka; t += blockDim.x) any |= fa[t];
-    for (int t = threadIdx.x; t < 4 * p.nkb; t += blockDim.x) any |= fb[t];
-  }
-  return __syncthreads_or((int)any) != 0;
+  return p.left[((int64_t)si * p.left_m + m0 / p.left_edge) * p.left_n + n0 / p.left_edge] != 0;
 }
 
 // LEFT: the launch that computes only those tiles.
@@ -81,7 +70,8 @@ __global__ __launch_bounds__(kThreads, 2) void coded_gemm_2d_kernel(GemmParams p
   const int per_sym = p.tiles_m * p.tiles_n;
   const int si = (int)blockIdx.x / per_sym;
   const int rem = (int)blockIdx.x - si * per_sym;
-  const int mt = rem / p.tiles_n, nt = rem - mt * p.tiles_n;
+  // (LEFT: each row of tiles turned by one, see coded_gemm_f32_kernel)
+  const int mt = rem / p.tiles_n, nt = LEFT ? (rem + mt + si) % p.tiles_n : rem - mt * p.tiles_n;
   const int64_t m0 = (int64_t)mt * BM, n0 = (int64_t)nt * BN;
   if (LEFT && !left_out(p, si, m0, n0)) return;
   const int id_off = p.syms[4 * si + 0];
@@ -308,7 +298,6 @@ __device__ __forceinline__ v4f bload_s(__amdgpu_buffer_rsrc_t r, uint32_t voff, 
 }
 }  // namespace w2d
 
-template <bool LEFT>
 __global__ __launch_bounds__(w2d::NT, 1) void coded_gemm_2d_wide_kernel(GemmParams p) {
   // local names shadow the 64 x 128 kernel's constants of the same names
   constexpr int BM = w2d::BM, BN = w2d::BN, BK = w2d::BK, WN = w2d::WN;
@@ -347,7 +336,6 @@ __global__ __launch_bounds__(w2d::NT, 1) void coded_gemm_2d_wide_kernel(GemmPara
     nt = r / gsz;
   }
   const int64_t m0 = (int64_t)mt * BM, n0 = (int64_t)nt * BN;
-  if (LEFT && !left_out(p, si, m0, n0)) return;
   const int id_off = p.syms[4 * si + 0];
   const int deg = p.syms[4 * si + 1];
   const int dest = p.syms[4 * si + 2];
@@ -545,8 +533,9 @@ bool gemm_2d_fits(const GemmParams& p) {
 hipError_t launch_coded_gemm_2d(const GemmParams& p0, int32_t tile, hipStream_t stream) {
   GemmParams p = p0;
   if (!gemm_2d_fits(p)) return hipErrorInvalidValue;
-  // 256 x 256 tiles where every block is full and the shapes divide
-  const bool wide = tile >= 4 && p.Mb % 256 == 0 && p.Nb % 256 == 0 && p.K % 32 == 0 &&
+  // 256 x 256 tiles where every block is full and the shapes divide (flagged
+  // panels alone: small tiles, see launch_coded_gemm)
+  const bool wide = tile >= 4 && !p.left && p.Mb % 256 == 0 && p.Nb % 256 == 0 && p.K % 32 == 0 &&
                     p.M == (int64_t)p.grid * p.Mb && p.N == (int64_t)p.grid * p.Nb &&
                     p.ldc % 4 == 0 && p.Nb % 4 == 0;
   if (wide) {
@@ -555,8 +544,8 @@ hipError_t launch_coded_gemm_2d(const GemmParams& p0, int32_t tile, hipStream_t 
     const int64_t blocks = (int64_t)p.n_sym * p.tiles_m * p.tiles_n;
     if (blocks == 0) return hipSuccess;
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(p.fa ? coded_gemm_2d_wide_kernel<true> : coded_gemm_2d_wide_kernel<false>,
-                       dim3((unsigned)blocks), dim3(w2d::NT), 0, stream, p);
+    hipLaunchKernelGGL(coded_gemm_2d_wide_kernel, dim3((unsigned)blocks), dim3(w2d::NT), 0,
+                       stream, p);
     return hipGetLastError();
   }
   p.tiles_m = (int32_t)((p.Mb + BM - 1) / BM);
@@ -564,7 +553,7 @@ hipError_t launch_coded_gemm_2d(const GemmParams& p0, int32_t tile, hipStream_t 
   const int64_t blocks = (int64_t)p.n_sym * p.tiles_m * p.tiles_n;
   if (blocks == 0) return hipSuccess;
   if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(p.fa ? coded_gemm_2d_kernel<true> : coded_gemm_2d_kernel<false>,
+  hipLaunchKernelGGL(p.left ? coded_gemm_2d_kernel<true> : coded_gemm_2d_kernel<false>,
                      dim3((unsigned)blocks), dim3(kThreads), 0, stream, p);
   return hipGetLastError();
 }

@@ -72,22 +72,14 @@ __device__ __forceinline__ void tile_coords(int L, int rows, int cols, int gm, i
   *col = r / gsz;
 }
 
-// Whether rows [r0, r0 + nr) of the stacked coded rows or columns [n0, n0 +
-// nc) belong to a 256-wide panel that the split planes leave to this kernel
-// (a pack block of it is flagged).  Every thread of the workgroup calls it.
-__device__ __forceinline__ bool left_out(const GemmParams& p, int64_t r0, int nr, int64_t n0,
-                                         int nc) {
+// Whether rows [r0, r0 + nr) of the stacked coded rows and the columns at n0
+// touch a tile that the split planes leave to this kernel (nr is at most their
+// edge, and a tile's columns lie in one of them).
+__device__ __forceinline__ bool left_out(const GemmParams& p, int64_t r0, int nr, int n0) {
   const int64_t R = (int64_t)p.n_sym * p.Mb;
-  const int64_t r1 = r0 + nr < R ? r0 + nr : R, n1 = n0 + nc < p.N ? n0 + nc : p.N;
-  unsigned any = 0;
-  // 8 pack blocks of 32 rows and 4 of 64 columns per panel
-  for (int64_t i = r0 / 256 * 8 * p.nka + threadIdx.x; i < ((r1 - 1) / 256 + 1) * 8 * p.nka;
-       i += blockDim.x)
-    any |= p.fa[i];
-  for (int64_t i = n0 / 256 * 4 * p.nkb + threadIdx.x; i < ((n1 - 1) / 256 + 1) * 4 * p.nkb;
-       i += blockDim.x)
-    any |= p.fb[i];
-  return __syncthreads_or((int)any) != 0;
+  const int64_t r1 = r0 + nr < R ? r0 + nr : R;
+  const unsigned* col = p.left + n0 / p.left_edge;
+  return (col[r0 / p.left_edge * p.left_n] | col[(r1 - 1) / p.left_edge * p.left_n]) != 0;
 }
 
 // LEFT: the launch that computes only what the split planes leave out (an
@@ -116,14 +108,21 @@ __global__ __launch_bounds__(kThreads, OCC) void coded_gemm_f32_kernel(GemmParam
     m0 = (rp - si * p.tiles_m) * 256 + (sub / SN) * BM;
     n0 = nt * 256 + (sub % SN) * BN;
   } else {
-    const int lin = xcd_remap(blockIdx.x, gridDim.x);
-    tile_coords(lin, p.n_sym * p.tiles_m, p.tiles_n, p.group_m, &rp, &nt);
+    if (LEFT) {
+      // Row by row, each row turned by one tile: workgroups go to the XCDs and
+      // CUs in turn, and a flagged panel, a row of tiles or a column, should
+      // fall on all of them (a column every tiles_n workgroups meets few).
+      rp = (int)blockIdx.x / p.tiles_n;
+      nt = ((int)blockIdx.x + rp) % p.tiles_n;
+    } else {
+      const int lin = xcd_remap(blockIdx.x, gridDim.x);
+      tile_coords(lin, p.n_sym * p.tiles_m, p.tiles_n, p.group_m, &rp, &nt);
+    }
     si = rp / p.tiles_m;
     m0 = (rp - si * p.tiles_m) * BM;
     n0 = nt * BN;
   }
-  if (LEFT && !left_out(p, si * p.Mb + m0, p.Mb - m0 < BM ? (int)(p.Mb - m0) : BM, n0, BN))
-    return;
+  if (LEFT && !left_out(p, si * p.Mb + m0, p.Mb - m0 < BM ? (int)(p.Mb - m0) : BM, n0)) return;
 
   const int id_off = p.syms[4 * si + 0];
   const int deg = p.syms[4 * si + 1];
@@ -400,7 +399,7 @@ __device__ __forceinline__ v4f bload(__amdgpu_buffer_rsrc_t r, uint32_t voff, ui
 }
 }  // namespace wide
 
-template <int WM, int WN, bool LEFT = false>
+template <int WM, int WN>
 __global__ __launch_bounds__(64 * WM * WN, 1) void coded_gemm_f32_wide_kernel(GemmParams p) {
   using namespace wide;
   constexpr int NT = 64 * WM * WN;               // threads
@@ -435,7 +434,6 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void coded_gemm_f32_wide_kernel(Ge
   const int si = rp / p.tiles_m;
   const int mt = rp - si * p.tiles_m;
   const int m0 = mt * BM, n0 = nt * BN;
-  if (LEFT && !left_out(p, si * p.Mb + m0, BM, n0, BN)) return;
 
   const int id_off = p.syms[4 * si + 0];
   const int deg = p.syms[4 * si + 1];
@@ -615,9 +613,13 @@ const TileEntry kTiles[] = {
 
 constexpr int32_t kWideTile = 4;
 
-// The flagged launch's forms of the two default shapes.
+// The launch for flagged panels, small tiles whatever the shape: how many there
+// are is not known here, and few tiles take as long as the longest of them.
+// Calls of 8192 x 8192 x 4096, (12,8,4) code, 2.65 ms without a flag: one value
+// of A flagged 3.7 ms (7.0 in 256 x 256 tiles, an XCD's range of tiles each), one
+// column panel 3.7 (5.0), everything 5.8 (6.5; these kernels alone 4.7); 1999 x
+// 1500 x 1001, 79 us without a flag: 258 (316), 245 (319) and 213 (267; 189).
 const TileEntry kLeftTile = {{64, 128, 32}, coded_gemm_f32_kernel<64, 128, 32, 2, true>, kThreads};
-const TileEntry kLeftWide = {{256, 256, 32}, coded_gemm_f32_wide_kernel<4, 2, true>, 512};
 
 }  // namespace
 
@@ -643,7 +645,7 @@ hipError_t launch_coded_gemm(const GemmParams& p0, int32_t tile, hipStream_t str
   p.wide_rem = 0;
   p.wide_lin0 = 0;
   p.wide_split = 0;
-  if (tile >= kWideTile) {
+  if (tile >= kWideTile && !p.left) {
     // The wide tile has no edge path: shapes with a partial tile, a partial
     // data block or a ragged last K-slice take the 64 x 128 tile.
     const bool fits = p.Mb % 256 == 0 && p.N % 256 == 0 && p.K % 32 == 0 &&
@@ -655,12 +657,11 @@ hipError_t launch_coded_gemm(const GemmParams& p0, int32_t tile, hipStream_t str
     // keeps every CU busy to the end.  Both kernels sum in the same order,
     // so the split does not change results.
     const int64_t rem = T % S;
-    // (A launch for flagged tiles alone has no rounds to fill.)
-    const int64_t wide_tiles = rem * 10 < S * 9 && !p.fa ? T - rem : T;
+    const int64_t wide_tiles = rem * 10 < S * 9 ? T - rem : T;
     if (T == 0 || T > 0x7fffffff / 8) {
       tile = 1;
     } else {
-      const TileEntry& e = p.fa ? kLeftWide : kTiles[tile];
+      const TileEntry& e = kTiles[tile];
       p.tiles_m = (int32_t)(p.Mb / 256);
       p.tiles_n = (int32_t)(p.N / 256);
       if (wide_tiles > 0) {
@@ -712,7 +713,7 @@ hipError_t launch_coded_gemm(const GemmParams& p0, int32_t tile, hipStream_t str
       return hipGetLastError();
     }
   }
-  const TileEntry& e = p.fa ? kLeftTile : kTiles[tile];
+  const TileEntry& e = p.left ? kLeftTile : kTiles[tile];
   p.tiles_m = (int32_t)((p.Mb + e.shape.bm - 1) / e.shape.bm);
   p.tiles_n = (int32_t)((p.N + e.shape.bn - 1) / e.shape.bn);
   const int64_t blocks = (int64_t)p.n_sym * p.tiles_m * p.tiles_n;

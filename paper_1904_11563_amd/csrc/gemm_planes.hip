@@ -565,7 +565,9 @@ __global__ __launch_bounds__(2 * S, 2) void gemm_planes_kernel(PlaneParams p) {
       for (int t = tid; t < 8 * p.nka; t += T::THREADS) bad |= p.fa[pa * 8 * p.nka + t];
       for (int t = tid; t < 4 * p.nkb; t += T::THREADS) bad |= p.fb[pb * 4 * p.nkb + t];
     }
-    if (__syncthreads_or((int)bad)) {
+    const int left = __syncthreads_or((int)bad);
+    if (tid == 0) p.ft[((int64_t)si * p.tiles_m + mt) * p.tiles_n + nt] = left ? 1u : 0u;
+    if (left) {
       wait_counts<0, false>();  // no copy may land in LDS that is no longer ours
       return;
     }
@@ -834,12 +836,12 @@ static double choose_tiles(PlaneParams* p, const int32_t* passes, int64_t* tiles
   return t128;
 }
 
-hipError_t launch_gemm_planes(const PlaneParams& p0, const int32_t* passes, hipStream_t stream) {
-  PlaneParams p = p0;
+hipError_t launch_gemm_planes(PlaneParams* p, const int32_t* passes, hipStream_t stream) {
   int64_t T;
-  choose_tiles(&p, passes, &T);
+  choose_tiles(p, passes, &T);
   if (T > 0x7fffffff / 32) return hipErrorInvalidValue;
-  return p.tile == 128 ? launch_gemm_tiles<128>(p, T, stream) : launch_gemm_tiles<256>(p, T, stream);
+  return p->tile == 128 ? launch_gemm_tiles<128>(*p, T, stream)
+                        : launch_gemm_tiles<256>(*p, T, stream);
 }
 
 // 15 us of launches (FP32, with its second product launch, 18), the GEMM's

@@ -249,13 +249,14 @@ struct bpx_plan {
     return (size_t)(plane_rows() + plane_cols()) / 32 * plane_kc() * a_chunk_bytes();
   }
   // Offsets of the plane parts, from the start of the workspace: packed A,
-  // packed B, flags (FP32) or scales (FP8) of A, of B, partial tiles; [5] the end.
+  // packed B, flags (FP32) or scales (FP8) of A, of B (FP32: then of up to four tiles per 256 x
+  // 256), partial tiles; [5] the end.
   void plane_layout(size_t off[6]) const {
     const size_t kc = (size_t)plane_kc();
     size_t b = base_bytes(), sa = 0, sb = 0;
     if (planes() == 3) {
       sa = (size_t)(plane_rows() / 32) * ((kc + 15) / 16) * 4;
-      sb = (size_t)(plane_cols() / 64) * ((kc + 3) / 4) * 4;
+      sb = ((size_t)(plane_cols() / 64) * ((kc + 3) / 4) + 4 * (size_t)plane_tiles()) * 4;
     } else if (is_fp8()) {
       sa = kc / 2 * (size_t)plane_rows();
       sb = kc / 2 * (size_t)(plane_cols() / 128) * 4;

@@ -51,14 +51,11 @@ struct GemmParams {
   const unsigned short* bt_hi;
   const unsigned short* bt_lo;
   int64_t kp;
-  // FP32 launch that only computes the tiles the split planes leave out: the
-  // pack blocks' flags (see PlaneParams), null for an ordinary launch
-  const unsigned* fa;
-  const unsigned* fb;
-  int32_t nka, nkb;
-  // ... of a two-dimensional product (PlaneParams)
-  const int32_t* sym_passes;
-  const int32_t* passes;
+  // FP32 launch that only computes the tiles the split planes leave out:
+  // PlaneParams::ft, null for an ordinary launch, the edge of those tiles and
+  // how many (per symbol in the two-dimensional form)
+  const unsigned* left;
+  int32_t left_edge, left_m, left_n;
 };
 
 // FP8 path (see gemm_fp8.hip for the workspace layout).
@@ -171,6 +168,7 @@ struct PlaneParams {
   unsigned short* bp;  // packed planes of B's columns
   unsigned* fa;        // planes == 3: per pack block, 1 if it holds a value
   unsigned* fb;        //   that is not split
+  unsigned* ft;        // ... and per tile, 1 if it belongs to such values' panels
   unsigned max_bits;   // planes == 3: bits of the smallest magnitude not split
   float* part;         // partial 256 x 256 tiles of the last round
   int32_t part_tiles;  // how many part holds
@@ -200,8 +198,9 @@ struct PlaneParams {
   int32_t full, split; // tiles computed whole; K pieces of each of the others
 };
 hipError_t launch_pack_planes(const PlaneParams& p, hipStream_t stream);
-// passes: in the two-dimensional form the passes of each symbol (host memory)
-hipError_t launch_gemm_planes(const PlaneParams& p, const int32_t* passes, hipStream_t stream);
+// passes: in the two-dimensional form the passes of each symbol (host memory).
+// Sets the tiles it chose.
+hipError_t launch_gemm_planes(PlaneParams* p, const int32_t* passes, hipStream_t stream);
 // Time that pack, product and peel of a row-block product are expected to take, in us.
 double planes_us(const PlaneParams& p);
 hipError_t launch_pack_fp8(const PlaneParams& p, hipStream_t stream);
