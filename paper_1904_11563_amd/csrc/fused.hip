@@ -176,75 +176,41 @@ __device__ __forceinline__ v4f bload(__amdgpu_buffer_rsrc_t r, uint32_t voff) {
 
 // Peel phase: every thread runs the whole program for its own elements.
 // Steps carry src = the releaser's Y tile, and every recovered block is
-// written to C (nothing reached C earlier).  Bound by one wave's instructions
-// per step (256 elements, a wave to a SIMD), so lane l works out step l's
-// addresses (at most one step per data block, and one subtrahend less than a
-// symbol's members), a step reads them across lanes, and what it does not use
-// it reads and writes at its own product's place instead of branching.  512^3,
-// eight steps: 5500 -> 5000 cycles, and fewer registers (below 128 two
-// workgroups share a CU where LDS allows: (6,4,2) 768 x 64 x 768, 288 tiles, FP32
-// 14.0 -> 10.3 us).
-constexpr int kMaxDeg = 4;  // members per symbol at most
-__device__ __forceinline__ void fused_peel(const FusedParams& p, float* yt, const float* xs,
+// written to C (nothing reached C earlier).  The program is the same for all
+// threads, so its words come from LDS as broadcasts and the branches are scalar.
+// (Step addresses worked out one per lane and read across lanes, every step
+// without a branch: 0.2 to 0.4 us slower, (6,4,2) 512^3 FP32 14.9 against 14.6, BF16
+// 11.7 against 11.3 us a launch.)
+__device__ __forceinline__ bool row_ok(const FusedParams& p, int64_t s, int64_t r) {
+  return r < p.Mb && s * p.Mb + r < p.M;
+}
+__device__ __forceinline__ void fused_peel(const FusedParams& p, const float* yt, float* xs,
                                            const FusedTables& t, int r0, int n0, int BN) {
-  const int tile = BM * BN, lane = (int)threadIdx.x & 63;
-  // byte offsets from yt
-  const int x0 = (int)((const char*)xs - (const char*)yt);
-  PeelStep mine = {};
-  int sub[kMaxDeg - 1] = {}, rows = 0;
-  uint64_t block = 0;
-  if (lane < p.nsteps) {
-    mine = t.steps[lane];
-    const int64_t first = (int64_t)mine.s * p.Mb;
-    rows = (int)max((int64_t)0, min(p.M - first, p.Mb));
-    block = reinterpret_cast<uint64_t>(p.C + first * p.ldc);
-#pragma unroll
-    for (int u = 0; u < kMaxDeg - 1; ++u)
-      sub[u] = u < mine.nsub ? x0 + t.subs[mine.sub_off + u] * tile * 4 : mine.src * tile * 4;
-  }
-  const int src = mine.src * tile * 4, kind = mine.nsub + (mine.f64 ? 8 : 0);
-  const int slot = mine.slot >= 0 ? x0 + mine.slot * tile * 4 : src;
-  const int lo = (int)block, hi = (int)(block >> 32);
-  auto of = [](int v, int st) __attribute__((always_inline)) {
-    return __builtin_amdgcn_readlane(v, st);
-  };
+  const int tile = BM * BN;
   for (int e = threadIdx.x; e < tile; e += kThreads) {
-    const int row = e / BN, r = r0 + row, n = n0 + e - row * BN;
-    const int last = n < p.N ? r : 0x7fffffff;  // (no row of a column past N)
-    const int64_t at = (int64_t)r * p.ldc + n;
-    char* mem = reinterpret_cast<char*>(yt + e);
-    auto word = [&](int off) __attribute__((always_inline)) -> float& {
-      return *reinterpret_cast<float*>(mem + off);
-    };
-    float y = word(of(src, 0));
+    const int row = e / BN, col = e - row * BN;
+    const int64_t r = r0 + row, n = n0 + col;
     for (int st = 0; st < p.nsteps; ++st) {
-      const float cur = y;
-      const float v0 = word(of(sub[0], st)), v1 = word(of(sub[1], st)), v2 = word(of(sub[2], st));
-      y = word(of(src, st + 1));  // (past the last step: lane's zeros, never used)
-      const int k = of(kind, st);
+      const PeelStep S = t.steps[st];
+      const float y = yt[S.src * tile + e];
+      const int32_t* sub = t.subs + S.sub_off;
       float x;
-      if (k < 8) {
-        float sum = cur, comp = 0.f;
-        auto take = [&](float v, bool on) __attribute__((always_inline)) {
-          const float w = -v - comp, tt = sum + w, c = (tt - sum) - w;
-          comp = on ? c : comp;
-          sum = on ? tt : sum;
-        };
-        take(v0, k > 0);
-        take(v1, k > 1);
-        take(v2, k > 2);
-        x = sum;
-      } else {
-        double acc = (double)cur;
-        if (k > 8) acc -= (double)v0;
-        if (k > 9) acc -= (double)v1;
-        if (k > 10) acc -= (double)v2;
+      if (S.f64) {
+        double acc = (double)y;
+        for (int u = 0; u < S.nsub; ++u) acc -= (double)xs[sub[u] * tile + e];
         x = (float)acc;
+      } else {
+        float sum = y, comp = 0.f;
+        for (int u = 0; u < S.nsub; ++u) {
+          const float v = -xs[sub[u] * tile + e] - comp;
+          const float tt = sum + v;
+          comp = (tt - sum) - v;
+          sum = tt;
+        }
+        x = sum;
       }
-      word(of(slot, st)) = x;
-      float* out = reinterpret_cast<float*>((uint64_t)(uint32_t)of(lo, st) |
-                                            (uint64_t)(uint32_t)of(hi, st) << 32);
-      if (last < of(rows, st)) out[at] = x;
+      if (S.slot >= 0) xs[S.slot * tile + e] = x;
+      if (n < p.N && row_ok(p, S.s, r)) p.C[((int64_t)S.s * p.Mb + r) * p.ldc + n] = x;
     }
   }
 }
@@ -368,6 +334,7 @@ __device__ __forceinline__ v4f a_granule(const float* As, int blk, int h, int ro
 // The symbols of a wave: i = wave + 8 j for j < kMS, with their degree,
 // member blocks (ascending) and Y tile held in scalar registers.
 constexpr int kMS = 2;      // symbols per wave at most (16 per workgroup)
+constexpr int kMaxDeg = 4;  // members per symbol at most
 struct WaveSyms {
   int n;
   int deg[kMS];
@@ -470,16 +437,14 @@ __device__ __forceinline__ void pipeline_idle(int ng, int stage, const ADma<KG>&
   }
 }
 
-// Waves per SIMD the registers are limited for: two workgroups on a CU where the
-// LDS of short products lets them (not the form whose strip fills it: BF16x3,
-// K = 1024, 21.3 us became 22.2 with the spills of 128 registers).
-constexpr int waves_per_simd(int jn, int kg, bool dma) {
-  return jn == 1 && (dma || kg == 32) ? 4 : 2;
-}
-
+// W: waves per SIMD the registers are limited for.  Four let two workgroups share
+// a CU where LDS allows; the forms with copies to LDS lose nothing by it, nor does
+// FP32 with 32 k to a group, but the BF16 ones with 32 k to a group spill: Table
+// III's code, 512 x 96 x 512, all tiles at once: BF16x3 9.6 us with four, 9.2 with
+// two, BF16 9.3 and 8.9; 768 x 64 x 768, 288 tiles: 11.8 and 13.3, 11.4 and 12.7.
 // ------------------------------------------------------------------ FP32 --
-template <int JN, int KG, bool DMA>
-__global__ __launch_bounds__(kThreads, waves_per_simd(JN, KG, DMA)) void fused_f32_kernel(FusedParams p) {
+template <int JN, int KG, bool DMA, int W>
+__global__ __launch_bounds__(kThreads, W) void fused_f32_kernel(FusedParams p) {
   constexpr int BN = 16 * JN, LDB = BN + kPadF32;
   typedef typename Vec<JN>::T vb;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
@@ -691,8 +656,8 @@ __device__ __forceinline__ void split8(v4f x0, v4f x1, v8bf* hi, v8bf* lo) {
   }
 }
 
-template <int JN, bool X3, int KG, bool DMA>
-__global__ __launch_bounds__(kThreads, waves_per_simd(JN, KG, DMA)) void fused_bf16_kernel(FusedParams p) {
+template <int JN, bool X3, int KG, bool DMA, int W>
+__global__ __launch_bounds__(kThreads, W) void fused_bf16_kernel(FusedParams p) {
   constexpr int BN = 16 * JN;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
   const FusedLds L = fused_lds(p);
@@ -901,23 +866,25 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(JN, KG, DMA)) void fused_b
 
 typedef void (*FusedKernel)(FusedParams);
 
-template <int KG, bool DMA>
+template <int KG, bool DMA, int W>
 FusedKernel fused_kernel_kg(int32_t prec, int jn) {
   if (prec == BPX_PREC_F32)
-    return jn == 1 ? fused_f32_kernel<1, KG, DMA>
-                   : jn == 2 ? fused_f32_kernel<2, KG, DMA> : fused_f32_kernel<4, KG, DMA>;
+    return jn == 1 ? fused_f32_kernel<1, KG, DMA, W>
+                   : jn == 2 ? fused_f32_kernel<2, KG, DMA, 2> : fused_f32_kernel<4, KG, DMA, 2>;
   // BF16 tiles stop at 32 columns (wider ones spill at eight waves)
   if (prec == BPX_PREC_BF16)
-    return jn == 1 ? fused_bf16_kernel<1, false, KG, DMA>
-                   : jn == 2 ? fused_bf16_kernel<2, false, KG, DMA> : nullptr;
+    return jn == 1 ? fused_bf16_kernel<1, false, KG, DMA, W>
+                   : jn == 2 ? fused_bf16_kernel<2, false, KG, DMA, 2> : nullptr;
   if (prec == BPX_PREC_BF16X3)
-    return jn == 1 ? fused_bf16_kernel<1, true, KG, DMA>
-                   : jn == 2 ? fused_bf16_kernel<2, true, KG, DMA> : nullptr;
+    return jn == 1 ? fused_bf16_kernel<1, true, KG, DMA, W>
+                   : jn == 2 ? fused_bf16_kernel<2, true, KG, DMA, 2> : nullptr;
   return nullptr;
 }
-FusedKernel fused_kernel_for(int32_t prec, int jn, int kg, int stages) {
-  if (stages == 3) return fused_kernel_kg<64, true>(prec, jn);
-  return kg == 64 ? fused_kernel_kg<64, false>(prec, jn) : fused_kernel_kg<32, false>(prec, jn);
+FusedKernel fused_kernel_for(const FusedParams& p) {
+  if (p.stages == 3) return fused_kernel_kg<64, true, 4>(p.prec, p.jn);
+  if (p.kg == 64) return fused_kernel_kg<64, false, 2>(p.prec, p.jn);
+  return p.pair || p.prec == BPX_PREC_F32 ? fused_kernel_kg<32, false, 4>(p.prec, p.jn)
+                                          : fused_kernel_kg<32, false, 2>(p.prec, p.jn);
 }
 
 constexpr size_t kLdsLimit = 160 * 1024;
@@ -941,8 +908,9 @@ bool fused_configure(FusedParams* p) {
   const int64_t cus = device_cu_count();
   for (int jn : {4, 2, 1}) {
     p->stages = 2;
-    if (!fused_kernel_for(p->prec, jn, p->kg, p->stages)) continue;
+    p->pair = 0;
     p->jn = jn;
+    if (!fused_kernel_for(*p)) continue;
     const int64_t tiles_n = (p->N + 16 * jn - 1) / (16 * jn);
     if (jn > 1 && tiles_m * tiles_n < cus) continue;
     if (fused_lds(*p).total > kLdsLimit) continue;
@@ -953,6 +921,8 @@ bool fused_configure(FusedParams* p) {
     // pipeline_halves
     p->stages = 3;
     if (p->n_sym > kWaves || p->kg != 64 || fused_lds(*p).total > kLdsLimit) p->stages = 2;
+    // more tiles than CUs: two 16-column workgroups to a CU where they fit
+    p->pair = jn == 1 && tiles_m * tiles_n > cus && 2 * fused_lds(*p).total <= kLdsLimit;
     return true;
   }
   return false;
@@ -965,8 +935,7 @@ bool fused_configure(FusedParams* p) {
 // symbols, two to a wave: 22.3 and 37.3, 19.1 and 30.8, 17.1 and 26.2.
 double fused_us(const FusedParams& p) {
   const int64_t cus = device_cu_count(), tiles = (int64_t)p.tiles_m * p.tiles_n;
-  const bool two = p.jn == 1 && 2 * fused_lds(p).total <= kLdsLimit && tiles > cus;
-  const double rounds = two ? 1.3 * (double)((tiles + 2 * cus - 1) / (2 * cus))
+  const double rounds = p.pair ? 1.3 * (double)((tiles + 2 * cus - 1) / (2 * cus))
                             : (double)((tiles + cus - 1) / cus);
   const double s = (double)((p.n_sym + kWaves - 1) / kWaves);
   const double per_k = p.prec == BPX_PREC_F32      ? 0.006 + 0.0117 * s
@@ -979,7 +948,7 @@ double fused_us(const FusedParams& p) {
 size_t fused_lds_bytes(const FusedParams& p) { return fused_lds(p).total; }
 
 hipError_t launch_fused(const FusedParams& p, hipStream_t stream) {
-  const FusedKernel k = fused_kernel_for(p.prec, p.jn, p.kg, p.stages);
+  const FusedKernel k = fused_kernel_for(p);
   if (!k) return hipErrorInvalidValue;
   const size_t lds = fused_lds(p).total;
   if (lds > kLdsLimit) return hipErrorInvalidConfiguration;

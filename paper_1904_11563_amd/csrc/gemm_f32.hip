@@ -616,8 +616,8 @@ constexpr int32_t kWideTile = 4;
 // The launch for flagged panels, small tiles whatever the shape: how many there
 // are is not known here, and few tiles take as long as the longest of them.
 // Calls of 8192 x 8192 x 4096, (12,8,4) code, 2.65 ms without a flag: one value
-// of A flagged 3.7 ms (7.0 in 256 x 256 tiles, an XCD's range of tiles each), one
-// column panel 3.7 (5.0), everything 5.8 (6.5; these kernels alone 4.7); 1999 x
+// of A flagged 3.6 ms (7.0 in 256 x 256 tiles, an XCD's range of tiles each), one
+// column panel 3.6 (5.0), everything 5.8 (6.5; these kernels alone 4.7); 1999 x
 // 1500 x 1001, 79 us without a flag: 258 (316), 245 (319) and 213 (267; 189).
 const TileEntry kLeftTile = {{64, 128, 32}, coded_gemm_f32_kernel<64, 128, 32, 2, true>, kThreads};
 

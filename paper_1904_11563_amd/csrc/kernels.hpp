@@ -307,6 +307,7 @@ struct FusedParams {
   int32_t max_deg;  // largest degree of a computed symbol
   int32_t kg;       // k per A-stage group (32 or 64)
   int32_t stages;   // LDS buffers of a k group (3: copied straight to LDS)
+  int32_t pair;     // two workgroups share a CU
   int64_t kp;  // K rounded up to the k group
 };
 // Picks the tile width and checks that the workgroup's LDS fits; false if

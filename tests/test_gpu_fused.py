@@ -189,3 +189,28 @@ def test_fused_group_edges_exact(M, K, N, prec):
         # sums of at most 3 x 8 and K products of at most 24 x 8 are exact
         assert torch.equal(C[:, :N].double(), A[:, :K].double() @ B[:, :N].double())
         assert bool(C[:, N:].isnan().all())
+
+
+# Codes of 9 blocks (32 k to a group): all workgroups on the chip at once, and two
+# to a CU, with registers for one and for two
+@pytest.mark.parametrize("prec", [bpx.PREC_F32, bpx.PREC_BF16X3, bpx.PREC_BF16])
+@pytest.mark.parametrize("M,K,N", [(100, 36, 40), (1289, 64, 801), (2304, 28, 512)])
+def test_fused_nine_blocks_exact(M, K, N, prec):
+    code = bpx.Code.table3()
+    g = torch.Generator(device="cuda").manual_seed(M)
+    A = torch.randint(-8, 9, (M, K), generator=g, device="cuda").float()
+    B = torch.full((K, -(-N // 4) * 4), float("nan"), device="cuda")
+    B[:, :N] = torch.randint(-8, 9, (K, N), generator=g, device="cuda").float()
+    for arrival in ([0, 1, 2, 3, 4], [4, 2, 0, 1, 3]):
+        plan = bpx.Plan(code, arrival, 0, bpx.MODE_STRAGGLER, M, K, N, prec)
+        C = torch.full((M, -(-N // 4) * 4), float("nan"), device="cuda")
+        _say("fused nine blocks", M, K, N, "prec", prec)
+        bpx.set_fused_peel(2)
+        try:
+            assert plan.fused()
+            bpx.coded_matmul(plan, A, B[:, :N], C[:, :N], bpx.alloc_workspace(plan))
+            torch.cuda.synchronize()
+        finally:
+            bpx.set_fused_peel(1)
+        # sums of at most 2 x 8 and K products of at most 16 x 8 are exact
+        assert torch.equal(C[:, :N].double(), A.double() @ B[:, :N].double())
