@@ -246,16 +246,20 @@ bpx_status bpx_plan_peel_program(const bpx_plan* plan, const int32_t** steps, in
  * the size of the buffer bpx_encode writes (n_computed coded blocks of
  * Mb x K floats).  A call whose workspace holds the parts of
  * bpx_plan_workspace_layout only is accepted: it runs the kernels that read A
- * and B directly. */
+ * and B directly.  So is any size in between: packed operands are used if they
+ * fit, and tiles are split along K into as many pieces as the rest holds.  All of
+ * these give the same product, but not the same bits: they sum in other orders. */
 bpx_status bpx_plan_workspace_bytes(const bpx_plan* plan, size_t* ws_bytes,
                                     size_t* encode_bytes);
 
 /* Byte offsets of the parts of the plan's workspace (n entries written,
  * at most 7), every part 256-byte aligned; a part the precision does not
  * use has size 0 (its offset equals the next one); entry 6 is the end of
- * these parts (behind it, up to ws_bytes, come the packed operands, flags or
- * scales and partial tiles of products large enough to run on packed operands;
- * of the parts below only Y is then written).
+ * these parts.  Products large enough to run on packed operands keep those, their
+ * flags or scales and partial tiles behind them (BF16*: behind Y); of the parts
+ * below such a call fills only Y, FP32 also the partial tiles, and FP8 leaves the
+ * codes and scales as they were.  A caller who reads those of a product past 2^31
+ * multiply-adds brings entry 6's bytes and no more, or forces a tile shape.
  *   F32:     [0] Y slots, [1] split-K partial tiles: when Mb and N are
  *            multiples of 256, K of 32 and M of Mb, room for min(256, 4 T)
  *            FP32 tiles of 256 x 256 (T = computed symbols x Mb/256 x N/256),
@@ -353,13 +357,16 @@ bpx_status bpx_plan_fused_program(const bpx_plan* plan, const int32_t** steps, i
 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
- * product as bpx_coded_matmul, with the workspace
- * taken from a static device array of the library (32 MiB per GPU, held by
- * every device that uses it until the process ends) instead of a caller
- * buffer.  Allocates nothing: the plan's tables must already be on the
+ * product as bpx_coded_matmul, with the workspace taken from a static device
+ * array of the library (32 MiB per GPU, held by every device that uses it until
+ * the process ends) instead of a caller buffer: the same kernels and results as
+ * bpx_coded_matmul with a workspace of 32 MiB.  (Those of its full workspace too
+ * where Y, the packed operands and the pieces of split tiles fit in 32 MiB; larger
+ * products split less or read A and B directly, see bpx_plan_workspace_bytes.)
+ * Allocates nothing: the plan's tables must already be on the
  * current device (bpx_plan_upload), else BPX_E_INVALID; a plan whose
- * workspace parts (bpx_plan_workspace_layout, entry 6) exceed 32 MiB get
- * BPX_E_UNSUPPORTED; the split planes are used when they fit as well.  Every call on one GPU shares that GPU's array, and
+ * workspace parts (bpx_plan_workspace_layout, entry 6) exceed 32 MiB gets
+ * BPX_E_UNSUPPORTED.  Every call on one GPU shares that GPU's array, and
  * nothing in it needs to start at zero (each call writes every byte it
  * reads first): calls that overlap on one GPU (other streams, other
  * threads) race and must be serialised by the caller. */
@@ -377,9 +384,9 @@ bpx_status bpx_coded_matmul_noalloc(bpx_plan* plan, const float* A, int64_t lda,
  *
  * bpx_group_workspace_bytes: device workspace for the plans: each plan's
  *   parts (bpx_plan_workspace_layout, entry 6) rounded up to 256, back to
- *   back, and, for groups of enough work, every product's operands split into
- *   BF16 planes behind them.  A workspace of the parts alone is accepted: the
- *   group then runs the kernels that read A directly.
+ *   back, or, for groups of enough work, room for every product's Y slots and
+ *   operands split into BF16 planes.  A workspace of the parts alone is accepted:
+ *   the group then runs the kernels that read A directly.
  * bpx_group_create: host setup, done once: uploads the plans' tables and one
  *   block of per-product descriptors and a tile list (hipMalloc + one
  *   synchronous copy).  ws (256-byte aligned) and every operand pointer are

@@ -181,8 +181,8 @@ bpx_status check_matrix(const float* ptr, int64_t ld, int64_t cols, const char* 
   return BPX_OK;
 }
 
-// A call has to bring the parts every path needs; the split planes are used
-// when the workspace holds them too.
+// A call has to bring the parts every path needs; packed operands are used
+// when the workspace holds them.
 bpx_status check_workspace(const bpx_plan* plan, const void* ws, size_t ws_bytes) {
   const size_t need = plan->base_bytes();
   if (need > 0 && (!ws || ws_bytes < need || ((uintptr_t)ws & 255u)))
@@ -228,8 +228,7 @@ void plane_params(const bpx_plan* plan, const GemmParams& p, PlaneParams* out) {
     q.sym_passes = q.op_ids + plan->ops.ids.size();
     q.passes = q.sym_passes + plan->ops.sym_passes.size();
     q.n_passes = (int32_t)plan->n_products();
-    for (size_t i = 1; i < plan->ops.sym_passes.size(); i += 2)
-      q.n_single += plan->ops.sym_passes[i] == 1;
+    for (int32_t n : plan->ops.counts) q.n_single += n == 1;
   }
 }
 
@@ -281,7 +280,7 @@ bool fused_setup(const bpx_plan* plan, const float* A, int64_t lda, const float*
 // 1800 x 100 31 against 20), nor with that form switched off, so that it and the
 // two launches keep giving the same bits.
 bool on_planes(const bpx_plan* plan, int64_t lda, int64_t ldb, size_t ws_bytes) {
-  if (!plan->has_planes() || ws_bytes < plan->ws_bytes() ||
+  if (!plan->has_planes() || ws_bytes < plan->plane_bytes() ||
       tile_chosen(plan->prec, plan->Mb, plan->N, plan->K))
     return false;
   FusedParams f;
@@ -296,15 +295,17 @@ bool on_planes(const bpx_plan* plan, int64_t lda, int64_t ldb, size_t ws_bytes) 
   g.n_sym = f.n_sym;
   PlaneParams q;
   plane_params(plan, g, &q);
-  q.part_tiles = plan->plane_part_tiles();
+  size_t at;
+  q.part_tiles = plan->plane_parts(ws_bytes, &at);
   return planes_us(q) < fused_us(f);
 }
 
 // Coded products on split planes (see gemm_planes.hip): pack, multiply and,
 // for FP32, the tiles that hold a value the planes do not represent.
-bpx_status gemm_planes_impl(bpx_plan* plan, GemmParams p, void* ws, hipStream_t stream) {
+bpx_status gemm_planes_impl(bpx_plan* plan, GemmParams p, void* ws, size_t ws_bytes,
+                            hipStream_t stream) {
   char* w = static_cast<char*>(ws);
-  size_t off[6];
+  size_t off[5], part;
   plan->plane_layout(off);
   PlaneParams q;
   plane_params(plan, p, &q);
@@ -313,8 +314,8 @@ bpx_status gemm_planes_impl(bpx_plan* plan, GemmParams p, void* ws, hipStream_t 
   q.fa = reinterpret_cast<unsigned*>(w + off[2]);
   q.fb = reinterpret_cast<unsigned*>(w + off[3]);
   q.ft = q.fb + (size_t)q.cols64 * ((q.kc + 3) / 4);
-  q.part = reinterpret_cast<float*>(w + off[4]);
-  q.part_tiles = plan->plane_part_tiles();
+  q.part_tiles = plan->plane_parts(ws_bytes, &part);
+  q.part = reinterpret_cast<float*>(w + part);
   if (plan->is_fp8()) {
     q.ea = reinterpret_cast<unsigned char*>(w + off[2]);
     q.eb = reinterpret_cast<unsigned*>(w + off[3]);
@@ -323,10 +324,7 @@ bpx_status gemm_planes_impl(bpx_plan* plan, GemmParams p, void* ws, hipStream_t 
     return e == hipSuccess ? BPX_OK : hip_fail(e, "packed FP8 gemm launch");
   }
   hipError_t e = launch_pack_planes(q, stream);
-  std::vector<int32_t> passes;
-  for (size_t i = 1; i < plan->ops.sym_passes.size(); i += 2)
-    passes.push_back(plan->ops.sym_passes[i]);
-  if (e == hipSuccess) e = launch_gemm_planes(&q, passes.data(), stream);
+  if (e == hipSuccess) e = launch_gemm_planes(&q, plan->pass_counts(), stream);
   if (e == hipSuccess && q.planes == 3) {
     p.left = q.ft;
     p.left_edge = q.tile;
@@ -385,7 +383,7 @@ bpx_status gemm_impl(bpx_plan* plan, const float* A, int64_t lda, const float* B
       return fail(BPX_E_UNSUPPORTED, "FP8 grid too large");
   }
   if (on_planes(plan, lda, ldb, usable_workspace(ws, ws_bytes)))
-    return gemm_planes_impl(plan, p, ws, stream);
+    return gemm_planes_impl(plan, p, ws, ws_bytes, stream);
   const int32_t tile = choose_tile(plan->prec, plan->Mb, plan->N, plan->K);
   hipError_t e;
   if (plan->grid > 1) {
@@ -574,11 +572,12 @@ bool group_planes(bpx_plan* const* plans, int32_t count) {
   return tiles >= 256 && tiles < (int64_t)1 << 31 &&
          macs >= 96.0 * plans[0]->planes() * values;
 }
-// ... and the packed operands behind those parts.
+// ... and what it needs then, Y slots and packed operands product by product
+// (more than the parts: packed operands are larger than BF16's planes of B).
 size_t group_ws_bytes(bpx_plan* const* plans, int32_t count) {
-  size_t b = group_base_bytes(plans, count);
-  if (group_planes(plans, count))
-    for (int32_t i = 0; i < count; ++i) b += bpx_plan::align256(plans[i]->packed_bytes());
+  if (!group_planes(plans, count)) return group_base_bytes(plans, count);
+  size_t b = 0;
+  for (int32_t i = 0; i < count; ++i) b += plans[i]->group_plane_bytes();
   return b;
 }
 
@@ -651,7 +650,6 @@ bpx_status group_build(bpx_plan* const* plans, const float* const* A, const floa
   std::vector<std::vector<GroupTile>> by_tile(bf16_tile_count());
   std::vector<std::vector<int64_t>> key(bf16_tile_count());
   char* w = static_cast<char*>(ws);
-  char* packed = w + base;
   int64_t tb = 0, tp = 0;
   int32_t max_slots = 0;
   size_t max_program = 0;
@@ -689,9 +687,8 @@ bpx_status group_build(bpx_plan* const* plans, const float* const* A, const floa
     if (split) {
       PlaneParams& q = d.pl;
       plane_params(pl, p, &q);
-      q.ap = reinterpret_cast<unsigned short*>(packed);
+      q.ap = reinterpret_cast<unsigned short*>(planes);  // (in the place of bt_hi)
       q.bp = q.ap + (size_t)pl->plane_rows() * pl->plane_kc() * 16 * q.planes;
-      packed += bpx_plan::align256(pl->packed_bytes());
       pack_blocks = planes_group_setup(&q);
       p.tiles_m = q.tiles_m;
       p.tiles_n = q.tiles_n;
@@ -746,7 +743,7 @@ bpx_status group_build(bpx_plan* const* plans, const float* const* A, const floa
     tb += split ? pack_blocks : (int64_t)d.b_tn * d.b_tk;
     pstart[i] = tp;
     if (pe.nsteps > 0) tp += (pl->Mb * (pl->N / 4) + 127) / 128;
-    w += bpx_plan::align256(pl->base_bytes());
+    w += split ? pl->group_plane_bytes() : bpx_plan::align256(pl->base_bytes());
   }
   if ((size_t)max_slots * 128 * 16 + max_program > 160 * 1024)
     return fail(BPX_E_UNSUPPORTED, "peel needs more LDS than a workgroup has");
@@ -971,6 +968,22 @@ bpx_status bpx_code_csr(const bpx_code* code, const int32_t** col_ptr, const int
 
 void bpx_code_free(bpx_code* code) { delete code; }
 
+// The partial tiles a plan's products take on packed operands (256 CUs; no GPU is
+// asked).
+static void plan_parts(bpx_plan* plan) {
+  if (!plan->decodable || !plan->has_planes()) return;
+  GemmParams g{};
+  g.M = plan->M;
+  g.K = plan->K;
+  g.N = plan->N;
+  g.Mb = plan->Mb;
+  g.n_sym = (int32_t)plan->computed.size();
+  PlaneParams q;
+  plane_params(plan, g, &q);
+  q.part_tiles = bpx_plan::kPartTiles;
+  plan->part_want = plan->is_fp8() ? fp8_part_tiles(q) : planes_part_tiles(q, plan->pass_counts());
+}
+
 bpx_status bpx_plan_create(const bpx_code* code, const int32_t* arrival, int32_t n_arrival,
                            int32_t n_lost, int32_t mode, int64_t M, int64_t K, int64_t N,
                            int32_t prec, bpx_plan** out) {
@@ -984,6 +997,7 @@ bpx_status bpx_plan_create(const bpx_code* code, const int32_t* arrival, int32_t
     delete p;
     return fail(BPX_E_INVALID, err);
   }
+  plan_parts(p);
   *out = p;
   if (st == BPX_E_UNDECODABLE) return fail(BPX_E_UNDECODABLE, "available columns do not peel");
   return BPX_OK;
@@ -1011,6 +1025,7 @@ bpx_status bpx_plan_create2d(const bpx_code* code, const int32_t* arrival, int32
     delete p;
     return fail(BPX_E_INVALID, err);
   }
+  plan_parts(p);
   *out = p;
   if (st == BPX_E_UNDECODABLE) return fail(BPX_E_UNDECODABLE, "available columns do not peel");
   return BPX_OK;

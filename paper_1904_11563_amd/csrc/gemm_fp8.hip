@@ -997,12 +997,24 @@ hipError_t launch_pack_fp8(const PlaneParams& p0, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// The tiles of a packed product and how the last round of them is split.
+static int64_t split_packed(PlaneParams* p, int64_t cus) {
+  planes_tiles(p);
+  const int64_t T = (int64_t)p->tiles_m * p->tiles_n;
+  planes_split(p, nullptr, T, p->planes == 2 ? 1.3 : 0.7, 4, cus);
+  return T;
+}
+
+int32_t fp8_part_tiles(const PlaneParams& p0) {
+  PlaneParams p = p0;
+  const int64_t T = split_packed(&p, 256);
+  return planes_parts(p, T);
+}
+
 hipError_t launch_gemm_fp8_packed(const PlaneParams& p0, hipStream_t stream) {
   PlaneParams p = p0;
-  planes_tiles(&p);
+  const int64_t T = split_packed(&p, device_cu_count());
   p.row_group = 2;
-  const int64_t T = (int64_t)p.tiles_m * p.tiles_n;
-  planes_split(&p, nullptr, T, p.planes == 2 ? 1.3 : 0.7, 4);
   hipLaunchKernelGGL(p.planes == 2 ? gemm_fp8_packed_kernel<1> : gemm_fp8_packed_kernel<0>,
                      dim3((unsigned)(p.full + (T - p.full) * p.split)), dim3(NT), 0, stream, p);
   const hipError_t e = hipGetLastError();

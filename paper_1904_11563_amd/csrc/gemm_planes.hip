@@ -754,8 +754,8 @@ static int64_t longest_queue(const int32_t* passes, int64_t n_sym, int64_t per, 
 // round, and the symbols' passes (host memory) give the time of the others:
 // 4096 x 2048 x 4096, 288 large tiles of up to three passes, takes three
 // passes' time on 256 CUs however the last tiles are split.
-double planes_split(PlaneParams* p, const int32_t* passes, int64_t T, double us, int min_chunks) {
-  const int64_t S = device_cu_count();
+double planes_split(PlaneParams* p, const int32_t* passes, int64_t T, double us, int min_chunks,
+                    int64_t S) {
   const bool grid = p->grid > 1;
   const int64_t per = grid ? T / p->n_sym : 1;
   const int64_t units = grid ? p->n_passes * per : T;
@@ -817,7 +817,7 @@ static hipError_t launch_gemm_tiles(const PlaneParams& p, int64_t T, hipStream_t
 // -> 67 us).  The large tile keeps what the model puts within 7 %: it draws less
 // power, which the model leaves out (Construction B, 8192 x 8192 x 4096, 3.75
 // rounds of large tiles: FP32 4.52 ms, 4.76 in small ones).
-static double choose_tiles(PlaneParams* p, const int32_t* passes, int64_t* tiles) {
+static double choose_tiles(PlaneParams* p, const int32_t* passes, int64_t S, int64_t* tiles) {
   planes_tiles(p);
   const int64_t syms = p->grid > 1 ? p->n_sym : 1, lim = 0x7fffffff / 32;
   const int64_t T = (int64_t)p->tiles_m * p->tiles_n * syms;
@@ -827,18 +827,31 @@ static double choose_tiles(PlaneParams* p, const int32_t* passes, int64_t* tiles
   tiles_of_128(&s);
   const int64_t T128 = (int64_t)s.tiles_m * s.tiles_n * syms;
   const int P = p->planes;
-  const double t = planes_split(p, passes, T, P == 3 ? 2.0 : P == 2 ? 1.05 : 0.45, 8);
+  const double t = planes_split(p, passes, T, P == 3 ? 2.0 : P == 2 ? 1.05 : 0.45, 8, S);
   if (T128 > lim) return t;
-  const double t128 = planes_split(&s, passes, T128, P == 3 ? 0.53 : P == 2 ? 0.295 : 0.123, 8);
+  const double t128 =
+      planes_split(&s, passes, T128, P == 3 ? 0.53 : P == 2 ? 0.295 : 0.123, 8, S);
   if (t128 >= 0.93 * t) return t;
   *p = s;
   *tiles = T128;
   return t128;
 }
 
+int32_t planes_parts(const PlaneParams& p, int64_t T) {
+  const int64_t pieces = (T - p.full) * p.split, per = (256 / p.tile) * (256 / p.tile);
+  return p.split > 1 ? (int32_t)((pieces + per - 1) / per) : 0;
+}
+
+int32_t planes_part_tiles(const PlaneParams& p0, const int32_t* passes) {
+  PlaneParams p = p0;
+  int64_t T;
+  choose_tiles(&p, passes, 256, &T);
+  return planes_parts(p, T);
+}
+
 hipError_t launch_gemm_planes(PlaneParams* p, const int32_t* passes, hipStream_t stream) {
   int64_t T;
-  choose_tiles(p, passes, &T);
+  choose_tiles(p, passes, device_cu_count(), &T);
   if (T > 0x7fffffff / 32) return hipErrorInvalidValue;
   return p->tile == 128 ? launch_gemm_tiles<128>(*p, T, stream)
                         : launch_gemm_tiles<256>(*p, T, stream);
@@ -851,7 +864,7 @@ hipError_t launch_gemm_planes(PlaneParams* p, const int32_t* passes, hipStream_t
 double planes_us(const PlaneParams& p0) {
   PlaneParams p = p0;
   int64_t T;
-  const double gemm = choose_tiles(&p, nullptr, &T);
+  const double gemm = choose_tiles(&p, nullptr, device_cu_count(), &T);
   const double K = (double)p.K, N = (double)p.N, rows = (double)p.n_sym * (double)p.Mb;
   const double bytes = 4.0 * K * ((double)p.M + N) + 4.0 * p.planes * K * (rows + N) +
                        12.0 * rows * N;

@@ -44,6 +44,7 @@ struct PlaneOps {
   std::vector<int32_t> a_ops, b_ops, ids;  // {offset, count}
   std::vector<int32_t> sym_passes;         // {first pass, passes}
   std::vector<int32_t> passes;             // {A op, B op}
+  std::vector<int32_t> counts;             // passes of each symbol
 };
 
 struct bpx_plan {
@@ -173,7 +174,7 @@ struct bpx_plan {
     return off[6];
   }
   // Operands packed in the order of MFMA fragments (gemm_planes.hip: BF16
-  // planes; gemm_fp8.hip: codes), behind the parts above.
+  // planes; gemm_fp8.hip: codes).
   int32_t planes() const {
     switch (prec) {
       case BPX_PREC_F32: return 3;
@@ -202,9 +203,10 @@ struct bpx_plan {
   // ... and at most one symbol (summed without rounding to FP32 in between).
   int32_t max_passes() const {
     int32_t n = 1;
-    for (size_t i = 1; i < ops.sym_passes.size(); i += 2) n = std::max(n, ops.sym_passes[i]);
+    for (int32_t c : ops.counts) n = std::max(n, c);
     return n;
   }
+  const int32_t* pass_counts() const { return ops.counts.data(); }
   double n_macs() const { return (double)n_products() * (double)Mb * (double)K * (double)Nb; }
   int64_t plane_tiles() const {
     return grid > 1 ? (int64_t)computed.size() * (r256(Mb) / 256) * (r256(Nb) / 256)
@@ -244,16 +246,21 @@ struct bpx_plan {
              (double)computed.size() * (double)r128(Mb) / 128 * (double)kc < (double)lim;
     return plane_rows() / 32 * ((kc + 15) / 16) + plane_cols() / 64 * ((kc + 3) / 4) < lim;
   }
-  // Packed operands of a grouped product (no flags, no partial tiles).
   size_t packed_bytes() const {
-    return (size_t)(plane_rows() + plane_cols()) / 32 * plane_kc() * a_chunk_bytes();
+    return (size_t)plane_kc() * ((size_t)plane_rows() / 32 * a_chunk_bytes() +
+                                 (size_t)plane_cols() / 32 * b_chunk_bytes());
   }
+  // Workspace of a grouped product on split planes (no flags, no partial tiles).
+  size_t group_plane_bytes() const { return align256(y_bytes()) + align256(packed_bytes()); }
   // Offsets of the plane parts, from the start of the workspace: packed A,
-  // packed B, flags (FP32) or scales (FP8) of A, of B (FP32: then of up to four tiles per 256 x
-  // 256), partial tiles; [5] the end.
-  void plane_layout(size_t off[6]) const {
+  // packed B, flags (FP32) or scales (FP8) of A, of B (FP32: then of up to four
+  // tiles per 256 x 256); [4] the end, what a call on packed operands has to
+  // bring.  Of the parts of layout() these calls use Y and, for FP32, the partial
+  // tiles; BF16's planes of B give up their place (packed A and B are larger), the
+  // FP8 codes keep theirs.
+  void plane_layout(size_t off[5]) const {
     const size_t kc = (size_t)plane_kc();
-    size_t b = base_bytes(), sa = 0, sb = 0;
+    size_t b = is_bf16() ? align256(y_bytes()) : base_bytes(), sa = 0, sb = 0;
     if (planes() == 3) {
       sa = (size_t)(plane_rows() / 32) * ((kc + 15) / 16) * 4;
       sb = ((size_t)(plane_cols() / 64) * ((kc + 3) / 4) + 4 * (size_t)plane_tiles()) * 4;
@@ -270,20 +277,40 @@ struct bpx_plan {
     off[3] = b;
     b += align256(sb);
     off[4] = b;
-    b += (size_t)plane_part_tiles() * 65536 * sizeof(float);
-    off[5] = b;
   }
-  // At most 16 pieces of a tile, of 8 k chunks (FP8: 4) at least.
+  size_t plane_bytes() const {
+    size_t off[5];
+    plane_layout(off);
+    return off[4];
+  }
+  // Partial tiles (256 x 256 FP32) of tiles split along K: at most 16 pieces of a
+  // tile, of 8 k chunks (FP8: 4) at least.  part_want is what the split takes on
+  // 256 CUs; a card run in partitions of fewer CUs splits otherwise, which gets
+  // room for 256 as long as that is no more than the packed operands themselves.
   static constexpr int32_t kPartTiles = 512;
+  static constexpr size_t kPartBytes = 65536 * sizeof(float);
+  int32_t part_want = 0;
   int32_t plane_part_tiles() const {
     const int64_t q = std::min<int64_t>(16, plane_kc() / (is_fp8() ? 4 : 8));
-    return q < 2 ? 0 : (int32_t)std::min<int64_t>(plane_tiles() * q, kPartTiles);
+    if (q < 2) return 0;
+    const int64_t room = std::min<int64_t>(256, (int64_t)(packed_bytes() / kPartBytes));
+    return (int32_t)std::max<int64_t>(part_want, std::min<int64_t>(plane_tiles() * q, room));
+  }
+  // Where a call with this much workspace keeps them, and how many: behind the
+  // packed operands, or in layout()'s place for them if that holds more.
+  int32_t plane_parts(size_t have, size_t* at) const {
+    size_t off[7];
+    layout(off);
+    const size_t end = plane_bytes(), most = (size_t)plane_part_tiles();
+    const size_t own = std::min(most, part_bytes() / kPartBytes);
+    const size_t behind = have > end ? std::min(most, (have - end) / kPartBytes) : 0;
+    *at = behind >= own ? end : off[1];
+    return (int32_t)std::max(own, behind);
   }
   size_t ws_bytes() const {
     if (!has_planes()) return base_bytes();
-    size_t off[6];
-    plane_layout(off);
-    return off[5];
+    const size_t most = (size_t)plane_part_tiles();
+    return plane_bytes() + (most > part_bytes() / kPartBytes ? most * kPartBytes : 0);
   }
 };
 

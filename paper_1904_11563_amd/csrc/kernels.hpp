@@ -210,7 +210,13 @@ hipError_t launch_gemm_fp8_packed(const PlaneParams& p, hipStream_t stream);
 // k chunk of a tile in us (returns the time it expects); and the kernel that
 // sums the pieces.
 void planes_tiles(PlaneParams* p);
-double planes_split(PlaneParams* p, const int32_t* passes, int64_t T, double us, int min_chunks);
+double planes_split(PlaneParams* p, const int32_t* passes, int64_t T, double us, int min_chunks,
+                    int64_t cus);
+// Room for partial tiles (of 256 x 256) that a split takes; that a product's split
+// takes on 256 CUs (host work only).
+int32_t planes_parts(const PlaneParams& p, int64_t T);
+int32_t planes_part_tiles(const PlaneParams& p, const int32_t* passes);
+int32_t fp8_part_tiles(const PlaneParams& p);
 hipError_t launch_planes_reduce(const PlaneParams& p, int64_t T, hipStream_t stream);
 
 int32_t bf16_tile_count();

@@ -266,10 +266,12 @@ int make_plan(const bpx_code& code, const int32_t* arrival, int32_t n_arrival, i
       o.sym_passes.push_back((int32_t)(o.passes.size() / 2));
       if (same_r || same_c) {
         o.sym_passes.push_back(1);
+        o.counts.push_back(1);
         o.passes.push_back(op(a_of, o.a_ops, same_c ? r : std::vector<int32_t>{r[0]}));
         o.passes.push_back(op(b_of, o.b_ops, same_c ? std::vector<int32_t>{c[0]} : c));
       } else {
         o.sym_passes.push_back(deg);
+        o.counts.push_back(deg);
         for (int32_t m = 0; m < deg; ++m) {
           o.passes.push_back(op(a_of, o.a_ops, {r[m]}));
           o.passes.push_back(op(b_of, o.b_ops, {c[m]}));

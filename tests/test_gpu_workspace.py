@@ -2,6 +2,7 @@
 workspace that the plan's parts fit in is accepted, and what does not fit, or
 cannot be addressed, is left to the kernels that need less."""
 import ctypes
+import functools
 import sys
 
 import pytest
@@ -14,7 +15,9 @@ torch = pytest.importorskip("torch")
 from paper_1904_11563_amd import bpx  # noqa: E402
 
 
-def _code(s):
+@functools.lru_cache
+def _code():
+    s = inputs.CODE_1284
     return bpx.Code.search(s.n, s.k, s.b, s.sigma, s.seed, s.restarts, s.iters, walk=s.walk)
 
 
@@ -63,3 +66,103 @@ def test_plan_without_parts_takes_any_workspace(entry):
     assert _raw(entry, plan, A, B, C, buf.data_ptr(), need) == 0
     assert not bool((buf == 0xA5).all())
     assert float(torch.linalg.norm(C.double() - R) / torch.linalg.norm(R)) <= 1e-5
+
+
+def _run(entry, plan, A, B, ws=None):
+    C = torch.full((plan.M, -(-plan.N // 4) * 4), float("nan"), device="cuda")[:, :plan.N]
+    if entry == "noalloc":
+        bpx.coded_matmul_noalloc(plan, A, B, C)
+    else:
+        bpx.coded_matmul(plan, A, B, C, ws)
+    torch.cuda.synchronize()
+    return C.clone()
+
+
+def _err(X, R):
+    return float(torch.linalg.norm(X.double() - R) / torch.linalg.norm(R))
+
+
+def _view(x):
+    r, c = x.shape
+    t = torch.zeros((r, -(-c // 4) * 4), device="cuda")
+    t[:, :c] = x
+    return t[:, :c]
+
+
+# Products whose packed operands fit in the library's 32 MiB, with and without all
+# the room for partial tiles: the same kernels, the same bits
+@pytest.mark.parametrize("prec", [bpx.PREC_F32, bpx.PREC_BF16X3, bpx.PREC_BF16])
+@pytest.mark.parametrize("M,K,N", [(1024, 1024, 1024), (1100, 1028, 777), (419, 2052, 373)])
+def test_library_scratch_holds_packed_operands(M, K, N, prec):
+    arrival, _ = inputs.shifted_exp_arrival(0, 12)
+    plan = bpx.Plan(_code(), arrival, 0, bpx.MODE_STRAGGLER, M, K, N, prec)
+    plan.upload()
+    A, B = _ops(2, M, K, N)
+    A, B = _view(A), _view(B)
+    full = torch.full((plan.workspace_bytes()[0],), 0xA5, dtype=torch.uint8, device="cuda")
+    want = _run("matmul", plan, A, B, full)
+    print("scratch", M, K, N, prec, len(full) >> 20, "MiB", file=sys.stderr, flush=True)
+    assert torch.equal(_run("noalloc", plan, A, B), want)
+    if prec == bpx.PREC_F32:      # not those of the kernels that read A and B directly
+        direct = _run("matmul", plan, A, B, full[:plan.workspace_layout()[6]])
+        assert not torch.equal(direct, want)
+
+
+# Every size from the parts alone to all of it: exact on integers, FP32 accuracy
+@pytest.mark.parametrize("prec", [bpx.PREC_F32, bpx.PREC_FP8])
+@pytest.mark.parametrize("M,K,N", [(419, 3428, 373), (2048, 2048, 1024)])
+def test_any_workspace_between(M, K, N, prec):
+    arrival, _ = inputs.shifted_exp_arrival(0, 12)
+    plan = bpx.Plan(_code(), arrival, 0, bpx.MODE_STRAGGLER, M, K, N, prec)
+    most, least = plan.workspace_bytes()[0], plan.workspace_layout()[6]
+    buf = torch.full((most,), 0xA5, dtype=torch.uint8, device="cuda")
+    g = torch.Generator(device="cuda").manual_seed(3)
+    A = _view(torch.randint(-8, 9, (M, K), generator=g, device="cuda").float())
+    B = _view(torch.randint(-8, 9, (K, N), generator=g, device="cuda").float())
+    Af, Bf = map(_view, _ops(4, M, K, N))
+    R = Af.double() @ Bf.double()
+    sizes = [least, (least + most) // 2 // 256 * 256, most - (1 << 20), most - 256, most]
+    for nbytes in sizes:
+        if nbytes < least:
+            continue
+        print("workspace", M, K, N, prec, nbytes, "of", most, file=sys.stderr, flush=True)
+        buf.fill_(0xA5)
+        if prec == bpx.PREC_F32:
+            assert torch.equal(_run("matmul", plan, A, B, buf[:nbytes]).double(),
+                               A.double() @ B.double())
+            assert _err(_run("matmul", plan, Af, Bf, buf[:nbytes]), R) <= 1e-5
+        else:            # the codes are the same: only the MFMA's own summation differs
+            got = _run("matmul", plan, Af, Bf, buf[:nbytes])
+            direct = got if nbytes == least else direct
+            # 1.5e-5 per product, times what the releases make of it
+            assert _err(got, direct.double()) <= 1e-3
+        assert bool((buf[nbytes:] == 0xA5).all())
+
+
+# FP8 products past 2^31 multiply-adds: the documented codes and scales of B in a
+# workspace of the parts alone, left alone in a larger one
+def test_fp8_codes_in_a_workspace_of_the_parts():
+    M, K, N = 2048, 2048, 1024
+    arrival, _ = inputs.shifted_exp_arrival(0, 12)
+    plan = bpx.Plan(_code(), arrival, 0, bpx.MODE_STRAGGLER, M, K, N,
+                    bpx.PREC_FP8)
+    off, most = plan.workspace_layout(), plan.workspace_bytes()[0]
+    assert most > off[6]
+    A, B = _ops(5, M, K, N)
+    B = B * torch.logspace(-3, 3, K, device="cuda")[:, None]
+    blocks = B.view(K // 128, 128, N // 128, 128).abs().amax(dim=(1, 3))
+    scale = torch.exp2(torch.ceil(torch.log2(blocks.double() / 448)))
+    want = (B.double() / scale.repeat_interleave(128, 0).repeat_interleave(128, 1)).float()
+    want = want.to(torch.float8_e4m3fn).t().contiguous().view(torch.uint8)
+    for nbytes in (off[6], most):
+        ws = torch.full((nbytes,), 0xA5, dtype=torch.uint8, device="cuda")
+        print("fp8 codes", nbytes, "of", most, file=sys.stderr, flush=True)
+        C = torch.empty((M, N), device="cuda")
+        bpx.coded_gemm(plan, A, B, C, ws)
+        torch.cuda.synchronize()
+        if nbytes == off[6]:
+            assert torch.equal(ws[off[4]:off[4] + N * K].view(N, K), want)
+            assert torch.equal(ws[off[5]:off[6]].view(torch.float32)[:scale.numel()].double(),
+                               scale.flatten())
+        else:
+            assert bool((ws[off[1]:off[6]] == 0xA5).all())
