@@ -391,15 +391,16 @@ bpx_status bpx_coded_matmul_noalloc(bpx_plan* plan, const float* A, int64_t lda,
  *   block of per-product descriptors and a tile list (hipMalloc + one
  *   synchronous copy).  ws (256-byte aligned) and every operand pointer are
  *   baked into the descriptors and must stay valid while the group lives.
- *   Each product gets the GEMM tile shape bpx_set_tile_table selects for
- *   its (Mb, N, K); tiles of one shape form one persistent launch whose
- *   workgroups stride over the tile list, longest K first.  On split planes
- *   all products share one persistent launch of 256x256 tiles, dealt to the
- *   workgroups by their K.
+ *   Products whose (Mb, N, K) bpx_set_tile_table names a GEMM tile shape for,
+ *   and all of a group that does not run on split planes, take that shape or the
+ *   default; tiles of one shape form one persistent launch whose workgroups
+ *   stride over the tile list, longest K first.  The products on split planes
+ *   share one persistent launch of 256x256 tiles, dealt to the workgroups by
+ *   their K.
  *   Returns BPX_E_UNDECODABLE if any plan is undecodable (nothing created).
- * bpx_group_launch: enqueue, on stream: one grouped B-split (pack) launch, one
- *   persistent grouped GEMM launch per tile shape present, one grouped peel
- *   launch.  No allocation, copy or synchronisation: graph-capturable.
+ * bpx_group_launch: enqueue, on stream: one grouped B-split or pack launch (one
+ *   of each where both are needed), one persistent grouped GEMM launch per tile
+ *   shape present, one grouped peel launch.  No allocation, copy or synchronisation: graph-capturable.
  *   Calls on one group must not overlap (they share the workspace).
  * bpx_coded_matmul_grouped: create, launch, synchronise the stream, free. */
 typedef struct bpx_group bpx_group;
@@ -421,7 +422,9 @@ bpx_status bpx_coded_matmul_grouped(bpx_plan* const* plans, const float* const* 
  * table mapping shape buckets (log2 of ceil(x/128), clamped to [0, 7], for
  * x = Mb, N, K) and the precision to a tile-shape index, indexed
  * ((prec*8 + bMb)*8 + bN)*8 + bK (8*8*8*5 entries; NULL clears it; entries
- * < 0 fall back to the default shape).  bpx_force_tile forces one shape for
+ * < 0 fall back to the default).  Shapes are those of the kernels that read A and
+ * B directly: a product that the table names one for runs on these, also where
+ * its operands would be packed, and in a group only it.  bpx_force_tile forces one shape for
  * every call (for the autotuner and tests), which also keeps every call on
  * the two-launch form; -1 returns to the table.
  * BF16 / BF16x3 shapes 0-3 are 128x128, 64x128, 128x256 and 64x256 tiles of

@@ -3,12 +3,15 @@
 Products are grouped into shape buckets (log2 of ceil(x/128), clamped to
 [0, 7], for x = Mb, N, K: the buckets of the library's table).  Tiles are
 tuned where they are used, inside one grouped launch of the whole batch:
-starting from the library's default shape for every product, each bucket
+starting from the library's own choice for every product, each bucket
 (largest total work first) tries every compiled shape for its products
 while the others keep theirs, and keeps the shape that gives the shortest
-grouped GEMM phase.  A change must beat the default, timed again in the
-same round, by more than 1 % and by no more than 1.5 times the bucket's
-share of the work (a bucket cannot save more than its own time; larger
+first two phases of the grouped launch (B split or pack, then the GEMMs).
+The library's own choice is the 128 x 256 flat tiling or, in groups of
+enough work, packed operands; a shape in the table takes its products off
+packed operands, and no others.  A change must beat the library's choice,
+timed again in the same round, by more than 1 % and by no more than 1.5
+times the bucket's share of the work (a bucket cannot save more than its own time; larger
 "gains" are noise).  Timing products
 one at a time misleads here: a small product alone cannot fill the GPU with
 large tiles, but inside the batch every CU is busy anyway.
@@ -44,19 +47,24 @@ def index(prec: int, Mb: int, N: int, K: int) -> int:
     return ((prec * 8 + bucket(Mb)) * 8 + bucket(N)) * 8 + bucket(K)
 
 
-KERNEL_SOURCE = os.path.join(HERE, "csrc", "gemm_bf16.hip")
-# The library's BF16 / BF16x3 shape where the table has no entry (the flat
-# 128 x 256 tiling, tile 4 of bpx_tile_count): an entry naming it would be
-# no override at all.
+# The sources a table's times depend on: the tuned kernels, the packed operands
+# they compete with, and the rules that choose between them.
+KERNEL_SOURCES = ("gemm_bf16.hip", "gemm_planes.hip", "planes.hpp", "kernels.hpp", "host.hpp",
+                  "abi.cpp")
+# The shape where the table has no entry and operands are not packed (the flat
+# 128 x 256 tiling, tile 4 of bpx_tile_count).
 DEFAULT_TILE = 4
 
 
-def kernel_source_hash() -> str:
-    """Hash of the source holding the tuned kernels: a table measured on
-    other kernels is stale."""
+def kernel_source_hash(folder: str = os.path.join(HERE, "csrc")) -> str:
+    """Hash of the sources a table's times depend on: a table measured on
+    others is stale."""
     import hashlib
-    with open(KERNEL_SOURCE, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
+    h = hashlib.sha256()
+    for name in KERNEL_SOURCES:
+        with open(os.path.join(folder, name), "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()[:16]
 
 
 def load(path: str = TABLE_PATH) -> str:
@@ -90,11 +98,11 @@ def accept(ref_ms: float, best_ms: float, share: float) -> bool:
 
 
 def _gemm_phase_ms(bpx, torch, plans, As, Bs, Cs, ws, reps):
-    """Shortest of `reps` timings of the grouped GEMM phase (group built with
-    the table currently installed)."""
+    """Shortest of `reps` timings of the grouped split, pack and GEMM phases
+    (group built with the table currently installed)."""
     group = bpx.Group(plans, As, Bs, Cs, ws)
-    group.launch_phase(0)                      # B split, once
     for _ in range(2):
+        group.launch_phase(0)
         group.launch_phase(1)
     torch.cuda.synchronize()
     best = float("inf")
@@ -102,6 +110,7 @@ def _gemm_phase_ms(bpx, torch, plans, As, Bs, Cs, ws, reps):
         e0 = torch.cuda.Event(enable_timing=True)
         e1 = torch.cuda.Event(enable_timing=True)
         e0.record()
+        group.launch_phase(0)
         group.launch_phase(1)
         e1.record()
         torch.cuda.synchronize()
@@ -132,11 +141,12 @@ def tune_grouped(prec_name: str, shapes, codes_by_k, reps: int = 5, seed: int = 
         Bs.append(torch.randn(K, N, device=dev))
         Cs.append(torch.empty(M, N, device=dev))
     ws = torch.empty(bpx.group_workspace_bytes(plans), dtype=torch.uint8, device=dev)
+    packed = ws.numel() > sum(-(-p.workspace_layout()[6] // 256) * 256 for p in plans)
     n_tiles = bpx.tile_count(prec)
     table = [-1] * N_ENTRIES
     bpx.set_tile_table(table)
     best = _gemm_phase_ms(bpx, torch, plans, As, Bs, Cs, ws, reps)
-    log(f"default shapes: grouped GEMM {best:.3f} ms")
+    log(f"library's choice: split, pack and GEMMs {best:.3f} ms")
     chosen = {}
     total = sum(work.values())
     for key in sorted(work, key=lambda x: -work[x]):
@@ -147,7 +157,7 @@ def tune_grouped(prec_name: str, shapes, codes_by_k, reps: int = 5, seed: int = 
         ref = _gemm_phase_ms(bpx, torch, plans, As, Bs, Cs, ws, reps)
         times = {}
         for t in range(n_tiles):
-            if t == DEFAULT_TILE:
+            if t == DEFAULT_TILE and not packed:
                 continue  # the default is what the reference run used
             table[key] = t
             bpx.set_tile_table(table)
@@ -191,7 +201,7 @@ def main():
     shapes = inputs.batch_shapes(0, args.count)
     entries, ms = tune_grouped(args.prec, shapes, {4: c4, 8: c8}, reps=args.reps)
     save(entries, {"prec": args.prec, "workload": "batch", "count": args.count,
-                   "criterion": "grouped GEMM phase of the whole batch",
+                   "criterion": "split, pack and GEMM phases of the whole batch",
                    "grouped_gemm_ms": round(ms, 4), "seconds": round(time.time() - t0, 1),
                    "gemm_source": kernel_source_hash()})
     print(f"saved {len(entries)} bucket overrides to {TABLE_PATH}", flush=True)

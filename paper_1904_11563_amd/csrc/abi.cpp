@@ -532,12 +532,13 @@ struct bpx_group {
   const int64_t* d_pstart = nullptr;
   const bpx::GroupTile* d_tiles = nullptr;
   const int32_t* d_bmap = nullptr;  // product of each split-B block
+  const int32_t* d_kmap = nullptr;  // planes: product of each pack block
   const int32_t* d_pmap = nullptr;  // product of each peel block
   const int64_t* d_wstart = nullptr;  // first peel block of each peel workgroup
   const int32_t* d_tstart = nullptr;  // planes: first tile of each GEMM workgroup
-  int32_t planes = 0;                 // planes per operand (0: direct kernels)
+  int32_t planes = 0;                 // planes per operand (0: direct kernels only)
   int32_t gemm_grid = 0;
-  int64_t total_b = 0, total_p = 0, peel_grid = 0;
+  int64_t total_b = 0, total_k = 0, total_p = 0, peel_grid = 0;
   int32_t max_slots = 0;
   size_t max_program = 0;
   std::vector<bpx::GroupLaunch> launches;
@@ -552,17 +553,19 @@ size_t group_base_bytes(bpx_plan* const* plans, int32_t count) {
   for (int32_t i = 0; i < count; ++i) b += bpx_plan::align256(plans[i]->base_bytes());
   return b;
 }
-// ... whether the group runs on split planes: enough 256 x 256 tiles to give
+// ... whether those of the products that are not skipped run on split planes:
+// enough 256 x 256 tiles to give
 // every CU one (32 products of 256-1024, 221 tiles, took the same time either
 // way; 272 tiles of 2048 ran 1.2 times as fast), and products large enough
 // that each packed value is multiplied often, in multiply-adds per value
 // (BF16x3: 128-640 with 160 per value lost 3 %, 256-4096 with 650 gained 18 %
 // and with 1180 44 %; BF16, which packs half the bytes, gained 12 % at 160) ...
-bool group_planes(bpx_plan* const* plans, int32_t count) {
+bool group_planes(bpx_plan* const* plans, int32_t count, const std::vector<char>& skip = {}) {
   int64_t tiles = 0;
   double macs = 0.0, values = 0.0;
   for (int32_t i = 0; i < count; ++i) {
     const bpx_plan* p = plans[i];
+    if (!skip.empty() && skip[i]) continue;
     if (!p->planes_fit() || p->grid != 1) return false;
     tiles += p->plane_tiles();
     const double rows = (double)p->computed.size() * (double)p->Mb;
@@ -639,18 +642,24 @@ bpx_status group_build(bpx_plan* const* plans, const float* const* A, const floa
   const size_t base = group_base_bytes(plans, count);
   if (!ws || ((uintptr_t)ws & 255u) || ws_bytes < base)
     return fail(BPX_E_INVALID, "workspace missing, not 256-byte aligned or too small");
-  // Split planes if the workspace holds them and no product's tile shape is
-  // named by the caller.
-  bool split = group_planes(plans, count) && ws_bytes >= group_ws_bytes(plans, count);
-  for (int32_t i = 0; i < count; ++i)
-    split = split && !tile_chosen(prec, plans[i]->Mb, plans[i]->N, plans[i]->K);
+  // Split planes if the workspace holds them, but for products whose tile shape
+  // the caller names: those alone run on the kernels that read A directly.
+  std::vector<char> direct(count, 0);
+  size_t need = 0;
+  for (int32_t i = 0; i < count; ++i) {
+    direct[i] = tile_chosen(prec, plans[i]->Mb, plans[i]->N, plans[i]->K);
+    need += direct[i] ? bpx_plan::align256(plans[i]->base_bytes()) : plans[i]->group_plane_bytes();
+  }
+  if (!group_planes(plans, count, direct) || ws_bytes < need) direct.assign(count, 1);
 
   std::vector<GroupDesc> desc(count);
   std::vector<int64_t> bstart(count), pstart(count);
   std::vector<std::vector<GroupTile>> by_tile(bf16_tile_count());
   std::vector<std::vector<int64_t>> key(bf16_tile_count());
+  std::vector<GroupTile> packed_tiles;
+  std::vector<int64_t> packed_key;
   char* w = static_cast<char*>(ws);
-  int64_t tb = 0, tp = 0;
+  int64_t tb = 0, tk = 0, tp = 0;
   int32_t max_slots = 0;
   size_t max_program = 0;
   for (int32_t i = 0; i < count; ++i) {
@@ -681,7 +690,7 @@ bpx_status group_build(bpx_plan* const* plans, const float* const* A, const floa
     p.kp = pl->kp();
     int32_t t = choose_tile(prec, pl->Mb, pl->N, pl->K);
     if (bf16_tile_is_flat(t) && !bf16_flat_ok(p)) t = 1;
-    if (split) t = 0;  // one list
+    const bool split = !direct[i];
     const TileShape sh = bf16_tile_shape(t);
     int64_t nt, pack_blocks = 0;
     if (split) {
@@ -718,8 +727,8 @@ bpx_status group_build(bpx_plan* const* plans, const float* const* A, const floa
       const int64_t rows = std::min<int64_t>(kRowGroup, panels - first);
       const int64_t r = q % per_group;
       const int64_t l = (first + r % rows) * p.tiles_n + r / rows;
-      by_tile[t].push_back(GroupTile{i, (int32_t)l});
-      key[t].push_back(pl->K);
+      (split ? packed_tiles : by_tile[t]).push_back(GroupTile{i, (int32_t)l});
+      (split ? packed_key : key[t]).push_back(pl->K);
     }
     PeelParams& pe = d.pe;
     pe.Y = p.Y;
@@ -739,8 +748,8 @@ bpx_status group_build(bpx_plan* const* plans, const float* const* A, const floa
     max_slots = std::max(max_slots, pl->n_lds_slots);
     d.b_tn = (int32_t)((pl->N + 63) / 64);
     d.b_tk = (int32_t)((pl->kp() + 63) / 64);
-    bstart[i] = tb;
-    tb += split ? pack_blocks : (int64_t)d.b_tn * d.b_tk;
+    bstart[i] = split ? tk : tb;  // (in its own list)
+    (split ? tk : tb) += split ? pack_blocks : (int64_t)d.b_tn * d.b_tk;
     pstart[i] = tp;
     if (pe.nsteps > 0) tp += (pl->Mb * (pl->N / 4) + 127) / 128;
     w += split ? pl->group_plane_bytes() : bpx_plan::align256(pl->base_bytes());
@@ -751,23 +760,15 @@ bpx_status group_build(bpx_plan* const* plans, const float* const* A, const floa
   std::vector<GroupTile> tiles;
   std::vector<GroupLaunch> launches;
   std::vector<int32_t> tstart;
+  auto longest_first = [](const std::vector<int64_t>& k) {
+    std::vector<size_t> idx(k.size());
+    for (size_t j = 0; j < idx.size(); ++j) idx[j] = j;
+    std::stable_sort(idx.begin(), idx.end(), [&](size_t a, size_t b) { return k[a] > k[b]; });
+    return idx;
+  };
   for (int32_t t = 0; t < (int32_t)by_tile.size(); ++t) {
     if (by_tile[t].empty()) continue;
-    std::vector<size_t> idx(by_tile[t].size());
-    for (size_t j = 0; j < idx.size(); ++j) idx[j] = j;
-    std::stable_sort(idx.begin(), idx.end(),
-                     [&](size_t a, size_t b) { return key[t][a] > key[t][b]; });
-    if (split) {
-      std::vector<GroupTile> sorted;
-      std::vector<int64_t> stages;
-      for (size_t j : idx) {
-        sorted.push_back(by_tile[t][j]);
-        stages.push_back((key[t][j] + 31) / 32);
-      }
-      g->gemm_grid = (int32_t)std::min<int64_t>((int64_t)sorted.size(), device_cu_count());
-      deal_tiles(sorted, stages, g->gemm_grid, &tiles, &tstart);
-      break;
-    }
+    const std::vector<size_t> idx = longest_first(key[t]);
     GroupLaunch L{t, (int32_t)tiles.size(), (int32_t)idx.size(), 0};
     for (size_t j : idx) tiles.push_back(by_tile[t][j]);
     const TileShape sh = bf16_tile_shape(t);
@@ -775,12 +776,26 @@ bpx_status group_build(bpx_plan* const* plans, const float* const* A, const floa
     L.grid = std::min(L.n, slots);
     launches.push_back(L);
   }
-  // block -> product maps of the split-B and peel grids
-  std::vector<int32_t> bmap(tb), pmap(tp);
-  for (int32_t i = 0; i < count; ++i) {
-    const int64_t bend = i + 1 < count ? bstart[i + 1] : tb;
+  if (!packed_tiles.empty()) {
+    std::vector<GroupTile> sorted;
+    std::vector<int64_t> stages;
+    for (size_t j : longest_first(packed_key)) {
+      sorted.push_back(packed_tiles[j]);
+      stages.push_back((packed_key[j] + 31) / 32);
+    }
+    g->gemm_grid = (int32_t)std::min<int64_t>((int64_t)sorted.size(), device_cu_count());
+    deal_tiles(sorted, stages, g->gemm_grid, &tiles, &tstart);
+  }
+  // block -> product maps of the split-B, pack and peel grids (blocks of a
+  // product follow each other, products in order)
+  std::vector<int32_t> bmap(tb), kmap(tk), pmap(tp);
+  int64_t bend = tb, kend = tk;
+  for (int32_t i = count; i-- > 0;) {
     const int64_t pend = i + 1 < count ? pstart[i + 1] : tp;
-    for (int64_t b = bstart[i]; b < bend; ++b) bmap[b] = i;
+    std::vector<int32_t>& map = direct[i] ? bmap : kmap;
+    int64_t& end = direct[i] ? bend : kend;
+    for (int64_t b = bstart[i]; b < end; ++b) map[b] = i;
+    end = bstart[i];
     for (int64_t b = pstart[i]; b < pend; ++b) pmap[b] = i;
   }
   // Peel workgroup ranges: a block of product i costs its program's steps
@@ -808,7 +823,8 @@ bpx_status group_build(bpx_plan* const* plans, const float* const* A, const floa
       cum += n * c;
     }
   }
-  // one device block: descriptors | bstart | pstart | tiles | bmap | pmap | wstart | tstart
+  // one device block: descriptors | bstart | pstart | tiles | bmap | pmap | wstart |
+  // tstart | kmap
   auto al = [](size_t x) { return (x + 255) / 256 * 256; };
   const size_t s0 = al(desc.size() * sizeof(GroupDesc));
   const size_t s1 = al(bstart.size() * 8);
@@ -818,7 +834,8 @@ bpx_status group_build(bpx_plan* const* plans, const float* const* A, const floa
   const size_t s5 = al(std::max<size_t>(pmap.size(), 1) * 4);
   const size_t s6 = al(wstart.size() * 8);
   const size_t s7 = al(std::max<size_t>(tstart.size(), 1) * 4);
-  std::string host(s0 + s1 + s2 + s3 + s4 + s5 + s6 + s7, '\0');
+  const size_t s8 = al(std::max<size_t>(kmap.size(), 1) * 4);
+  std::string host(s0 + s1 + s2 + s3 + s4 + s5 + s6 + s7 + s8, '\0');
   std::memcpy(&host[0], desc.data(), desc.size() * sizeof(GroupDesc));
   std::memcpy(&host[s0], bstart.data(), bstart.size() * 8);
   std::memcpy(&host[s0 + s1], pstart.data(), pstart.size() * 8);
@@ -827,6 +844,7 @@ bpx_status group_build(bpx_plan* const* plans, const float* const* A, const floa
   std::memcpy(&host[s0 + s1 + s2 + s3 + s4], pmap.data(), pmap.size() * 4);
   std::memcpy(&host[s0 + s1 + s2 + s3 + s4 + s5], wstart.data(), wstart.size() * 8);
   std::memcpy(&host[s0 + s1 + s2 + s3 + s4 + s5 + s6], tstart.data(), tstart.size() * 4);
+  std::memcpy(&host[s0 + s1 + s2 + s3 + s4 + s5 + s6 + s7], kmap.data(), kmap.size() * 4);
   void* dptr = nullptr;
   hipError_t e = hipMalloc(&dptr, host.size());
   if (e != hipSuccess) return hip_fail(e, "hipMalloc(group descriptors)");
@@ -850,9 +868,11 @@ bpx_status group_build(bpx_plan* const* plans, const float* const* A, const floa
   g->d_pmap = reinterpret_cast<const int32_t*>(dblock + s0 + s1 + s2 + s3 + s4);
   g->d_wstart = reinterpret_cast<const int64_t*>(dblock + s0 + s1 + s2 + s3 + s4 + s5);
   g->d_tstart = reinterpret_cast<const int32_t*>(dblock + s0 + s1 + s2 + s3 + s4 + s5 + s6);
-  g->planes = split ? plans[0]->planes() : 0;
+  g->d_kmap = g->d_tstart + s7 / 4;
+  g->planes = packed_tiles.empty() ? 0 : plans[0]->planes();
   g->peel_grid = pgrid;
   g->total_b = tb;
+  g->total_k = tk;
   g->total_p = tp;
   g->max_slots = max_slots;
   g->max_program = max_program;
@@ -863,16 +883,18 @@ bpx_status group_build(bpx_plan* const* plans, const float* const* A, const floa
 bpx_status group_launch(bpx_group* g, int32_t phase, hipStream_t stream) {
   hipError_t e;
   if (phase < 0 || phase == 0) {
-    e = g->planes ? launch_pack_planes_grouped(g->d_desc, g->d_bstart, g->d_bmap, g->total_b,
-                                               g->planes, stream)
-                  : launch_split_b_grouped(g->d_desc, g->d_bstart, g->d_bmap, g->total_b, stream);
+    e = launch_split_b_grouped(g->d_desc, g->d_bstart, g->d_bmap, g->total_b, stream);
+    if (e == hipSuccess)
+      e = launch_pack_planes_grouped(g->d_desc, g->d_bstart, g->d_kmap, g->total_k, g->planes,
+                                     stream);
     if (e != hipSuccess) return hip_fail(e, "grouped B-split or pack launch");
   }
-  if (g->planes && (phase < 0 || phase == 1)) {
-    e = launch_gemm_planes_grouped(g->d_desc, g->d_tiles, g->d_tstart, g->planes, g->gemm_grid,
-                                   stream);
-    if (e != hipSuccess) return hip_fail(e, "grouped GEMM launch");
-  } else if (phase < 0 || phase == 1) {
+  if (phase < 0 || phase == 1) {
+    if (g->planes) {
+      e = launch_gemm_planes_grouped(g->d_desc, g->d_tiles, g->d_tstart, g->planes, g->gemm_grid,
+                                     stream);
+      if (e != hipSuccess) return hip_fail(e, "grouped GEMM launch");
+    }
     const int32_t split = g->prec == BPX_PREC_BF16X3 ? 3 : 1;
     for (const GroupLaunch& L : g->launches) {
       e = launch_gemm_bf16_grouped(g->d_desc, g->d_tiles + L.offset, L.n, L.tile, split, L.grid,

@@ -39,3 +39,19 @@ def test_accept_rule():
     assert not autotune.accept(4.70, 4.60, 0.001)
     # a loss is never kept
     assert not autotune.accept(4.70, 4.80, 0.50)
+
+
+def test_table_is_stale_after_any_of_its_kernels_changed(tmp_path):
+    """The tuned kernels, the packed operands they compete with, the rules that
+    choose: a change of any makes a table stale."""
+    import os
+    import shutil
+    csrc = os.path.join(os.path.dirname(autotune.__file__), "csrc")
+    here = autotune.kernel_source_hash()
+    for name in ("gemm_bf16.hip", "gemm_planes.hip", "planes.hpp", "host.hpp", "abi.cpp"):
+        copy = tmp_path / name.replace(".", "_")
+        shutil.copytree(csrc, copy)
+        assert autotune.kernel_source_hash(str(copy)) == here
+        with open(copy / name, "a") as f:
+            f.write("// changed")
+        assert autotune.kernel_source_hash(str(copy)) != here, name

@@ -166,3 +166,57 @@ def test_fp8_codes_in_a_workspace_of_the_parts():
                                scale.flatten())
         else:
             assert bool((ws[off[1]:off[6]] == 0xA5).all())
+
+
+# A tile table that names a shape for one product of a group: that product on the
+# kernels that read A directly, the others on packed operands as without it
+def test_named_shape_takes_only_its_product_off_packed_operands():
+    from paper_1904_11563_amd import autotune
+    shapes = [(2048, 1024, 2048)] * 4 + [(2304, 512, 1800), (2048, 4096, 2048)]
+    plans = []
+    for i, (M, K, N) in enumerate(shapes):
+        arrival, _ = inputs.shifted_exp_arrival(i, 12)
+        plans.append(bpx.Plan(_code(), arrival, 0, bpx.MODE_STRAGGLER, M, K, N,
+                              bpx.PREC_BF16X3))
+    base = sum(-(-p.workspace_layout()[6] // 256) * 256 for p in plans)
+    nbytes = bpx.group_workspace_bytes(plans)
+    assert nbytes > base
+    ops = [_ops(20 + i, *s) for i, s in enumerate(shapes)]
+    As, Bs = [a for a, _ in ops], [b for _, b in ops]
+
+    def run(table, size, integers=False):
+        A = [torch.round(a * 4) for a in As] if integers else As
+        B = [torch.round(b * 4) for b in Bs] if integers else Bs
+        Cs = [torch.full((M, N), float("nan"), device="cuda") for M, _, N in shapes]
+        bpx.set_tile_table(table)
+        try:
+            ws = torch.full((size,), 0xA5, dtype=torch.uint8, device="cuda")
+            group = bpx.Group(plans, A, B, Cs, ws)
+        finally:
+            bpx.set_tile_table(None)
+        print("group with a table" if table else "group", size, file=sys.stderr, flush=True)
+        for _ in range(2):
+            group.launch()
+        torch.cuda.synchronize()
+        if integers:
+            for a, b, c in zip(A, B, Cs):
+                assert torch.equal(c.double(), a.double() @ b.double())
+        del group
+        return Cs
+
+    named = 5
+    table = [-1] * autotune.N_ENTRIES
+    M, K, N = shapes[named]
+    table[autotune.index(bpx.PREC_BF16X3, plans[named].info()["Mb"], N, K)] = 1
+    packed, direct = run(None, nbytes), run(None, base)
+    mixed = run(table, nbytes)
+    for i in range(len(shapes)):
+        assert _err(mixed[i], As[i].double() @ Bs[i].double()) <= 1e-4
+        if i != named:
+            assert torch.equal(mixed[i], packed[i]), i
+    assert not torch.equal(mixed[named], packed[named])
+    run(table, nbytes, integers=True)
+    # named throughout: the direct kernels, whatever the workspace
+    table = [4] * autotune.N_ENTRIES
+    for got, want in zip(run(table, nbytes), direct):
+        assert torch.equal(got, want)
