@@ -78,8 +78,7 @@ struct bpx_plan {
   // The same program for the peel whose values all stay in LDS, one record per
   // step: {src, nsub | f64 << 8 | write << 9, eight subtrahends a byte each (the
   // steps that recover them), brow | bcol << 16, where in peel_more the other
-  // subtrahends are, 0, 0}.  A record of zeros follows the last.  Empty if the
-  // program has more steps than a byte names.
+  // subtrahends are, 0, 0}.  Empty if the program has more steps than a byte names.
   static constexpr int32_t kPeelRec = 8;
   std::vector<int32_t> peel_recs, peel_more;
 

@@ -408,7 +408,6 @@ int make_plan(const bpx_code& code, const int32_t* arrival, int32_t n_arrival, i
       }
       plan->peel_recs.insert(plan->peel_recs.end(), rec, rec + bpx_plan::kPeelRec);
     }
-    plan->peel_recs.insert(plan->peel_recs.end(), bpx_plan::kPeelRec, 0);
   }
   return ok ? BPX_OK : BPX_E_UNDECODABLE;
 }
