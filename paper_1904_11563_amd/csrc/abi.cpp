@@ -4,6 +4,7 @@
 #include <algorithm>
 #include <cstring>
 #include <functional>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <queue>
@@ -34,6 +35,10 @@ bpx_status fail(bpx_status st, const std::string& msg) {
   set_error(msg);
   return st;
 }
+
+// For the entries that allocate: host memory that runs out is a status, no
+// exception may pass a C entry.  (The text fits in a string without allocating.)
+bpx_status no_memory() { return fail(BPX_E_NOMEM, "no host memory"); }
 
 bpx_status hip_fail(hipError_t e, const char* what) {
   return fail(BPX_E_HIP, std::string(what) + ": " + hipGetErrorString(e));
@@ -876,7 +881,7 @@ bpx_status group_build(bpx_plan* const* plans, const float* const* A, const floa
   g->total_p = tp;
   g->max_slots = max_slots;
   g->max_program = max_program;
-  g->launches = launches;
+  g->launches = std::move(launches);
   return BPX_OK;
 }
 
@@ -919,23 +924,22 @@ extern "C" {
 
 const char* bpx_last_error(void) { return get_error(); }
 
-bpx_status bpx_code_build(const bpx_code_params* params, bpx_code** out) {
+bpx_status bpx_code_build(const bpx_code_params* params, bpx_code** out) try {
   if (!params || !out) return fail(BPX_E_INVALID, "null argument");
   *out = nullptr;
-  bpx_code* c = new (std::nothrow) bpx_code();
+  std::unique_ptr<bpx_code> c(new (std::nothrow) bpx_code());
   if (!c) return fail(BPX_E_NOMEM, "out of host memory");
   std::string err;
-  int st = build_code(*params, c, &err);
-  if (st != BPX_OK) {
-    delete c;
-    return fail((bpx_status)st, err);
-  }
-  *out = c;
+  int st = build_code(*params, c.get(), &err);
+  if (st != BPX_OK) return fail((bpx_status)st, err);
+  *out = c.release();
   return BPX_OK;
+} catch (const std::bad_alloc&) {
+  return no_memory();
 }
 
 bpx_status bpx_code_from_csr(int32_t n, int32_t k, int32_t b, const int32_t* col_ptr,
-                             const int32_t* sym_ptr, const uint16_t* sym_data, bpx_code** out) {
+                             const int32_t* sym_ptr, const uint16_t* sym_data, bpx_code** out) try {
   if (!out || !col_ptr || !sym_ptr) return fail(BPX_E_INVALID, "null argument");
   *out = nullptr;
   if (n < 1 || k < 1 || b < 1 || (int64_t)k * b > 65535)
@@ -954,7 +958,7 @@ bpx_status bpx_code_from_csr(int32_t n, int32_t k, int32_t b, const int32_t* col
         return fail(BPX_E_INVALID, "ids of a symbol must be strictly ascending");
     }
   }
-  bpx_code* c = new (std::nothrow) bpx_code();
+  std::unique_ptr<bpx_code> c(new (std::nothrow) bpx_code());
   if (!c) return fail(BPX_E_NOMEM, "out of host memory");
   c->kind = -1;
   c->n = n;
@@ -963,8 +967,10 @@ bpx_status bpx_code_from_csr(int32_t n, int32_t k, int32_t b, const int32_t* col
   c->col_ptr.assign(col_ptr, col_ptr + n + 1);
   c->sym_ptr.assign(sym_ptr, sym_ptr + ns + 1);
   c->sym_data.assign(sym_data, sym_data + sym_ptr[ns]);
-  *out = c;
+  *out = c.release();
   return BPX_OK;
+} catch (const std::bad_alloc&) {
+  return no_memory();
 }
 
 bpx_status bpx_code_info(const bpx_code* code, int32_t* n, int32_t* k, int32_t* b,
@@ -1008,26 +1014,25 @@ static void plan_parts(bpx_plan* plan) {
 
 bpx_status bpx_plan_create(const bpx_code* code, const int32_t* arrival, int32_t n_arrival,
                            int32_t n_lost, int32_t mode, int64_t M, int64_t K, int64_t N,
-                           int32_t prec, bpx_plan** out) {
+                           int32_t prec, bpx_plan** out) try {
   if (!code || !out) return fail(BPX_E_INVALID, "null argument");
   *out = nullptr;
-  bpx_plan* p = new (std::nothrow) bpx_plan();
+  std::unique_ptr<bpx_plan> p(new (std::nothrow) bpx_plan());
   if (!p) return fail(BPX_E_NOMEM, "out of host memory");
   std::string err;
-  int st = make_plan(*code, arrival, n_arrival, n_lost, mode, M, K, N, prec, 1, p, &err);
-  if (st == BPX_E_INVALID) {
-    delete p;
-    return fail(BPX_E_INVALID, err);
-  }
-  plan_parts(p);
-  *out = p;
+  int st = make_plan(*code, arrival, n_arrival, n_lost, mode, M, K, N, prec, 1, p.get(), &err);
+  if (st == BPX_E_INVALID) return fail(BPX_E_INVALID, err);
+  plan_parts(p.get());
+  *out = p.release();
   if (st == BPX_E_UNDECODABLE) return fail(BPX_E_UNDECODABLE, "available columns do not peel");
   return BPX_OK;
+} catch (const std::bad_alloc&) {
+  return no_memory();
 }
 
 bpx_status bpx_plan_create2d(const bpx_code* code, const int32_t* arrival, int32_t n_arrival,
                              int32_t n_lost, int32_t mode, int64_t M, int64_t K, int64_t N,
-                             int32_t prec, bpx_plan** out) {
+                             int32_t prec, bpx_plan** out) try {
   if (!code || !out) return fail(BPX_E_INVALID, "null argument");
   *out = nullptr;
   const int32_t kb = code->kb();
@@ -1039,18 +1044,17 @@ bpx_status bpx_plan_create2d(const bpx_code* code, const int32_t* arrival, int32
   if (K % 4 != 0 || N % m != 0 || (N / m) % 4 != 0)
     return fail(BPX_E_UNSUPPORTED, "the two-dimensional form needs K % 4 == 0 and N / grid a "
                                    "multiple of 4");
-  bpx_plan* p = new (std::nothrow) bpx_plan();
+  std::unique_ptr<bpx_plan> p(new (std::nothrow) bpx_plan());
   if (!p) return fail(BPX_E_NOMEM, "out of host memory");
   std::string err;
-  int st = make_plan(*code, arrival, n_arrival, n_lost, mode, M, K, N, prec, m, p, &err);
-  if (st == BPX_E_INVALID) {
-    delete p;
-    return fail(BPX_E_INVALID, err);
-  }
-  plan_parts(p);
-  *out = p;
+  int st = make_plan(*code, arrival, n_arrival, n_lost, mode, M, K, N, prec, m, p.get(), &err);
+  if (st == BPX_E_INVALID) return fail(BPX_E_INVALID, err);
+  plan_parts(p.get());
+  *out = p.release();
   if (st == BPX_E_UNDECODABLE) return fail(BPX_E_UNDECODABLE, "available columns do not peel");
   return BPX_OK;
+} catch (const std::bad_alloc&) {
+  return no_memory();
 }
 
 bpx_status bpx_plan_grid(const bpx_plan* plan, int32_t* grid, int64_t* Nb) {
@@ -1119,9 +1123,11 @@ bpx_status bpx_plan_workspace_layout(const bpx_plan* plan, size_t* offsets, int3
   return BPX_OK;
 }
 
-bpx_status bpx_plan_upload(bpx_plan* plan) {
+bpx_status bpx_plan_upload(bpx_plan* plan) try {
   if (!plan) return fail(BPX_E_INVALID, "null plan");
   return upload(plan);
+} catch (const std::bad_alloc&) {
+  return no_memory();
 }
 
 void bpx_plan_free(bpx_plan* plan) {
@@ -1131,7 +1137,7 @@ void bpx_plan_free(bpx_plan* plan) {
 }
 
 bpx_status bpx_encode(bpx_plan* plan, const float* A, int64_t lda, float* coded_out,
-                      bpx_stream stream) {
+                      bpx_stream stream) try {
   bpx_status st = check_device_call(plan);
   if (st != BPX_OK) return st;
   if ((st = check_matrix(A, lda, plan->K, "A")) != BPX_OK) return st;
@@ -1152,27 +1158,33 @@ bpx_status bpx_encode(bpx_plan* plan, const float* A, int64_t lda, float* coded_
   hipError_t e = launch_encode(p, reinterpret_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "encode launch");
   return BPX_OK;
+} catch (const std::bad_alloc&) {
+  return no_memory();
 }
 
 bpx_status bpx_coded_gemm(bpx_plan* plan, const float* A, int64_t lda, const float* B,
                           int64_t ldb, float* C, int64_t ldc, void* ws, size_t ws_bytes,
-                          bpx_stream stream) {
+                          bpx_stream stream) try {
   bpx_status st = check_device_call(plan);
   if (st != BPX_OK) return st;
   return gemm_impl(plan, A, lda, B, ldb, C, ldc, ws, ws_bytes,
                    reinterpret_cast<hipStream_t>(stream));
+} catch (const std::bad_alloc&) {
+  return no_memory();
 }
 
 bpx_status bpx_peel_decode(bpx_plan* plan, const void* ws, size_t ws_bytes, float* C,
-                           int64_t ldc, bpx_stream stream) {
+                           int64_t ldc, bpx_stream stream) try {
   bpx_status st = check_device_call(plan);
   if (st != BPX_OK) return st;
   return peel_impl(plan, ws, ws_bytes, C, ldc, reinterpret_cast<hipStream_t>(stream));
+} catch (const std::bad_alloc&) {
+  return no_memory();
 }
 
 bpx_status bpx_coded_matmul(bpx_plan* plan, const float* A, int64_t lda, const float* B,
                             int64_t ldb, float* C, int64_t ldc, void* ws, size_t ws_bytes,
-                            bpx_stream stream) {
+                            bpx_stream stream) try {
   bpx_status st = check_device_call(plan);
   if (st != BPX_OK) return st;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
@@ -1191,10 +1203,12 @@ bpx_status bpx_coded_matmul(bpx_plan* plan, const float* A, int64_t lda, const f
   st = gemm_impl(plan, A, lda, B, ldb, C, ldc, ws, ws_bytes, s);
   if (st != BPX_OK) return st;
   return peel_impl(plan, ws, ws_bytes, C, ldc, s);
+} catch (const std::bad_alloc&) {
+  return no_memory();
 }
 
 bpx_status bpx_coded_matmul_noalloc(bpx_plan* plan, const float* A, int64_t lda, const float* B,
-                                    int64_t ldb, float* C, int64_t ldc, bpx_stream stream) {
+                                    int64_t ldb, float* C, int64_t ldc, bpx_stream stream) try {
   if (!plan) return fail(BPX_E_INVALID, "null plan");
   if (!plan->decodable) return fail(BPX_E_UNDECODABLE, "plan is not decodable");
   int dev = 0;
@@ -1226,6 +1240,8 @@ bpx_status bpx_coded_matmul_noalloc(bpx_plan* plan, const float* A, int64_t lda,
   st = gemm_impl(plan, A, lda, B, ldb, C, ldc, ws, kScratchBytes, s);
   if (st != BPX_OK) return st;
   return peel_impl(plan, ws, kScratchBytes, C, ldc, s);
+} catch (const std::bad_alloc&) {
+  return no_memory();
 }
 
 bpx_status bpx_group_workspace_bytes(bpx_plan* const* plans, int32_t count, size_t* bytes) {
@@ -1238,18 +1254,17 @@ bpx_status bpx_group_workspace_bytes(bpx_plan* const* plans, int32_t count, size
 
 bpx_status bpx_group_create(bpx_plan* const* plans, const float* const* A, const float* const* B,
                             float* const* C, int32_t count, void* ws, size_t ws_bytes,
-                            bpx_group** out) {
+                            bpx_group** out) try {
   if (!out) return fail(BPX_E_INVALID, "null argument");
   *out = nullptr;
-  bpx_group* g = new (std::nothrow) bpx_group();
+  std::unique_ptr<bpx_group> g(new (std::nothrow) bpx_group());
   if (!g) return fail(BPX_E_NOMEM, "out of host memory");
-  bpx_status st = group_build(plans, A, B, C, count, ws, ws_bytes, g);
-  if (st != BPX_OK) {
-    delete g;
-    return st;
-  }
-  *out = g;
+  bpx_status st = group_build(plans, A, B, C, count, ws, ws_bytes, g.get());
+  if (st != BPX_OK) return st;
+  *out = g.release();
   return BPX_OK;
+} catch (const std::bad_alloc&) {
+  return no_memory();
 }
 
 bpx_status bpx_group_launch_phase(bpx_group* group, int32_t phase, bpx_stream stream) {
@@ -1310,7 +1325,7 @@ bpx_status bpx_set_fused_peel(int32_t mode) {
   return BPX_OK;
 }
 
-bpx_status bpx_plan_fused(bpx_plan* plan, int32_t* fused) {
+bpx_status bpx_plan_fused(bpx_plan* plan, int32_t* fused) try {
   if (!plan || !fused) return fail(BPX_E_INVALID, "null argument");
   FusedParams f;
   *fused = plan->decodable &&
@@ -1319,6 +1334,8 @@ bpx_status bpx_plan_fused(bpx_plan* plan, int32_t* fused) {
                ? 1
                : 0;
   return BPX_OK;
+} catch (const std::bad_alloc&) {
+  return no_memory();
 }
 
 bpx_status bpx_plan_fused_program(const bpx_plan* plan, const int32_t** steps, int32_t* n_steps,
