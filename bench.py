@@ -60,11 +60,11 @@ def parse():
     return ap.parse_args()
 
 
-def packed_operands(gemm_flops, tile):
-    """Whether the library multiplies this workload's product on packed operands:
-    those of more than 2^31 multiply-adds, no tile forced (the 512^3 ones take
-    the fused form)."""
-    return tile < 0 and gemm_flops > 2 ** 32
+def packed_operands(plan, tile):
+    """Whether the library multiplies this plan's product on packed operands: the
+    workspace it asks for then holds more than the parts of the other kernels."""
+    return (tile < 0 and not plan.fused() and
+            plan.workspace_bytes()[0] > plan.workspace_layout()[6])
 
 
 GEMM_SOURCE = {"f32": "gemm_f32.hip", "bf16": "gemm_bf16.hip", "bf16x3": "gemm_bf16.hip",
@@ -328,12 +328,12 @@ def run_single(args):
         f32_kernel = "coded_gemm_f32_kernel<64,128,32,2>"
     bf16_kernel = ("fused_bf16_kernel (coded products and peel, one launch)" if fused else
                    "split_b + coded_gemm_bf16_flat_kernel, one call")
-    planes = packed_operands(gemm_flops, args.tile)
+    planes = packed_operands(plan, args.tile)
     fp8_kernel = "quant_b + quant_a + coded_gemm_fp8_wide_kernel, one call"
     if planes:
         fp8_kernel = "pack_fp8 + gemm_fp8_packed_kernel (256x256 tiles), one call"
-        f32_kernel = bf16_kernel = ("pack_planes + gemm_planes_kernel (256x256 tiles of BF16 "
-                                    "planes, last round split along K), one call")
+        f32_kernel = bf16_kernel = ("pack_planes + gemm_planes_kernel (256x256 or 128x128 tiles "
+                                    "of BF16 planes, last round split along K), one call")
     kernel = {"f32": f32_kernel, "bf16": bf16_kernel, "bf16x3": bf16_kernel,
               "fp8": fp8_kernel, "fp8x2": fp8_kernel}[prec_name]
     source = ("gemm_planes.hip" if planes and not prec_name.startswith("fp8") else

@@ -220,7 +220,12 @@ struct bpx_plan {
   // 192 35 and 32; 300 47 and 38; 321 x 3256 x 451 256 and 45; past 2^31 it does
   // for any K.  Two-dimensional: from 2^25 and K = 128 (Table I's code: 400 x 128 x
   // 400 17 and 21 us, 1024 x 128 x 1024 45 and 24; K = 32 to 64 within a quarter
-  // of each other).  FP8: past 2^31.
+  // of each other).  FP8: past 2^31 only, since up to there a call leaves the codes
+  // and scales that layout() names in the workspace.  It costs time where blocks
+  // have under 128 rows (packed rows are not padded; us direct and packed: (12,8,4)
+  // 1024^3 FP8 38 and 36, 640 x 2048 x 640 89 and 38; Mojette (24,16,8) 1024^3 65
+  // and 29) and saves some for FP8x2 in blocks of whole 128s ((6,4,2) 1024^3 34 and
+  // 40, FP8 29 both ways).
   bool has_planes() const {
     const double macs = n_macs();
     const bool enough = is_fp8()    ? false
