@@ -176,41 +176,77 @@ __device__ __forceinline__ v4f bload(__amdgpu_buffer_rsrc_t r, uint32_t voff) {
 
 // Peel phase: every thread runs the whole program for its own elements.
 // Steps carry src = the releaser's Y tile, and every recovered block is
-// written to C (nothing reached C earlier).  The program is the same for all
-// threads, so its words come from LDS as broadcasts and the branches are scalar.
-// (Step addresses worked out one per lane and read across lanes, every step
-// without a branch: 0.2 to 0.4 us slower, (6,4,2) 512^3 FP32 14.9 against 14.6, BF16
-// 11.7 against 11.3 us a launch.)
-__device__ __forceinline__ bool row_ok(const FusedParams& p, int64_t s, int64_t r) {
-  return r < p.Mb && s * p.Mb + r < p.M;
-}
-__device__ __forceinline__ void fused_peel(const FusedParams& p, const float* yt, float* xs,
+// written to C (nothing reached C earlier).  Bound by one wave's instructions
+// per step (256 elements, a wave to a SIMD), so lane l works out step l's
+// addresses (at most one step per data block, and one subtrahend less than a
+// symbol's members) and a step reads them across lanes; a scalar branch passes
+// by the subtrahends of a step that has none, what a step with some does not use
+// it reads and writes at its own product's place.  us a launch, graph replay,
+// against the program's words read from LDS in every step: (6,4,2) 512^3 FP32 14.3
+// and 14.6; (12,8,2), 16 steps, 30 x 12 x 2135 BF16 9.4 and 10.4; 16 uncoded
+// blocks 304 x 60 x 1370 FP32 9.0 and 10.1 (11.2 without the branch).
+constexpr int kMaxDeg = 4;  // members per symbol at most
+__device__ __forceinline__ void fused_peel(const FusedParams& p, float* yt, const float* xs,
                                            const FusedTables& t, int r0, int n0, int BN) {
-  const int tile = BM * BN;
+  const int tile = BM * BN, lane = (int)threadIdx.x & 63;
+  // byte offsets from yt
+  const int x0 = (int)((const char*)xs - (const char*)yt);
+  PeelStep mine = {};
+  int sub[kMaxDeg - 1] = {}, rows = 0;
+  uint64_t block = 0;
+  if (lane < p.nsteps) {
+    mine = t.steps[lane];
+    const int64_t first = (int64_t)mine.s * p.Mb;
+    rows = (int)max((int64_t)0, min(p.M - first, p.Mb));
+    block = reinterpret_cast<uint64_t>(p.C + first * p.ldc);
+#pragma unroll
+    for (int u = 0; u < kMaxDeg - 1; ++u)
+      sub[u] = u < mine.nsub ? x0 + t.subs[mine.sub_off + u] * tile * 4 : mine.src * tile * 4;
+  }
+  const int src = mine.src * tile * 4, kind = mine.nsub + (mine.f64 ? 8 : 0);
+  const int slot = mine.slot >= 0 ? x0 + mine.slot * tile * 4 : src;
+  const int lo = (int)block, hi = (int)(block >> 32);
+  auto of = [](int v, int st) __attribute__((always_inline)) {
+    return __builtin_amdgcn_readlane(v, st);
+  };
   for (int e = threadIdx.x; e < tile; e += kThreads) {
-    const int row = e / BN, col = e - row * BN;
-    const int64_t r = r0 + row, n = n0 + col;
+    const int row = e / BN, r = r0 + row, n = n0 + e - row * BN;
+    const int last = n < p.N ? r : 0x7fffffff;  // (no row of a column past N)
+    const int64_t at = (int64_t)r * p.ldc + n;
+    char* mem = reinterpret_cast<char*>(yt + e);
+    auto word = [&](int off) __attribute__((always_inline)) -> float& {
+      return *reinterpret_cast<float*>(mem + off);
+    };
+    float y = word(of(src, 0));
     for (int st = 0; st < p.nsteps; ++st) {
-      const PeelStep S = t.steps[st];
-      const float y = yt[S.src * tile + e];
-      const int32_t* sub = t.subs + S.sub_off;
-      float x;
-      if (S.f64) {
-        double acc = (double)y;
-        for (int u = 0; u < S.nsub; ++u) acc -= (double)xs[sub[u] * tile + e];
-        x = (float)acc;
-      } else {
-        float sum = y, comp = 0.f;
-        for (int u = 0; u < S.nsub; ++u) {
-          const float v = -xs[sub[u] * tile + e] - comp;
-          const float tt = sum + v;
-          comp = (tt - sum) - v;
-          sum = tt;
+      const float cur = y;
+      y = word(of(src, st + 1));  // (past the last step: lane's zeros, never used)
+      const int k = of(kind, st);
+      float x = cur;
+      if (k & 7) {
+        const float v0 = word(of(sub[0], st)), v1 = word(of(sub[1], st)), v2 = word(of(sub[2], st));
+        if (k < 8) {
+          float sum = cur, comp = 0.f;
+          auto take = [&](float v, bool on) __attribute__((always_inline)) {
+            const float w = -v - comp, tt = sum + w, c = (tt - sum) - w;
+            comp = on ? c : comp;
+            sum = on ? tt : sum;
+          };
+          take(v0, true);
+          take(v1, k > 1);
+          take(v2, k > 2);
+          x = sum;
+        } else {
+          double acc = (double)cur - (double)v0;
+          if (k > 9) acc -= (double)v1;
+          if (k > 10) acc -= (double)v2;
+          x = (float)acc;
         }
-        x = sum;
       }
-      if (S.slot >= 0) xs[S.slot * tile + e] = x;
-      if (n < p.N && row_ok(p, S.s, r)) p.C[((int64_t)S.s * p.Mb + r) * p.ldc + n] = x;
+      word(of(slot, st)) = x;
+      float* out = reinterpret_cast<float*>((uint64_t)(uint32_t)of(lo, st) |
+                                            (uint64_t)(uint32_t)of(hi, st) << 32);
+      if (last < of(rows, st)) out[at] = x;
     }
   }
 }
@@ -334,7 +370,6 @@ __device__ __forceinline__ v4f a_granule(const float* As, int blk, int h, int ro
 // The symbols of a wave: i = wave + 8 j for j < kMS, with their degree,
 // member blocks (ascending) and Y tile held in scalar registers.
 constexpr int kMS = 2;      // symbols per wave at most (16 per workgroup)
-constexpr int kMaxDeg = 4;  // members per symbol at most
 struct WaveSyms {
   int n;
   int deg[kMS];
@@ -440,8 +475,8 @@ __device__ __forceinline__ void pipeline_idle(int ng, int stage, const ADma<KG>&
 // W: waves per SIMD the registers are limited for.  Four let two workgroups share
 // a CU where LDS allows; the forms with copies to LDS lose nothing by it, nor does
 // FP32 with 32 k to a group, but the BF16 ones with 32 k to a group spill: Table
-// III's code, 512 x 96 x 512, all tiles at once: BF16x3 9.6 us with four, 9.2 with
-// two, BF16 9.3 and 8.9; 768 x 64 x 768, 288 tiles: 11.8 and 13.3, 11.4 and 12.7.
+// III's code, 512 x 96 x 512, all tiles at once: BF16x3 9.6 us with four, 9.3 with
+// two, BF16 9.3 and 8.9; 768 x 64 x 768, 288 tiles: 11.2 and 13.7, 10.9 and 13.2.
 // ------------------------------------------------------------------ FP32 --
 template <int JN, int KG, bool DMA, int W>
 __global__ __launch_bounds__(kThreads, W) void fused_f32_kernel(FusedParams p) {
