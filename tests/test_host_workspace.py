@@ -50,3 +50,20 @@ def test_groups_do_not_reserve_both_forms():
         need += off[1] + rows * 2048 * 4 + 512
     base = sum(_up(p.workspace_layout()[6], 256) for p in plans)
     assert base < bpx.group_workspace_bytes(plans) <= need
+
+
+# Two-dimensional products on either side of the line from which they are packed:
+# K over a symbol's passes, and multiply-adds
+@pytest.mark.parametrize("code,mode,shape,packed", [
+    ("uncoded", bpx.MODE_STRAGGLER, (1035, 256, 1568), False),
+    ("uncoded", bpx.MODE_STRAGGLER, (2191, 128, 1256), False),
+    ("uncoded", bpx.MODE_STRAGGLER, (649, 448, 464), True),
+    ("uncoded", bpx.MODE_STRAGGLER, (5116, 128, 1744), True),
+    ("uncoded", bpx.MODE_STRAGGLER, (5116, 124, 1744), False),
+    ("table1", bpx.MODE_FULL, (700, 148, 704), True),     # two passes: 296
+    ("table1", bpx.MODE_FULL, (700, 144, 704), False)])
+def test_two_dimensional_products_are_packed_where_it_pays(code, mode, shape, packed):
+    lib = bpx.Code.identity(2, 2) if code == "uncoded" else bpx.Code.table1()
+    n = lib.info()["n"]
+    plan = bpx.Plan(lib, list(range(n)), 0, mode, *shape, two_d=True)
+    assert (plan.workspace_bytes()[0] > plan.workspace_layout()[6]) == packed
