@@ -45,32 +45,32 @@ __device__ __forceinline__ void copy_panel(v4i rsrc, int lds, int voff, int soff
   if constexpr (COUNT == 1)
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
                  "buffer_load_dwordx4 %1, %2, %3 offen lds"
-                 ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0");
+                 ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
   if constexpr (COUNT == 2)
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
                  "buffer_load_dwordx4 %1, %2, %3 offen lds\n\t"
                  "buffer_load_dwordx4 %1, %2, %3 offen offset:1024 lds"
-                 ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0");
+                 ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
   if constexpr (COUNT == 3)
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
                  "buffer_load_dwordx4 %1, %2, %3 offen lds\n\t"
                  "buffer_load_dwordx4 %1, %2, %3 offen offset:1024 lds\n\t"
                  "buffer_load_dwordx4 %1, %2, %3 offen offset:2048 lds"
-                 ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0");
+                 ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
   if constexpr (COUNT == 4)
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
                  "buffer_load_dwordx4 %1, %2, %3 offen lds\n\t"
                  "buffer_load_dwordx4 %1, %2, %3 offen offset:1024 lds\n\t"
                  "buffer_load_dwordx4 %1, %2, %3 offen offset:2048 lds\n\t"
                  "buffer_load_dwordx4 %1, %2, %3 offen offset:3072 lds"
-                 ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0");
+                 ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
   static_assert(COUNT >= 1 && COUNT <= 4, "KiB per panel and stage");
 }
 // 64 words straight to LDS, lane l the word at voff.
 __device__ __forceinline__ void copy_words(v4i rsrc, int lds, int voff, int soff) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
                "buffer_load_dword %1, %2, %3 offen lds"
-               ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0");
+               ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
 }
 
 // Consecutive workgroups go to different XCDs; each XCD gets a contiguous
