@@ -190,9 +190,9 @@ bpx_status bpx_plan_create(const bpx_code* code, const int32_t* arrival, int32_t
  * grid*Nb, K a multiple of 32) run on 256x256 tiles when the FP32 tile
  * shape is one of the 256x256 ones (the default), other shapes and calls on
  * 64x128 tiles; both sum every product in the same order (identical
- * results).  Products of more than 2^25 multiply-adds over all passes with more
- * than 288 K over the passes of a symbol, of more than 2^29 with K >= 128, and of
- * more than 2^31 run on split planes (bpx_coded_gemm).
+ * results).  Products with K >= 128 of more than 2^25 multiply-adds over all
+ * passes (2^29 where K over the passes of a symbol is 288 or less), and any of more
+ * than 2^31, run on split planes (bpx_coded_gemm).
  * bpx_encode and grouped launches do not take such plans. */
 bpx_status bpx_plan_create2d(const bpx_code* code, const int32_t* arrival, int32_t n_arrival,
                              int32_t n_lost, int32_t mode, int64_t M, int64_t K, int64_t N,

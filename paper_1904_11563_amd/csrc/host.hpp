@@ -218,11 +218,11 @@ struct bpx_plan {
   // code: direct 41, packed 34).  FP32 packs six bytes per value, so it takes
   // longer K to pay: (12,8,4), 1024 x K x 1024: K = 128 direct 28, packed 29 us;
   // 192 35 and 32; 300 47 and 38; 321 x 3256 x 451 256 and 45; past 2^31 it does
-  // for any K.  Two-dimensional: from 2^25 and a tile's K over all its passes of
-  // more than 288 (us direct and packed: Table I's code, two passes, 1058 x 320 x
+  // for any K.  Two-dimensional: from K = 128 and 2^25 where a tile's K over all its
+  // passes is more than 288 (us direct and packed: Table I's code, two passes, 1058 x 320 x
   // 3224 46 and 45, 1229 x 320 x 1032 53 and 41, (12,8,2) 2895 x 256 x 720 84 and 83;
   // uncoded 1035 x 256 x 1568 21 and 26, 3809 x 320 x 304 25 and 26, 649 x 448 x 464
-  // 32 and 24), and from 2^29 and K = 128 (uncoded 2191 x 128 x 1256, 2^28.4, 18 and
+  // 32 and 24), and from 2^29 otherwise (uncoded 2191 x 128 x 1256, 2^28.4, 18 and
   // 21; 3076 x 128 x 1344, 2^29, 27 both ways; 5116 x 128 x 1744 42 and 35).  FP8: past 2^31 only, since up to there a call leaves the codes
   // and scales that layout() names in the workspace.  It costs time where blocks
   // have under 128 rows (packed rows are not padded; us direct and packed: (12,8,4)
@@ -233,8 +233,8 @@ struct bpx_plan {
     const double macs = n_macs();
     const bool enough = is_fp8()    ? false
                         : is_bf16() ? macs > 16777216.0
-                        : grid > 1  ? (macs > 33554432.0 && K * max_passes() > 288) ||
-                                         (macs > 536870912.0 && K >= 128)
+                        : grid > 1  ? K >= 128 && macs > (K * max_passes() > 288 ? 33554432.0
+                                                                                 : 536870912.0)
                                     : macs > 16777216.0 && K > 192;
     return (enough || macs > 2147483648.0) && planes_fit();
   }
