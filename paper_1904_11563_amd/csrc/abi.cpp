@@ -559,12 +559,12 @@ size_t group_base_bytes(bpx_plan* const* plans, int32_t count) {
   return b;
 }
 // ... whether those of the products that are not skipped run on split planes:
-// enough 256 x 256 tiles to give
-// every CU one (32 products of 256-1024, 221 tiles, took the same time either
-// way; 272 tiles of 2048 ran 1.2 times as fast), and products large enough
-// that each packed value is multiplied often, in multiply-adds per value
-// (BF16x3: 128-640 with 160 per value lost 3 %, 256-4096 with 650 gained 18 %
-// and with 1180 44 %; BF16, which packs half the bytes, gained 12 % at 160) ...
+// enough 256 x 256 tiles to give every CU one (32 products of 256-1024, 221 tiles,
+// took the same time either way; 272 tiles of 2048 ran 1.2 times as fast), and
+// products large enough that each packed value is multiplied often, in
+// multiply-adds per value (BF16x3: 128-640 with 160 per value lost 3 %, 256-4096
+// with 650 gained 18 % and with 1180 44 %; BF16, which packs half the bytes, gained
+// 12 % at 160) ...
 bool group_planes(bpx_plan* const* plans, int32_t count, const std::vector<char>& skip = {}) {
   int64_t tiles = 0;
   double macs = 0.0, values = 0.0;

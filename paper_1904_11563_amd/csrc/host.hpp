@@ -212,23 +212,25 @@ struct bpx_plan {
                     : plane_rows() / 256 * (plane_cols() / 256);
   }
   // Whether the products run on packed operands where the workspace holds them
-  // (small row-block products may still take the fused form).  BF16: from 2^24
-  // multiply-adds, below which nearly all of either way is launches (400 x 64 x
-  // 400 on Construction B, 2^24: 14 and 13 us; 2048 x 300 x 2048 on the (12,8,4)
-  // code: direct 41, packed 34).  FP32 packs six bytes per value, so it takes
-  // longer K to pay: (12,8,4), 1024 x K x 1024: K = 128 direct 28, packed 29 us;
-  // 192 35 and 32; 300 47 and 38; 321 x 3256 x 451 256 and 45; past 2^31 it does
-  // for any K.  Two-dimensional: from K = 128 and 2^25 where a tile's K over all its
-  // passes is more than 288 (us direct and packed: Table I's code, two passes, 1058 x 320 x
-  // 3224 46 and 45, 1229 x 320 x 1032 53 and 41, (12,8,2) 2895 x 256 x 720 84 and 83;
-  // uncoded 1035 x 256 x 1568 21 and 26, 3809 x 320 x 304 25 and 26, 649 x 448 x 464
-  // 32 and 24), and from 2^29 otherwise (uncoded 2191 x 128 x 1256, 2^28.4, 18 and
-  // 21; 3076 x 128 x 1344, 2^29, 27 both ways; 5116 x 128 x 1744 42 and 35).  FP8: past 2^31 only, since up to there a call leaves the codes
-  // and scales that layout() names in the workspace.  It costs time where blocks
-  // have under 128 rows (packed rows are not padded; us direct and packed: (12,8,4)
-  // 1024^3 FP8 38 and 36, 640 x 2048 x 640 89 and 38; Mojette (24,16,8) 1024^3 65
-  // and 29) and saves some for FP8x2 in blocks of whole 128s ((6,4,2) 1024^3 34 and
-  // 40, FP8 29 both ways).
+  // (small row-block products may still take the fused form).  us, direct and
+  // packed, at the lines:
+  //   BF16  from 2^24 multiply-adds, below which nearly all of either way is
+  //     launches (400 x 64 x 400 on Construction B, 2^24: 14 and 13; 2048 x 300 x
+  //     2048 on the (12,8,4) code: 41 and 34).
+  //   FP32  packs six bytes per value, so it takes longer K to pay: (12,8,4), 1024 x
+  //     K x 1024: K = 128 28 and 29, 192 35 and 32, 300 47 and 38; 321 x 3256 x 451
+  //     256 and 45; past 2^31 it does for any K.
+  //   Two-dimensional  from K = 128 and 2^25 where a tile's K over all its passes is
+  //     more than 288 (Table I's code, two passes, 1058 x 320 x 3224 46 and 45, 1229
+  //     x 320 x 1032 53 and 41; (12,8,2) 2895 x 256 x 720 84 and 83; uncoded 1035 x
+  //     256 x 1568 21 and 26, 3809 x 320 x 304 25 and 26, 649 x 448 x 464 32 and 24),
+  //     from 2^29 otherwise (uncoded 2191 x 128 x 1256, 2^28.4, 18 and 21; 3076 x 128
+  //     x 1344, 2^29, 27 and 27; 5116 x 128 x 1744 42 and 35).
+  //   FP8  past 2^31 only, since up to there a call leaves the codes and scales that
+  //     layout() names in the workspace.  It costs time where blocks have under 128
+  //     rows (packed rows are not padded: (12,8,4) 1024^3 FP8 38 and 36, 640 x 2048 x
+  //     640 89 and 38; Mojette (24,16,8) 1024^3 65 and 29) and saves some for FP8x2
+  //     in blocks of whole 128s ((6,4,2) 1024^3 34 and 40, FP8 29 and 29).
   bool has_planes() const {
     const double macs = n_macs();
     const bool enough = is_fp8()    ? false
