@@ -645,7 +645,7 @@ __global__ __launch_bounds__(256) void pack_planes_grouped_kernel(const GroupDes
 
 // Sums the pieces of each split tile of S x S, one float4 per thread, in
 // piece order (fixed, so results do not depend on scheduling).
-template <bool GRID, int S>
+template <bool GRID, int S, bool SCALED>
 __global__ __launch_bounds__(256) void planes_reduce_kernel(PlaneParams p) {
   constexpr int BLOCKS = S * S / 1024;
   const int t = blockIdx.x / BLOCKS;
@@ -660,7 +660,7 @@ __global__ __launch_bounds__(256) void planes_reduce_kernel(PlaneParams p) {
   v4f sum = *reinterpret_cast<const v4f*>(src);
   for (int k = 1; k < p.split; ++k)
     sum += *reinterpret_cast<const v4f*>(src + (int64_t)k * (S * S));
-  sum *= p.planes == 3 ? kPlaneDown : 1.f;
+  if (SCALED) sum *= kPlaneDown;
 #pragma unroll
   for (int c = 0; c < 4; ++c)
     if (n + c < p.Nb) out[n + c] = sum[c];
@@ -786,10 +786,12 @@ double planes_split(PlaneParams* p, const int32_t* passes, int64_t T, double us,
 
 hipError_t launch_planes_reduce(const PlaneParams& p, int64_t T, hipStream_t stream) {
   if (p.full == T) return hipSuccess;
-  const bool grid = p.grid > 1, small = p.tile == 128;
-  void (*k)(PlaneParams) = grid    ? small ? planes_reduce_kernel<true, 128> : planes_reduce_kernel<true, 256>
-                           : small ? planes_reduce_kernel<false, 128>
-                                   : planes_reduce_kernel<false, 256>;
+  const bool small = p.tile == 128;
+  void (*k)(PlaneParams) =
+      p.grid > 1 ? (small ? planes_reduce_kernel<true, 128, true> : planes_reduce_kernel<true, 256, true>)
+      : p.planes == 3
+          ? (small ? planes_reduce_kernel<false, 128, true> : planes_reduce_kernel<false, 256, true>)
+          : (small ? planes_reduce_kernel<false, 128, false> : planes_reduce_kernel<false, 256, false>);
   hipLaunchKernelGGL(k, dim3((unsigned)((T - p.full) * (small ? 16 : 64))), dim3(256), 0, stream, p);
   return hipGetLastError();
 }

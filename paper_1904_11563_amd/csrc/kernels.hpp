@@ -168,8 +168,6 @@ struct PlaneParams {
   unsigned short* bp;  // packed planes of B's columns
   unsigned* fa;        // planes == 3: per pack block, 1 if it holds a value
   unsigned* fb;        //   that is not split
-  unsigned* ft;        // ... and per tile, 1 if it belongs to such values' panels
-  unsigned max_bits;   // planes == 3: bits of the smallest magnitude not split
   float* part;         // partial 256 x 256 tiles of the last round
   int32_t part_tiles;  // how many part holds
   int32_t kc;          // 16-wide k chunks of the packed operands (FP8: 64-wide)
@@ -196,6 +194,8 @@ struct PlaneParams {
   int32_t row_group;   // row panels per group of the tile order
   int32_t nka, nkb;    // pack blocks along k of A (256 wide) and of B (64 wide)
   int32_t full, split; // tiles computed whole; K pieces of each of the others
+  unsigned* ft;        // planes == 3: per tile, 1 if it belongs to a panel with a value
+  unsigned max_bits;   //   that is not split; bits of the smallest such magnitude
 };
 hipError_t launch_pack_planes(const PlaneParams& p, hipStream_t stream);
 // passes: in the two-dimensional form the passes of each symbol (host memory).
